@@ -203,13 +203,6 @@ void fill_tables(const ClassPlan &cp, const Layout &lay, char *h, char *d, Class
   T->first_skip_at = ~0ull;
 }
 
-bool mostly_short_rows(const ClassPlan &cp) {
-  uint64_t short_bytes = 0;
-  for (const Xfer &x : cp.xfers)
-    if (x.rows > 1 && x.row_bytes <= 2048) short_bytes += x.row_bytes * x.rows;
-  return 2 * short_bytes > cp.payload;
-}
-
 // Launch shape when the caller has not tuned it.
 //
 // pool->pool is bound by HBM. One workgroup per CU, each holding a whole 64 KiB tile in
@@ -237,15 +230,8 @@ uint32_t default_workgroups(const ft_pool *p, int cls, bool with_p2p) {
   return with_p2p ? 16u : 64u;
 }
 
-// short_rows: most of the class's payload sits in pitched descriptors with rows of at
-// most 2 KiB (a gather of image crops). Such a job is bound by latency and by what a compute
-// unit's memory pipeline does with windows of 16 bytes at any address, not by HBM: it runs the
-// kernel's light build (blocks of 16 KiB instead of 64 KiB, under 200 registers per lane), two
-// workgroups per compute unit, and a tile costs a few microseconds whatever its size (its
-// ticket - the counter hands out about 70 million a second, all workgroups together -, the
-// decode, the barriers, a memory round trip per piece). Crops of the traffic workload, 512
-// workgroups: 47.7 us at 16 KiB tiles, 39.8 at 26 KiB, 38.1 at 43 KiB, 39.1 at 64 KiB (fewer
-// than two tiles per workgroup are left to balance the launch's end).
+// short_rows: most of the class's payload sits in pitched descriptors with rows of at most 2 KiB, in a job that the
+// wave kernel does not take (launch_code): such a tile is bound by latency, and smaller ones balance the launch's end.
 uint64_t default_tile(int cls, bool with_p2p, bool short_rows, uint64_t payload) {
   if (cls == FT_P2P) return short_rows ? 43u * 1024u : 64u * 1024u;
   if (cls == FT_P2H) return with_p2p || payload <= 256u * 1024u ? 8u * 1024u : 16u * 1024u;
@@ -397,16 +383,23 @@ namespace ft {
 // Tile shape per class, then the descriptor table and the runs of empty tiles that go with it.
 void shape_classes(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_bytes) {
   const bool with_p2p = plan.cls[FT_P2P].nchunks > 0;
+  const bool alone = plan.cls[FT_H2P].nchunks == 0 && plan.cls[FT_P2H].nchunks == 0;
   for (int c = 0; c < FT_NCLASS; ++c) {
     ClassPlan &cp = plan.cls[c];
     if (cp.nchunks == 0) continue;
     ClassRun &r = job->run[c];
     const Tuning &tn = p->tuning[c];
     const bool short_rows = mostly_short_rows(cp);
-    r.light = c == FT_P2P && short_rows && tn.workgroups == 0;
-    tile_shape(chunk_bytes, tn.tile_bytes ? tn.tile_bytes : default_tile(c, with_p2p, short_rows, cp.payload),
-               &r.tile_bytes, &r.tiles_per_chunk);
-    build_chunk_table(cp, chunk_bytes, r.tile_bytes, r.tiles_per_chunk);
+    r.code = launch_code(cp, c, chunk_bytes, tn.workgroups != 0 || tn.tile_bytes != 0, alone);
+    if (r.code >= kWaveTiles) {
+      tile_shape(chunk_bytes, wave_tile(cp.payload), &r.tile_bytes, &r.tiles_per_chunk);
+      cp.chunk_desc.clear();  // a wavefront finds its descriptor by comparing 64 of them at a time
+      cp.desc_per = 1;
+    } else {
+      tile_shape(chunk_bytes, tn.tile_bytes ? tn.tile_bytes : default_tile(c, with_p2p, short_rows, cp.payload),
+                 &r.tile_bytes, &r.tiles_per_chunk);
+      build_chunk_table(cp, chunk_bytes, r.tile_bytes, r.tiles_per_chunk);
+    }
     build_skips(cp, chunk_bytes, r.tile_bytes, r.tiles_per_chunk, &r.skips, &r.table.ntickets);
   }
 }
@@ -496,10 +489,6 @@ int prepare_class(ft_pool *p, Job *job, int c, const ClassPlan &cp, const Layout
   return rc;
 }
 
-// Largest single tensor that is copied with ordinary (cached) loads and stores: with its copy it
-// still fits the chip's 256 MiB last-level cache.
-constexpr uint64_t kCacheResidentBytes = 128ull << 20;
-
 // A job of one link class whose tables fit into a kernel argument is launched on the
 // caller's stream itself, tables in the launch: one launch and one event record instead
 // of a table upload, a fork and a join across streams - 4 us of host time instead of
@@ -531,12 +520,16 @@ int launch_with_the_launch(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chun
   const uint64_t ntickets = r.table.ntickets;
   // host->pool: more than 64 tiles of 16 KiB requested at once is more than the link
   // takes (2 MiB as 128 x 16 KiB: 52 us; as 64 workgroups drawing tickets: 43 us)
-  const uint64_t most = only == FT_P2P ? (r.light ? 2u : 1u) * (uint64_t)p->ctx->cu_count : only == FT_H2P ? 64u : 128u;
+  const bool wave = r.code >= kWaveTiles;
+  const uint64_t most = cp.payload <= kWaveTilesBytes && wave ? ntickets : only == FT_P2P ? (uint64_t)p->ctx->cu_count : only == FT_H2P ? 64u : 128u;
   // one contiguous transfer between 16-byte aligned addresses (any length): the workgroups share the tiles out
-  // themselves (ClassTable::single >= 2)
-  const bool direct = cp.funcs.size() == 1 && cp.xfers.size() == 1 && cp.funcs[0].chunk_base == 0 && !(flags & FT_LOG) &&
+  // themselves (ClassTable::single >= 2). Pool->pool only where a small chunk makes small tiles, of which the counter
+  // hands out no more than 70 million a second (1 MiB in chunks of 512 bytes: 5.7 us dealt out, 31 us by tickets);
+  // whole 64 KiB tiles are faster by tickets (256 MiB 99 us dealt out, 83 us by tickets, 1 GiB 403 and 312 us).
+  const bool direct = (only != FT_P2P || (!wave && r.tile_bytes < 64 * 1024)) && cp.funcs.size() == 1 &&
+                      cp.xfers.size() == 1 && cp.funcs[0].chunk_base == 0 && !(flags & FT_LOG) &&
                       cp.xfers[0].rows == 1 && ((cp.xfers[0].src | cp.xfers[0].dst) & 15) == 0;
-  const bool each_its_own = !direct && ntickets <= most;
+  const bool each_its_own = wave || (!direct && ntickets <= most);  // no counter
   // a job with more tiles than that holds the caller's stream for a while: not what FT_DETACHED asked for
   if (ntickets > most && (flags & FT_DETACHED)) return FT_OK;
   if (!each_its_own && !direct) {
@@ -554,21 +547,18 @@ int launch_with_the_launch(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chun
   uint64_t wg = ntickets;
   if (direct) {
     T.ticket = p->ctx->idle_counter;  // never consulted
-    // A tensor that fits the last-level cache together with its copy (256 MiB on this chip) moves with
-    // ordinary loads and stores: its producer has just written it and its consumer is about to read the
-    // copy, so both may be served from that cache (64 MiB: 26 -> 20 us, 128 MiB: 51 -> 36 us when the
-    // source is still there). Larger ones stream past the caches like every other pool->pool transfer.
     T.single = only == FT_P2P && cp.payload <= kCacheResidentBytes ? 3u : 2u;
     // Host->pool: the link is full with 256 KiB of reads in flight, and a lone transfer is the faster the
     // less is asked for at once beyond that (1 MiB: 64 workgroups x 16 KiB 25 us, 16 x 16 KiB 21 us).
-    wg = only == FT_H2P ? 16u : default_workgroups(p, only, only == FT_P2P);
+    wg = only == FT_H2P ? 16u : default_workgroups(p, only, false);
     if (wg > ntickets) wg = ntickets;
   } else if (each_its_own) {
     T.ticket = p->ctx->idle_counter;
+    if (wave) wg = wave_workgroups(p->ctx->cu_count, r.code, ntickets);
   } else {
     T.ticket = p->ctx->counter_pairs + 2 * r.counter_pair;
     T.self_reset = 1;
-    wg = (r.light ? 2u : 1u) * default_workgroups(p, only, only == FT_P2P);
+    wg = default_workgroups(p, only, only == FT_P2P);
     if (wg > ntickets) wg = ntickets;
   }
   r.workgroups = (uint32_t)wg;
@@ -583,9 +573,9 @@ int launch_with_the_launch(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chun
   if (r.ev_begin == nullptr) {
     // the done event is bound to the dispatch itself (it fires with the kernel's own completion
     // signal) instead of being a marker queued behind it: 2 us less from submit to the end of wait
-    e = launch_copy(T, r.light ? kLightPoolToPool : only, r.workgroups, user, nullptr, r.ev_done, job->inline_tables.get());
+    e = launch_copy(T, r.code, r.workgroups, user, nullptr, r.ev_done, job->inline_tables.get());
   } else {
-    e = launch_copy(T, r.light ? kLightPoolToPool : only, r.workgroups, user, r.ev_begin, r.ev_end, job->inline_tables.get());
+    e = launch_copy(T, r.code, r.workgroups, user, r.ev_begin, r.ev_end, job->inline_tables.get());
     if (e == hipSuccess) e = hipEventRecord(r.ev_done, user);
   }
   if (e != hipSuccess) {
@@ -622,7 +612,7 @@ int launch_with_uploaded_tables(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t
     if (rc != FT_OK) return fail_submit(p, job, rc);
     ClassTable &T = r.table;
     const Tuning &tn = p->tuning[c];
-    uint64_t wg = tn.workgroups ? tn.workgroups : (r.light ? 2u : 1u) * default_workgroups(p, c, with_p2p);
+    uint64_t wg = tn.workgroups ? tn.workgroups : r.code >= kWaveTiles ? wave_workgroups(p->ctx->cu_count, r.code, T.ntickets) : default_workgroups(p, c, with_p2p);
     if (wg > T.ntickets) wg = T.ntickets;
     r.workgroups = dma ? 0 : (uint32_t)wg;
     if ((flags & FT_LOG) && !dma) {
@@ -661,10 +651,10 @@ int launch_with_uploaded_tables(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t
     if (straight) {
       r.stream = user;
       if (timing) {
-        e = launch_copy(r.table, r.light ? kLightPoolToPool : c, r.workgroups, user, r.ev_begin, r.ev_end);
+        e = launch_copy(r.table, r.code, r.workgroups, user, r.ev_begin, r.ev_end);
         if (e == hipSuccess) e = hipEventRecord(r.ev_done, user);
       } else {
-        e = launch_copy(r.table, r.light ? kLightPoolToPool : c, r.workgroups, user, nullptr, r.ev_done);
+        e = launch_copy(r.table, r.code, r.workgroups, user, nullptr, r.ev_done);
       }
       if (e != hipSuccess) return hip_fail(e, "launch on the caller's stream");
       continue;
@@ -704,7 +694,7 @@ int launch_with_uploaded_tables(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t
         if (e != hipSuccess) return hip_fail(e, "hipEventRecord(end)");
       }
     } else {
-      e = launch_copy(r.table, r.light ? kLightPoolToPool : c, r.workgroups, s, r.ev_begin, r.ev_end);
+      e = launch_copy(r.table, r.code, r.workgroups, s, r.ev_begin, r.ev_end);
       if (e != hipSuccess) return hip_fail(e, "launch_copy");
     }
     e = hipEventRecord(r.ev_done, s);

@@ -34,8 +34,7 @@ struct ClassRun {
   uint64_t tile_bytes = 0;
   uint32_t tiles_per_chunk = 0;
   uint32_t workgroups = 0;
-  // pool->pool job of short pitched rows: the kernel's light build, two workgroups per compute unit
-  bool light = false;
+  int code = 0;             // what launch_copy is given: the link class, or a launch code of the wave kernel
   bool on_user_stream = false;  // launched on the caller's stream, tables in the launch
   hipStream_t stream = nullptr; // the library's stream it runs on otherwise
   int counter_pair = -1;        // its self-resetting counter pair, if it needed a counter
@@ -214,7 +213,6 @@ void fill_class_table(const ClassPlan &cp, const Layout &lay, char *h, char *d, 
 uint32_t default_workgroups(const ft_pool *p, int cls, bool with_p2p);
 // payload: bytes of the class in the job (all ones for an open job, whose traffic is not known in advance)
 uint64_t default_tile(int cls, bool with_p2p, bool short_rows, uint64_t payload);
-bool mostly_short_rows(const ClassPlan &cp);
 
 // ft_open.cpp. All but open_wait are called with the pool's mutex held and the pool's
 // device current; open_wait blocks and must be called without the pool's mutex.

@@ -10,6 +10,7 @@
 #include <hip/hip_ext.h>
 
 #include "ft_kernels.h"
+#include "ft_windows.h"
 
 namespace ft {
 
@@ -71,7 +72,6 @@ constexpr uint32_t kThreads = 256;  // 4 wavefronts per workgroup, one workgroup
 // U = 16 (64 KiB blocks, the whole tile in registers). The host-link classes use U = 4:
 // their tiles are 8-16 KiB, and the smaller register footprint lets a host-link
 // workgroup share a CU with a pool->pool workgroup instead of taking the CU for itself.
-// CLS 3 (kLightPoolToPool) is pool->pool with U = 4: two such workgroups fit a CU.
 template <int CLS>
 struct UnrollOf {
   static constexpr uint32_t value = CLS == 2 ? 16u : 4u;
@@ -490,125 +490,93 @@ __device__ __forceinline__ void st16_any(uint64_t addr, u32x4 v) {
   else *reinterpret_cast<u32x4_any FT_GLOBAL *>(addr) = v;
 }
 
-// Part of one row (fewer than 4096 bytes), a lane's share of it: a window of 16 bytes at any address,
-// the last one moved back so that it ends with the part (it overlaps the one before with the same
-// bytes), or one byte if the part is shorter than a window. Loaded in one call, stored in another, so
-// that the caller can put other work between the two.
-struct RowPart {
-  uint64_t d = 0, s = 0;  // first byte of the part on either side; d == 0: no such part
-  uint32_t len = 0;
-  u32x4 v;
-  uint8_t b;
-};
+// N lanes' share of one pass over the windows of a pitched piece (ft_windows.h): R windows of W bytes per lane from
+// window `blk` on, at whatever addresses they have (the memory pipeline splits an access that straddles aligned
+// granules). All loads before the first store; no load is predicated (a lane past the last window repeats it).
+template <uint32_t W>
+struct Window;
+template <>
+struct Window<16> { typedef u32x4_any type; };
+template <>
+struct Window<8> { typedef uint64_t type __attribute__((aligned(1))); };
+template <>
+struct Window<4> { typedef uint32_t type __attribute__((aligned(1))); };
+template <>
+struct Window<2> { typedef uint16_t type __attribute__((aligned(1))); };
+template <>
+struct Window<1> { typedef uint8_t type; };
 
-template <int NT>
-__device__ __forceinline__ void row_part_load(RowPart &P, uint32_t tid) {
-  if (P.d == 0) return;
-  if (P.len < 16) {
-    if (tid < P.len) P.b = ld8(P.s + tid);
-  } else if ((tid << 4) < P.len) {
-    const uint32_t col = (tid << 4) + 16 <= P.len ? tid << 4 : P.len - 16;
-    P.v = ld16_any<NT>(P.s + col);
-  }
-}
-
-template <int NT>
-__device__ __forceinline__ void row_part_store(const RowPart &P, uint32_t tid) {
-  if (P.d == 0) return;
-  if (P.len < 16) {
-    if (tid < P.len) st8(P.d + tid, P.b);
-  } else if ((tid << 4) < P.len) {
-    const uint32_t col = (tid << 4) + 16 <= P.len ? tid << 4 : P.len - 16;
-    st16_any<NT>(P.d + col, P.v);
-  }
-}
-
-// Whole rows r0 .. rl of a pitched descriptor, R windows per lane and pass (see copy_rows_windows).
-template <int NT, uint32_t R>
-__device__ __forceinline__ void move_windows(const Xfer &X, uint64_t r0, uint64_t rl, uint32_t tid) {
-  const uint32_t rb = (uint32_t)X.row_bytes;
-  const uint32_t S = (rb + 15) >> 4;
-  const uint32_t magic = (uint32_t)((1ull << 32) / S) + 1;  // q / S = mulhi(q, magic) or one less
-  const uint32_t Q = (uint32_t)(rl - r0 + 1) * S;
-  const uint64_t sb = X.src + r0 * X.src_pitch, db = X.dst + r0 * X.dst_pitch;
-  for (uint32_t blk = 0; blk < Q; blk += R * kThreads) {
-    u32x4 v[R];
-    uint64_t to[R];
+template <uint32_t N, uint32_t W, uint32_t R>
+__device__ __forceinline__ void rows_pass(const Xfer &X, const RowWindows &w, uint64_t d0, uint64_t s0, uint32_t blk, uint32_t lane) {
+  typedef typename Window<W>::type FT_GLOBAL *P;
+  typename Window<W>::type v[R];
+  uint64_t to[R];
 #pragma unroll
-    for (uint32_t k = 0; k < R; ++k) {
-      uint32_t q = blk + tid + k * kThreads;
-      const bool active = q < Q;
-      q = active ? q : Q - 1;
-      uint32_t i = S == 1 ? q : __umulhi(q, magic);  // (2^32 / 1 + 1 does not fit the magic)
-      i -= (i * S > q) ? 1u : 0u;
-      const uint32_t j = q - i * S;
-      const uint32_t col = j + 1 < S ? j << 4 : rb - 16;
-      v[k] = ld16_any<NT>(sb + (uint64_t)i * X.src_pitch + col);
-      to[k] = active ? db + (uint64_t)i * X.dst_pitch + col : 0;
+  for (uint32_t i = 0; i < R; ++i) {
+    const uint32_t q = blk + lane + i * N;
+    const RowCursor c = row_window<W>(w, q < w.count ? q : w.count - 1);
+    const uint32_t col = row_window_col<W>(w, c);
+    v[i] = *reinterpret_cast<const P>(s0 + c.row * X.src_pitch + col);
+    to[i] = q < w.count ? d0 + c.row * X.dst_pitch + col : 0;
+  }
+#pragma unroll
+  for (uint32_t i = 0; i < R; ++i)
+    if (to[i] != 0) *reinterpret_cast<P>(to[i]) = v[i];
+}
+
+// Bytes [c0, c0 + take) counted from the start of row r0 of a pitched descriptor with rows of at least W bytes (fewer
+// than 2^30), take < 2^30, with N lanes. Passes are no deeper than what is left: a load beyond the last window costs
+// as much as any other. The bytes of a part of a row that is shorter than a window are loaded before the passes
+// and stored after them.
+template <uint32_t N, uint32_t W, uint32_t RMAX>
+__device__ __forceinline__ void copy_row_windows(const Xfer &X, uint64_t r0, uint32_t c0, uint32_t take, uint32_t lane) {
+  const RowWindows w = row_windows<W>((uint32_t)X.row_bytes, c0, take);
+  const uint64_t s0 = X.src + r0 * X.src_pitch, d0 = X.dst + r0 * X.dst_pitch;
+  // lanes 0 .. 15: the first part's bytes, lanes 16 .. 31: the last part's
+  const bool edge = lane < 16 ? lane < w.short_first : lane - 16 < w.short_last;
+  const uint64_t es = lane < 16 ? s0 + c0 + lane : s0 + (uint64_t)w.more * X.src_pitch + (lane - 16);
+  const uint64_t ed = lane < 16 ? d0 + c0 + lane : d0 + (uint64_t)w.more * X.dst_pitch + (lane - 16);
+  uint8_t eb = 0;
+  if (edge) eb = ld8(es);
+  for (uint32_t blk = 0; blk < w.count;) {
+    const uint32_t deep = (w.count - blk + N - 1) / N;
+    if (RMAX <= 4 || deep <= 4) {
+      rows_pass<N, W, 4>(X, w, d0, s0, blk, lane);
+      blk += 4 * N;
+    } else {
+      rows_pass<N, W, RMAX>(X, w, d0, s0, blk, lane);
+      blk += RMAX * N;
     }
-#pragma unroll
-    for (uint32_t k = 0; k < R; ++k)
-      if (to[k] != 0) st16_any<NT>(to[k], v[k]);
+  }
+  if (edge) st8(ed, eb);
+}
+
+// Payload bytes [p, p+take) of a pitched descriptor, pool->pool. Rows shorter than a tile: windows as wide as the rows let
+// them be, so that a tile costs a memory round trip or two whatever its rows' length (rows of 5760 bytes one after the
+// other: 1.0 TB/s). Ordinary rather than nontemporal accesses: neighbouring windows share memory lines, and such rows
+// come out of frames that several consumers crop (47.2 -> 45.5 us on the crops of the traffic workload).
+template <int NT, uint32_t U>
+__device__ __forceinline__ void copy_rows_in_pool(const Xfer &X, uint64_t p, uint64_t take, uint32_t tid) {
+  const uint64_t rb = X.row_bytes;
+  while (take > 0) {
+    const uint64_t r0 = p / rb, c0 = p - r0 * rb;
+    uint64_t n;
+    if (rb >= 65536) {
+      n = take < rb - c0 ? take : rb - c0;
+      copy_piece<NT, U>(X.dst + r0 * X.dst_pitch + c0, X.src + r0 * X.src_pitch + c0, n, tid);
+    } else {
+      n = take < (1u << 29) ? take : (1u << 29);  // windows are numbered in 32 bits
+      if (rb >= 16) copy_row_windows<kThreads, 16, 12>(X, r0, (uint32_t)c0, (uint32_t)n, tid);
+      else if (rb >= 4) copy_row_windows<kThreads, 4, 4>(X, r0, (uint32_t)c0, (uint32_t)n, tid);
+      else copy_row_windows<kThreads, 1, 4>(X, r0, (uint32_t)c0, (uint32_t)n, tid);
+    }
+    p += n;
+    take -= n;
   }
 }
 
-// Rows of 16 .. 4096 bytes between any two pitches (a gather into a packed buffer, a scatter out of
-// one, or pitched on both sides), window by window: a row of rb bytes is ceil(rb / 16) windows of 16 bytes, the last one moved back to end
-// with the row, and a lane moves a window with one load and one store at whatever addresses they
-// have (the memory pipeline splits an access that straddles aligned granules). Nothing is merged or
-// masked and a lane's arithmetic is one division by a constant: for rows of 64-256 bytes a tenth of
-// the vector instructions of a gather that owns aligned destination granules, and one load per
-// window instead of two. R windows per lane and pass, all loads before the first store. The rows
-// that the piece holds only a part of (its first and its last, where a tile boundary cuts a row) are
-// loaded before the whole rows and stored after them, so that they cost no memory round trip of
-// their own. Windows aligned to the destination's granules (51 against 46.5 us on the crops of the
-// traffic workload) or to the source's (46.6) measured no better than windows counted from the
-// row's first byte.
-template <int NT, uint32_t R>
-__device__ __forceinline__ void copy_rows_windows(const Xfer &X, uint64_t p, uint64_t take, uint32_t tid) {
-  const uint32_t rb = (uint32_t)X.row_bytes;
-  const uint64_t pend = p + take;
-  uint64_t r0 = p / rb;
-  const uint32_t c0 = (uint32_t)(p - r0 * rb);
-  uint64_t rl = (pend - 1) / rb;
-  const uint32_t cl = (uint32_t)(pend - rl * rb);  // one past the last column in the last row
-  RowPart first, last;
-  if (r0 == rl) {
-    first.d = X.dst + r0 * X.dst_pitch + c0;
-    first.s = X.src + r0 * X.src_pitch + c0;
-    first.len = cl - c0;
-    row_part_load<NT>(first, tid);
-    row_part_store<NT>(first, tid);
-    return;
-  }
-  if (c0 != 0) {
-    first.d = X.dst + r0 * X.dst_pitch + c0;
-    first.s = X.src + r0 * X.src_pitch + c0;
-    first.len = rb - c0;
-    r0 += 1;
-  }
-  if (cl != rb) {
-    last.d = X.dst + rl * X.dst_pitch;
-    last.s = X.src + rl * X.src_pitch;
-    last.len = cl;
-    rl -= 1;
-  }
-  row_part_load<NT>(first, tid);
-  row_part_load<NT>(last, tid);
-  if (r0 <= rl) {
-    // whole rows r0 .. rl; a lane without a window repeats the last one's load (no load is predicated),
-    // so a short piece takes a pass with fewer loads per lane
-    const uint64_t windows = (rl - r0 + 1) * ((rb + 15) >> 4);
-    if (windows <= 2 * kThreads) move_windows<NT, 2>(X, r0, rl, tid);
-    else if (windows <= 4 * kThreads) move_windows<NT, 4>(X, r0, rl, tid);
-    else move_windows<NT, R>(X, r0, rl, tid);
-  }
-  row_part_store<NT>(first, tid);
-  row_part_store<NT>(last, tid);
-}
-
-// Payload bytes [p, p+take) of a pitched descriptor.
-template <int NT, uint32_t U, bool P2P>
+// The same on the host link.
+template <int NT, uint32_t U>
 __device__ __forceinline__ void copy_rows(const Xfer &X, uint64_t p, uint64_t take, uint32_t tid) {
   const uint64_t rb = X.row_bytes;
   const uint64_t pend = p + take;
@@ -616,13 +584,6 @@ __device__ __forceinline__ void copy_rows(const Xfer &X, uint64_t p, uint64_t ta
   const uint64_t c0 = p - r0 * rb;
   const uint64_t rl = (pend - 1) / rb;
   const uint64_t cl = pend - rl * rb;  // one past the last column in the last row
-  if (P2P && rb >= 16 && rb <= 4096 && take < (1ull << 30)) {
-    // pool->pool. Ordinary rather than nontemporal accesses: neighbouring windows share memory lines,
-    // and such rows come out of frames that several consumers crop (47.2 -> 45.5 us on the crops
-    // of the traffic workload)
-    copy_rows_windows<false, 8>(X, p, take, tid);
-    return;
-  }
   if (X.dst_pitch == rb && rb >= 16 && rb <= 4096 && take < (1ull << 30)) {
     copy_rows_packed_pairs<NT, 2>(X, p, take, tid);
     return;
@@ -642,7 +603,6 @@ __device__ __forceinline__ void copy_rows(const Xfer &X, uint64_t p, uint64_t ta
     }
   }
 }
-
 
 // What a ticket names, decoded: bytes [b0, b1) of one function's stream (empty if
 // b0 >= b1) and the descriptor holding b0.
@@ -934,9 +894,8 @@ __device__ __forceinline__ void drain_barrier() {
 // for the stores and publishes it. Keeping a CU's reads and writes in separate bursts,
 // one workgroup per CU, is what the memory controllers serve fastest.
 //
-// CLS (the link class, or kLightPoolToPool) selects the block size of the copy routines and gives each
-// class's kernel a name of its own, so that profiles keep host-link launches and
-// pool->pool launches apart.
+// CLS (the link class) selects the block size of the copy routines and gives each class's kernel a
+// name of its own, so that profiles keep host-link launches and pool->pool launches apart.
 template <bool NT, int CLS>
 __global__ __launch_bounds__(kThreads, (CLS == 2 ? 1 : 2)) void ft_copy_kernel(ClassTable T, InlineBlob) {
   constexpr uint32_t U = UnrollOf<CLS>::value;
@@ -950,7 +909,7 @@ __global__ __launch_bounds__(kThreads, (CLS == 2 ? 1 : 2)) void ft_copy_kernel(C
     // tile t of the one stream - so the tiles are dealt out round robin, workgroup b taking
     // tiles b, b + workgroups, ...: no counter, no decode by one wavefront for the others, no
     // hand-over through LDS, and the first tile's loads are issued a microsecond after entry.
-    if (T.single == 3) deal_out_tiles<false, U>(T, CT.xfers[0].src, CT.xfers[0].dst, CT.xfers[0].row_bytes, tid);
+    if (CLS == 2 && T.single == 3) deal_out_tiles<0, U>(T, CT.xfers[0].src, CT.xfers[0].dst, CT.xfers[0].row_bytes, tid);
     else deal_out_tiles<MODE, U>(T, CT.xfers[0].src, CT.xfers[0].dst, CT.xfers[0].row_bytes, tid);
     return;
   }
@@ -1008,7 +967,8 @@ __global__ __launch_bounds__(kThreads, (CLS == 2 ? 1 : 2)) void ft_copy_kernel(C
         Xfer Xn = X;
         if (more) Xn = read_xfer(CT.xfers, ++x);
         if (X.rows == 1) copy_piece<MODE, U>(X.dst + p, X.src + p, take, tid);
-        else copy_rows<MODE, U, (CLS >= 2)>(X, p, take, tid);
+        else if (CLS == 2) copy_rows_in_pool<MODE, U>(X, p, take, tid);
+        else copy_rows<MODE, U>(X, p, take, tid);
         pos += take;
         if (more) {
           X = Xn;
@@ -1018,7 +978,7 @@ __global__ __launch_bounds__(kThreads, (CLS == 2 ? 1 : 2)) void ft_copy_kernel(C
       // pool->pool: the draw follows the last piece's stores. In front of the tile's loads it would hold
       // every store back until the counter has answered, and the ticket would be held for the whole of a
       // tile that takes long (several pieces, rows): large_mixed 83.4 -> 80.8 us per launch, crops 38.6 -> 34.7
-      if (CLS >= 2 && tid == 0) claimed = atomicAdd(T.ticket, 1ull);
+      if (CLS == 2 && tid == 0) claimed = atomicAdd(T.ticket, 1ull);
     }
     if (lead) {
       // lane 0 holds the counter's answer; all 64 lanes of this wavefront are enabled
@@ -1061,6 +1021,237 @@ __global__ __launch_bounds__(kThreads, (CLS == 2 ? 1 : 2)) void ft_copy_kernel(C
       __hip_atomic_store(T.ticket, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       __hip_atomic_store(T.ticket + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
+  }
+}
+
+// ---- one tile per wavefront -------------------------------------------------------------------------
+//
+// The kernel of pool->pool jobs that latency bounds rather than HBM: jobs of at most 16 MiB and jobs of pitched
+// rows (the rule stands with launch_code in ft_api.cpp). Every wavefront takes tiles of its own, of 1 .. 16 KiB,
+// decodes them itself and moves them without a barrier, so a tile's memory round trips (table reads, one or
+// more per piece) overlap those of the other 15 wavefronts of its compute unit. The host sends it only
+// what 32-bit arithmetic covers (wave_tiles_fit): its instructions arrive from memory at every launch, and a
+// launch of this kind lasts about as long as the fetch of a few thousand of them.
+
+// Sum over the wavefront, in every lane. All 64 lanes take part.
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) {
+#pragma unroll
+  for (int m = 32; m >= 1; m >>= 1) v += (uint32_t)__shfl_xor((int)v, m, 64);
+  return uniform32(v);
+}
+
+// How many of the 64 lanes say yes.
+__device__ __forceinline__ uint32_t wave_count(bool yes) { return (uint32_t)__popcll(__ballot(yes)); }
+
+// decode_ticket for a wavefront that comes to ticket t without having seen the tickets before it: the
+// cursors' places are found by comparing 64 table entries at a time, one per lane, so whatever the
+// number of functions the way to the bytes is four or five dependent reads: runs of empty tiles and
+// phases together, slot, function, (the descriptors' stream offsets,) descriptor.
+__device__ __forceinline__ Work decode_ticket_wave(const ClassTable &T, const ConstTables &CT, uint32_t t, uint32_t lane) {
+  Work w;
+  w.fl = 0;
+  w.stage = 0;
+  uint32_t v = t, x = 0, nx = 1;
+  uint64_t stream_bytes;
+  uint32_t rank, ti;
+  if (!T.single) {
+    uint64_t base = lane < T.nphases ? CT.phases[lane].rank_base : ~0ull;  // on its way while the runs are summed
+    for (uint32_t j0 = 0; j0 < T.nskips; j0 += 64) {
+      const uint32_t j = j0 + lane;
+      const bool before = j < T.nskips && CT.skips[j].at <= t;
+      v += wave_sum(before ? (uint32_t)CT.skips[j].gap : 0u);
+      if (wave_count(before) < 64) break;
+    }
+    rank = uniform32(v / T.tiles_per_chunk);
+    ti = v - rank * T.tiles_per_chunk;
+    uint32_t idx = wave_count(base <= rank);
+    for (uint32_t j0 = 64; j0 < T.nphases && idx == j0; j0 += 64) {
+      base = j0 + lane < T.nphases ? CT.phases[j0 + lane].rank_base : ~0ull;
+      idx += wave_count(base <= rank);
+    }
+    const CPhaseP ph = CT.phases + (idx - 1);  // the first phase begins at rank 0
+    const uint32_t rel = rank - (uint32_t)ph->rank_base;
+    const uint32_t round = uniform32(rel / ph->nslots);
+    const CSlotP sl = CT.slots + (ph->slot_off + rel - round * ph->nslots);
+    w.fl = sl->fl;
+    w.k = ((uint32_t)ph->round_base + round) * sl->weight + sl->i;
+    const CFuncP F = CT.funcs + w.fl;
+    stream_bytes = F->stream_bytes;
+    x = F->desc_off;
+    nx = F->ndesc;
+  } else {
+    rank = uniform32(v / T.tiles_per_chunk);
+    ti = v - rank * T.tiles_per_chunk;
+    w.k = rank;
+    stream_bytes = CT.xfers[0].row_bytes * CT.xfers[0].rows;
+  }
+  const uint64_t c0 = w.k * T.chunk_bytes;
+  const uint64_t lo = ti * T.tile_bytes;
+  uint64_t hi = lo + T.tile_bytes;
+  if (hi > T.chunk_bytes) hi = T.chunk_bytes;
+  w.b0 = c0 + lo;
+  w.b1 = c0 + hi;
+  if (w.b1 > stream_bytes) w.b1 = stream_bytes;
+  while (nx > 1) {  // the last descriptor at or before b0, 64 compared at a time
+    const uint32_t step = (nx + 63) / 64;
+    const uint32_t j = lane * step;
+    const uint32_t at = (wave_count(j < nx && CT.xfers[x + (j < nx ? j : 0u)].stream_off <= w.b0) - 1) * step;
+    x += at;
+    nx = step < nx - at ? step : nx - at;
+  }
+  w.x = x;
+  return w;
+}
+
+// An address off a base that is the same in every lane: base in scalar registers, 32 bits of offset per lane.
+// Loads are ordinary ones unless NT: the source has often just been written, and a piece's lines may be wanted
+// again. Stores are nontemporal always. Against ordinary stores that is as good or better wherever it was
+// measured (64 tensors, 34 MB: source in the last-level cache 12.6 -> 11.1 us, not there 18.7 -> 16.8); with
+// nontemporal loads as well, what the cache holds is not served from it (34 MB 11.1 against 16.7 us), beyond its size
+// they are the faster ones.
+template <class V, int NT>
+__device__ __forceinline__ V ld_off(uint64_t base, uint32_t off) {
+  const V FT_GLOBAL *at = reinterpret_cast<const V FT_GLOBAL *>(reinterpret_cast<const char FT_GLOBAL *>(base) + off);
+  return NT ? __builtin_nontemporal_load(at) : *at;
+}
+template <class V>
+__device__ __forceinline__ void st_off(uint64_t base, uint32_t off, V v) {
+  __builtin_nontemporal_store(v, reinterpret_cast<V FT_GLOBAL *>(reinterpret_cast<char FT_GLOBAL *>(base) + off));
+}
+
+// Up to R * 64 windows of a contiguous run, from window `blk` on. All loads before the first store; no load is
+// predicated (a lane past the last window repeats it and stores nothing).
+template <int NT, uint32_t R>
+__device__ __forceinline__ void wave_run_pass(uint64_t d, uint64_t s, const RunWindows &w, uint32_t blk, uint32_t lane) {
+  u32x4_any v[R];
+#pragma unroll
+  for (uint32_t i = 0; i < R; ++i) v[i] = ld_off<u32x4_any, NT>(s, run_window_at(w, blk + lane + i * 64));
+#pragma unroll
+  for (uint32_t i = 0; i < R; ++i)
+    if (blk + lane + i * 64 < w.count) st_off<u32x4_any>(d, run_window_at(w, blk + lane + i * 64), v[i]);
+}
+
+// n bytes (< 2^30) of one contiguous run. Stores are whole destination granules but for the two ends; a source at
+// another alignment is the memory pipeline's business (it splits the loads).
+template <int NT>
+__device__ __forceinline__ void wave_copy_run(uint64_t d, uint64_t s, uint32_t n, uint32_t lane) {
+  if (n < 16) {
+    if (lane < n) st8(d + lane, ld8(s + lane));
+    return;
+  }
+  const RunWindows w = run_windows(d, n);
+  // a pass no deeper than what is left: a lane's load beyond the last window costs as much as any other
+  for (uint32_t blk = 0; blk < w.count;) {
+    const uint32_t deep = (w.count - blk + 63) / 64;
+    if (deep <= 2) {
+      wave_run_pass<NT, 2>(d, s, w, blk, lane);
+      blk += 2 * 64;
+    } else if (deep <= 5) {
+      wave_run_pass<NT, 5>(d, s, w, blk, lane);
+      blk += 5 * 64;
+    } else {  // a whole tile of 8 KiB at an odd address is 513 windows
+      wave_run_pass<NT, 9>(d, s, w, blk, lane);
+      blk += 9 * 64;
+    }
+  }
+}
+
+// R * 64 windows of pitched rows: `at` is the lane's first window, the others lie 64 windows apart, reached by
+// steps of `rows` rows and `cols` columns. Destinations are walked a second time instead of being kept.
+template <int NT, uint32_t R>
+__device__ __forceinline__ void wave_rows_pass(uint64_t d, uint64_t s, uint32_t d_pitch, uint32_t s_pitch, const RowWindows &w,
+                                               uint32_t rows, uint32_t cols, uint32_t safe, RowCursor *at, uint32_t left) {
+  u32x4_any v[R];
+  RowCursor c = *at;
+#pragma unroll
+  for (uint32_t i = 0; i < R; ++i) {
+    // no load is predicated: a lane past the last window loads the piece's first one
+    v[i] = ld_off<u32x4_any, NT>(s, i * 64 < left ? c.row * s_pitch + row_window_col<16>(w, c) : safe);
+    row_window_next<16>(w, rows, cols, &c);
+  }
+  const RowCursor next = c;
+  c = *at;
+  asm("" : "+v"(c.row), "+v"(c.col));  // (the compiler would keep every window's place in registers)
+#pragma unroll
+  for (uint32_t i = 0; i < R; ++i) {
+    if (i * 64 < left) st_off<u32x4_any>(d, c.row * d_pitch + row_window_col<16>(w, c), v[i]);
+    row_window_next<16>(w, rows, cols, &c);
+  }
+  *at = next;
+}
+
+// Payload bytes [p, p + take) of a pitched descriptor with rows of at least 16 bytes, window by window at whatever
+// addresses they have. The bytes of a part of a row that is shorter than a window are loaded before the passes and
+// stored after them.
+template <int NT>
+__device__ __forceinline__ void wave_copy_rows(const Xfer &X, uint32_t p, uint32_t take, uint32_t lane) {
+  const uint32_t rb = (uint32_t)X.row_bytes, s_pitch = (uint32_t)X.src_pitch, d_pitch = (uint32_t)X.dst_pitch;
+  const uint32_t r0 = uniform32(p / rb);
+  const RowWindows w = row_windows<16>(rb, p - r0 * rb, take);
+  const uint64_t s = X.src + (uint64_t)r0 * s_pitch, d = X.dst + (uint64_t)r0 * d_pitch;
+  // lanes 0 .. 15: the first part's bytes, lanes 16 .. 31: the last part's
+  const bool edge = lane < 16 ? lane < w.short_first : lane - 16 < w.short_last;
+  const uint32_t es = lane < 16 ? w.c0 + lane : w.more * s_pitch + (lane - 16);
+  const uint32_t ed = lane < 16 ? w.c0 + lane : w.more * d_pitch + (lane - 16);
+  uint8_t eb = 0;
+  if (edge) eb = ld_off<uint8_t, 0>(s, es);
+  const uint32_t rows = uniform32(w.magic == 0 ? 64u : mul_hi32(64, w.magic));  // 64 / per_row: 64 windows on
+  const uint32_t cols = (64 - rows * w.per_row) * 16;
+  const RowCursor zero = row_window<16>(w, 0);
+  const uint32_t safe = zero.row * s_pitch + row_window_col<16>(w, zero);
+  RowCursor at = row_window<16>(w, lane);
+  for (uint32_t blk = 0; blk < w.count;) {
+    const uint32_t rem = w.count - blk;
+    const uint32_t left = lane < rem ? rem - lane : 0u;  // windows from the lane's own to the last, in steps of 64
+    if (rem <= 3 * 64) {
+      wave_rows_pass<NT, 3>(d, s, d_pitch, s_pitch, w, rows, cols, safe, &at, left);
+      blk += 3 * 64;
+    } else if (rem <= 6 * 64) {
+      wave_rows_pass<NT, 6>(d, s, d_pitch, s_pitch, w, rows, cols, safe, &at, left);
+      blk += 6 * 64;
+    } else {
+      wave_rows_pass<NT, 9>(d, s, d_pitch, s_pitch, w, rows, cols, safe, &at, left);
+      blk += 9 * 64;
+    }
+  }
+  if (edge) st_off<uint8_t>(d, ed, eb);
+}
+
+template <int NT>
+__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void ft_wave_kernel(ClassTable T, InlineBlob) {
+  const ConstTables CT = const_tables(T);
+  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t step = gridDim.x * (blockDim.x >> 6);
+  if (T.log && threadIdx.x == 0) {
+    T.wg_log[blockIdx.x].t_entry = wall_clock64();
+    T.wg_log[blockIdx.x].unit = compute_unit_id();
+  }
+  // neighbouring tickets go to different compute units
+  for (uint32_t t = uniform32(threadIdx.x >> 6) * gridDim.x + blockIdx.x; t < (uint32_t)T.ntickets; t += step) {
+    uint64_t t_begin = 0;
+    if (T.log) t_begin = wall_clock64();
+    const Work w = decode_ticket_wave(T, CT, t, lane);
+    uint64_t pos = w.b0;
+    for (uint32_t x = w.x; pos < w.b1; ++x) {
+      const Xfer X = read_xfer(CT.xfers, x);
+      const uint64_t p = pos - X.stream_off;
+      uint64_t take = X.row_bytes * X.rows - p;
+      if (take > w.b1 - pos) take = w.b1 - pos;
+      if (X.rows == 1) wave_copy_run<NT>(X.dst + p, X.src + p, (uint32_t)take, lane);
+      else wave_copy_rows<NT>(X, (uint32_t)p, (uint32_t)take, lane);
+      pos += take;
+    }
+    if (T.log && lane == 0) {
+      log_decoded(T, t, w);
+      __builtin_amdgcn_s_waitcnt(0);
+      T.log[t].t_begin = t_begin;
+      T.log[t].t_end = wall_clock64();
+      T.log[t].wg = blockIdx.x;
+    }
+  }
+  if (T.log) {
+    __syncthreads();
+    if (threadIdx.x == 0) T.wg_log[blockIdx.x].t_exit = wall_clock64();
   }
 }
 
@@ -1122,13 +1313,17 @@ hipError_t launch_copy(const ClassTable &T, int link_class, uint32_t workgroups,
   const dim3 grid(workgroups), block(kThreads);
   const InlineBlob &B = tables ? *tables : kNoTables;
   // with events, they are bound to this dispatch: they read the kernel's own start and end
+  if (link_class >= kWaveTiles) {
+    const uint32_t threads = wave_code_threads(link_class);
+    if (threads == 0) return hipErrorInvalidValue;
+    if (link_class & kWaveStreams) hipExtLaunchKernelGGL(ft_wave_kernel<kStream>, grid, dim3(threads), 0, stream, ev_start, ev_stop, 0, T, B);
+    else hipExtLaunchKernelGGL(ft_wave_kernel<0>, grid, dim3(threads), 0, stream, ev_start, ev_stop, 0, T, B);
+    return hipGetLastError();
+  }
   switch (link_class) {
     case 0: hipExtLaunchKernelGGL((ft_copy_kernel<true, 0>), grid, block, 0, stream, ev_start, ev_stop, 0, T, B); break;
     case 1: hipExtLaunchKernelGGL((ft_copy_kernel<true, 1>), grid, block, 0, stream, ev_start, ev_stop, 0, T, B); break;
     case 2: hipExtLaunchKernelGGL((ft_copy_kernel<true, 2>), grid, block, 0, stream, ev_start, ev_stop, 0, T, B); break;
-    case kLightPoolToPool:
-      hipExtLaunchKernelGGL((ft_copy_kernel<true, kLightPoolToPool>), grid, block, 0, stream, ev_start, ev_stop, 0, T, B);
-      break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();

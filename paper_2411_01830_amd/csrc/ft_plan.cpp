@@ -82,6 +82,74 @@ void build_skips(const ClassPlan &cp, uint64_t chunk_bytes, uint64_t tile_bytes,
   *ntickets = cp.nchunks * tiles_per_chunk - gone;
 }
 
+bool mostly_short_rows(const ClassPlan &cp) {
+  uint64_t short_bytes = 0;
+  for (const Xfer &x : cp.xfers)
+    if (x.rows > 1 && x.row_bytes <= 2048) short_bytes += x.row_bytes * x.rows;
+  return 2 * short_bytes > cp.payload;
+}
+
+// Whether the wave kernel's 32-bit arithmetic covers a job (see ft_kernels.hip): tile and chunk numbers, the
+// payload of every pitched descriptor, and the distance of two rows of a tile (a tile is little more than 8 KiB at most and
+// a row at least 16 bytes: about 2^9 rows of at most 2^20 bytes). Beyond 256 functions a wavefront's search of the phases
+// and of the runs of empty tiles, 64 entries at a time, is no longer a step or two.
+static bool wave_tiles_fit(const ClassPlan &cp, uint64_t chunk_bytes) {
+  if (chunk_bytes < 1024 || chunk_bytes > (1ull << 29) || cp.funcs.size() > 256) return false;
+  if (cp.nchunks > (1ull << 31) / (chunk_bytes / 1024 + 1)) return false;
+  for (const Xfer &x : cp.xfers)
+    if (x.rows > 1 && (x.row_bytes < 16 || x.src_pitch > (1u << 20) || x.dst_pitch > (1u << 20) ||
+                       x.rows > ((1ull << 32) - 1) / x.row_bytes))
+      return false;
+  return true;
+}
+
+// What a class of a job is launched as (launch_copy's second argument): its link class, or for pool->pool one of
+// the wave kernel's codes. The 64 KiB tiles of the class's own kernel serve the memory controllers best once a
+// launch streams for long; below that a launch is bound by the round trips of its few tiles, by its table
+// reads and by the fetch of its instructions, and the wave kernel has many times as many tiles and short code.
+// Measured, kernel time in us, class's own kernel -> wave kernel, with the source in the last-level cache / not there:
+//   64 tensors of 8 functions   17 MB 11.1 -> 8.4 / 12.3 -> 12.2   50 MB 22.4 -> 16.9 / 23.2 -> 23.3   67 MB 29.1 -> 20.4 / 28.6 -> 32.9
+//   the same, misaligned        17 MB 11.7 -> 8.9 / 12.0 -> 12.3   67 MB 33.4 -> 21.1 / 33.6 -> 31.4   134 MB 55.6 -> 36.9 / 56.5 -> 56.7
+//   one tensor                  17 MB 5.7 -> 5.8 / 9.6 -> 8.2      67 MB 19.0 -> 17.9 / 27.5 -> 25.3   134 MB 36.8 -> 33.5 / 52.1 -> 49.2
+//   one tensor, misaligned      1 MB 6.5 -> 4.3                    17 MB 11.1 -> 7.2 / 11.3 -> 9.5     134 MB 50.4 -> 34.7 / 51.0 -> 51.6
+//   rows of 5760 bytes          34 MB 21.5 -> 11.6 / 24.7 -> 17.1  105 MB 47.4 -> 31.3 / 53.2 -> 41.7  419 MB 172 -> 148 (streamed)
+//   rows of 64 KiB              105 MB 41 -> 29                    419 MB 140 -> 150 (streamed)
+// so: any job up to 48 MiB; up to 128 MiB one tensor, mostly misaligned tensors, and rows; beyond that rows under 64 KiB.
+// alone: the job has no host-link traffic beside it. Beside a host-link kernel, whose workgroups hold their
+// compute units for milliseconds, only workgroups of one wavefront are used, which find room anywhere,
+// and long contiguous jobs keep the class's kernel, whose shape is chosen for that company.
+int launch_code(const ClassPlan &cp, int cls, uint64_t chunk_bytes, bool tuned, bool alone) {
+  if (cls != FT_P2P || tuned || !wave_tiles_fit(cp, chunk_bytes)) return cls;
+  if (cp.payload <= kWaveTilesBytes) return kWaveTiles;
+  const bool streams = cp.payload > kCacheResidentBytes;
+  uint64_t short_rows = 0, rows = 0, misaligned = 0;
+  for (const Xfer &x : cp.xfers) {
+    const uint64_t n = x.row_bytes * x.rows;
+    if (x.rows == 1) misaligned += ((x.src ^ x.dst) & 15) != 0 ? n : 0;
+    else rows += !streams || x.row_bytes < 65536 ? n : 0;
+    if (x.rows > 1 && x.row_bytes <= 2048) short_rows += n;
+  }
+  if (2 * rows > cp.payload)
+    return (!alone ? kWaveTiles : 2 * short_rows > cp.payload ? kWaveTwoPerUnit : kWaveOnePerUnit) | (streams ? kWaveStreams : 0);
+  if (!alone || streams) return cls;
+  return cp.payload <= kWaveAnyBytes || cp.xfers.size() == 1 || 2 * (misaligned + rows) > cp.payload ? kWaveOnePerUnit : cls;
+}
+
+// Tile of a wave-kernel launch. About 4000 tiles, sixteen wavefronts on every compute unit, each with a tile that it can
+// hold in registers: more tiles cost more decodes than they hide (15.6 MB in 1024 tensors: 4000 tiles 11.0 us, 7000
+// 12.2, 2000 11.7), fewer leave compute units idle. 2 KiB is two loads per lane.
+uint64_t wave_tile(uint64_t payload) {
+  const uint64_t t = payload / 4000;
+  return t < 2048 ? 2048 : t > 8192 ? 8192 : (t + 15) / 16 * 16;
+}
+
+// Workgroups of a wave-kernel launch of this many tickets.
+uint64_t wave_workgroups(int cu_count, int code, uint64_t ntickets) {
+  if ((code & 15) == kWaveTiles) return ntickets;
+  const uint64_t most = ((code & 15) == kWaveTwoPerUnit ? 2ull : 1ull) * (uint64_t)cu_count;
+  return ntickets < most ? ntickets : most;
+}
+
 namespace {
 
 // slot a before slot b: smaller finish tag (i+1)/w, ties to the lower function

@@ -61,6 +61,19 @@ void build_chunk_table(ClassPlan &cp, uint64_t chunk_bytes, uint64_t tile_bytes,
 void build_skips(const ClassPlan &cp, uint64_t chunk_bytes, uint64_t tile_bytes, uint32_t tiles_per_chunk,
                  std::vector<Skip> *skips, uint64_t *ntickets);
 
+// Most of the payload sits in pitched descriptors with rows of at most 2 KiB.
+bool mostly_short_rows(const ClassPlan &cp);
+
+// How a class of a job is launched (the link class or a launch code of the wave kernel, see ft_tables.h), the tile
+// of a wave-kernel launch and its workgroups.
+// Largest pool->pool job that, with its copy, fits the chip's 256 MiB last-level cache.
+constexpr uint64_t kCacheResidentBytes = 128ull << 20;
+// Largest job that is sent as one wavefront per workgroup, and largest job of any kind for the wave kernel.
+constexpr uint64_t kWaveTilesBytes = 16ull << 20, kWaveAnyBytes = 48ull << 20;
+int launch_code(const ClassPlan &cp, int cls, uint64_t chunk_bytes, bool tuned, bool alone);
+uint64_t wave_tile(uint64_t payload);
+uint64_t wave_workgroups(int cu_count, int code, uint64_t ntickets);
+
 // Bytes per ticket and tickets per chunk for a chunk size and a wanted tile size.
 void tile_shape(uint64_t chunk_bytes, uint64_t want_tile, uint64_t *tile_bytes, uint32_t *tiles_per_chunk);
 

@@ -69,6 +69,7 @@ struct StaticClass {
   std::vector<Skip> skips;
   uint64_t ntickets = 0, tile_bytes = 0;
   uint32_t tiles_per_chunk = 0;
+  int code = 0;
 };
 
 }  // namespace ft
@@ -93,8 +94,15 @@ extern "C" int ft_submit_static(ft_pool *p, const ft_desc *descs, uint32_t ndesc
     if (cp.nchunks == 0) continue;
     StaticClass &s = sc[c];
     s.used = any = true;
-    tile_shape(chunk_bytes, default_tile(c, with_p2p, mostly_short_rows(cp), cp.payload), &s.tile_bytes, &s.tiles_per_chunk);
-    build_chunk_table(cp, chunk_bytes, s.tile_bytes, s.tiles_per_chunk);
+    s.code = launch_code(cp, c, chunk_bytes, false, true);  // the classes run one after another
+    if (s.code >= kWaveTiles) {
+      tile_shape(chunk_bytes, wave_tile(cp.payload), &s.tile_bytes, &s.tiles_per_chunk);
+      cp.chunk_desc.clear();
+      cp.desc_per = 1;
+    } else {
+      tile_shape(chunk_bytes, default_tile(c, with_p2p, mostly_short_rows(cp), cp.payload), &s.tile_bytes, &s.tiles_per_chunk);
+      build_chunk_table(cp, chunk_bytes, s.tile_bytes, s.tiles_per_chunk);
+    }
     build_skips(cp, chunk_bytes, s.tile_bytes, s.tiles_per_chunk, &s.skips, &s.ntickets);
     s.lay = layout_of(cp, 0, 1);
     if (s.lay.end > kStaticClassBytes && cp.desc_per == 1) {
@@ -133,9 +141,10 @@ extern "C" int ft_submit_static(ft_pool *p, const ft_desc *descs, uint32_t ndesc
       FT_HIP(p, hipGetLastError());
       zeroed = true;
     }
-    uint64_t wg = c == FT_P2P ? (uint64_t)sd.cu_count : (with_p2p || c == FT_P2H) ? 32u : 64u;
+    uint64_t wg = s.code >= kWaveTiles ? wave_workgroups(sd.cu_count, s.code, T.ntickets)
+                  : c == FT_P2P ? (uint64_t)sd.cu_count : (with_p2p || c == FT_P2H) ? 32u : 64u;
     if (wg > T.ntickets) wg = T.ntickets;
-    FT_HIP(p, launch_copy(T, c, (uint32_t)wg, stream, nullptr, nullptr));
+    FT_HIP(p, launch_copy(T, s.code, (uint32_t)wg, stream, nullptr, nullptr));
   }
   return FT_OK;
 }

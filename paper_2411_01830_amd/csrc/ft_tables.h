@@ -95,6 +95,17 @@ struct WgLogEntry {
   uint32_t _pad;
 };
 
+// Launch codes beside the three link classes: pool->pool in the kernel that gives every wavefront tiles of its own,
+// with workgroups of
+//   kWaveTiles       one wavefront, a workgroup per ticket
+//   kWaveTwoPerUnit  eight wavefronts, at most two workgroups per compute unit, which stride over the tickets
+//   kWaveOnePerUnit  sixteen wavefronts, at most one workgroup per compute unit, likewise
+// or'ed with kWaveStreams: nontemporal instead of ordinary loads (stores are nontemporal anyway).
+constexpr int kWaveTiles = 8, kWaveTwoPerUnit = 9, kWaveOnePerUnit = 10, kWaveStreams = 16;
+constexpr uint32_t wave_code_threads(int code) {
+  return (code & 15) == kWaveTiles ? 64u : (code & 15) == kWaveTwoPerUnit ? 512u : (code & 15) == kWaveOnePerUnit ? 1024u : 0u;
+}
+
 // Everything one class's kernel needs; passed by value as the kernel argument.
 struct ClassTable {
   const Phase *phases;

@@ -1,0 +1,159 @@
+// Host check of what the wave kernel (one tile per wavefront) relies on, built with the sanitizers: the windows that a
+// piece of a transfer is cut into (ft_windows.h, the kernel's own arithmetic) stay inside the piece and cover it, and
+// a ticket decoded without a cursor - 64 table entries compared at a time - names the bytes and the descriptor that
+// the general walk names, for every job that launch_code sends to that kernel.
+// Usage: wave_tiles <first seed> <count>
+#include <cstdio>
+#include <cstdlib>
+#include <random>
+#include <vector>
+#include "../../paper_2411_01830_amd/csrc/ft_plan.h"
+#include "../../paper_2411_01830_amd/csrc/ft_windows.h"
+using namespace ft;
+static uint64_t g_seed;
+#define CHECK(c) do { if (!(c)) { std::fprintf(stderr, "FAIL %s line %d seed %llu\n", #c, __LINE__, (unsigned long long)g_seed); std::abort(); } } while (0)
+
+template <uint32_t W>
+static void rows(uint32_t rb, uint64_t p, uint32_t take) {
+  const uint32_t c0 = (uint32_t)(p % rb);
+  const RowWindows w = row_windows<W>(rb, c0, take);
+  std::vector<uint8_t> hit(take, 0);
+  auto mark = [&](uint64_t row, uint64_t col, uint32_t n) {
+    const uint64_t b = row * rb + col;
+    CHECK(col + n <= rb && b >= c0 && b + n <= (uint64_t)c0 + take);
+    for (uint32_t i = 0; i < n; ++i) hit[b - c0 + i] = 1;
+  };
+  for (uint32_t q = 0; q < w.count; ++q) {
+    const RowCursor c = row_window<W>(w, q);
+    mark(c.row, row_window_col<W>(w, c), W);
+    if (q < 64) continue;
+    RowCursor d = row_window<W>(w, q - 64);  // reached by the kernel's step of 64 windows as well
+    row_window_next<W>(w, 64 / w.per_row, 64 % w.per_row * W, &d);
+    CHECK(d.row == c.row && d.col == c.col);
+  }
+  CHECK(w.short_first < W && w.short_last < W && W <= 16);
+  if (w.short_first) mark(0, c0, w.short_first);
+  if (w.short_last) mark(w.more, 0, w.short_last);
+  for (uint8_t h : hit) CHECK(h);
+}
+
+static void run(uint64_t dst, uint32_t n) {
+  const RunWindows w = run_windows(dst, n);
+  std::vector<uint8_t> hit(n, 0);
+  for (uint32_t j = 0; j < w.count + 130; ++j) {  // lanes past the last window repeat it
+    const uint32_t o = run_window_at(w, j);
+    CHECK(o + 16 <= n);
+    if (j > 0 && j + 1 < w.count) CHECK(((dst + o) & 15) == 0);
+    for (uint32_t i = 0; i < 16; ++i) hit[o + i] = 1;
+  }
+  CHECK(w.count <= n / 16 + 2);
+  for (uint8_t h : hit) CHECK(h);
+}
+
+static uint64_t n_tickets, n_jobs[32];
+
+static void job(std::mt19937_64 &r) {
+  auto U = [&](uint64_t a, uint64_t b) { return a + r() % (b - a + 1); };
+  ClassPlan cp;
+  const uint64_t Cs[] = {1024, 4096, 65536, 100000 / 16 * 16, 2u << 20};
+  const uint64_t C = Cs[U(0, 4)];
+  const uint32_t nf = (uint32_t)(r() % 4 == 0 ? U(1, 256) : U(1, 9));
+  const uint64_t scale = 1ull << U(6, 20);
+  for (uint32_t f = 0; f < nf; ++f) {
+    Func fn{};
+    fn.desc_off = (uint32_t)cp.xfers.size();
+    fn.ndesc = (uint32_t)(r() % 8 == 0 ? U(60, 140) : U(1, 7));
+    if (r() % 64 == 0) fn.ndesc = 5000;
+    for (uint32_t i = 0; i < fn.ndesc; ++i) {
+      Xfer x{};
+      x.rows = r() % 3 == 0 ? U(2, 60) : 1;
+      x.row_bytes = x.rows > 1 ? U(16, 6000) : U(1, fn.ndesc > 1000 ? 300 : scale);
+      x.src_pitch = x.dst_pitch = x.row_bytes + U(0, 99);
+      x.stream_off = fn.stream_bytes;
+      fn.stream_bytes += x.row_bytes * x.rows;
+      cp.xfers.push_back(x);
+    }
+    fn.nchunks = (fn.stream_bytes + C - 1) / C;
+    fn.func = f;
+    fn.weight = (uint32_t)U(1, 8);
+    cp.funcs.push_back(fn);
+    cp.payload += fn.stream_bytes;
+  }
+  CHECK(build_phases(cp.funcs, cp.phases, cp.slots, &cp.nchunks) == FT_OK);
+  const int code = launch_code(cp, FT_P2P, C, false, r() % 4 != 0);
+  CHECK(launch_code(cp, FT_P2P, C, true, true) == FT_P2P && launch_code(cp, FT_H2P, C, false, true) == FT_H2P);
+  n_jobs[code] += 1;
+  if (code < kWaveTiles) return;
+  uint64_t tile;
+  uint32_t tpc;
+  tile_shape(C, wave_tile(cp.payload), &tile, &tpc);
+  std::vector<Skip> skips;
+  uint64_t nt;
+  build_skips(cp, C, tile, tpc, &skips, &nt);
+  CHECK(nt < (1u << 31) && tile <= 16384 && wave_code_threads(code) != 0);
+  const uint64_t wg = wave_workgroups(256, code, nt);
+  CHECK(wg > 0 && wg <= nt && ((code & 15) != kWaveTiles || wg == nt));
+  const uint64_t stride = nt > 3000 ? nt / 3000 : 1;
+  for (uint64_t t = 0; t < nt; t += stride, ++n_tickets) {
+    // as the wave kernel decodes it
+    uint32_t v = (uint32_t)t;
+    for (size_t j0 = 0; j0 < skips.size(); j0 += 64) {
+      uint32_t before = 0;
+      for (size_t j = j0; j < j0 + 64 && j < skips.size(); ++j)
+        if (skips[j].at <= t) {
+          CHECK(skips[j].gap < 65536);
+          v += (uint32_t)skips[j].gap;
+          before += 1;
+        }
+      if (before < 64) break;
+    }
+    const uint32_t rank = v / tpc, ti = v - rank * tpc;
+    uint32_t idx = 0;
+    for (size_t j0 = 0; j0 < cp.phases.size() && idx == j0; j0 += 64)
+      for (size_t j = j0; j < j0 + 64 && j < cp.phases.size(); ++j) idx += cp.phases[j].rank_base <= rank ? 1 : 0;
+    const Phase &ph = cp.phases.at(idx - 1);
+    const uint32_t rel = rank - (uint32_t)ph.rank_base, round = rel / ph.nslots;
+    const Slot &sl = cp.slots.at(ph.slot_off + rel - round * ph.nslots);
+    const uint64_t k = (uint64_t)(((uint32_t)ph.round_base + round) * sl.weight + sl.i);
+    const Func &f = cp.funcs[sl.fl];
+    const uint64_t b0 = k * C + ti * tile;
+    uint32_t x = f.desc_off, nx = f.ndesc;
+    while (nx > 1) {
+      const uint32_t step = (nx + 63) / 64;
+      uint32_t at = 0;
+      for (uint32_t lane = 0; lane < 64; ++lane) at += lane * step < nx && cp.xfers[x + lane * step].stream_off <= b0 ? 1 : 0;
+      at = (at - 1) * step;
+      x += at;
+      nx = step < nx - at ? step : nx - at;
+    }
+    // the general walk
+    const uint64_t gv = ticket_to_tile(skips.data(), (uint32_t)skips.size(), t);
+    const ChunkId id = decode_rank(cp.phases.data(), (uint32_t)cp.phases.size(), cp.slots.data(), gv / tpc);
+    CHECK(gv == v && id.fl == sl.fl && id.k == k);
+    CHECK(x == find_xfer(cp.xfers.data(), f.desc_off, f.desc_off + f.ndesc - 1, b0));
+    CHECK(b0 < f.stream_bytes && cp.xfers[x].stream_off <= b0);
+  }
+}
+
+int main(int argc, char **argv) {
+  const uint64_t first = argc > 1 ? strtoull(argv[1], 0, 10) : 1, count = argc > 2 ? strtoull(argv[2], 0, 10) : 50;
+  for (uint32_t d = 0; d < 16; ++d)
+    for (uint32_t n = 16; n < 9000; n += n < 200 ? 1 : 61) run(d, n);
+  for (g_seed = first; g_seed < first + count; ++g_seed) {
+    std::mt19937_64 r(g_seed);
+    auto U = [&](uint64_t a, uint64_t b) { return a + r() % (b - a + 1); };
+    for (int i = 0; i < 3000; ++i) {
+      const uint32_t rb = (uint32_t)(i % 97 == 0 ? (1u << 30) - U(1, 99) : U(16, i % 3 == 0 ? 40 : i % 3 == 1 ? 400 : 70000));
+      const uint64_t p = i % 2 ? rb * U(0, 9) : i % 97 == 0 ? rb - U(1, 300) : U(0, 9ull * rb);
+      rows<16>(rb, p, (uint32_t)U(1, i % 5 == 0 ? 40 : 16400));
+      rows<4>((uint32_t)U(4, 15), U(0, 100000), (uint32_t)U(1, 3000));
+      rows<1>((uint32_t)U(1, 3), U(0, 100000), (uint32_t)U(1, 3000));
+    }
+    for (int i = 0; i < 8; ++i) job(r);
+  }
+  std::printf("tickets %llu; jobs: own kernel %llu, a workgroup per tile %llu, two workgroups per unit %llu, one %llu\n",
+              (unsigned long long)n_tickets, (unsigned long long)n_jobs[FT_P2P], (unsigned long long)n_jobs[kWaveTiles],
+              (unsigned long long)n_jobs[kWaveTwoPerUnit], (unsigned long long)n_jobs[kWaveOnePerUnit]);
+  std::printf("done %llu..%llu\n", (unsigned long long)first, (unsigned long long)(first + count - 1));
+  return 0;
+}

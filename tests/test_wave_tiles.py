@@ -1,0 +1,104 @@
+"""The kernel that gives every wavefront tiles of its own: jobs of at most 16 MiB, of at most 128 MiB, and jobs of
+pitched rows, at the sizes where its windows, its tiles and the rule that picks it change. Bit-exact against the oracle."""
+import numpy as np
+import pytest
+
+from oracle import OracleEngine
+from workloads import make_descs, FT_HOST, FT_POOL
+from workloads import format as fmt
+from test_host_logic import _host_sanitizer_run
+
+KiB, MiB = 1 << 10, 1 << 20
+
+
+def test_windows_and_decode_on_the_host(tmp_path):
+    """tests/host/wave_tiles.cpp: the kernel's window arithmetic covers every piece and stays inside it; a ticket
+    decoded by comparing 64 entries at a time names what the general walk names."""
+    _host_sanitizer_run(tmp_path, "wave_tiles", ["ft_plan.cpp", "ft_pool.cpp"], ["1", "60"], "done 1..60")
+
+
+def _runs(rng, n, sizes, funcs):
+    """Contiguous pieces: (row_bytes, rows, src pitch, dst pitch, function, src shift, dst shift)."""
+    return [(int(rng.choice(sizes)), 1, 0, 0, i % funcs, int(rng.integers(0, 16)), int(rng.integers(0, 16))) for i in range(n)]
+
+
+def _rows(rng, n, widths, total, funcs):
+    out = []
+    for i in range(n):
+        rb = int(rng.choice(widths))
+        out.append((rb, max(2, total // n // rb), rb + int(rng.integers(0, 50)), rb + int(rng.integers(0, 3)) * 7, i % funcs,
+                    int(rng.integers(0, 16)), int(rng.integers(0, 16))))
+    return out
+
+
+# name, pieces(rng), weights, chunk, flags, workgroups of the pool->pool launch (None: not asked)
+CASES = [
+    ("bytes around a window", lambda g: _runs(g, 200, [1, 15, 16, 17, 31, 32, 33, 1023, 1024, 1025], 3), [1, 2, 5], 1024, 0, "tickets"),
+    ("one tile and its edges", lambda g: _runs(g, 40, [2047, 2048, 2049, 8191, 8192, 8193, 8208], 2), [1, 1], 64 * KiB, 0, "tickets"),
+    ("5000 descriptors of one function", lambda g: _runs(g, 5000, [1, 60, 300, 700], 1), [1], 256 * KiB, 0, "tickets"),
+    ("256 functions", lambda g: _runs(g, 600, [64, 5000, 9000], 256), list(range(1, 257)), 4 * KiB, 0, "tickets"),
+    ("257 functions", lambda g: _runs(g, 600, [64, 5000, 9000], 257), [1] * 257, 4 * KiB, 0, None),
+    ("chunks under 1 KiB", lambda g: _runs(g, 20, [300, 5000], 2), [1, 3], 512, 0, None),
+    ("logged", lambda g: _runs(g, 60, [40, 3000, 70000], 4), [1, 2, 3, 4], 64 * KiB, fmt.FT_LOG, "tickets"),
+    ("detached", lambda g: _runs(g, 60, [40, 3000, 70000], 4), [1, 2, 3, 4], 64 * KiB, fmt.FT_DETACHED, "tickets"),
+    ("over 16 MiB", lambda g: _runs(g, 30, [600 * KiB, 700 * KiB + 5], 3), [1, 2, 4], 256 * KiB, 0, "one a unit"),
+    ("rows of 16 bytes and a bit", lambda g: _rows(g, 20, [16, 17, 31, 32, 33], 2 * MiB, 2), [1, 2], 100000 // 16 * 16, 0, "tickets"),
+    ("rows under 16 bytes", lambda g: _rows(g, 20, [1, 2, 3, 4, 5, 7, 8, 12, 15], 400 * KiB, 2), [1, 2], 64 * KiB, 0, None),
+    ("rows longer than a tile", lambda g: _rows(g, 6, [8193, 20000, 66000], 4 * MiB, 2), [3, 1], 1 * MiB, 0, "tickets"),
+    ("short rows over 16 MiB", lambda g: _rows(g, 24, [20, 100, 2000], 18 * MiB, 2), [3, 1], 256 * KiB, 0, "two a unit"),
+    ("long rows over 16 MiB", lambda g: _rows(g, 12, [2100, 5760, 30001], 18 * MiB, 2), [3, 1], 256 * KiB, 0, "one a unit"),
+    ("rows between 1 MiB pitches", lambda g: [(100, 9, 1 << 20, 200, 0, 3, 5), (70, 5, 100, 1 << 20, 1, 1, 2), (50, 6, (1 << 20) + 1, 60, 0, 0, 0)],
+     [1, 1], 64 * KiB, 0, None),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+@pytest.mark.parametrize("beside_host_link", [False, True])
+def test_wave_tiles_match_the_oracle(case, beside_host_link):
+    import torch
+    from paper_2411_01830_amd import binding, harness
+    name, pieces, weights, chunk, flags, shape = case
+    print(f"case wave tiles: {name}, host link beside: {beside_host_link}", flush=True)
+    rng = np.random.default_rng(len(name) + beside_host_link)
+    orc, eng = OracleEngine(), harness.GpuEngine()
+    try:
+        for e in (orc, eng):
+            e.host_arena(1 << 20)
+            e.pool_create(128 * MiB, 4 * KiB)
+        data = rng.integers(0, 256, 1 << 19, dtype=np.uint8)
+        orc.write_host(0, data)
+        eng.write_host(0, data)
+        recs = []
+        for rb, rows, sp, dp, f, ss, ds in pieces(rng):
+            es, ed = (rows - 1) * sp + rb, (rows - 1) * dp + rb
+            a, b = orc.slab_alloc(es + 16), orc.slab_alloc(ed + 16)
+            assert eng.slab_alloc(es + 16) == a and eng.slab_alloc(ed + 16) == b
+            fill = rng.integers(0, 256, es + 16, dtype=np.uint8)
+            orc.write_pool(a, fill)
+            eng.write_pool(a, fill)
+            recs.append(dict(func=f, src_space=FT_POOL, dst_space=FT_POOL, src=a + ss, dst=b + ds, row_bytes=rb, rows=rows,
+                             src_pitch=sp if rows > 1 else rb, dst_pitch=dp if rows > 1 else rb))
+        if beside_host_link:
+            b = orc.slab_alloc(200000)
+            assert eng.slab_alloc(200000) == b
+            recs.append(dict(func=0, src_space=FT_HOST, dst_space=FT_POOL, src=77, dst=b + 3, row_bytes=190001))
+        d = make_descs(recs)
+        jo = orc.submit(d, weights, chunk)
+        orc.wait(jo)
+        for _ in range(2):
+            jg = eng.submit(d, weights, chunk, flags | fmt.FT_KEEP | fmt.FT_VALIDATE)
+            eng.wait(jg)
+            assert eng.job_schedule(jg, 2) == orc.job_schedule(jo, 2)
+            st = binding.job_stats(eng.pool, jg).cls[2]
+            cus = torch.cuda.get_device_properties(0).multi_processor_count
+            want = {"tickets": st.tickets, "two a unit": 2 * cus, "one a unit": cus, None: st.workgroups}
+            if not beside_host_link:
+                assert st.workgroups == want[shape], (st.workgroups, st.tickets)
+            if flags & fmt.FT_LOG:
+                log = binding.job_log(eng.pool, jg, 2)
+                assert int(log["bytes"].sum()) == st.payload_bytes and len(log["bytes"]) == st.tickets
+            binding.job_release(eng.pool, jg)
+        assert np.array_equal(torch.cat([t for t, _ in eng.segments]).cpu().numpy(), orc.pool_mem)
+    finally:
+        eng.close()
