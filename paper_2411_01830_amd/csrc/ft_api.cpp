@@ -288,8 +288,9 @@ int run_dma(ft_pool *p, const ClassPlan &cp, uint64_t C, int cls, hipStream_t st
 }
 
 void retire(ft_pool *p, Job *job) {
+  SlabPool::Place near = p->slabs.begin();
   for (size_t i = 0; i < job->allocs.size(); ++i) {
-    Allocation *al = p->slabs.at(job->allocs[i]);
+    Allocation *al = p->slabs.at(job->allocs[i], &near);
     // (the allocation may have been returned in stream order meanwhile and its offset handed out again)
     if (al && al->serial == job->alloc_serials[i] && al->busy > 0) al->busy -= 1;
   }
@@ -301,8 +302,9 @@ void retire(ft_pool *p, Job *job) {
 void hold_allocations(ft_pool *p, Job *job, const std::vector<uint64_t> &allocs) {
   job->allocs = allocs;
   job->alloc_serials.assign(allocs.size(), 0);
+  SlabPool::Place near = p->slabs.begin();
   for (size_t i = 0; i < allocs.size(); ++i) {
-    Allocation *al = p->slabs.at(allocs[i]);
+    Allocation *al = p->slabs.at(allocs[i], &near);
     if (al) {
       al->busy += 1;
       job->alloc_serials[i] = al->serial;
@@ -630,11 +632,11 @@ int launch_with_uploaded_tables(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t
   }
   int rc = get_blob(p, total, true, &job->tables);
   if (rc != FT_OK) return fail_submit(p, job, rc);
-  std::memset(job->tables.host, 0, total);
   for (int c = 0; c < FT_NCLASS; ++c) {
     const ClassPlan &cp = plan.cls[c];
     if (cp.nchunks == 0) continue;
     ClassRun &r = job->run[c];
+    std::memset(job->tables.host + lay[c].ticket, 0, 256);  // the counter starts at zero; gaps between tables are never read
     rc = prepare_class(p, job, c, cp, lay[c], job->tables.host, job->tables.dev, chunk_bytes, timing);
     if (rc != FT_OK) return fail_submit(p, job, rc);
     ClassTable &T = r.table;

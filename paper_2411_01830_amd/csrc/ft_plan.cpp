@@ -358,9 +358,53 @@ int plan_submit(SlabPool &pool, const std::vector<HostWindow> &windows, const ft
     if (d.rows > 1 && (d.src_pitch < d.row_bytes || d.dst_pitch < d.row_bytes)) return FT_EINVAL;
   }
 
+  // ---- split by class, per-function streams in submission order: how many descriptors each function has in each class
+  // says where each one goes, so that it is resolved into its place
+  auto class_of = [](const ft_desc &d) {
+    return d.src_space != FT_POOL ? FT_H2P : (d.dst_space != FT_POOL ? FT_P2H : FT_P2P);
+  };
+  uint32_t in_class[FT_NCLASS] = {0, 0, 0};
+  for (uint32_t i = 0; i < ndesc; ++i) in_class[class_of(descs[i])] += 1;
+  std::vector<uint32_t> fn_of[FT_NCLASS];    // caller's function -> index into the class's table
+  std::vector<uint32_t> placed[FT_NCLASS];   // per function of the class: descriptors already in place
+  for (int c = 0; c < FT_NCLASS; ++c) {
+    ClassPlan &cp = out->cls[c];
+    cp = ClassPlan();
+    if (in_class[c] == 0) continue;  // a class without traffic costs no allocation (passing one tensor: two of three)
+    std::vector<uint32_t> &count = fn_of[c];
+    count.assign(nfunc, 0);
+    if (in_class[c] == ndesc) {
+      for (uint32_t i = 0; i < ndesc; ++i) count[descs[i].func] += 1;
+    } else {
+      for (uint32_t i = 0; i < ndesc; ++i)
+        if (class_of(descs[i]) == c) count[descs[i].func] += 1;
+    }
+    uint32_t off = 0;
+    for (uint32_t f = 0; f < nfunc; ++f) {
+      if (count[f] == 0) continue;
+      Func fn;
+      fn.stream_bytes = 0;
+      fn.nchunks = 0;
+      fn.func = f;
+      fn.weight = weights[f];
+      fn.desc_off = off;
+      fn.ndesc = count[f];
+      fn.chunk_off = 0;
+      fn._pad = 0;
+      fn.chunk_base = 0;
+      off += count[f];
+      count[f] = (uint32_t)cp.funcs.size();  // from here on: its place in the table
+      cp.funcs.push_back(fn);
+    }
+    cp.xfers.resize(off);
+    placed[c].assign(cp.funcs.size(), 0);
+  }
+  bool stream_overflow = false;
+
   // ---- pass 2: ranges; resolve both sides to device-visible addresses
-  std::vector<Xfer> resolved(ndesc);
-  std::vector<uint64_t> used;
+  std::vector<const Xfer *> resolved(flags & FT_VALIDATE ? ndesc : 0);  // for pass 3: descriptor i, resolved
+  std::vector<uint64_t> used[2];
+  SlabPool::Place near[2] = {pool.begin(), pool.begin()};
   // The allocations met last, most recent first: descriptors of one submit mostly name the
   // same few (the crops of a frame, the packed buffer of a consumer), and a hit spares the
   // search of the allocation map, the search of the segment list and an entry in `used`.
@@ -371,7 +415,11 @@ int plan_submit(SlabPool &pool, const std::vector<HostWindow> &windows, const ft
   Recent recent[4];
   for (uint32_t i = 0; i < ndesc; ++i) {
     const ft_desc &d = descs[i];
-    Xfer x;
+    const int c = class_of(d);
+    ClassPlan &cp = out->cls[c];
+    const uint32_t fl = fn_of[c][d.func];
+    Func &fn = cp.funcs[fl];
+    Xfer &x = cp.xfers[fn.desc_off + placed[c][fl]++];
     x.row_bytes = d.row_bytes;
     x.rows = d.rows;
     x.src_pitch = d.rows > 1 ? d.src_pitch : d.row_bytes;
@@ -397,9 +445,9 @@ int plan_submit(SlabPool &pool, const std::vector<HostWindow> &windows, const ft
           }
         if (hit < 0) {
           uint64_t start;
-          const Allocation *al = pool.owner(off, ext, &start);
+          const Allocation *al = pool.owner(off, ext, &start, &near[side]);
           if (al == nullptr) return FT_ERANGE;
-          used.push_back(start);
+          used[side].push_back(start);
           Recent r;
           r.lo = start;
           r.hi = start + al->nslabs * pool.slab_bytes();
@@ -430,7 +478,13 @@ int plan_submit(SlabPool &pool, const std::vector<HostWindow> &windows, const ft
       }
       if (side == 0) x.src = addr; else x.dst = addr;
     }
-    resolved[i] = x;
+    if (flags & FT_VALIDATE) resolved[i] = &x;
+    if (x.rows > 1 && x.src_pitch == x.row_bytes && x.dst_pitch == x.row_bytes) {
+      x.row_bytes = x.src_pitch = x.dst_pitch = payload;  // rows that touch are one contiguous run
+      x.rows = 1;
+    }
+    x.stream_off = fn.stream_bytes;
+    if (add_overflow(fn.stream_bytes, payload, &fn.stream_bytes)) stream_overflow = true;
   }
 
   // ---- pass 3: exact aliasing check, on request
@@ -449,7 +503,7 @@ int plan_submit(SlabPool &pool, const std::vector<HostWindow> &windows, const ft
       std::vector<Side> sides;
       for (uint32_t i = 0; i < ndesc; ++i) {
         const ft_desc &d = descs[i];
-        const Xfer &x = resolved[i];
+        const Xfer &x = *resolved[i];
         uint64_t ext = 0;
         // compare in the caller's own coordinates of that space (offsets or addresses)
         if (d.dst_space == space) {
@@ -475,7 +529,7 @@ int plan_submit(SlabPool &pool, const std::vector<HostWindow> &windows, const ft
         }
         if (has_dst && g1 - g0 > 1)
           for (size_t k = g0; k < g1; ++k) {
-            const Xfer &x = resolved[sides[k].desc];
+            const Xfer &x = *resolved[sides[k].desc];
             if (sides[k].is_dst) push_rows(dst, sides[k].lo, x.row_bytes, x.rows, x.dst_pitch);
             else push_rows(src, sides[k].lo, x.row_bytes, x.rows, x.src_pitch);
           }
@@ -485,89 +539,18 @@ int plan_submit(SlabPool &pool, const std::vector<HostWindow> &windows, const ft
     }
   }
 
-  // ---- split by class, per-function streams in submission order
-  std::sort(used.begin(), used.end());
-  used.erase(std::unique(used.begin(), used.end()), used.end());
-  out->allocs = used;
-  for (int c = 0; c < FT_NCLASS; ++c) {
-    ClassPlan &cp = out->cls[c];
-    cp = ClassPlan();
-    auto class_of = [](const ft_desc &d) {
-      return d.src_space != FT_POOL ? FT_H2P : (d.dst_space != FT_POOL ? FT_P2H : FT_P2P);
-    };
-    bool any = false;
-    for (uint32_t i = 0; i < ndesc && !any; ++i) any = class_of(descs[i]) == c;
-    if (!any) continue;  // a class without traffic costs no allocation (passing one tensor: two of three)
-    if (ndesc == 1) {
-      // one descriptor: one function with one stream, nothing to count or to sort into place
-      Xfer x = resolved[0];
-      if (x.rows > 1 && x.src_pitch == x.row_bytes && x.dst_pitch == x.row_bytes) {
-        x.row_bytes *= x.rows;  // rows that touch are one contiguous run (cannot wrap: checked in pass 2)
-        x.rows = 1;
-        x.src_pitch = x.dst_pitch = x.row_bytes;
-      }
-      x.stream_off = 0;
-      Func fn;
-      fn.stream_bytes = x.row_bytes * x.rows;
+  // the allocations in ascending order, each once; usually either side names them in that order already
+  for (int side = 0; side < 2; ++side)
+    if (!std::is_sorted(used[side].begin(), used[side].end())) std::sort(used[side].begin(), used[side].end());
+  out->allocs.resize(used[0].size() + used[1].size());
+  std::merge(used[0].begin(), used[0].end(), used[1].begin(), used[1].end(), out->allocs.begin());
+  out->allocs.erase(std::unique(out->allocs.begin(), out->allocs.end()), out->allocs.end());
+  if (stream_overflow) return FT_ERANGE;
+  for (ClassPlan &cp : out->cls) {
+    for (Func &fn : cp.funcs) {
       fn.nchunks = fn.stream_bytes / chunk_bytes + (fn.stream_bytes % chunk_bytes != 0);
-      fn.func = descs[0].func;
-      fn.weight = weights[descs[0].func];
-      fn.desc_off = 0;
-      fn.ndesc = 1;
-      fn.chunk_off = 0;
-      fn._pad = 0;
-      fn.chunk_base = 0;
-      cp.funcs.push_back(fn);
-      cp.xfers.push_back(x);
-      cp.payload = fn.stream_bytes;
-      int rc = build_phases(cp.funcs, cp.phases, cp.slots, &cp.nchunks);
-      if (rc != FT_OK) return rc;
-      continue;
+      cp.payload += fn.stream_bytes;
     }
-    std::vector<uint64_t> stream(nfunc, 0);
-    std::vector<uint32_t> count(nfunc, 0);
-    for (uint32_t i = 0; i < ndesc; ++i)
-      if (class_of(descs[i]) == c) {
-        count[descs[i].func] += 1;
-        uint64_t pay = resolved[i].row_bytes * resolved[i].rows;
-        if (add_overflow(stream[descs[i].func], pay, &stream[descs[i].func])) return FT_ERANGE;
-      }
-    std::vector<int64_t> slot_of(nfunc, -1);
-    uint32_t off = 0;
-    for (uint32_t f = 0; f < nfunc; ++f) {
-      if (stream[f] == 0) continue;
-      Func fn;
-      fn.stream_bytes = stream[f];
-      fn.nchunks = stream[f] / chunk_bytes + (stream[f] % chunk_bytes != 0);
-      fn.func = f;
-      fn.weight = weights[f];
-      fn.desc_off = off;
-      fn.ndesc = count[f];
-      fn.chunk_off = 0;
-      fn._pad = 0;
-      fn.chunk_base = 0;
-      off += count[f];
-      slot_of[f] = (int64_t)cp.funcs.size();
-      cp.funcs.push_back(fn);
-      cp.payload += stream[f];
-    }
-    cp.xfers.resize(off);
-    std::vector<uint32_t> fill(cp.funcs.size(), 0);
-    std::vector<uint64_t> run(cp.funcs.size(), 0);
-    for (uint32_t i = 0; i < ndesc; ++i)
-      if (class_of(descs[i]) == c) {
-        size_t fl = (size_t)slot_of[descs[i].func];
-        Xfer x = resolved[i];
-        // a pitched descriptor whose rows touch is one contiguous run
-        if (x.rows > 1 && x.src_pitch == x.row_bytes && x.dst_pitch == x.row_bytes) {
-          x.row_bytes *= x.rows;
-          x.rows = 1;
-          x.src_pitch = x.dst_pitch = x.row_bytes;
-        }
-        x.stream_off = run[fl];
-        run[fl] += x.row_bytes * x.rows;
-        cp.xfers[cp.funcs[fl].desc_off + fill[fl]++] = x;
-      }
     int rc = build_phases(cp.funcs, cp.phases, cp.slots, &cp.nchunks);
     if (rc != FT_OK) return rc;
   }

@@ -104,19 +104,43 @@ int SlabPool::free(uint64_t off, bool ordered) {
   return FT_OK;
 }
 
-Allocation *SlabPool::owner(uint64_t off, uint64_t extent, uint64_t *start_out) {
-  auto it = allocs_.upper_bound(off);
+Allocation *SlabPool::at(uint64_t start) {
+  auto it = allocs_.find(start);
+  return it == allocs_.end() ? nullptr : &it->second;
+}
+
+Allocation *SlabPool::owner(uint64_t off, uint64_t extent, uint64_t *start_out, Place *near) {
+  Place it = *near;
+  for (int step = 0; step < 2 && it != allocs_.end(); ++step, ++it) {
+    const uint64_t a0 = it->first, a1 = a0 + it->second.nslabs * slab_;
+    if (off < a0) break;
+    if (off >= a1) continue;
+    if (extent > a1 - off) return nullptr;  // allocations do not overlap: no other one holds `off`
+    *near = it;
+    if (start_out) *start_out = a0;
+    return &it->second;
+  }
+  it = allocs_.upper_bound(off);
   if (it == allocs_.begin()) return nullptr;
   --it;
-  uint64_t a0 = it->first, a1 = a0 + it->second.nslabs * slab_;
-  if (off < a0 || off >= a1 || extent > a1 - off) return nullptr;
+  const uint64_t a0 = it->first, a1 = a0 + it->second.nslabs * slab_;
+  if (off >= a1 || extent > a1 - off) return nullptr;
+  *near = it;
   if (start_out) *start_out = a0;
   return &it->second;
 }
 
-Allocation *SlabPool::at(uint64_t start) {
-  auto it = allocs_.find(start);
-  return it == allocs_.end() ? nullptr : &it->second;
+Allocation *SlabPool::at(uint64_t start, Place *near) {
+  Place it = *near;
+  for (int step = 0; step < 2 && it != allocs_.end(); ++step, ++it)
+    if (it->first == start) {
+      *near = it;
+      return &it->second;
+    }
+  it = allocs_.find(start);
+  if (it == allocs_.end()) return nullptr;
+  *near = it;
+  return &it->second;
 }
 
 void *SlabPool::ptr(uint64_t off) const {

@@ -35,9 +35,14 @@ class SlabPool {
   // FT_EBUSY while a job that has not been waited for refers to the allocation, unless `ordered`:
   // then the caller vouches that whatever reuses the slabs is ordered after those jobs on the device.
   int free(uint64_t off, bool ordered = false);
-  // Live allocation containing [off, off+extent), or nullptr. *start_out = its offset.
-  Allocation *owner(uint64_t off, uint64_t extent, uint64_t *start_out);
   Allocation *at(uint64_t start);
+  // Live allocation containing [off, off+extent), or nullptr. *start_out = its offset; and the one at `start`. For
+  // callers that ask for one allocation after another, mostly in ascending order: `near` is where the last answer lay (begin() at first; valid while nothing is allocated or freed), and the allocation behind it is
+  // looked at before the map is searched. A thousand tensors next to each other: 0.01 us an answer instead of 0.1.
+  typedef std::map<uint64_t, Allocation>::iterator Place;
+  Place begin() { return allocs_.begin(); }
+  Allocation *owner(uint64_t off, uint64_t extent, uint64_t *start_out, Place *near);
+  Allocation *at(uint64_t start, Place *near);
   void *ptr(uint64_t off) const;
   uint64_t slab_bytes() const { return slab_; }
   uint64_t total_bytes() const { return total_slabs_ * slab_; }
