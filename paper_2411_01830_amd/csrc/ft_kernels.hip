@@ -92,7 +92,9 @@ typedef uint8_t FT_GLOBAL *GByteP;
 // 260 us and then ended 80 us later, when the L2 had written its lines back over the link (50 GB/s);
 // written through, the link carries them while the kernel runs (55 GB/s, what host->pool reaches on the
 // same buffers). `sc0 sc1` measured 53.4 GB/s, `sc0 sc1 nt` 53.5. Towards HBM every other combination
-// of the bits is slower than `nt` alone.
+// of the bits is slower than `nt` alone. (The stores are inline assembly, and the compiler does not keep the next
+// instructions from writing a store's data registers before it has read them, which takes two wait states on this
+// architecture: hence the s_nop behind each.)
 constexpr int kStream = 1, kToHost = 2;
 
 template <int NT>
@@ -109,7 +111,7 @@ __device__ __forceinline__ u32x4 ld16_any(uint64_t addr) {
 }
 template <int NT>
 __device__ __forceinline__ void st16(uint64_t addr, u32x4 v) {
-  if (NT == kToHost) asm volatile("global_store_dwordx4 %0, %1, off sc1" ::"v"(addr), "v"(v) : "memory");
+  if (NT == kToHost) asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(addr), "v"(v) : "memory");
   else if (NT) __builtin_nontemporal_store(v, reinterpret_cast<GVecP>(addr));
   else *reinterpret_cast<GVecP>(addr) = v;
 }
