@@ -385,7 +385,7 @@ namespace ft {
 // Tile shape per class, then the descriptor table and the runs of empty tiles that go with it.
 void shape_classes(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_bytes) {
   const bool with_p2p = plan.cls[FT_P2P].nchunks > 0;
-  const bool alone = plan.cls[FT_H2P].nchunks == 0 && plan.cls[FT_P2H].nchunks == 0;
+  const bool alone = (plan.cls[FT_H2P].nchunks != 0) + (plan.cls[FT_P2H].nchunks != 0) + (plan.cls[FT_P2P].nchunks != 0) == 1;
   for (int c = 0; c < FT_NCLASS; ++c) {
     ClassPlan &cp = plan.cls[c];
     if (cp.nchunks == 0) continue;
@@ -394,7 +394,7 @@ void shape_classes(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_bytes)
     const bool short_rows = mostly_short_rows(cp);
     r.code = launch_code(cp, c, chunk_bytes, tn.workgroups != 0 || tn.tile_bytes != 0, alone);
     if (r.code >= kWaveTiles) {
-      tile_shape(chunk_bytes, wave_tile(cp.payload), &r.tile_bytes, &r.tiles_per_chunk);
+      tile_shape(chunk_bytes, wave_tile(r.code, cp.payload), &r.tile_bytes, &r.tiles_per_chunk);
       cp.chunk_desc.clear();  // a wavefront finds its descriptor by comparing 64 of them at a time
       cp.desc_per = 1;
     } else {
@@ -523,12 +523,13 @@ int launch_with_the_launch(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chun
   // host->pool: more than 64 tiles of 16 KiB requested at once is more than the link
   // takes (2 MiB as 128 x 16 KiB: 52 us; as 64 workgroups drawing tickets: 43 us)
   const bool wave = r.code >= kWaveTiles;
-  const uint64_t most = cp.payload <= kWaveTilesBytes && wave ? ntickets : only == FT_P2P ? (uint64_t)p->ctx->cu_count : only == FT_H2P ? 64u : 128u;
+  const uint64_t most = wave && cp.payload <= (only == FT_P2P ? kWaveTilesBytes : kWaveLinkTilesBytes) ? ntickets
+                        : only == FT_P2P ? (uint64_t)p->ctx->cu_count : only == FT_H2P ? 64u : 128u;
   // one contiguous transfer between 16-byte aligned addresses (any length): the workgroups share the tiles out
   // themselves (ClassTable::single >= 2). Pool->pool only where a small chunk makes small tiles, of which the counter
   // hands out no more than 70 million a second (1 MiB in chunks of 512 bytes: 5.7 us dealt out, 31 us by tickets);
   // whole 64 KiB tiles are faster by tickets (256 MiB 99 us dealt out, 83 us by tickets, 1 GiB 403 and 312 us).
-  const bool direct = (only != FT_P2P || (!wave && r.tile_bytes < 64 * 1024)) && cp.funcs.size() == 1 &&
+  const bool direct = !wave && (only != FT_P2P || r.tile_bytes < 64 * 1024) && cp.funcs.size() == 1 &&
                       cp.xfers.size() == 1 && cp.funcs[0].chunk_base == 0 && !(flags & FT_LOG) &&
                       cp.xfers[0].rows == 1 && ((cp.xfers[0].src | cp.xfers[0].dst) & 15) == 0;
   const bool each_its_own = wave || (!direct && ntickets <= most);  // no counter

@@ -94,8 +94,8 @@ typedef uint8_t FT_GLOBAL *GByteP;
 // same buffers). `sc0 sc1` measured 53.4 GB/s, `sc0 sc1 nt` 53.5. Towards HBM every other combination
 // of the bits is slower than `nt` alone. (The stores are inline assembly, and the compiler does not keep the next
 // instructions from writing a store's data registers before it has read them, which takes two wait states on this
-// architecture: hence the s_nop behind each.)
-constexpr int kStream = 1, kToHost = 2;
+// architecture: hence the s_nop behind each.) kFromHost: as kStream, for the wave kernel's sources in host memory.
+constexpr int kStream = 1, kToHost = 2, kFromHost = 3;
 
 template <int NT>
 __device__ __forceinline__ u32x4 ld16(uint64_t addr) {
@@ -1028,8 +1028,8 @@ __global__ __launch_bounds__(kThreads, (CLS == 2 ? 1 : 2)) void ft_copy_kernel(C
 
 // ---- one tile per wavefront -------------------------------------------------------------------------
 //
-// The kernel of pool->pool jobs that latency bounds rather than HBM: jobs of at most 16 MiB and jobs of pitched
-// rows (the rule stands with launch_code in ft_api.cpp). Every wavefront takes tiles of its own, of 1 .. 16 KiB,
+// The kernel of jobs that latency bounds rather than HBM or the host link: pool->pool jobs of some MiB and of pitched
+// rows, host-link jobs of many small pieces (the rules stand with launch_code in ft_plan.cpp). Every wavefront takes tiles of its own, of 1 .. 16 KiB,
 // decodes them itself and moves them without a barrier, so a tile's memory round trips (table reads, one or
 // more per piece) overlap those of the other 15 wavefronts of its compute unit. The host sends it only
 // what 32-bit arithmetic covers (wave_tiles_fit): its instructions arrive from memory at every launch, and a
@@ -1114,10 +1114,14 @@ __device__ __forceinline__ Work decode_ticket_wave(const ClassTable &T, const Co
 template <class V, int NT>
 __device__ __forceinline__ V ld_off(uint64_t base, uint32_t off) {
   const V FT_GLOBAL *at = reinterpret_cast<const V FT_GLOBAL *>(reinterpret_cast<const char FT_GLOBAL *>(base) + off);
-  return NT ? __builtin_nontemporal_load(at) : *at;
+  return NT == kStream || NT == kFromHost ? __builtin_nontemporal_load(at) : *at;
 }
-template <class V>
+template <class V, int NT>
 __device__ __forceinline__ void st_off(uint64_t base, uint32_t off, V v) {
+  if (NT == kToHost && sizeof(V) == 16) {  // written through to the fabric at once
+    asm volatile("global_store_dwordx4 %0, %1, %2 sc1\n\ts_nop 1" ::"v"(off), "v"(v), "s"(base) : "memory");
+    return;
+  }
   __builtin_nontemporal_store(v, reinterpret_cast<V FT_GLOBAL *>(reinterpret_cast<char FT_GLOBAL *>(base) + off));
 }
 
@@ -1130,7 +1134,7 @@ __device__ __forceinline__ void wave_run_pass(uint64_t d, uint64_t s, const RunW
   for (uint32_t i = 0; i < R; ++i) v[i] = ld_off<u32x4_any, NT>(s, run_window_at(w, blk + lane + i * 64));
 #pragma unroll
   for (uint32_t i = 0; i < R; ++i)
-    if (blk + lane + i * 64 < w.count) st_off<u32x4_any>(d, run_window_at(w, blk + lane + i * 64), v[i]);
+    if (blk + lane + i * 64 < w.count) st_off<u32x4_any, NT>(d, run_window_at(w, blk + lane + i * 64), v[i]);
 }
 
 // n bytes (< 2^30) of one contiguous run. Stores are whole destination granules but for the two ends; a source at
@@ -1141,7 +1145,7 @@ __device__ __forceinline__ void wave_copy_run(uint64_t d, uint64_t s, uint32_t n
     if (lane < n) st8(d + lane, ld8(s + lane));
     return;
   }
-  const RunWindows w = run_windows(d, n);
+  const RunWindows w = run_windows(NT == kFromHost ? s : d, n);  // whole granules on the side that is dearer
   // a pass no deeper than what is left: a lane's load beyond the last window costs as much as any other
   for (uint32_t blk = 0; blk < w.count;) {
     const uint32_t deep = (w.count - blk + 63) / 64;
@@ -1176,7 +1180,7 @@ __device__ __forceinline__ void wave_rows_pass(uint64_t d, uint64_t s, uint32_t 
   asm("" : "+v"(c.row), "+v"(c.col));  // (the compiler would keep every window's place in registers)
 #pragma unroll
   for (uint32_t i = 0; i < R; ++i) {
-    if (i * 64 < left) st_off<u32x4_any>(d, c.row * d_pitch + row_window_col<16>(w, c), v[i]);
+    if (i * 64 < left) st_off<u32x4_any, NT>(d, c.row * d_pitch + row_window_col<16>(w, c), v[i]);
     row_window_next<16>(w, rows, cols, &c);
   }
   *at = next;
@@ -1216,7 +1220,7 @@ __device__ __forceinline__ void wave_copy_rows(const Xfer &X, uint32_t p, uint32
       blk += 9 * 64;
     }
   }
-  if (edge) st_off<uint8_t>(d, ed, eb);
+  if (edge) st_off<uint8_t, 0>(d, ed, eb);
 }
 
 template <int NT>
@@ -1318,7 +1322,9 @@ hipError_t launch_copy(const ClassTable &T, int link_class, uint32_t workgroups,
   if (link_class >= kWaveTiles) {
     const uint32_t threads = wave_code_threads(link_class);
     if (threads == 0) return hipErrorInvalidValue;
-    if (link_class & kWaveStreams) hipExtLaunchKernelGGL(ft_wave_kernel<kStream>, grid, dim3(threads), 0, stream, ev_start, ev_stop, 0, T, B);
+    if (link_class & kWaveFromHost) hipExtLaunchKernelGGL(ft_wave_kernel<kFromHost>, grid, dim3(threads), 0, stream, ev_start, ev_stop, 0, T, B);
+    else if (link_class & kWaveToHost) hipExtLaunchKernelGGL(ft_wave_kernel<kToHost>, grid, dim3(threads), 0, stream, ev_start, ev_stop, 0, T, B);
+    else if (link_class & kWaveStreams) hipExtLaunchKernelGGL(ft_wave_kernel<kStream>, grid, dim3(threads), 0, stream, ev_start, ev_stop, 0, T, B);
     else hipExtLaunchKernelGGL(ft_wave_kernel<0>, grid, dim3(threads), 0, stream, ev_start, ev_stop, 0, T, B);
     return hipGetLastError();
   }

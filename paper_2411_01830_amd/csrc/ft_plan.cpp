@@ -103,6 +103,29 @@ static bool wave_tiles_fit(const ClassPlan &cp, uint64_t chunk_bytes) {
   return true;
 }
 
+// The same for a job of one host-link class. A workgroup of the class's own kernel moves a tile of 16 KiB piece by piece,
+// a trip over the link per piece; with 256 wavefronts that each move 4 KiB as much is in flight (1 MiB, what the link
+// takes) whatever the pieces are. Measured, kernel time in us, class's own kernel -> wave kernel, host->pool and
+// pool->host: 32 pieces of 4 KiB 12.1 -> 7.6, 7.5 -> 5.8; 1024 of 1000 bytes 35.4 -> 26.0, 25.1 -> 22.9; 256 of
+// 20 KB 96.7 -> 107, 95.7 -> 98.4 (not sent); rows of 500 bytes scattered 120 -> 68, 106 -> 68; of 100 bytes 67 -> 54, 123 -> 72;
+// gathered rows, which the class's kernel moves as whole granules of the packed side, 16 bytes 87 -> 80, 16 -> 11, 100
+// bytes 110 -> 113, 50 -> 50, 2000 bytes 181 -> 189, 177 -> 187 (not sent); rows of 3000 bytes 188 either way. A tensor
+// of 64 KiB at an odd address 6.7 -> 4.8, 6.4 -> 4.0.
+static int link_code(const ClassPlan &cp, int cls) {
+  uint64_t fine = 0, pieces = 0, runs = 0;
+  for (const Xfer &x : cp.xfers) {
+    if (x.rows == 1) {
+      runs += x.row_bytes;
+      pieces += 1;
+    } else if (x.row_bytes <= (x.dst_pitch == x.row_bytes ? 64u : 2048u)) {
+      fine += x.row_bytes * x.rows;
+    }
+  }
+  if (pieces != 0 && runs / pieces <= 4096) fine += runs;
+  if (cp.payload > 128 * 1024 && 2 * fine <= cp.payload) return cls;
+  return (cp.payload <= kWaveLinkTilesBytes ? kWaveTiles : kWaveLink) | (cls == FT_H2P ? kWaveFromHost : kWaveToHost);
+}
+
 // What a class of a job is launched as (launch_copy's second argument): its link class, or for pool->pool one of
 // the wave kernel's codes. The 64 KiB tiles of the class's own kernel serve the memory controllers best once a
 // launch streams for long; below that a launch is bound by the round trips of its few tiles, by its table
@@ -119,7 +142,8 @@ static bool wave_tiles_fit(const ClassPlan &cp, uint64_t chunk_bytes) {
 // compute units for milliseconds, only workgroups of one wavefront are used, which find room anywhere,
 // and long contiguous jobs keep the class's kernel, whose shape is chosen for that company.
 int launch_code(const ClassPlan &cp, int cls, uint64_t chunk_bytes, bool tuned, bool alone) {
-  if (cls != FT_P2P || tuned || !wave_tiles_fit(cp, chunk_bytes)) return cls;
+  if (tuned || !wave_tiles_fit(cp, chunk_bytes)) return cls;
+  if (cls != FT_P2P) return alone ? link_code(cp, cls) : cls;
   if (cp.payload <= kWaveTilesBytes) return kWaveTiles;
   const bool streams = cp.payload > kCacheResidentBytes;
   uint64_t short_rows = 0, rows = 0, misaligned = 0;
@@ -137,8 +161,10 @@ int launch_code(const ClassPlan &cp, int cls, uint64_t chunk_bytes, bool tuned, 
 
 // Tile of a wave-kernel launch. About 4000 tiles, sixteen wavefronts on every compute unit, each with a tile that it can
 // hold in registers: more tiles cost more decodes than they hide (15.6 MB in 1024 tensors: 4000 tiles 11.0 us, 7000
-// 12.2, 2000 11.7), fewer leave compute units idle. 2 KiB is two loads per lane.
-uint64_t wave_tile(uint64_t payload) {
+// 12.2, 2000 11.7), fewer leave compute units idle. 2 KiB is two loads per lane. Host link: see link_code; up to 128 KiB
+// a lane's single load.
+uint64_t wave_tile(int code, uint64_t payload) {
+  if (code & (kWaveFromHost | kWaveToHost)) return payload <= 128 * 1024 ? 1024 : 4096;
   const uint64_t t = payload / 4000;
   return t < 2048 ? 2048 : t > 8192 ? 8192 : (t + 15) / 16 * 16;
 }
@@ -146,6 +172,7 @@ uint64_t wave_tile(uint64_t payload) {
 // Workgroups of a wave-kernel launch of this many tickets.
 uint64_t wave_workgroups(int cu_count, int code, uint64_t ntickets) {
   if ((code & 15) == kWaveTiles) return ntickets;
+  if ((code & 15) == kWaveLink) return ntickets < 64 ? ntickets : 64;
   const uint64_t most = ((code & 15) == kWaveTwoPerUnit ? 2ull : 1ull) * (uint64_t)cu_count;
   return ntickets < most ? ntickets : most;
 }

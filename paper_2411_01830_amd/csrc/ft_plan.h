@@ -70,8 +70,10 @@ bool mostly_short_rows(const ClassPlan &cp);
 constexpr uint64_t kCacheResidentBytes = 128ull << 20;
 // Largest job that is sent as one wavefront per workgroup, and largest job of any kind for the wave kernel.
 constexpr uint64_t kWaveTilesBytes = 16ull << 20, kWaveAnyBytes = 48ull << 20;
+// and on the host link.
+constexpr uint64_t kWaveLinkTilesBytes = 1ull << 20;
 int launch_code(const ClassPlan &cp, int cls, uint64_t chunk_bytes, bool tuned, bool alone);
-uint64_t wave_tile(uint64_t payload);
+uint64_t wave_tile(int code, uint64_t payload);
 uint64_t wave_workgroups(int cu_count, int code, uint64_t ntickets);
 
 // Bytes per ticket and tickets per chunk for a chunk size and a wanted tile size.

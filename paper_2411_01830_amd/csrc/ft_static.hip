@@ -96,7 +96,7 @@ extern "C" int ft_submit_static(ft_pool *p, const ft_desc *descs, uint32_t ndesc
     s.used = any = true;
     s.code = launch_code(cp, c, chunk_bytes, false, true);  // the classes run one after another
     if (s.code >= kWaveTiles) {
-      tile_shape(chunk_bytes, wave_tile(cp.payload), &s.tile_bytes, &s.tiles_per_chunk);
+      tile_shape(chunk_bytes, wave_tile(s.code, cp.payload), &s.tile_bytes, &s.tiles_per_chunk);
       cp.chunk_desc.clear();
       cp.desc_per = 1;
     } else {

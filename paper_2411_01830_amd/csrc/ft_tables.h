@@ -95,15 +95,17 @@ struct WgLogEntry {
   uint32_t _pad;
 };
 
-// Launch codes beside the three link classes: pool->pool in the kernel that gives every wavefront tiles of its own,
-// with workgroups of
+// Launch codes beside the three link classes: the kernel that gives every wavefront tiles of its own, with workgroups of
 //   kWaveTiles       one wavefront, a workgroup per ticket
 //   kWaveTwoPerUnit  eight wavefronts, at most two workgroups per compute unit, which stride over the tickets
 //   kWaveOnePerUnit  sixteen wavefronts, at most one workgroup per compute unit, likewise
-// or'ed with kWaveStreams: nontemporal instead of ordinary loads (stores are nontemporal anyway).
-constexpr int kWaveTiles = 8, kWaveTwoPerUnit = 9, kWaveOnePerUnit = 10, kWaveStreams = 16;
+//   kWaveLink        four wavefronts, at most 64 workgroups, likewise
+// or'ed with kWaveStreams: nontemporal instead of ordinary loads (stores are nontemporal anyway), or on the host link
+// with the direction, kWaveFromHost or kWaveToHost.
+constexpr int kWaveTiles = 8, kWaveTwoPerUnit = 9, kWaveOnePerUnit = 10, kWaveLink = 11;
+constexpr int kWaveStreams = 16, kWaveFromHost = 32, kWaveToHost = 64;
 constexpr uint32_t wave_code_threads(int code) {
-  return (code & 15) == kWaveTiles ? 64u : (code & 15) == kWaveTwoPerUnit ? 512u : (code & 15) == kWaveOnePerUnit ? 1024u : 0u;
+  return (code & 15) == kWaveTiles ? 64u : (code & 15) == kWaveTwoPerUnit ? 512u : (code & 15) == kWaveOnePerUnit ? 1024u : (code & 15) == kWaveLink ? 256u : 0u;
 }
 
 // Everything one class's kernel needs; passed by value as the kernel argument.

@@ -50,7 +50,7 @@ static void run(uint64_t dst, uint32_t n) {
   for (uint8_t h : hit) CHECK(h);
 }
 
-static uint64_t n_tickets, n_jobs[32];
+static uint64_t n_tickets, n_jobs[128];
 
 static void job(std::mt19937_64 &r) {
   auto U = [&](uint64_t a, uint64_t b) { return a + r() % (b - a + 1); };
@@ -80,13 +80,15 @@ static void job(std::mt19937_64 &r) {
     cp.payload += fn.stream_bytes;
   }
   CHECK(build_phases(cp.funcs, cp.phases, cp.slots, &cp.nchunks) == FT_OK);
-  const int code = launch_code(cp, FT_P2P, C, false, r() % 4 != 0);
-  CHECK(launch_code(cp, FT_P2P, C, true, true) == FT_P2P && launch_code(cp, FT_H2P, C, false, true) == FT_H2P);
+  const int cls = (int)U(0, 5) < 4 ? FT_P2P : (int)U(FT_H2P, FT_P2H);
+  const int code = launch_code(cp, cls, C, false, r() % 4 != 0);
+  CHECK(launch_code(cp, cls, C, true, true) == cls && (cls == FT_P2P || launch_code(cp, cls, C, false, false) == cls));
+  CHECK(code < kWaveTiles || (cls == FT_P2P) == ((code & (kWaveFromHost | kWaveToHost)) == 0));
   n_jobs[code] += 1;
   if (code < kWaveTiles) return;
   uint64_t tile;
   uint32_t tpc;
-  tile_shape(C, wave_tile(cp.payload), &tile, &tpc);
+  tile_shape(C, wave_tile(code, cp.payload), &tile, &tpc);
   std::vector<Skip> skips;
   uint64_t nt;
   build_skips(cp, C, tile, tpc, &skips, &nt);
@@ -151,9 +153,9 @@ int main(int argc, char **argv) {
     }
     for (int i = 0; i < 8; ++i) job(r);
   }
-  std::printf("tickets %llu; jobs: own kernel %llu, a workgroup per tile %llu, two workgroups per unit %llu, one %llu\n",
+  std::printf("tickets %llu; jobs: own kernel %llu, a workgroup per tile %llu, two workgroups per unit %llu, one %llu, host link %llu\n",
               (unsigned long long)n_tickets, (unsigned long long)n_jobs[FT_P2P], (unsigned long long)n_jobs[kWaveTiles],
-              (unsigned long long)n_jobs[kWaveTwoPerUnit], (unsigned long long)n_jobs[kWaveOnePerUnit]);
+              (unsigned long long)n_jobs[kWaveTwoPerUnit], (unsigned long long)n_jobs[kWaveOnePerUnit], (unsigned long long)(n_jobs[kWaveLink | kWaveFromHost] + n_jobs[kWaveLink | kWaveToHost] + n_jobs[kWaveTiles | kWaveFromHost] + n_jobs[kWaveTiles | kWaveToHost]));
   std::printf("done %llu..%llu\n", (unsigned long long)first, (unsigned long long)(first + count - 1));
   return 0;
 }

@@ -1,5 +1,5 @@
-"""The kernel that gives every wavefront tiles of its own: jobs of at most 16 MiB, of at most 128 MiB, and jobs of
-pitched rows, at the sizes where its windows, its tiles and the rule that picks it change. Bit-exact against the oracle."""
+"""The kernel that gives every wavefront tiles of its own: pool->pool jobs of at most 16, 48 or 128 MiB and jobs of
+pitched rows, host-link jobs of small pieces, at the sizes where its windows, its tiles and the rule that picks it change. Bit-exact against the oracle."""
 import numpy as np
 import pytest
 
@@ -100,5 +100,80 @@ def test_wave_tiles_match_the_oracle(case, beside_host_link):
                 assert int(log["bytes"].sum()) == st.payload_bytes and len(log["bytes"]) == st.tickets
             binding.job_release(eng.pool, jg)
         assert np.array_equal(torch.cat([t for t, _ in eng.segments]).cpu().numpy(), orc.pool_mem)
+    finally:
+        eng.close()
+
+
+# name, pieces(rng), chunk, flags, in one launch of a workgroup per ticket
+LINK_CASES = [
+    ("bytes around a window", lambda g: _runs(g, 150, [1, 15, 16, 17, 31, 32, 33, 1023, 1024, 1025], 3), 1024, 0, True),
+    ("one tensor", lambda g: _runs(g, 1, [65536 + 5], 1), 64 * KiB, 0, True),
+    ("128 KiB and a byte of long pieces", lambda g: _runs(g, 2, [64 * KiB + 1], 2), 64 * KiB, 0, False),
+    ("small pieces under 1 MiB", lambda g: _runs(g, 240, [3000, 4095, 4096], 3), 256 * KiB, fmt.FT_LOG, True),
+    ("small pieces over 1 MiB", lambda g: _runs(g, 300, [3000, 4095, 4096, 4097], 3), 256 * KiB, 0, False),
+    ("small pieces over 1 MiB, detached", lambda g: _runs(g, 300, [3000, 4095], 3), 256 * KiB, fmt.FT_DETACHED, False),
+    ("rows apart on both sides", lambda g: _rows(g, 12, [16, 33, 100, 500, 2048], 1 * MiB, 2), 100000 // 16 * 16, 0, None),
+    ("narrow gathered rows", lambda g: [(w, 700, w + 40, w, i % 2, 3 * i % 16, 5 * i % 16) for i, w in enumerate([16, 17, 40, 63, 64])], 64 * KiB, 0, None),
+    ("rows under 16 bytes", lambda g: _rows(g, 6, [1, 3, 9, 15], 40 * KiB, 2), 64 * KiB, 0, None),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", LINK_CASES, ids=[c[0] for c in LINK_CASES])
+@pytest.mark.parametrize("to_host", [False, True])
+def test_wave_tiles_on_the_host_link(case, to_host):
+    """The same over the host link, each direction; what lies around every destination stays as it was."""
+    import torch
+    from paper_2411_01830_amd import binding, harness
+    name, pieces, chunk, flags, tickets = case
+    print(f"case wave tiles over the host link: {name}, to the host: {to_host}", flush=True)
+    rng = np.random.default_rng(len(name) + to_host)
+    orc, eng = OracleEngine(), harness.GpuEngine()
+    cls = 1 if to_host else 0
+    try:
+        host = 8 * MiB
+        for e in (orc, eng):
+            e.host_arena(host)
+            e.pool_create(32 * MiB, 4 * KiB)
+        if not to_host:
+            data = rng.integers(0, 256, host, dtype=np.uint8)
+            orc.write_host(0, data)
+            eng.write_host(0, data)
+        recs, at = [], 0
+        for rb, rows, sp, dp, f, ss, ds in pieces(rng):
+            es, ed = (rows - 1) * sp + rb, (rows - 1) * dp + rb
+            in_pool, on_host = (es, ed) if to_host else (ed, es)
+            a = orc.slab_alloc(in_pool + 16)
+            assert eng.slab_alloc(in_pool + 16) == a
+            if to_host:
+                fill = rng.integers(0, 256, in_pool + 16, dtype=np.uint8)
+                orc.write_pool(a, fill)
+                eng.write_pool(a, fill)
+            src, dst = (a + ss, at + ds) if to_host else (at + ss, a + ds)
+            recs.append(dict(func=f, src_space=FT_POOL if to_host else FT_HOST, dst_space=FT_HOST if to_host else FT_POOL, src=src,
+                             dst=dst, row_bytes=rb, rows=rows, src_pitch=sp if rows > 1 else rb, dst_pitch=dp if rows > 1 else rb))
+            at += on_host + 32
+            assert at < host
+        d = make_descs(recs)
+        w = [2, 1, 5][:max(r["func"] for r in recs) + 1]
+        jo = orc.submit(d, w, chunk)
+        orc.wait(jo)
+        for _ in range(2):
+            jg = eng.submit(d, w, chunk, flags | fmt.FT_KEEP | fmt.FT_VALIDATE)
+            eng.wait(jg)
+            assert eng.job_schedule(jg, cls) == orc.job_schedule(jo, cls)
+            st = binding.job_stats(eng.pool, jg).cls[cls]
+            if tickets:
+                assert st.workgroups == st.tickets
+            elif tickets is False:
+                assert st.workgroups == min(64, st.tickets)
+            if flags & fmt.FT_DETACHED:
+                assert st.in_launch == 0     # it would hold the caller's stream
+            if flags & fmt.FT_LOG:
+                log = binding.job_log(eng.pool, jg, cls)
+                assert int(log["bytes"].sum()) == st.payload_bytes and len(log["bytes"]) == st.tickets
+            binding.job_release(eng.pool, jg)
+        assert np.array_equal(torch.cat([t for t, _ in eng.segments]).cpu().numpy(), orc.pool_mem)
+        assert np.array_equal(eng.host_np[:len(orc.host_mem)], orc.host_mem)
     finally:
         eng.close()
