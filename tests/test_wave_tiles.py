@@ -177,3 +177,40 @@ def test_wave_tiles_on_the_host_link(case, to_host):
         assert np.array_equal(eng.host_np[:len(orc.host_mem)], orc.host_mem)
     finally:
         eng.close()
+
+
+@pytest.mark.gpu
+def test_static_submits_with_and_without_the_device_array():
+    """ft_submit_static back to back: a job whose tables travel with its launch, one that goes through the library's
+    device array, one tensor, and the first shape again, all on one stream with nothing in between."""
+    import torch
+    from paper_2411_01830_amd import harness
+    print("case static submits with and without the device array", flush=True)
+    rng = np.random.default_rng(5)
+    orc, eng = OracleEngine(), harness.GpuEngine()
+    try:
+        for e in (orc, eng):
+            e.host_arena(1 << 20)
+            e.pool_create(96 * MiB, 4 * KiB)
+        jobs = []
+        for pieces, w in ((_runs(rng, 12, [5000, 70001], 3), [1, 2, 3]), (_runs(rng, 120, [100, 9000], 4), [4, 3, 2, 1]),
+                          (_runs(rng, 1, [300001], 1), [1]), (_rows(rng, 10, [100, 4000], 1 * MiB, 2), [1, 5])):
+            recs = []
+            for rb, rows, sp, dp, f, ss, ds in pieces:
+                es, ed = (rows - 1) * sp + rb, (rows - 1) * dp + rb
+                a, b = orc.slab_alloc(es + 16), orc.slab_alloc(ed + 16)
+                assert eng.slab_alloc(es + 16) == a and eng.slab_alloc(ed + 16) == b
+                fill = rng.integers(0, 256, es + 16, dtype=np.uint8)
+                orc.write_pool(a, fill)
+                eng.write_pool(a, fill)
+                recs.append(dict(func=f, src_space=FT_POOL, dst_space=FT_POOL, src=a + ss, dst=b + ds, row_bytes=rb, rows=rows,
+                                 src_pitch=sp if rows > 1 else rb, dst_pitch=dp if rows > 1 else rb))
+            jobs.append((make_descs(recs), w))
+        torch.cuda.synchronize()
+        for d, w in jobs:
+            orc.wait(orc.submit(d, w, 64 * KiB))
+            eng.submit_static(d, w, 64 * KiB, fmt.FT_VALIDATE)
+        torch.cuda.synchronize()
+        assert np.array_equal(torch.cat([t for t, _ in eng.segments]).cpu().numpy(), orc.pool_mem)
+    finally:
+        eng.close()
