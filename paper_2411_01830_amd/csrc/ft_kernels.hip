@@ -215,12 +215,40 @@ __device__ __forceinline__ unsigned long long copy_rows_of_vectors_draw(uint64_t
                                                                         unsigned long long *ticket) {
   u32x4 v[R];
 #pragma unroll
-  for (uint32_t j = 0; j < R; ++j) v[j] = ld16<NT>(s + ((uint64_t)(tid + j * kThreads) << 4));
+  for (uint32_t j = 0; j < R; ++j) {
+    v[j] = ld16<NT>(s + ((uint64_t)(tid + j * kThreads) << 4));
+    // in this order: the first store waits for the first load alone (a build in which the compiler had moved that load
+    // behind eight others let no store go before half of the tile was there: 520 MB in 64 tensors 165.7 -> 169.5 us)
+    __builtin_amdgcn_sched_barrier(0);
+  }
   unsigned long long claimed = 0;
 #pragma unroll
   for (uint32_t j = 0; j < R; ++j) {
     if (j == R * 3 / 4 && tid == 0) claimed = atomicAdd(ticket, 1ull);
     st16<NT>(d + ((uint64_t)(tid + j * kThreads) << 4), v[j]);
+  }
+  return claimed;
+}
+
+// The same for a tile whose first n1 vectors belong to one transfer and the rest to the next: d2 and s2 are that
+// transfer's addresses for vector n1, less n1 vectors. A tile in which one tensor ends and the next begins costs one memory
+// round trip like any other instead of one per piece (kernel time, us: 4000 tensors of 60 KB, 240 MB, 104 -> 94; 2000 of
+// 200 KB, 398 MB, 147 -> 139; 600 of 447 KB, 269 MB, 101 -> 97).
+template <int NT, uint32_t R>
+__device__ __forceinline__ unsigned long long copy_two_runs_draw(uint64_t d, uint64_t s, uint64_t d2, uint64_t s2, uint32_t n1,
+                                                                 uint32_t tid, unsigned long long *ticket) {
+  u32x4 v[R];
+#pragma unroll
+  for (uint32_t j = 0; j < R; ++j) {
+    const uint32_t i = tid + j * kThreads;
+    v[j] = ld16<NT>((i < n1 ? s : s2) + ((uint64_t)i << 4));
+  }
+  unsigned long long claimed = 0;
+#pragma unroll
+  for (uint32_t j = 0; j < R; ++j) {
+    const uint32_t i = tid + j * kThreads;
+    if (j == R * 3 / 4 && tid == 0) claimed = atomicAdd(ticket, 1ull);
+    st16<NT>((i < n1 ? d : d2) + ((uint64_t)i << 4), v[j]);
   }
   return claimed;
 }
@@ -791,24 +819,42 @@ struct WorkSlot {
   // what the common case needs, in the first 32 bytes: one full aligned block
   uint64_t t;     // the ticket; >= ntickets: none left
   uint64_t fd;    // destination and
-  uint64_t fs;    // source of the block, or 0 / 0 if the ticket is not of that kind
-  uint64_t _pad;
+  uint64_t fs;    // source of the block, or 0 / 0 if the ticket is not of that kind; bit 0 of fs: only the block's
+  uint64_t n1;    // first n1 vectors lie there, the rest at fd2 / fs2
   // everything else
   uint64_t b0, b1;
   uint64_t x;
   uint64_t stage;
   Xfer first;
+  uint64_t fd2, fs2;  // the block's second transfer: its addresses for vector n1, less n1 vectors
 };
 
-// block_bytes: the size of a full block of this class's copy routines
-__device__ __forceinline__ void put_work(WorkSlot &slot, uint64_t t, const Work &w, uint64_t block_bytes) {
+// block_bytes: the size of a full block of this class's copy routines; two_runs: a block may also be the end of one
+// contiguous transfer and the beginning of the function's next
+__device__ __forceinline__ void put_work(WorkSlot &slot, uint64_t t, const Work &w, uint64_t block_bytes, bool two_runs, CXferP xfers) {
   const uint64_t p0 = w.b0 - w.first.stream_off;
   const uint64_t len = w.b1 - w.b0;
   const uint64_t fd = w.first.dst + p0, fs = w.first.src + p0;
-  const bool fast = w.first.rows == 1 && len == block_bytes && ((fd | fs) & 15) == 0 && p0 + len <= w.first.row_bytes;
+  bool fast = w.first.rows == 1 && len == block_bytes && ((fd | fs) & 15) == 0;
+  uint64_t n1 = 0;
+  if (__builtin_expect(fast && p0 + len > w.first.row_bytes, 0)) {
+    fast = false;
+    const uint64_t n = w.first.row_bytes - p0;  // bytes of the block in its first transfer
+    if (two_runs && (n & 15) == 0) {
+      const CXferP X = xfers + (w.x + 1);  // exists: the block's bytes go on
+      const uint64_t d2 = X->dst, s2 = X->src;
+      if (X->rows == 1 && ((d2 | s2) & 15) == 0 && len - n <= X->row_bytes) {
+        fast = true;
+        n1 = n >> 4;
+        slot.fd2 = d2 - n;
+        slot.fs2 = s2 - n;
+      }
+    }
+  }
   slot.t = t;
+  slot.n1 = n1;
   slot.fd = fast ? fd : 0;
-  slot.fs = fast ? fs : 0;
+  slot.fs = fast ? fs | (n1 != 0 ? 1u : 0u) : 0;
   slot.b0 = w.b0;
   slot.b1 = w.b1;
   slot.x = w.x;
@@ -936,7 +982,7 @@ __global__ __launch_bounds__(kThreads, (CLS == 2 ? 1 : 2)) void ft_copy_kernel(C
     const uint64_t t_first = T.ticket_base + blockIdx.x;
     const Work w = decode_ticket(T, CT, pc, sc, t_first);
     if (tid == 0) {
-      put_work(s_work[0], t_first, w, (uint64_t)kThreads * U * 16);
+      put_work(s_work[0], t_first, w, (uint64_t)kThreads * U * 16, CLS == 2, CT.xfers);
       log_decoded(T, t_first, w);
     }
   }
@@ -947,10 +993,13 @@ __global__ __launch_bounds__(kThreads, (CLS == 2 ? 1 : 2)) void ft_copy_kernel(C
     uint64_t t_begin = 0;
     if (T.log) t_begin = wall_clock64();
     unsigned long long claimed = 0;
-    if (fd != 0) {
+    if (fd != 0 && __builtin_expect((fs & 1) == 0, 1)) {
       // the common case, one full aligned block (64 KiB for pool->pool): 32 bytes read
       // from LDS, then straight-line code to the last store, the ticket draw on the way
       claimed = copy_rows_of_vectors_draw<MODE, U>(fd, fs, tid, T.ticket);
+    } else if (CLS == 2 && fd != 0) {
+      claimed = copy_two_runs_draw<MODE, U>(fd, fs - 1, uniform64(s_work[slot].fd2), uniform64(s_work[slot].fs2),
+                                            uniform32((uint32_t)s_work[slot].n1), tid, T.ticket);
     } else {
       // Host-link classes draw before the tile's pieces: a tile lasts as long as the link takes, the
       // counter's answer is there long before, and the workgroups run ahead of the link anyway.
@@ -987,7 +1036,7 @@ __global__ __launch_bounds__(kThreads, (CLS == 2 ? 1 : 2)) void ft_copy_kernel(C
       const uint64_t t_drawn = T.ticket_base + gridDim.x + uniform64(claimed);
       const Work next = decode_ticket(T, CT, pc, sc, t_drawn);
       if (tid == 0) {
-        put_work(s_work[slot ^ 1], t_drawn, next, (uint64_t)kThreads * U * 16);
+        put_work(s_work[slot ^ 1], t_drawn, next, (uint64_t)kThreads * U * 16, CLS == 2, CT.xfers);
         log_decoded(T, t_drawn, next);
       }
     }

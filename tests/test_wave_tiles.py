@@ -214,3 +214,50 @@ def test_static_submits_with_and_without_the_device_array():
         assert np.array_equal(torch.cat([t for t, _ in eng.segments]).cpu().numpy(), orc.pool_mem)
     finally:
         eng.close()
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("flags", [0, fmt.FT_LOG])
+def test_tiles_in_which_one_tensor_ends_and_the_next_begins(flags):
+    """The copy kernel proper (asked for by its tile size) moves a full tile of two aligned tensors in one pass: lengths
+    around a tile and around a vector, three tensors in a tile, a second one that is misaligned or pitched."""
+    import torch
+    from paper_2411_01830_amd import binding, harness
+    print(f"case two tensors in a tile, flags {flags}", flush=True)
+    rng = np.random.default_rng(9)
+    orc, eng = OracleEngine(), harness.GpuEngine()
+    try:
+        for e in (orc, eng):
+            e.host_arena(1 << 20)
+            e.pool_create(160 * MiB, 4 * KiB)
+        binding.set_tuning(eng.pool, 2, 0, 64 * KiB)
+        sizes = [65536, 65520, 65552, 131072, 40000, 16, 32, 65536 - 32, 90000, 131056, 48, 65504, 77, 65536, 4096]
+        recs = []
+        for f in range(3):
+            for i in range(60):
+                n, rows = int(rng.choice(sizes)), 1
+                shift = (0, 0)
+                if f == 1 and i % 7 == 3:
+                    shift = (int(rng.integers(0, 16)), int(rng.integers(0, 16)))
+                if f == 2 and i % 5 == 2:
+                    n, rows = 400, 30
+                pitch = n + 48
+                a, b = orc.slab_alloc(pitch * rows + 16), orc.slab_alloc(pitch * rows + 16)
+                assert eng.slab_alloc(pitch * rows + 16) == a and eng.slab_alloc(pitch * rows + 16) == b
+                fill = rng.integers(0, 256, pitch * rows + 16, dtype=np.uint8)
+                orc.write_pool(a, fill)
+                eng.write_pool(a, fill)
+                recs.append(dict(func=f, src_space=FT_POOL, dst_space=FT_POOL, src=a + shift[0], dst=b + shift[1], row_bytes=n,
+                                 rows=rows, src_pitch=pitch if rows > 1 else n, dst_pitch=pitch if rows > 1 else n))
+        d = make_descs(recs)
+        for chunk in (64 * KiB, 2 * MiB):
+            jo = orc.submit(d, [1, 2, 3], chunk)
+            orc.wait(jo)
+            jg = eng.submit(d, [1, 2, 3], chunk, flags | fmt.FT_KEEP | fmt.FT_VALIDATE)
+            eng.wait(jg)
+            assert binding.job_stats(eng.pool, jg).cls[2].tile_bytes == 64 * KiB
+            assert eng.job_schedule(jg, 2) == orc.job_schedule(jo, 2)
+            binding.job_release(eng.pool, jg)
+            assert np.array_equal(torch.cat([t for t, _ in eng.segments]).cpu().numpy(), orc.pool_mem)
+    finally:
+        eng.close()
