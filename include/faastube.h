@@ -241,14 +241,15 @@ int ft_set_stage_threads(ft_pool *p, uint32_t threads);
  * one total order: chunk j of function f carries the finish tag (j+1)/w_f, smaller
  * tags first, equal tags by lower f - i.e. always serve the unfinished function with
  * the smallest (served+1)/weight. Persistent workgroups draw tickets from a device
- * counter in that order; the classes run concurrently on streams of their own.
+ * counter in that order (jobs that latency bounds - a few MiB, many small pieces, pitched rows - have
+ * a wavefront per ticket instead, dispatched in that order); the classes run concurrently on streams of their own.
  * A job of a single link class whose tables fit 3 KiB (not with FT_PATH_DMA,
  * FT_OPEN or a tuned workgroup count) is launched on hip_stream itself with its tables
  * as a kernel argument: same result and order, a tenth of the host time. If it has at
- * most one tile per workgroup (256 tiles pool->pool, 64 host->pool, 128 pool->host) it
- * needs no counter; a larger one takes one of 256 self-clearing counter pairs per device
+ * most one tile per workgroup (up to 16 MiB pool->pool, 64 tiles host->pool, 128 pool->host) or
+ * a wavefront per ticket it needs no counter; a larger one takes one of 256 self-clearing counter pairs per device
  * (and the ordinary route if none is free or if FT_DETACHED is set, since the job holds
- * hip_stream like any kernel on it). One contiguous transfer between 16-byte aligned
+ * hip_stream like any kernel on it). One contiguous transfer over the host link between 16-byte aligned
  * addresses (Sec. 5.1: passing one tensor) needs neither: its tiles are dealt
  * out round robin among the workgroups. Any other job of a single link class without
  * FT_DETACHED also runs on hip_stream itself, its tables copied to the device ahead of it
@@ -306,8 +307,8 @@ int ft_job_stats(ft_pool *p, ft_job_t job, ft_job_stats_t *out);
  * held until the process ends).
  *   Arguments as for ft_submit_transfers; flags: 0 or FT_VALIDATE. Sides: FT_HOST and FT_POOL only.
  *   Same validation, same chunk order, same copy kernel and tile shapes, same bytes afterwards.
- *   Everything is launched on hip_stream (table pieces travel with small launches, then one copy
- *   kernel per link class in use, one after the other). There is no job handle and nothing to
+ *   Everything is launched on hip_stream (table pieces travel with small launches, or the whole tables with the
+ *   copy kernel itself if they fit; then one copy kernel per link class in use, one after the other). There is no job handle and nothing to
  *   wait for but the stream: the transfers are complete when the work queued on hip_stream by
  *   this call is. The caller keeps every allocation it names alive until then (no FT_EBUSY
  *   protects them) and may not have two such calls in flight at once on one GPU unless they are

@@ -4,6 +4,7 @@
 // persistent workgroups draw tickets from one device counter; a ticket names a tile
 // of a chunk, chunks are numbered in the proportional order of Sec. 6.1, so the
 // counter hands the link's bandwidth out to functions by weight at tile granularity.
+// ft_wave_kernel does the same for jobs that latency bounds, one tile per wavefront.
 // Bytes move as 16-byte vectors, one per lane, consecutive lanes on consecutive
 // vectors, so every wavefront load/store covers 1 KiB of contiguous memory.
 #include <hip/hip_runtime.h>

@@ -72,6 +72,20 @@ struct StaticClass {
   int code = 0;
 };
 
+// What the class's tables would take with the descriptor table that the copy kernel proper needs and the wave kernel does
+// without: the limit of this entry point does not depend on the kernel that a job happens to get. (A table with
+// an entry per chunk alone can be left out, then the kernel searches; one with an entry per tile cannot.)
+uint64_t tables_with_descriptor_table(const ClassPlan &cp, int c, bool with_p2p, uint64_t chunk_bytes) {
+  uint64_t tile;
+  uint32_t tiles_per_chunk;
+  tile_shape(chunk_bytes, default_tile(c, with_p2p, mostly_short_rows(cp), cp.payload), &tile, &tiles_per_chunk);
+  const Layout lay = layout_of(cp, 0, 1);
+  const uint64_t entries = cp.nchunks * tiles_per_chunk + cp.funcs.size();
+  const bool per_tile = tiles_per_chunk > 1 && cp.xfers.size() > 2 * cp.nchunks && entries <= kMaxChunkTable;
+  const uint64_t skips = align_up(lay.chunks + entries * sizeof(uint32_t), 64);
+  return per_tile ? align_up(skips + cp.funcs.size() * sizeof(Skip), 256) : lay.end;
+}
+
 }  // namespace ft
 
 using namespace ft;
@@ -99,6 +113,7 @@ extern "C" int ft_submit_static(ft_pool *p, const ft_desc *descs, uint32_t ndesc
       tile_shape(chunk_bytes, wave_tile(s.code, cp.payload), &s.tile_bytes, &s.tiles_per_chunk);
       cp.chunk_desc.clear();
       cp.desc_per = 1;
+      if (tables_with_descriptor_table(cp, c, with_p2p, chunk_bytes) > kStaticClassBytes) return FT_E2BIG;
     } else {
       tile_shape(chunk_bytes, default_tile(c, with_p2p, mostly_short_rows(cp), cp.payload), &s.tile_bytes, &s.tiles_per_chunk);
       build_chunk_table(cp, chunk_bytes, s.tile_bytes, s.tiles_per_chunk);
