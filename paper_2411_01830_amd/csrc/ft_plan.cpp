@@ -392,14 +392,21 @@ int plan_submit(SlabPool &pool, const std::vector<HostWindow> &windows, const ft
   };
   uint32_t in_class[FT_NCLASS] = {0, 0, 0};
   for (uint32_t i = 0; i < ndesc; ++i) in_class[class_of(descs[i])] += 1;
-  std::vector<uint32_t> fn_of[FT_NCLASS];    // caller's function -> index into the class's table
-  std::vector<uint32_t> placed[FT_NCLASS];   // per function of the class: descriptors already in place
+  // Caller's function -> index into the class's table; up to 16 functions without an allocation.
+  uint32_t small[FT_NCLASS][16];
+  std::vector<uint32_t> large[FT_NCLASS];
+  uint32_t *fn_of[FT_NCLASS];
   for (int c = 0; c < FT_NCLASS; ++c) {
     ClassPlan &cp = out->cls[c];
     cp = ClassPlan();
     if (in_class[c] == 0) continue;  // a class without traffic costs no allocation (passing one tensor: two of three)
-    std::vector<uint32_t> &count = fn_of[c];
-    count.assign(nfunc, 0);
+    uint32_t *count = small[c];
+    if (nfunc > 16) {
+      large[c].resize(nfunc);
+      count = large[c].data();
+    }
+    std::fill(count, count + nfunc, 0u);
+    fn_of[c] = count;
     if (in_class[c] == ndesc) {
       for (uint32_t i = 0; i < ndesc; ++i) count[descs[i].func] += 1;
     } else {
@@ -415,7 +422,7 @@ int plan_submit(SlabPool &pool, const std::vector<HostWindow> &windows, const ft
       fn.func = f;
       fn.weight = weights[f];
       fn.desc_off = off;
-      fn.ndesc = count[f];
+      fn.ndesc = 0;  // counted up again as its descriptors are put into their places
       fn.chunk_off = 0;
       fn._pad = 0;
       fn.chunk_base = 0;
@@ -424,7 +431,6 @@ int plan_submit(SlabPool &pool, const std::vector<HostWindow> &windows, const ft
       cp.funcs.push_back(fn);
     }
     cp.xfers.resize(off);
-    placed[c].assign(cp.funcs.size(), 0);
   }
   bool stream_overflow = false;
 
@@ -444,9 +450,8 @@ int plan_submit(SlabPool &pool, const std::vector<HostWindow> &windows, const ft
     const ft_desc &d = descs[i];
     const int c = class_of(d);
     ClassPlan &cp = out->cls[c];
-    const uint32_t fl = fn_of[c][d.func];
-    Func &fn = cp.funcs[fl];
-    Xfer &x = cp.xfers[fn.desc_off + placed[c][fl]++];
+    Func &fn = cp.funcs[fn_of[c][d.func]];
+    Xfer &x = cp.xfers[fn.desc_off + fn.ndesc++];
     x.row_bytes = d.row_bytes;
     x.rows = d.rows;
     x.src_pitch = d.rows > 1 ? d.src_pitch : d.row_bytes;
@@ -569,8 +574,13 @@ int plan_submit(SlabPool &pool, const std::vector<HostWindow> &windows, const ft
   // the allocations in ascending order, each once; usually either side names them in that order already
   for (int side = 0; side < 2; ++side)
     if (!std::is_sorted(used[side].begin(), used[side].end())) std::sort(used[side].begin(), used[side].end());
-  out->allocs.resize(used[0].size() + used[1].size());
-  std::merge(used[0].begin(), used[0].end(), used[1].begin(), used[1].end(), out->allocs.begin());
+  if (used[0].empty() || used[1].empty() || used[0].back() <= used[1].front()) {
+    out->allocs.swap(used[0]);
+    out->allocs.insert(out->allocs.end(), used[1].begin(), used[1].end());
+  } else {
+    out->allocs.resize(used[0].size() + used[1].size());
+    std::merge(used[0].begin(), used[0].end(), used[1].begin(), used[1].end(), out->allocs.begin());
+  }
   out->allocs.erase(std::unique(out->allocs.begin(), out->allocs.end()), out->allocs.end());
   if (stream_overflow) return FT_ERANGE;
   for (ClassPlan &cp : out->cls) {
