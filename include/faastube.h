@@ -241,13 +241,20 @@ int ft_set_stage_threads(ft_pool *p, uint32_t threads);
  * one total order: chunk j of function f carries the finish tag (j+1)/w_f, smaller
  * tags first, equal tags by lower f - i.e. always serve the unfinished function with
  * the smallest (served+1)/weight. Persistent workgroups draw tickets from a device
- * counter in that order (jobs that latency bounds - a few MiB, many small pieces, pitched rows - have
- * a wavefront per ticket instead, dispatched in that order); the classes run concurrently on streams of their own.
+ * counter in that order; the classes run concurrently on streams of their own. Jobs that latency
+ * bounds (pool->pool up to 48 MiB, one tensor or mostly misaligned ones up to 128 MiB, pitched rows under
+ * 64 KiB of any amount; host-link jobs of small pieces) have a wavefront per ticket. Up to 16 MiB pool->pool and
+ * 1 MiB on the host link that is one workgroup per ticket, begun in the order's sequence. Beyond that there are
+ * 4096 wavefronts (256 on the host link): each begins one ticket, and the tickets behind those follow in the
+ * order, in batches of 8 (4) that the workgroups draw from the counter; a workgroup holds the rest of one batch
+ * and one more at most, whatever its tiles cost. Two exceptions, in which every wavefront takes each 4096th (256th)
+ * ticket: jobs of up to one and a half times as many tickets, most of which are begun at once, and one tensor, which has no
+ * order to keep.
  * A job of a single link class whose tables fit 3 KiB (not with FT_PATH_DMA,
  * FT_OPEN or a tuned workgroup count) is launched on hip_stream itself with its tables
- * as a kernel argument: same result and order, a tenth of the host time. If it has at
- * most one tile per workgroup (up to 16 MiB pool->pool, 64 tiles host->pool, 128 pool->host) or
- * a wavefront per ticket it needs no counter; a larger one takes one of 256 self-clearing counter pairs per device
+ * as a kernel argument: same result and order, a tenth of the host time. If the workgroups have its
+ * tiles from the start (up to 16 MiB pool->pool and whatever else takes no batch from the counter as said above, 64 tiles
+ * host->pool, 128 pool->host) it needs no counter; a larger one takes one of 256 self-clearing counter pairs per device
  * (and the ordinary route if none is free or if FT_DETACHED is set, since the job holds
  * hip_stream like any kernel on it). One contiguous transfer over the host link between 16-byte aligned
  * addresses (Sec. 5.1: passing one tensor) needs neither: its tiles are dealt

@@ -532,7 +532,9 @@ int launch_with_the_launch(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chun
   const bool direct = !wave && (only != FT_P2P || r.tile_bytes < 64 * 1024) && cp.funcs.size() == 1 &&
                       cp.xfers.size() == 1 && cp.funcs[0].chunk_base == 0 && !(flags & FT_LOG) &&
                       cp.xfers[0].rows == 1 && ((cp.xfers[0].src | cp.xfers[0].dst) & 15) == 0;
-  const bool each_its_own = wave || (!direct && ntickets <= most);  // no counter
+  const uint64_t waves_wg = wave ? wave_workgroups(p->ctx->cu_count, r.code, ntickets) : 0;
+  const bool single = cp.funcs.size() == 1 && cp.xfers.size() == 1 && cp.funcs[0].chunk_base == 0;
+  const bool each_its_own = wave ? !wave_draws(r.code, waves_wg, ntickets, single) : !direct && ntickets <= most;  // no counter
   // a job with more tiles than that holds the caller's stream for a while: not what FT_DETACHED asked for
   if (ntickets > most && (flags & FT_DETACHED)) return FT_OK;
   if (!each_its_own && !direct) {
@@ -546,7 +548,7 @@ int launch_with_the_launch(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chun
   int rc = prepare_class(p, job, only, cp, lay, h, nullptr, chunk_bytes, (flags & FT_TIMING) != 0);
   if (rc != FT_OK) return fail_submit(p, job, rc);
   ClassTable &T = r.table;
-  T.single = cp.funcs.size() == 1 && cp.xfers.size() == 1 && cp.funcs[0].chunk_base == 0 ? 1u : 0u;
+  T.single = single ? 1u : 0u;
   uint64_t wg = ntickets;
   if (direct) {
     T.ticket = p->ctx->idle_counter;  // never consulted
@@ -557,11 +559,11 @@ int launch_with_the_launch(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chun
     if (wg > ntickets) wg = ntickets;
   } else if (each_its_own) {
     T.ticket = p->ctx->idle_counter;
-    if (wave) wg = wave_workgroups(p->ctx->cu_count, r.code, ntickets);
+    if (wave) wg = waves_wg;
   } else {
     T.ticket = p->ctx->counter_pairs + 2 * r.counter_pair;
     T.self_reset = 1;
-    wg = default_workgroups(p, only, only == FT_P2P);
+    wg = wave ? waves_wg : default_workgroups(p, only, only == FT_P2P);
     if (wg > ntickets) wg = ntickets;
   }
   r.workgroups = (uint32_t)wg;

@@ -7,10 +7,9 @@
 namespace ft {
 
 // Persistent copy kernel of one link class (0 host->pool, 1 pool->host, 2 pool->pool), or a launch code of the wave
-// kernel, which consults no counter.
-// Workgroup b starts on ticket b, the counter *T.ticket hands out the following ones: it
-// must be zero when the kernel starts unless workgroups >= the launch's tickets (then its
-// value does not matter). ev_start / ev_stop (both, neither, or ev_stop alone) are events that will
+// kernel. Workgroup b starts on ticket b (the wave kernel: on one ticket per wavefront and a batch), the counter *T.ticket
+// hands out the following ones: it must be zero when the kernel starts unless workgroups >= the launch's tickets (the wave
+// kernel: unless wave_draws denies that it is read; then its value does not matter). ev_start / ev_stop (both, neither, or ev_stop alone) are events that will
 // read the start and the end of this dispatch. `tables`: the job's tables when
 // T.inline_tables is set, else null.
 hipError_t launch_copy(const ClassTable &T, int link_class, uint32_t workgroups, hipStream_t stream,

@@ -10,6 +10,7 @@
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
+#include "ft_batches.h"
 #include "ft_kernels.h"
 #include "ft_windows.h"
 
@@ -927,6 +928,13 @@ __device__ __forceinline__ void drain_barrier() {
   asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
 }
 
+// ClassTable::self_reset, by one lane of a workgroup whose draws have all been answered (the last answer ended its loop).
+__device__ __forceinline__ void reset_counters_after_last(const ClassTable &T) {
+  if (atomicAdd(T.ticket + 1, 1ull) != gridDim.x - 1) return;
+  __hip_atomic_store(T.ticket, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(T.ticket + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // Persistent workgroups. Workgroup b starts on ticket b and every later ticket comes from
 // the counter (which therefore hands out the tickets from the grid size on; the host never
 // launches more workgroups than there are tickets). When all workgroups of a launch ask
@@ -1067,21 +1075,15 @@ __global__ __launch_bounds__(kThreads, (CLS == 2 ? 1 : 2)) void ft_copy_kernel(C
     fs = fs_next;
   }
   if (T.log && tid == 0) T.wg_log[blockIdx.x].t_exit = wall_clock64();
-  if (T.self_reset && tid == 0) {
-    // this workgroup's draws have all been answered (the last answer ended its loop)
-    if (atomicAdd(T.ticket + 1, 1ull) == gridDim.x - 1) {
-      __hip_atomic_store(T.ticket, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      __hip_atomic_store(T.ticket + 1, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-  }
+  if (T.self_reset && tid == 0) reset_counters_after_last(T);
 }
 
 // ---- one tile per wavefront -------------------------------------------------------------------------
 //
 // The kernel of jobs that latency bounds rather than HBM or the host link: pool->pool jobs of some MiB and of pitched
-// rows, host-link jobs of many small pieces (the rules stand with launch_code in ft_plan.cpp). Every wavefront takes tiles of its own, of 1 .. 16 KiB,
-// decodes them itself and moves them without a barrier, so a tile's memory round trips (table reads, one or
-// more per piece) overlap those of the other 15 wavefronts of its compute unit. The host sends it only
+// rows, host-link jobs of many small pieces (the rules stand with launch_code in ft_plan.cpp). Every wavefront takes tiles
+// of its own, of 1 .. 8 KiB, decodes them itself and moves them without a barrier, so a tile's memory round trips (table
+// reads, one or more per piece) overlap those of the other 15 wavefronts of its compute unit. The host sends it only
 // what 32-bit arithmetic covers (wave_tiles_fit): its instructions arrive from memory at every launch, and a
 // launch of this kind lasts about as long as the fetch of a few thousand of them.
 
@@ -1273,20 +1275,59 @@ __device__ __forceinline__ void wave_copy_rows(const Xfer &X, uint32_t p, uint32
   if (edge) st_off<uint8_t, 0>(d, ed, eb);
 }
 
+// A workgroup's batches of tickets (ft_batches.h), in LDS.
+struct WaveBatches {
+  unsigned long long taken;
+  uint32_t next;
+  __device__ uint64_t add_taken() { return __hip_atomic_fetch_add(&taken, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+  __device__ uint64_t word() { return __hip_atomic_load(&taken, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+  __device__ void set_word(uint64_t v) { __hip_atomic_store(&taken, (unsigned long long)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+  __device__ uint32_t ahead() { return __hip_atomic_load(&next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+  __device__ void set_ahead(uint32_t t) {
+    __hip_atomic_store(&next, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+    asm volatile("" ::: "memory");  // a wavefront's LDS operations complete in their order; here it is the compiler's too
+  }
+  __device__ void pause() { __builtin_amdgcn_s_sleep(1); }
+};
+
+// Every wavefront starts on a ticket of its own. A launch with many more tickets than wavefronts (wave_shares) hands the
+// others out in order: workgroup b has batch b behind the first round from the start, *T.ticket counts the batches drawn
+// beyond those (zero at launch). One tensor has no order to keep: its tickets are dealt out. With every ticket dealt out the
+// order was what equal speeds made of it: of two functions of equal weight with alternating tiles, rows of 16 and of 2000 bytes,
+// 200 MB each, the slow one had 21 % of the tiles begun at half time, now 50 %. Kernel time, us, dealt out -> by batches: rows of
+// 256 bytes 419 MB 147 -> 147, of 5760 bytes 110 MB 31 -> 32, 1.6 GB 587 -> 530; 64 misaligned tensors 105 MB 35 -> 34; host->pool
+// 20 000 pieces of 4000 bytes 1566 -> 1464 (a wavefront that the link serves late keeps none of the others' work).
 template <int NT>
 __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void ft_wave_kernel(ClassTable T, InlineBlob) {
+  __shared__ WaveBatches s_batches;
   const ConstTables CT = const_tables(T);
   const uint32_t lane = threadIdx.x & 63;
-  const uint32_t step = gridDim.x * (blockDim.x >> 6);
+  const uint32_t waves = blockDim.x >> 6, round = gridDim.x * waves;
+  const uint32_t batch = wave_batch(waves);
+  const bool shares = !T.single && wave_shares(round, T.ntickets);  // both the same for the whole launch
+  const bool counts = wave_counts(gridDim.x, waves, T.ntickets);
   if (T.log && threadIdx.x == 0) {
     T.wg_log[blockIdx.x].t_entry = wall_clock64();
     T.wg_log[blockIdx.x].unit = compute_unit_id();
   }
-  // neighbouring tickets go to different compute units
-  for (uint32_t t = uniform32(threadIdx.x >> 6) * gridDim.x + blockIdx.x; t < (uint32_t)T.ntickets; t += step) {
+  if (shares) {
+    if (threadIdx.x == 0) {
+      s_batches.taken = batch;
+      s_batches.next = round + blockIdx.x * batch;
+    }
+    __syncthreads();
+  }
+  // neighbouring tickets of the first round go to different compute units
+  const uint32_t wave = uniform32(threadIdx.x >> 6);
+  uint32_t t = wave * gridDim.x + blockIdx.x;
+  bool draw = false;
+  while (t < (uint32_t)T.ntickets) {
     uint64_t t_begin = 0;
     if (T.log) t_begin = wall_clock64();
+    unsigned long long drawn = 0;
+    if (draw && counts && lane == 0) drawn = atomicAdd(T.ticket, 1ull);  // answered while the tables are read
     const Work w = decode_ticket_wave(T, CT, t, lane);
+    if (draw && lane == 0) s_batches.set_ahead(counts ? round + (gridDim.x + (uint32_t)drawn) * batch : (uint32_t)T.ntickets);
     uint64_t pos = w.b0;
     for (uint32_t x = w.x; pos < w.b1; ++x) {
       const Xfer X = read_xfer(CT.xfers, x);
@@ -1304,11 +1345,19 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void 
       T.log[t].t_end = wall_clock64();
       T.log[t].wg = blockIdx.x;
     }
+    if (!shares) {
+      t += round;
+      continue;
+    }
+    uint32_t taken = 0;
+    bool owes = false;
+    if (lane == 0) taken = take_ticket(s_batches, batch, (uint32_t)T.ntickets, &owes);
+    t = uniform32(taken);
+    draw = uniform32(owes ? 1u : 0u) != 0;
   }
-  if (T.log) {
-    __syncthreads();
-    if (threadIdx.x == 0) T.wg_log[blockIdx.x].t_exit = wall_clock64();
-  }
+  if (T.log || T.self_reset) __syncthreads();
+  if (T.log && threadIdx.x == 0) T.wg_log[blockIdx.x].t_exit = wall_clock64();
+  if (T.self_reset && threadIdx.x == 0) reset_counters_after_last(T);
 }
 
 __global__ void ft_decode_kernel(ClassTable T, InlineBlob, uint32_t *func_out, uint32_t *chunk_out, uint64_t cap) {

@@ -1,5 +1,7 @@
 #include "ft_plan.h"
 
+#include "ft_batches.h"
+
 #include <algorithm>
 #include <numeric>
 
@@ -175,6 +177,10 @@ uint64_t wave_workgroups(int cu_count, int code, uint64_t ntickets) {
   if ((code & 15) == kWaveLink) return ntickets < 64 ? ntickets : 64;
   const uint64_t most = ((code & 15) == kWaveTwoPerUnit ? 2ull : 1ull) * (uint64_t)cu_count;
   return ntickets < most ? ntickets : most;
+}
+
+bool wave_draws(int code, uint64_t workgroups, uint64_t ntickets, bool single) {
+  return !single && wave_counts(workgroups, wave_code_threads(code) / 64, ntickets);
 }
 
 namespace {

@@ -75,6 +75,8 @@ constexpr uint64_t kWaveLinkTilesBytes = 1ull << 20;
 int launch_code(const ClassPlan &cp, int cls, uint64_t chunk_bytes, bool tuned, bool alone);
 uint64_t wave_tile(int code, uint64_t payload);
 uint64_t wave_workgroups(int cu_count, int code, uint64_t ntickets);
+// Whether a wave-kernel launch draws tickets from its counter; single: its table says one function with one descriptor.
+bool wave_draws(int code, uint64_t workgroups, uint64_t ntickets, bool single);
 
 // Bytes per ticket and tickets per chunk for a chunk size and a wanted tile size.
 void tile_shape(uint64_t chunk_bytes, uint64_t want_tile, uint64_t *tile_bytes, uint32_t *tiles_per_chunk);

@@ -144,13 +144,14 @@ extern "C" int ft_submit_static(ft_pool *p, const ft_desc *descs, uint32_t ndesc
                   : c == FT_P2P ? (uint64_t)sd.cu_count : (with_p2p || c == FT_P2H) ? 32u : 64u;
     if (wg > s.ntickets) wg = s.ntickets;
     const Layout small = inline_layout_of(cp);
-    if (s.code >= kWaveTiles && small.end <= kInlineBytes) {
+    const bool single = cp.funcs.size() == 1 && cp.xfers.size() == 1;
+    if (s.code >= kWaveTiles && !wave_draws(s.code, wg, s.ntickets, single) && small.end <= kInlineBytes) {
       // no counter and tables that fit the launch: nothing has to reach the array first (11 tensors, 18 MB: 11.0 -> 7.7 us
       // a call back to back, one tensor 10.5 -> 6.1: the small launch in front and the gap behind it are gone)
       ClassTable T{};
       fill_class_table(cp, small, reinterpret_cast<char *>(piece.w), nullptr, s.skips, s.ntickets, chunk_bytes, s.tile_bytes,
                        s.tiles_per_chunk, &T);
-      T.single = cp.funcs.size() == 1 && cp.xfers.size() == 1 ? 1u : 0u;
+      T.single = single ? 1u : 0u;
       FT_HIP(p, launch_copy(T, s.code, (uint32_t)wg, stream, nullptr, nullptr, &piece));
       continue;
     }

@@ -97,11 +97,11 @@ struct WgLogEntry {
 
 // Launch codes beside the three link classes: the kernel that gives every wavefront tiles of its own, with workgroups of
 //   kWaveTiles       one wavefront, a workgroup per ticket
-//   kWaveTwoPerUnit  eight wavefronts, at most two workgroups per compute unit, which stride over the tickets
-//   kWaveOnePerUnit  sixteen wavefronts, at most one workgroup per compute unit, likewise
-//   kWaveLink        four wavefronts, at most 64 workgroups, likewise
+//   kWaveTwoPerUnit  eight wavefronts, at most two workgroups per compute unit
+//   kWaveOnePerUnit  sixteen wavefronts, at most one workgroup per compute unit
+//   kWaveLink        four wavefronts, at most 64 workgroups
 // or'ed with kWaveStreams: nontemporal instead of ordinary loads (stores are nontemporal anyway), or on the host link
-// with the direction, kWaveFromHost or kWaveToHost.
+// with the direction, kWaveFromHost or kWaveToHost. How a launch with more tickets than wavefronts shares them out: ft_batches.h.
 constexpr int kWaveTiles = 8, kWaveTwoPerUnit = 9, kWaveOnePerUnit = 10, kWaveLink = 11;
 constexpr int kWaveStreams = 16, kWaveFromHost = 32, kWaveToHost = 64;
 constexpr uint32_t wave_code_threads(int code) {

@@ -261,3 +261,82 @@ def test_tiles_in_which_one_tensor_ends_and_the_next_begins(flags):
             assert np.array_equal(torch.cat([t for t, _ in eng.segments]).cpu().numpy(), orc.pool_mem)
     finally:
         eng.close()
+
+
+def test_batches_of_tickets_on_the_host(tmp_path):
+    """tests/host/ticket_batches.cpp: the protocol by which a workgroup's wavefronts share out the tickets behind the first
+    round, run by threads: each ticket once, every wavefront ends, also beside one that is arbitrarily slow."""
+    _host_sanitizer_run(tmp_path, "ticket_batches", [], ["1", "600"], "done 1..600")
+
+
+def _move_with_torch(mem, host, rec):
+    """One descriptor by plain strided torch copies; mem: the pool's bytes, host: pinned bytes."""
+    view = lambda space, at, pitch: (mem if space == FT_POOL else host).as_strided((rec["rows"], rec["row_bytes"]), (pitch, 1), at)
+    view(rec["dst_space"], rec["dst"], rec["dst_pitch"]).copy_(view(rec["src_space"], rec["src"], rec["src_pitch"]))
+
+
+# name, link class, (row bytes, payload MiB) of a slow and of a fast function, chunk = tile, descriptors of each, flags
+ORDER_CASES = [
+    ("pool, short rows", 2, (16, 2000), 50, 8192, 4, 0),
+    ("pool, short rows, uploaded tables", 2, (16, 2000), 50, 8192, 40, 0),
+    ("pool, short rows, beyond the cache", 2, (16, 2000), 100, 8192, 4, 0),
+    ("pool, long rows", 2, (2049, 60000), 50, 8192, 4, 0),
+    ("pool, long rows, detached", 2, (2049, 60000), 50, 8192, 4, fmt.FT_DETACHED),
+    ("host to pool", 0, (16, 2000), 8, 4096, 4, 0),
+    ("pool to host", 1, (16, 2000), 8, 4096, 4, 0),
+    ("pool to host, uploaded tables", 1, (16, 2000), 8, 4096, 40, 0),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", ORDER_CASES, ids=[c[0] for c in ORDER_CASES])
+def test_the_weighted_order_holds_whatever_the_tiles_cost(case):
+    """Two functions of equal weight whose tiles alternate, one of them of slow tiles: when half of the tickets have been
+    begun, half of those are the slow function's. A workgroup has at most the rest of one batch to begin, of which one
+    function has at most one ticket more than the other: |A - B| <= workgroups, so the share is off by at most
+    workgroups / tickets (and one per cent for tickets taken but not yet logged). Bytes against plain strided copies."""
+    import torch
+    from paper_2411_01830_amd import binding, harness
+    name, cls, widths, mib, chunk, nd, flags = case
+    print(f"case weighted order: {name}", flush=True)
+    eng = harness.GpuEngine()
+    try:
+        eng.host_arena(64 * MiB)
+        eng.pool_create(640 * MiB if mib == 50 else 1200 * MiB if mib == 100 else 64 * MiB, 4 * KiB)
+        mem = eng.segments[0][0]
+        mem.random_(0, 256, generator=torch.Generator("cuda").manual_seed(7))
+        eng.host.random_(0, 256, generator=torch.Generator().manual_seed(8))
+        recs, at = [], 32
+        for f, rb in enumerate(widths):
+            rows, pitch = mib * MiB // rb // nd, rb + 16 + f
+            for _ in range(nd):
+                extent = rows * pitch + 64
+                a = eng.slab_alloc(extent) if cls != 0 else at
+                b = eng.slab_alloc(extent) if cls != 1 else at
+                at += extent if cls != 2 else 0
+                recs.append(dict(func=f, src_space=FT_HOST if cls == 0 else FT_POOL, dst_space=FT_HOST if cls == 1 else FT_POOL, src=a + 1,
+                                 dst=b + 2, row_bytes=rb, rows=rows, src_pitch=pitch, dst_pitch=pitch))
+        assert at < 64 * MiB
+        want_mem, want_host = mem.clone(), eng.host.clone()
+        for r in recs:
+            _move_with_torch(want_mem, want_host, r)
+        torch.cuda.synchronize()
+        shares = []
+        for i in range(3):     # the counter has to be back at zero for the next launch
+            if i == 2:
+                flags |= fmt.FT_LOG
+            jg = eng.submit(make_descs(recs), [1, 1], chunk, flags | fmt.FT_KEEP)
+            eng.wait(jg)
+            st = binding.job_stats(eng.pool, jg).cls[cls]
+            assert st.tile_bytes == chunk and st.workgroups * 8 < st.tickets
+            if flags & fmt.FT_LOG:
+                log = binding.job_log(eng.pool, jg, cls)
+                assert int(log["bytes"].sum()) == st.payload_bytes
+                first = np.argsort(log["t_begin_ns"], kind="stable")[:st.tickets // 2]
+                shares.append(float((log["func"][first] == 0).mean()))
+                assert abs(shares[-1] - 0.5) <= st.workgroups / st.tickets + 0.01, (shares, st.workgroups, st.tickets)
+            binding.job_release(eng.pool, jg)
+            assert torch.equal(mem, want_mem) and torch.equal(eng.host, want_host), i
+        print(f"share of the slow function {shares}", flush=True)
+    finally:
+        eng.close()
