@@ -242,14 +242,15 @@ int ft_set_stage_threads(ft_pool *p, uint32_t threads);
  * tags first, equal tags by lower f - i.e. always serve the unfinished function with
  * the smallest (served+1)/weight. Persistent workgroups draw tickets from a device
  * counter in that order; the classes run concurrently on streams of their own. Jobs that latency
- * bounds (pool->pool up to 48 MiB, one tensor or mostly misaligned ones up to 128 MiB, pitched rows under
- * 64 KiB of any amount; host-link jobs of small pieces) have a wavefront per ticket. Up to 16 MiB pool->pool and
- * 1 MiB on the host link that is one workgroup per ticket, begun in the order's sequence. Beyond that there are
- * 4096 wavefronts (256 on the host link): each begins one ticket, and the tickets behind those follow in the
- * order, in batches of 8 (4) that the workgroups draw from the counter; a workgroup holds the rest of one batch
- * and one more at most, whatever its tiles cost. Two exceptions, in which every wavefront takes each 4096th (256th)
- * ticket: jobs of up to one and a half times as many tickets, most of which are begun at once, and one tensor, which has no
- * order to keep.
+ * bounds (pool->pool up to 48 MiB, one tensor or mostly misaligned ones up to 128 MiB, pitched rows
+ * under 64 KiB of any amount; host-link jobs of small pieces) give every ticket to a single wavefront:
+ *  - up to 16 MiB pool->pool and 1 MiB on the host link a workgroup per ticket, begun in the order;
+ *  - beyond that 4096 wavefronts (2048 for rows of over 128 MiB beside host-link traffic of the same
+ *    job, 256 on the host link) that begin with one ticket each; the tickets behind those follow
+ *    in the order, in batches of 8 (4 on the host link) that workgroups draw from the counter. Whatever
+ *    its tiles cost, a workgroup keeps the rest of one batch and one more to itself at most;
+ *  - but a job of up to one and a half times as many tickets as wavefronts, most of which are begun at
+ *    once, and one tensor, which has no order to keep, are dealt out.
  * A job of a single link class whose tables fit 3 KiB (not with FT_PATH_DMA,
  * FT_OPEN or a tuned workgroup count) is launched on hip_stream itself with its tables
  * as a kernel argument: same result and order, a tenth of the host time. If the workgroups have its

@@ -140,9 +140,13 @@ static int link_code(const ClassPlan &cp, int cls) {
 //   rows of 5760 bytes          34 MB 21.5 -> 11.6 / 24.7 -> 17.1  105 MB 47.4 -> 31.3 / 53.2 -> 41.7  419 MB 172 -> 148 (streamed)
 //   rows of 64 KiB              105 MB 41 -> 29                    419 MB 140 -> 150 (streamed)
 // so: any job up to 48 MiB; up to 128 MiB one tensor, mostly misaligned tensors, and rows; beyond that rows under 64 KiB.
-// alone: the job has no host-link traffic beside it. Beside a host-link kernel, whose workgroups hold their
-// compute units for milliseconds, only workgroups of one wavefront are used, which find room anywhere,
-// and long contiguous jobs keep the class's kernel, whose shape is chosen for that company.
+// alone: the job has no host-link traffic beside it. Beside a host-link kernel, whose workgroups hold their compute units
+// for milliseconds, long contiguous jobs keep the class's kernel, whose shape is chosen for that company, and rows go in
+// workgroups of eight wavefronts: two per compute unit find room beside one host-link workgroup (the 48 at most of both
+// directions leave more than enough units free). Rows that stream through HBM are given one per unit: with sixteen wavefronts
+// on every unit or more, the link's reads queue behind theirs. Measured, us, host->pool 128 MiB / rows of 5760 bytes 1.6 GB:
+// class's own kernel 2343 / 1540, a workgroup per tile 2506 / 584, two of eight wavefronts per unit 2487 / 571, one 2348 /
+// 552. Rows that the last-level cache holds, 110 MB, host->pool 32 MiB: 597 / 126, 597 / 33, 595 / 40, 595 / 46.
 int launch_code(const ClassPlan &cp, int cls, uint64_t chunk_bytes, bool tuned, bool alone) {
   if (tuned || !wave_tiles_fit(cp, chunk_bytes)) return cls;
   if (cls != FT_P2P) return alone ? link_code(cp, cls) : cls;
@@ -155,8 +159,10 @@ int launch_code(const ClassPlan &cp, int cls, uint64_t chunk_bytes, bool tuned, 
     else rows += !streams || x.row_bytes < 65536 ? n : 0;
     if (x.rows > 1 && x.row_bytes <= 2048) short_rows += n;
   }
-  if (2 * rows > cp.payload)
-    return (!alone ? kWaveTiles : 2 * short_rows > cp.payload ? kWaveTwoPerUnit : kWaveOnePerUnit) | (streams ? kWaveStreams : 0);
+  if (2 * rows > cp.payload) {
+    if (!alone) return streams ? kWaveBeside | kWaveStreams : kWaveTwoPerUnit;
+    return (2 * short_rows > cp.payload ? kWaveTwoPerUnit : kWaveOnePerUnit) | (streams ? kWaveStreams : 0);
+  }
   if (!alone || streams) return cls;
   return cp.payload <= kWaveAnyBytes || cp.xfers.size() == 1 || 2 * (misaligned + rows) > cp.payload ? kWaveOnePerUnit : cls;
 }

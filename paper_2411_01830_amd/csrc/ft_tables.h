@@ -100,12 +100,19 @@ struct WgLogEntry {
 //   kWaveTwoPerUnit  eight wavefronts, at most two workgroups per compute unit
 //   kWaveOnePerUnit  sixteen wavefronts, at most one workgroup per compute unit
 //   kWaveLink        four wavefronts, at most 64 workgroups
+//   kWaveBeside      eight wavefronts, at most one workgroup per compute unit
 // or'ed with kWaveStreams: nontemporal instead of ordinary loads (stores are nontemporal anyway), or on the host link
 // with the direction, kWaveFromHost or kWaveToHost. How a launch with more tickets than wavefronts shares them out: ft_batches.h.
-constexpr int kWaveTiles = 8, kWaveTwoPerUnit = 9, kWaveOnePerUnit = 10, kWaveLink = 11;
+constexpr int kWaveTiles = 8, kWaveTwoPerUnit = 9, kWaveOnePerUnit = 10, kWaveLink = 11, kWaveBeside = 12;
 constexpr int kWaveStreams = 16, kWaveFromHost = 32, kWaveToHost = 64;
 constexpr uint32_t wave_code_threads(int code) {
-  return (code & 15) == kWaveTiles ? 64u : (code & 15) == kWaveTwoPerUnit ? 512u : (code & 15) == kWaveOnePerUnit ? 1024u : (code & 15) == kWaveLink ? 256u : 0u;
+  switch (code & 15) {
+    case kWaveTiles: return 64;
+    case kWaveTwoPerUnit: case kWaveBeside: return 512;
+    case kWaveOnePerUnit: return 1024;
+    case kWaveLink: return 256;
+    default: return 0;
+  }
 }
 
 // Everything one class's kernel needs; passed by value as the kernel argument.

@@ -94,7 +94,7 @@ static void job(std::mt19937_64 &r) {
   build_skips(cp, C, tile, tpc, &skips, &nt);
   CHECK(nt < (1u << 31) && tile <= 16384 && wave_code_threads(code) != 0);
   const uint64_t wg = wave_workgroups(256, code, nt);
-  CHECK(wg > 0 && wg <= nt && ((code & 15) != kWaveTiles || wg == nt));
+  CHECK(wg > 0 && wg <= nt && ((code & 15) != kWaveTiles || wg == nt) && wg * wave_code_threads(code) < (1ull << 32));
   const uint64_t stride = nt > 3000 ? nt / 3000 : 1;
   for (uint64_t t = 0; t < nt; t += stride, ++n_tickets) {
     // as the wave kernel decodes it
@@ -137,8 +137,43 @@ static void job(std::mt19937_64 &r) {
   }
 }
 
+// A launch has fewer than 2^32 threads however much there is to move: pitched rows in the smallest chunks that the wave
+// kernel takes, up to what fits the device's memory twice, alone and beside host-link traffic.
+static void largest_launches() {
+  for (uint64_t gib = 1; gib <= 144; gib *= 2)
+    for (uint64_t C : {1024ull, 4096ull, 2ull << 20})
+      for (uint64_t rb : {16ull, 2000ull, 5760ull, 60000ull})
+        for (int alone = 0; alone < 2; ++alone) {
+          ClassPlan cp;
+          Func fn{};
+          fn.weight = 1;
+          while (fn.stream_bytes < gib << 30) {
+            Xfer x{};
+            x.row_bytes = rb;
+            x.rows = (1ull << 30) / rb + 1;
+            x.src_pitch = x.dst_pitch = rb + 16;
+            x.stream_off = fn.stream_bytes;
+            fn.stream_bytes += x.row_bytes * x.rows;
+            cp.xfers.push_back(x);
+          }
+          fn.ndesc = (uint32_t)cp.xfers.size();
+          fn.nchunks = cp.nchunks = (fn.stream_bytes + C - 1) / C;
+          cp.payload = fn.stream_bytes;
+          cp.funcs.push_back(fn);
+          const int code = launch_code(cp, FT_P2P, C, false, alone != 0);
+          CHECK(code >= kWaveTiles || C == 1024);
+          if (code < kWaveTiles) continue;
+          uint64_t tile;
+          uint32_t tpc;
+          tile_shape(C, wave_tile(code, cp.payload), &tile, &tpc);
+          const uint64_t nt = cp.nchunks * tpc, wg = wave_workgroups(256, code, nt);
+          CHECK(nt < (1ull << 31) && wg * wave_code_threads(code) < (1ull << 32));
+        }
+}
+
 int main(int argc, char **argv) {
   const uint64_t first = argc > 1 ? strtoull(argv[1], 0, 10) : 1, count = argc > 2 ? strtoull(argv[2], 0, 10) : 50;
+  largest_launches();
   for (uint32_t d = 0; d < 16; ++d)
     for (uint32_t n = 16; n < 9000; n += n < 200 ? 1 : 61) run(d, n);
   for (g_seed = first; g_seed < first + count; ++g_seed) {

@@ -340,3 +340,52 @@ def test_the_weighted_order_holds_whatever_the_tiles_cost(case):
         print(f"share of the slow function {shares}", flush=True)
     finally:
         eng.close()
+
+
+# name, pieces(rng), beside the host link, chunk, workgroups per compute unit, tile
+LARGE_CASES = [
+    ("rows beside the host link", lambda g: _rows(g, 12, [300, 5761, 30000], 40 * MiB, 3), True, 256 * KiB, 2, 8192),
+    ("rows beyond the cache beside the host link", lambda g: _rows(g, 12, [300, 5761, 30000], 150 * MiB, 3), True, 1 * MiB, 1, 8192),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", LARGE_CASES, ids=[c[0] for c in LARGE_CASES])
+def test_large_jobs_against_plain_copies(case):
+    """Jobs of tens to hundreds of MiB, the whole pool compared with what plain strided copies make of it; the tile names the
+    kernel that ran (the copy kernel proper has 43 and 64 KiB), the workgroups its form."""
+    import torch
+    from paper_2411_01830_amd import binding, harness
+    name, pieces, beside, chunk, per_unit, tile = case
+    print(f"case large job: {name}", flush=True)
+    rng = np.random.default_rng(len(name))
+    eng = harness.GpuEngine()
+    try:
+        eng.host_arena(8 * MiB)
+        pcs = pieces(rng)
+        eng.pool_create(sum(2 * ((rows * max(sp, dp, rb) + 16) // KiB // 4 + 2) * 4 * KiB for rb, rows, sp, dp, *_ in pcs) + 8 * MiB, 4 * KiB)
+        mem = eng.segments[0][0]
+        mem.random_(0, 256, generator=torch.Generator("cuda").manual_seed(3))
+        eng.host.random_(0, 256, generator=torch.Generator().manual_seed(4))
+        recs = []
+        for rb, rows, sp, dp, f, ss, ds in pcs:
+            sp, dp = (sp, dp) if rows > 1 else (rb, rb)
+            a, b = eng.slab_alloc((rows - 1) * sp + rb + 16), eng.slab_alloc((rows - 1) * dp + rb + 16)
+            recs.append(dict(func=f, src_space=FT_POOL, dst_space=FT_POOL, src=a + ss, dst=b + ds, row_bytes=rb, rows=rows, src_pitch=sp, dst_pitch=dp))
+        if beside:
+            b = eng.slab_alloc(4 * MiB)
+            recs.append(dict(func=0, src_space=FT_HOST, dst_space=FT_POOL, src=5, dst=b + 3, row_bytes=4 * MiB - 77, rows=1, src_pitch=4 * MiB - 77, dst_pitch=4 * MiB - 77))
+        want = mem.clone()
+        for r in recs:
+            _move_with_torch(want, eng.host, r)
+        torch.cuda.synchronize()
+        weights = [1 + f for f in range(1 + max(r["func"] for r in recs))]
+        for _ in range(2):
+            jg = eng.submit(make_descs(recs), weights, chunk, fmt.FT_KEEP)
+            eng.wait(jg)
+            st = binding.job_stats(eng.pool, jg).cls[2]
+            assert (st.tile_bytes, st.workgroups) == (tile, per_unit * torch.cuda.get_device_properties(0).multi_processor_count)
+            binding.job_release(eng.pool, jg)
+            assert torch.equal(mem, want)
+    finally:
+        eng.close()
