@@ -592,14 +592,11 @@ int launch_with_the_launch(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chun
   return FT_OK;
 }
 
-// Tables of `bytes` bytes (a multiple of 256) from a blob's pinned twin to its device buffer, on `stream`. From 16 KiB
-// on the runtime hands its copy to the copy engine, whose start and whose completion signal the kernel behind it
-// waits for (10 us in front of the launch); there the wave kernel fetches the tables, as one tensor in tiles of
-// 1 KiB. Submit to end of wait, 8 KB tensors: 256 of them 38.5 -> 28.7 us, 1024 63.5 -> 55.0 us; 128 of them (12 KiB
-// of tables, which the runtime copies with a kernel too) 24.5 us either way.
+// Tables of `bytes` bytes (a multiple of 256) from a blob's pinned twin to its device buffer, on `stream`: by the runtime's
+// copy, or as one tensor by the wave kernel, whose loads are then those for host memory (the rule stands with table_fetch_tile).
 hipError_t upload_tables(const Blob &b, uint64_t bytes, unsigned long long *idle_counter, hipStream_t stream) {
-  if (bytes < 16 * 1024) return hipMemcpyAsync(b.dev, b.host, bytes, hipMemcpyHostToDevice, stream);
-  constexpr uint64_t kTile = 1024;
+  const uint64_t tile = table_fetch_tile(bytes);
+  if (tile == 0) return hipMemcpyAsync(b.dev, b.host, bytes, hipMemcpyHostToDevice, stream);
   InlineBlob tables;
   Xfer x{};
   x.src = reinterpret_cast<uint64_t>(b.host);
@@ -610,13 +607,13 @@ hipError_t upload_tables(const Blob &b, uint64_t bytes, unsigned long long *idle
   std::memcpy(tables.w, &x, sizeof(x));
   ClassTable T{};
   T.ticket = idle_counter;
-  T.ntickets = T.nchunks = (bytes + kTile - 1) / kTile;
-  T.chunk_bytes = T.tile_bytes = kTile;
+  T.ntickets = T.nchunks = (bytes + tile - 1) / tile;
+  T.chunk_bytes = T.tile_bytes = tile;
   T.tiles_per_chunk = 1;
   T.desc_per = 1;
   T.inline_tables = 1;
   T.single = 1;
-  return launch_copy(T, kWaveTiles, (uint32_t)T.ntickets, stream, nullptr, nullptr, &tables);
+  return launch_copy(T, kTableFetch, (uint32_t)T.ntickets, stream, nullptr, nullptr, &tables);
 }
 
 // The general way: the tables of all classes in one blob, copied to the device on the caller's

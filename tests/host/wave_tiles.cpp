@@ -171,9 +171,19 @@ static void largest_launches() {
         }
 }
 
+// A launch that fetches tables asks host memory for no more than fills the link, and with the loads meant for it.
+static void table_fetches() {
+  for (uint64_t n = 256; n < 64u << 20; n += n < 1u << 20 ? 256 : 65536) {
+    const uint64_t tile = table_fetch_tile(n);
+    if (tile != 0) CHECK(tile % 16 == 0 && (n + tile - 1) / tile * tile <= 256 * 1024);
+  }
+  CHECK(table_fetch_tile(100000 / 256 * 256) != 0 && (kTableFetch & kWaveFromHost) && wave_code_threads(kTableFetch) == 64);
+}
+
 int main(int argc, char **argv) {
   const uint64_t first = argc > 1 ? strtoull(argv[1], 0, 10) : 1, count = argc > 2 ? strtoull(argv[2], 0, 10) : 50;
   largest_launches();
+  table_fetches();
   for (uint32_t d = 0; d < 16; ++d)
     for (uint32_t n = 16; n < 9000; n += n < 200 ? 1 : 61) run(d, n);
   for (g_seed = first; g_seed < first + count; ++g_seed) {
