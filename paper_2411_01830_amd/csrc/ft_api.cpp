@@ -594,8 +594,9 @@ int launch_with_the_launch(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chun
 
 // Tables of `bytes` bytes (a multiple of 256) from a blob's pinned twin to its device buffer, on `stream`: by the runtime's
 // copy, or as one tensor by the wave kernel, whose loads are then those for host memory (the rule stands with table_fetch_tile).
-hipError_t upload_tables(const Blob &b, uint64_t bytes, unsigned long long *idle_counter, hipStream_t stream) {
-  const uint64_t tile = table_fetch_tile(bytes);
+// dma: a job by the copy engines, which does not wait for a free compute unit.
+hipError_t upload_tables(const Blob &b, uint64_t bytes, bool dma, unsigned long long *idle_counter, hipStream_t stream) {
+  const uint64_t tile = dma ? 0 : table_fetch_tile(bytes);
   if (tile == 0) return hipMemcpyAsync(b.dev, b.host, bytes, hipMemcpyHostToDevice, stream);
   InlineBlob tables;
   Xfer x{};
@@ -668,7 +669,7 @@ int launch_with_uploaded_tables(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t
     put_event(p, false, fork);
     return fail_submit(p, job, FT_EHIP);
   };
-  hipError_t e = upload_tables(job->tables, total, p->ctx->idle_counter, user);
+  hipError_t e = upload_tables(job->tables, total, dma, p->ctx->idle_counter, user);
   if (e != hipSuccess) return hip_fail(e, "upload of the tables");
   if (!straight) {
     e = hipEventRecord(fork, user);

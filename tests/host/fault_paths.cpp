@@ -174,6 +174,31 @@ static int pass(World &w, bool inject, const char *point, int n) {
   return failures;
 }
 
+// A job by the copy engines launches no kernel, however long its tables.
+static void copy_engines_alone(World &w) {
+  std::vector<ft_desc> d(1000);
+  ft_off_t src = 0, dst = 0;
+  CHECK(ft_slab_alloc(w.pool, 1 * MiB, &src) == FT_OK && ft_slab_alloc(w.pool, 1 * MiB, &dst) == FT_OK);
+  for (size_t i = 0; i < d.size(); ++i) {
+    std::memset(&d[i], 0, sizeof(ft_desc));
+    d[i].src_space = d[i].dst_space = FT_POOL;
+    d[i].src = src + i * 1024;
+    d[i].dst = dst + i * 1024;
+    d[i].row_bytes = 700;
+    d[i].rows = 1;
+  }
+  for (uint64_t i = 0; i < 1 * MiB; ++i) w.dev[src + i] = (char)(i * 97 >> 3);
+  const uint32_t weight = 1;
+  ft_job_t job = 0;
+  CHECK(stand_in_fail("launch_copy", 1) == 0);
+  CHECK(ft_submit_transfers(w.pool, d.data(), (uint32_t)d.size(), &weight, 1, 64 * KiB, FT_PATH_DMA, nullptr, &job) == FT_OK);
+  CHECK(ft_wait(w.pool, job) == FT_OK);
+  CHECK(stand_in_fail("launch_copy", 0) == 0);
+  for (const ft_desc &x : d) CHECK(std::memcmp(w.dev + x.src, w.dev + x.dst, x.row_bytes) == 0);
+  CHECK(ft_slab_free(w.pool, src) == FT_OK && ft_slab_free(w.pool, dst) == FT_OK);
+  std::memcpy(w.expect.data(), w.dev, w.pool_bytes);
+}
+
 int main() {
   World w;
   CHECK(hipMalloc(reinterpret_cast<void **>(&w.dev), w.pool_bytes) == hipSuccess);
@@ -188,6 +213,7 @@ int main() {
   w.pageable_expect = w.pageable;
   CHECK(ft_pageable_window_add(w.pool, w.pageable.data(), w.pageable.size()) == FT_OK);
   CHECK(pass(w, false, "-", 0) == 0);  // also creates the per-device resources
+  copy_engines_alone(w);
   const char *points[] = {"hipMemcpyAsync", "hipEventRecord", "hipStreamWaitEvent", "hipEventCreateWithFlags",
                           "hipMalloc",      "hipHostMalloc",  "hipEventSynchronize", "launch_copy"};
   int hit = 0;
