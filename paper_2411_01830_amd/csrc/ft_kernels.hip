@@ -1170,8 +1170,11 @@ __device__ __forceinline__ V ld_off(uint64_t base, uint32_t off) {
 }
 template <class V, int NT>
 __device__ __forceinline__ void st_off(uint64_t base, uint32_t off, V v) {
-  if (NT == kToHost && sizeof(V) == 16) {  // written through to the fabric at once
-    asm volatile("global_store_dwordx4 %0, %1, %2 sc1\n\ts_nop 1" ::"v"(off), "v"(v), "s"(base) : "memory");
+  if (NT == kToHost && sizeof(V) == 16) {
+    // Written through to the fabric at once, as st16 does. The whole address in vector registers: between a vector instruction
+    // that writes a scalar register and a store that reads it there must be five wait states, which the compiler does not
+    // see to for inline assembly.
+    asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(base + off), "v"(v) : "memory");
     return;
   }
   __builtin_nontemporal_store(v, reinterpret_cast<V FT_GLOBAL *>(reinterpret_cast<char FT_GLOBAL *>(base) + off));

@@ -1,5 +1,7 @@
 """The kernel that gives every wavefront tiles of its own: pool->pool jobs of at most 16, 48 or 128 MiB and jobs of
 pitched rows, host-link jobs of small pieces, at the sizes where its windows, its tiles and the rule that picks it change. Bit-exact against the oracle."""
+import os
+
 import numpy as np
 import pytest
 
@@ -15,6 +17,24 @@ def test_windows_and_decode_on_the_host(tmp_path):
     """tests/host/wave_tiles.cpp: the kernel's window arithmetic covers every piece and stays inside it; a ticket
     decoded by comparing 64 entries at a time names what the general walk names."""
     _host_sanitizer_run(tmp_path, "wave_tiles", ["ft_plan.cpp", "ft_pool.cpp"], ["1", "60"], "done 1..60")
+
+
+def test_inline_assembly_stores_leave_no_hazard_to_the_scheduler(tmp_path):
+    """The stores that are written through to the host are inline assembly, for which the compiler inserts no wait states: each
+    has its two before its data may be overwritten, and none takes its address from a scalar register, which a vector
+    instruction may have written within the five before."""
+    import re
+    import subprocess
+    from paper_2411_01830_amd import build
+    out = tmp_path / "kernels.s"
+    subprocess.run([build.hipcc(), "-x", "hip", *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, "ft_kernels.hip"), "-o", str(out)],
+                   check=True, capture_output=True)
+    lines = [re.sub(r"\s+", " ", l.split("//")[0]).strip() for l in open(out)]
+    stores = [i for i, l in enumerate(lines) if l.startswith("global_store_dwordx4") and l.endswith(" sc1")]
+    assert len(stores) > 100
+    for i in stores:
+        assert re.fullmatch(r"global_store_dwordx4 v\[\d+:\d+\], [va]\[\d+:\d+\], off sc1", lines[i]), lines[i]
+        assert lines[i + 1] == "s_nop 1", lines[i:i + 2]
 
 
 def _runs(rng, n, sizes, funcs):
