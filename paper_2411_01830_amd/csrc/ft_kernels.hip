@@ -1278,6 +1278,28 @@ __device__ __forceinline__ void wave_copy_rows(const Xfer &X, uint32_t p, uint32
   if (edge) st_off<uint8_t, 0>(d, ed, eb);
 }
 
+// The bytes of a decoded ticket, and its entry in the log.
+template <int NT>
+__device__ __forceinline__ void wave_move(const ClassTable &T, const ConstTables &CT, uint32_t t, const Work &w, uint64_t t_begin, uint32_t lane) {
+  uint64_t pos = w.b0;
+  for (uint32_t x = w.x; pos < w.b1; ++x) {
+    const Xfer X = read_xfer(CT.xfers, x);
+    const uint64_t p = pos - X.stream_off;
+    uint64_t take = X.row_bytes * X.rows - p;
+    if (take > w.b1 - pos) take = w.b1 - pos;
+    if (X.rows == 1) wave_copy_run<NT>(X.dst + p, X.src + p, (uint32_t)take, lane);
+    else wave_copy_rows<NT>(X, (uint32_t)p, (uint32_t)take, lane);
+    pos += take;
+  }
+  if (T.log && lane == 0) {
+    log_decoded(T, t, w);
+    __builtin_amdgcn_s_waitcnt(0);
+    T.log[t].t_begin = t_begin;
+    T.log[t].t_end = wall_clock64();
+    T.log[t].wg = blockIdx.x;
+  }
+}
+
 // A workgroup's batches of tickets (ft_batches.h), in LDS.
 struct WaveBatches {
   unsigned long long taken;
@@ -1293,27 +1315,39 @@ struct WaveBatches {
   __device__ void pause() { __builtin_amdgcn_s_sleep(1); }
 };
 
-// Every wavefront starts on a ticket of its own. A launch with many more tickets than wavefronts (wave_shares) hands the
-// others out in order: workgroup b has batch b behind the first round from the start, *T.ticket counts the batches drawn
-// beyond those (zero at launch). One tensor has no order to keep: its tickets are dealt out. With every ticket dealt out the
-// order was what equal speeds made of it: of two functions of equal weight with alternating tiles, rows of 16 and of 2000 bytes,
-// 200 MB each, the slow one had 21 % of the tiles begun at half time, now 50 %. Kernel time, us, dealt out -> by batches: rows of
-// 256 bytes 419 MB 147 -> 147, of 5760 bytes 110 MB 31 -> 32, 1.6 GB 587 -> 530; 64 misaligned tensors 105 MB 35 -> 34; host->pool
-// 20 000 pieces of 4000 bytes 1566 -> 1464 (a wavefront that the link serves late keeps none of the others' work).
-template <int NT>
-__global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void ft_wave_kernel(ClassTable T, InlineBlob) {
-  __shared__ WaveBatches s_batches;
+// Every wavefront starts on a ticket of its own; how it comes to others:
+//   kOneTicket  not at all: a launch of as many workgroups of one wavefront as there are tickets
+//   kDealt      each round-th ticket, where that is as good as the order (wave_shares) or there is no order to keep: one tensor
+//   kShared     in the order: workgroup b has batch b behind the first round from the start, *T.ticket counts the batches
+//               drawn beyond those (zero at launch)
+// The forms are kernels of their own because short launches pay for every instruction that they fetch: kOneTicket with the
+// other forms' code in its kernel 1024 tensors of 10 KB 7.8 us, with that of kShared too 8.3, alone 7.4.
+// With every ticket of long launches dealt out the order was what equal speeds made of it: of two functions of equal weight with
+// alternating tiles, rows of 16 and of 2000 bytes, 200 MB each, the slow one had 21 % of the tiles begun at half time, now
+// 50 %. Kernel time, us, dealt out -> in the order: rows of 256 bytes 63 MB 18.4 -> 19.2, 419 MB 147 -> 147, of 5760 bytes 110 MB
+// 32 -> 32, 1.6 GB 588 -> 531; 64 misaligned tensors 105 MB 35 -> 35; host->pool 20 000 pieces of 4000 bytes 1574 -> 1467 (a
+// wavefront that the link serves late keeps none of the others' work).
+constexpr int kOneTicket = 0, kDealt = 1, kShared = 2;
+template <int NT, int FORM>
+__global__ __launch_bounds__(FORM == kOneTicket ? 64 : 1024) __attribute__((amdgpu_waves_per_eu(7))) void ft_wave_kernel(ClassTable T, InlineBlob) {
   const ConstTables CT = const_tables(T);
   const uint32_t lane = threadIdx.x & 63;
-  const uint32_t waves = blockDim.x >> 6, round = gridDim.x * waves;
-  const uint32_t batch = wave_batch(waves);
-  const bool shares = !T.single && wave_shares(round, T.ntickets);  // both the same for the whole launch
-  const bool counts = wave_counts(gridDim.x, waves, T.ntickets);
+  uint64_t t_begin = 0;
+  if (T.log) t_begin = wall_clock64();
   if (T.log && threadIdx.x == 0) {
-    T.wg_log[blockIdx.x].t_entry = wall_clock64();
+    T.wg_log[blockIdx.x].t_entry = t_begin;
     T.wg_log[blockIdx.x].unit = compute_unit_id();
   }
-  if (shares) {
+  if (FORM == kOneTicket) {
+    wave_move<NT>(T, CT, blockIdx.x, decode_ticket_wave(T, CT, blockIdx.x, lane), t_begin, lane);
+    if (T.log && lane == 0) T.wg_log[blockIdx.x].t_exit = wall_clock64();
+    return;
+  }
+  __shared__ WaveBatches s_batches;
+  const uint32_t waves = blockDim.x >> 6, round = gridDim.x * waves;
+  const uint32_t batch = wave_batch(waves);
+  const bool counts = wave_counts(gridDim.x, waves, T.ntickets);
+  if (FORM == kShared) {
     if (threadIdx.x == 0) {
       s_batches.taken = batch;
       s_batches.next = round + blockIdx.x * batch;
@@ -1321,46 +1355,28 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(7))) void 
     __syncthreads();
   }
   // neighbouring tickets of the first round go to different compute units
-  const uint32_t wave = uniform32(threadIdx.x >> 6);
-  uint32_t t = wave * gridDim.x + blockIdx.x;
+  uint32_t t = uniform32(threadIdx.x >> 6) * gridDim.x + blockIdx.x;
   bool draw = false;
   while (t < (uint32_t)T.ntickets) {
-    uint64_t t_begin = 0;
     if (T.log) t_begin = wall_clock64();
     unsigned long long drawn = 0;
-    if (draw && counts && lane == 0) drawn = atomicAdd(T.ticket, 1ull);  // answered while the tables are read
+    if (FORM == kShared && draw && counts && lane == 0) drawn = atomicAdd(T.ticket, 1ull);  // answered while the tables are read
     const Work w = decode_ticket_wave(T, CT, t, lane);
-    if (draw && lane == 0) s_batches.set_ahead(counts ? round + (gridDim.x + (uint32_t)drawn) * batch : (uint32_t)T.ntickets);
-    uint64_t pos = w.b0;
-    for (uint32_t x = w.x; pos < w.b1; ++x) {
-      const Xfer X = read_xfer(CT.xfers, x);
-      const uint64_t p = pos - X.stream_off;
-      uint64_t take = X.row_bytes * X.rows - p;
-      if (take > w.b1 - pos) take = w.b1 - pos;
-      if (X.rows == 1) wave_copy_run<NT>(X.dst + p, X.src + p, (uint32_t)take, lane);
-      else wave_copy_rows<NT>(X, (uint32_t)p, (uint32_t)take, lane);
-      pos += take;
+    if (FORM == kShared && draw && lane == 0)
+      s_batches.set_ahead(counts ? round + (gridDim.x + (uint32_t)drawn) * batch : (uint32_t)T.ntickets);
+    wave_move<NT>(T, CT, t, w, t_begin, lane);
+    t += round;
+    if (FORM == kShared) {
+      uint32_t taken = 0;
+      bool owes = false;
+      if (lane == 0) taken = take_ticket(s_batches, batch, (uint32_t)T.ntickets, &owes);
+      t = uniform32(taken);
+      draw = uniform32(owes ? 1u : 0u) != 0;
     }
-    if (T.log && lane == 0) {
-      log_decoded(T, t, w);
-      __builtin_amdgcn_s_waitcnt(0);
-      T.log[t].t_begin = t_begin;
-      T.log[t].t_end = wall_clock64();
-      T.log[t].wg = blockIdx.x;
-    }
-    if (!shares) {
-      t += round;
-      continue;
-    }
-    uint32_t taken = 0;
-    bool owes = false;
-    if (lane == 0) taken = take_ticket(s_batches, batch, (uint32_t)T.ntickets, &owes);
-    t = uniform32(taken);
-    draw = uniform32(owes ? 1u : 0u) != 0;
   }
   if (T.log || T.self_reset) __syncthreads();
   if (T.log && threadIdx.x == 0) T.wg_log[blockIdx.x].t_exit = wall_clock64();
-  if (T.self_reset && threadIdx.x == 0) reset_counters_after_last(T);
+  if (FORM == kShared && T.self_reset && threadIdx.x == 0) reset_counters_after_last(T);
 }
 
 __global__ void ft_decode_kernel(ClassTable T, InlineBlob, uint32_t *func_out, uint32_t *chunk_out, uint64_t cap) {
@@ -1415,6 +1431,16 @@ __global__ __launch_bounds__(kThreads) void ft_plain_fill_kernel(u32x4 *dst, uin
 // What a launch passes as tables when the job's own are in device memory.
 static const InlineBlob kNoTables{};
 
+template <int NT>
+static hipError_t launch_wave(int form, dim3 grid, uint32_t waves, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop,
+                              const ClassTable &T, const InlineBlob &B) {
+  const dim3 block(waves * 64);
+  if (form == kOneTicket) hipExtLaunchKernelGGL((ft_wave_kernel<NT, kOneTicket>), grid, block, 0, stream, ev_start, ev_stop, 0, T, B);
+  else if (form == kDealt) hipExtLaunchKernelGGL((ft_wave_kernel<NT, kDealt>), grid, block, 0, stream, ev_start, ev_stop, 0, T, B);
+  else hipExtLaunchKernelGGL((ft_wave_kernel<NT, kShared>), grid, block, 0, stream, ev_start, ev_stop, 0, T, B);
+  return hipGetLastError();
+}
+
 hipError_t launch_copy(const ClassTable &T, int link_class, uint32_t workgroups, hipStream_t stream,
                        hipEvent_t ev_start, hipEvent_t ev_stop, const InlineBlob *tables) {
   if (workgroups == 0 || (T.inline_tables != 0) != (tables != nullptr)) return hipErrorInvalidValue;
@@ -1422,13 +1448,16 @@ hipError_t launch_copy(const ClassTable &T, int link_class, uint32_t workgroups,
   const InlineBlob &B = tables ? *tables : kNoTables;
   // with events, they are bound to this dispatch: they read the kernel's own start and end
   if (link_class >= kWaveTiles) {
-    const uint32_t threads = wave_code_threads(link_class);
-    if (threads == 0) return hipErrorInvalidValue;
-    if (link_class & kWaveFromHost) hipExtLaunchKernelGGL(ft_wave_kernel<kFromHost>, grid, dim3(threads), 0, stream, ev_start, ev_stop, 0, T, B);
-    else if (link_class & kWaveToHost) hipExtLaunchKernelGGL(ft_wave_kernel<kToHost>, grid, dim3(threads), 0, stream, ev_start, ev_stop, 0, T, B);
-    else if (link_class & kWaveStreams) hipExtLaunchKernelGGL(ft_wave_kernel<kStream>, grid, dim3(threads), 0, stream, ev_start, ev_stop, 0, T, B);
-    else hipExtLaunchKernelGGL(ft_wave_kernel<0>, grid, dim3(threads), 0, stream, ev_start, ev_stop, 0, T, B);
-    return hipGetLastError();
+    const uint32_t waves = wave_code_threads(link_class) / 64;
+    const int form = (link_class & 15) == kWaveTiles ? kOneTicket : !T.single && wave_shares(workgroups * waves, T.ntickets) ? kShared : kDealt;
+    if (waves == 0 || (form == kOneTicket && workgroups != T.ntickets)) return hipErrorInvalidValue;
+    switch (link_class & ~15) {
+      case 0: return launch_wave<0>(form, grid, waves, stream, ev_start, ev_stop, T, B);
+      case kWaveStreams: return launch_wave<kStream>(form, grid, waves, stream, ev_start, ev_stop, T, B);
+      case kWaveFromHost: return launch_wave<kFromHost>(form, grid, waves, stream, ev_start, ev_stop, T, B);
+      case kWaveToHost: return launch_wave<kToHost>(form, grid, waves, stream, ev_start, ev_stop, T, B);
+      default: return hipErrorInvalidValue;
+    }
   }
   switch (link_class) {
     case 0: hipExtLaunchKernelGGL((ft_copy_kernel<true, 0>), grid, block, 0, stream, ev_start, ev_stop, 0, T, B); break;
