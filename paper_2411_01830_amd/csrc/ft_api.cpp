@@ -593,11 +593,11 @@ int launch_with_the_launch(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chun
 }
 
 // Tables of `bytes` bytes (a multiple of 256) from a blob's pinned twin to its device buffer, on `stream`: by the runtime's
-// copy, or as one tensor by the wave kernel, whose loads are then those for host memory (the rule stands with table_fetch_tile).
+// copy, or as one tensor by the wave kernel, whose loads are then those for host memory (the rule stands with table_fetch_code).
 // dma: a job by the copy engines, which does not wait for a free compute unit.
 hipError_t upload_tables(const Blob &b, uint64_t bytes, bool dma, unsigned long long *idle_counter, hipStream_t stream) {
-  const uint64_t tile = dma ? 0 : table_fetch_tile(bytes);
-  if (tile == 0) return hipMemcpyAsync(b.dev, b.host, bytes, hipMemcpyHostToDevice, stream);
+  const int code = dma ? 0 : table_fetch_code(bytes);
+  if (code == 0) return hipMemcpyAsync(b.dev, b.host, bytes, hipMemcpyHostToDevice, stream);
   InlineBlob tables;
   Xfer x{};
   x.src = reinterpret_cast<uint64_t>(b.host);
@@ -608,13 +608,13 @@ hipError_t upload_tables(const Blob &b, uint64_t bytes, bool dma, unsigned long 
   std::memcpy(tables.w, &x, sizeof(x));
   ClassTable T{};
   T.ticket = idle_counter;
-  T.ntickets = T.nchunks = (bytes + tile - 1) / tile;
-  T.chunk_bytes = T.tile_bytes = tile;
+  T.ntickets = T.nchunks = (bytes + kTableTile - 1) / kTableTile;
+  T.chunk_bytes = T.tile_bytes = kTableTile;
   T.tiles_per_chunk = 1;
   T.desc_per = 1;
   T.inline_tables = 1;
   T.single = 1;
-  return launch_copy(T, kTableFetch, (uint32_t)T.ntickets, stream, nullptr, nullptr, &tables);
+  return launch_copy(T, code, (uint32_t)wave_workgroups(0, code, T.ntickets), stream, nullptr, nullptr, &tables);
 }
 
 // The general way: the tables of all classes in one blob, copied to the device on the caller's

@@ -186,13 +186,16 @@ uint64_t wave_workgroups(int cu_count, int code, uint64_t ntickets) {
 }
 
 // From 16 KiB on the runtime hands its copy to the copy engine, whose start and whose completion signal the kernel behind it
-// waits for (10 us in front of the launch). Submit to end of wait, 8 KB tensors, runtime's copy -> wave kernel: 256 of them 38.5 ->
-// 28.7 us, 1024 (100 KB of tables) 63.5 -> 55.0 us; 128 of them (12 KiB, which the runtime copies with a kernel too) 24.5 us either
-// way. Beyond some 100 KB planning hides the difference (4096 descriptors 95 us either way, 16384 240), and every tile is a
-// read of host memory in flight: with a workgroup per KiB of any amount 1 GiB pool->pool beside a submit of 16384
-// descriptors took 341 us instead of 325, a host->pool job 1199 instead of 1193. So no more than the 256 KiB of reads that fill
-// the link.
-uint64_t table_fetch_tile(uint64_t bytes) { return bytes < 16 * 1024 || bytes > 256 * 1024 ? 0 : 1024; }
+// waits for (10 us in front of the launch), and what it wrote comes from HBM (2000 functions, 600 KB: kernel behind it 287 us, behind a
+// launch 258). Submit to end of wait, 8 KB tensors, runtime's copy -> wave kernel: 256 of them 38.5 -> 28.7 us, 1024 63.5 ->
+// 55.0 us; 128 of them (12 KiB, which the runtime copies with a kernel too) 24.5 us either way. Every wavefront has a tile
+// of host memory in flight: with a workgroup per KiB of any amount 1 GiB pool->pool beside a submit of 16 384 descriptors took
+// 341 us instead of 325, a host->pool job 1199 instead of 1193. So beyond the 256 KiB of reads that fill the link the
+// tiles are dealt out to 256 wavefronts.
+int table_fetch_code(uint64_t bytes) {
+  if (bytes < 16 * 1024) return 0;
+  return (bytes <= 256 * 1024 ? kWaveTiles : kWaveLink) | kWaveFromHost;
+}
 
 bool wave_draws(int code, uint64_t workgroups, uint64_t ntickets, bool single) {
   return !single && wave_counts(workgroups, wave_code_threads(code) / 64, ntickets);

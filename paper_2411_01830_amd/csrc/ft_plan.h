@@ -78,10 +78,10 @@ uint64_t wave_workgroups(int cu_count, int code, uint64_t ntickets);
 // Whether a wave-kernel launch draws tickets from its counter; single: its table says one function with one descriptor.
 bool wave_draws(int code, uint64_t workgroups, uint64_t ntickets, bool single);
 
-// How a job's tables reach the device: tiles of this many bytes by a wave-kernel launch of code kTableFetch with a workgroup
-// per tile; 0: by the runtime's copy.
-constexpr int kTableFetch = kWaveTiles | kWaveFromHost;
-uint64_t table_fetch_tile(uint64_t bytes);
+// How a job's tables of this many bytes reach the device: 0 by the runtime's copy, otherwise by a wave-kernel launch of this
+// code as one tensor in tiles of kTableTile.
+constexpr uint64_t kTableTile = 1024;
+int table_fetch_code(uint64_t bytes);
 
 // Bytes per ticket and tickets per chunk for a chunk size and a wanted tile size.
 void tile_shape(uint64_t chunk_bytes, uint64_t want_tile, uint64_t *tile_bytes, uint32_t *tiles_per_chunk);

@@ -174,10 +174,13 @@ static void largest_launches() {
 // A launch that fetches tables asks host memory for no more than fills the link, and with the loads meant for it.
 static void table_fetches() {
   for (uint64_t n = 256; n < 64u << 20; n += n < 1u << 20 ? 256 : 65536) {
-    const uint64_t tile = table_fetch_tile(n);
-    if (tile != 0) CHECK(tile % 16 == 0 && (n + tile - 1) / tile * tile <= 256 * 1024);
+    const int code = table_fetch_code(n);
+    if (code == 0) continue;
+    const uint64_t nt = (n + kTableTile - 1) / kTableTile, wg = wave_workgroups(0, code, nt);
+    CHECK(wg > 0 && wg * (wave_code_threads(code) / 64) * kTableTile <= 256 * 1024);
+    CHECK((code & kWaveFromHost) != 0 && ((code & 15) != kWaveTiles || wg == nt) && !wave_draws(code, wg, nt, true));
   }
-  CHECK(table_fetch_tile(100000 / 256 * 256) != 0 && (kTableFetch & kWaveFromHost) && wave_code_threads(kTableFetch) == 64);
+  CHECK(table_fetch_code(256) == 0 && table_fetch_code(100096) != 0);
 }
 
 int main(int argc, char **argv) {
