@@ -57,7 +57,7 @@ static void job(std::mt19937_64 &r) {
   ClassPlan cp;
   const uint64_t Cs[] = {1024, 4096, 65536, 100000 / 16 * 16, 2u << 20};
   const uint64_t C = Cs[U(0, 4)];
-  const uint32_t nf = (uint32_t)(r() % 4 == 0 ? U(1, 256) : U(1, 9));
+  const uint32_t nf = (uint32_t)(r() % 4 == 0 ? U(1, 1024) : U(1, 9));
   const uint64_t scale = 1ull << U(6, 20);
   for (uint32_t f = 0; f < nf; ++f) {
     Func fn{};
@@ -171,6 +171,39 @@ static void largest_launches() {
         }
 }
 
+// Rows however far apart: what is sent to the wave kernel fits its 32-bit distances from a tile's first row to the end of its
+// last, and rows of a few MiB apart are sent, as are jobs of up to 1024 functions.
+static void far_rows() {
+  for (uint64_t rb : {16ull, 17ull, 64ull, 100ull, 2000ull, 8191ull, 8208ull, 60000ull, 1ull << 20})
+    for (uint64_t pitch = rb; pitch < 1ull << 34; pitch = pitch * 3 / 2 + 1)
+      for (uint64_t C : {1024ull, 65536ull, 2ull << 20, 1ull << 29})
+        for (int cls = 0; cls < FT_NCLASS; ++cls)
+          for (uint32_t nf : {1u, 257u, 1024u, 1025u}) {
+            ClassPlan cp;
+            for (uint32_t f = 0; f < nf; ++f) {
+              Func fn{};
+              Xfer x{};
+              x.row_bytes = rb;
+              x.rows = 40;
+              x.src_pitch = f % 2 ? rb : pitch;
+              x.dst_pitch = f % 2 ? pitch : rb;
+              fn.stream_bytes = rb * x.rows;
+              fn.nchunks = (fn.stream_bytes + C - 1) / C;
+              cp.nchunks += fn.nchunks;
+              cp.payload += fn.stream_bytes;
+              cp.xfers.push_back(x);
+              cp.funcs.push_back(fn);
+            }
+            const int code = launch_code(cp, cls, C, false, true);
+            if (cls == FT_P2P && cp.payload <= 16u << 20) CHECK((code >= kWaveTiles) == (nf <= 1024 && pitch <= 0xffffffffu / (8208 / rb + 3)));
+            if (code < kWaveTiles) continue;
+            uint64_t tile;
+            uint32_t tpc;
+            tile_shape(C, wave_tile(code, cp.payload), &tile, &tpc);
+            CHECK(((tile + rb - 2) / rb + 1) * pitch + rb < 1ull << 32);
+          }
+}
+
 // A launch that fetches tables asks host memory for no more than fills the link, and with the loads meant for it.
 static void table_fetches() {
   for (uint64_t n = 256; n < 64u << 20; n += n < 1u << 20 ? 256 : 65536) {
@@ -186,6 +219,7 @@ static void table_fetches() {
 int main(int argc, char **argv) {
   const uint64_t first = argc > 1 ? strtoull(argv[1], 0, 10) : 1, count = argc > 2 ? strtoull(argv[2], 0, 10) : 50;
   largest_launches();
+  far_rows();
   table_fetches();
   for (uint32_t d = 0; d < 16; ++d)
     for (uint32_t n = 16; n < 9000; n += n < 200 ? 1 : 61) run(d, n);
