@@ -31,7 +31,8 @@ def check_registers(remarks):
     host-link workgroup that took a CU for itself would idle that CU's share of HBM.
     The limit checked is 480, not 512: builds whose two kernels added up to 488 and 496
     registers measured 1.2 % less of the host link beside pool->pool launches (large_mixed:
-    99.6 -> 98.3 % of the measured peak), the build at 480 does not."""
+    99.6 -> 98.3 % of the measured peak), the build at 480 does not.
+    No kernel may use scratch memory: every dispatch of one that does needs its queue's."""
     import re
     regs = {}
     name = None
@@ -43,6 +44,9 @@ def check_registers(remarks):
         m = re.search(r"\b(VGPRs|AGPRs): (\d+)", line)
         if m and name and "Spill" not in line:
             regs[name] += int(m.group(2))
+        m = re.search(r"ScratchSize \[bytes/lane\]: (\d+)", line)
+        if m and int(m.group(1)) != 0:
+            raise RuntimeError(f"{name} uses {m.group(1)} bytes of scratch memory a lane")
     up8 = lambda v: (v + 7) // 8 * 8
     per_class = {}
     for k, v in regs.items():

@@ -485,3 +485,20 @@ def test_bench_traffic_constants_are_the_figures_in_the_profiles():
         assert found, f"{path} states no `traffic / algorithmic = X`"
         assert float(found[-1]) == factor, (name, factor, found)
         assert "bench.py" in text and "rocprofv3 --pmc" in text
+
+
+def test_the_build_refuses_kernels_that_do_not_fit():
+    """build.check_registers on the compiler's remarks: scratch memory, and kernels that no longer share a compute unit."""
+    from paper_2411_01830_amd import build
+
+    def remarks(copy=(200, 200, 256), wave=72, scratch=0):
+        out = []
+        for k, v in [(f"_ZN2ft14ft_copy_kernelILb1ELi{c}EEEv", v) for c, v in enumerate(copy)] + [("_ZN2ft14ft_wave_kernelILi0ELi0EEEv", wave)]:
+            out += [f"x.hip:1:1: remark: Function Name: {k} [-Rpass]", f"remark:     VGPRs: {v} [-Rpass]", "remark:     AGPRs: 0 [-Rpass]",
+                    f"remark:     ScratchSize [bytes/lane]: {scratch if 'copy' in k else 0} [-Rpass]", "remark:     VGPRs Spill: 0 [-Rpass]"]
+        return "\n".join(out)
+
+    assert build.check_registers(remarks()) == {0: 200, 1: 200, 2: 256, 3: 72}
+    for bad in (dict(scratch=36), dict(wave=80), dict(copy=(200, 232, 256))):
+        with pytest.raises(RuntimeError):
+            build.check_registers(remarks(**bad))
