@@ -102,8 +102,10 @@ static bool wave_tiles_fit(const ClassPlan &cp, uint64_t chunk_bytes) {
   if (cp.nchunks > (1ull << 31) / (chunk_bytes / 1024 + 1)) return false;
   for (const Xfer &x : cp.xfers) {
     if (x.rows <= 1) continue;
-    if (x.row_bytes < 16 || x.rows > ((1ull << 32) - 1) / x.row_bytes) return false;
-    if ((x.src_pitch > x.dst_pitch ? x.src_pitch : x.dst_pitch) > ((1ull << 32) - 1) / (8208 / x.row_bytes + 3)) return false;
+    if (x.row_bytes < 16 || (x.rows | x.row_bytes) >> 32 != 0 || x.rows * x.row_bytes >> 32 != 0) return false;
+    const uint64_t pitch = x.src_pitch > x.dst_pitch ? x.src_pitch : x.dst_pitch;
+    // (a division for the rare descriptor alone: one for each of 1536 took 4 us of planning)
+    if (pitch > 1u << 20 && pitch > ((1ull << 32) - 1) / (8208 / x.row_bytes + 3)) return false;
   }
   return true;
 }
