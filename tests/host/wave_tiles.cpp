@@ -52,6 +52,8 @@ static void run(uint64_t dst, uint32_t n) {
 
 static uint64_t n_tickets, n_jobs[128];
 
+static int decode_all(ClassPlan &cp, uint64_t C, int cls, bool alone);
+
 static void job(std::mt19937_64 &r) {
   auto U = [&](uint64_t a, uint64_t b) { return a + r() % (b - a + 1); };
   ClassPlan cp;
@@ -79,13 +81,18 @@ static void job(std::mt19937_64 &r) {
     cp.funcs.push_back(fn);
     cp.payload += fn.stream_bytes;
   }
-  CHECK(build_phases(cp.funcs, cp.phases, cp.slots, &cp.nchunks) == FT_OK);
   const int cls = (int)U(0, 5) < 4 ? FT_P2P : (int)U(FT_H2P, FT_P2H);
-  const int code = launch_code(cp, cls, C, false, r() % 4 != 0);
+  decode_all(cp, C, cls, r() % 4 != 0);
+}
+
+// The launch code that a job gets, and every n-th ticket of it as the wave kernel decodes it against the general walk.
+static int decode_all(ClassPlan &cp, uint64_t C, int cls, bool alone) {
+  CHECK(build_phases(cp.funcs, cp.phases, cp.slots, &cp.nchunks) == FT_OK);
+  const int code = launch_code(cp, cls, C, false, alone);
   CHECK(launch_code(cp, cls, C, true, true) == cls && (cls == FT_P2P || launch_code(cp, cls, C, false, false) == cls));
   CHECK(code < kWaveTiles || (cls == FT_P2P) == ((code & (kWaveFromHost | kWaveToHost)) == 0));
   n_jobs[code] += 1;
-  if (code < kWaveTiles) return;
+  if (code < kWaveTiles) return code;
   uint64_t tile;
   uint32_t tpc;
   tile_shape(C, wave_tile(code, cp.payload), &tile, &tpc);
@@ -135,6 +142,73 @@ static void job(std::mt19937_64 &r) {
     CHECK(x == find_xfer(cp.xfers.data(), f.desc_off, f.desc_off + f.ndesc - 1, b0));
     CHECK(b0 < f.stream_bytes && cp.xfers[x].stream_off <= b0);
   }
+  return code;
+}
+
+// A job for every rule of launch_code: what it says, and the tickets of it decoded.
+static void each_rule() {
+  const uint64_t KiB = 1 << 10, MiB = 1 << 20;
+  struct Rule {
+    int cls;
+    bool alone;
+    uint64_t bytes;  // of the whole job, in `pieces` descriptors of eight functions
+    uint64_t pieces, row_bytes;  // row_bytes 0: contiguous
+    uint64_t misaligned;
+    int code;
+  };
+  const int S = kWaveStreams, F = kWaveFromHost, T = kWaveToHost;
+  const Rule rules[] = {
+      {FT_P2P, true, 10 * MiB, 64, 0, 0, kWaveTiles},
+      {FT_P2P, false, 10 * MiB, 64, 0, 0, kWaveTiles},
+      {FT_P2P, true, 30 * MiB, 64, 0, 0, kWaveOnePerUnit},
+      {FT_P2P, false, 30 * MiB, 64, 0, 0, FT_P2P},
+      {FT_P2P, true, 60 * MiB, 64, 0, 0, FT_P2P},
+      {FT_P2P, true, 60 * MiB, 1, 0, 0, kWaveOnePerUnit},
+      {FT_P2P, true, 60 * MiB, 64, 0, 3, kWaveOnePerUnit},
+      {FT_P2P, false, 60 * MiB, 64, 0, 3, FT_P2P},
+      {FT_P2P, true, 200 * MiB, 1, 0, 0, FT_P2P},
+      {FT_P2P, true, 200 * MiB, 64, 0, 3, FT_P2P},
+      {FT_P2P, true, 20 * MiB, 64, 300, 0, kWaveTwoPerUnit},
+      {FT_P2P, true, 20 * MiB, 64, 5000, 0, kWaveOnePerUnit},
+      {FT_P2P, false, 20 * MiB, 64, 5000, 0, kWaveTwoPerUnit},
+      {FT_P2P, true, 200 * MiB, 64, 300, 0, kWaveTwoPerUnit | S},
+      {FT_P2P, true, 200 * MiB, 64, 5000, 0, kWaveOnePerUnit | S},
+      {FT_P2P, true, 200 * MiB, 64, 65536, 0, FT_P2P},
+      {FT_P2P, false, 200 * MiB, 64, 300, 0, kWaveBeside | S},
+      {FT_P2P, true, 10 * MiB, 64, 15, 0, FT_P2P},
+      {FT_H2P, true, 100 * KiB, 3, 0, 0, kWaveTiles | F},
+      {FT_P2H, true, 100 * KiB, 3, 0, 0, kWaveTiles | T},
+      {FT_H2P, true, 2 * MiB, 600, 0, 0, kWaveLink | F},
+      {FT_P2H, true, 2 * MiB, 600, 0, 0, kWaveLink | T},
+      {FT_P2H, true, 2 * MiB, 300, 0, 0, FT_P2H},
+      {FT_H2P, true, 2 * MiB, 8, 300, 0, kWaveLink | F},
+      {FT_H2P, false, 2 * MiB, 600, 0, 0, FT_H2P},
+  };
+  for (const Rule &q : rules)
+    for (uint64_t C : {64 * KiB, 2 * MiB}) {
+      ClassPlan cp;
+      const uint32_t nf = q.pieces < 8 ? 1 : 8;
+      for (uint32_t f = 0; f < nf; ++f) {
+        Func fn{};
+        fn.desc_off = (uint32_t)cp.xfers.size();
+        fn.func = f;
+        fn.weight = 1 + f % 3;
+        for (uint64_t i = f; i < q.pieces; i += nf, ++fn.ndesc) {
+          Xfer x{};
+          x.row_bytes = q.row_bytes ? q.row_bytes : q.bytes / q.pieces;
+          x.rows = q.row_bytes ? q.bytes / q.pieces / q.row_bytes : 1;
+          x.src_pitch = x.dst_pitch = x.row_bytes + 99;
+          x.dst = q.misaligned;
+          x.stream_off = fn.stream_bytes;
+          fn.stream_bytes += x.row_bytes * x.rows;
+          cp.xfers.push_back(x);
+        }
+        fn.nchunks = (fn.stream_bytes + C - 1) / C;
+        cp.funcs.push_back(fn);
+        cp.payload += fn.stream_bytes;
+      }
+      CHECK(decode_all(cp, C, q.cls, q.alone) == q.code);
+    }
 }
 
 // A launch has fewer than 2^32 threads however much there is to move: pitched rows in the smallest chunks that the wave
@@ -219,6 +293,10 @@ static void table_fetches() {
 int main(int argc, char **argv) {
   const uint64_t first = argc > 1 ? strtoull(argv[1], 0, 10) : 1, count = argc > 2 ? strtoull(argv[2], 0, 10) : 50;
   largest_launches();
+  each_rule();
+  for (int code : {kWaveTiles, kWaveTwoPerUnit, kWaveOnePerUnit, kWaveTwoPerUnit | kWaveStreams, kWaveOnePerUnit | kWaveStreams, kWaveBeside | kWaveStreams,
+                   kWaveTiles | kWaveFromHost, kWaveTiles | kWaveToHost, kWaveLink | kWaveFromHost, kWaveLink | kWaveToHost, (int)FT_P2P, (int)FT_H2P, (int)FT_P2H})
+    CHECK(n_jobs[code] > 0);
   far_rows();
   table_fetches();
   for (uint32_t d = 0; d < 16; ++d)

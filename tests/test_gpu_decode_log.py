@@ -6,7 +6,7 @@ not prove the ORDER the kernel follows. Here every ticket's (function, chunk, st
 decoded on the device by the hot path itself is compared with oracle.stride_order: all five workloads,
 the routes on which a small job travels with its launch (including the one-descriptor shortcut), jobs
 with a descriptor-table entry per tile, and open jobs whose later orders start in the middle of the
-streams."""
+streams. The pool->pool jobs here are small and go to the wave kernel; test_gpu_copy_kernel.py has the copy kernel's order."""
 import time
 
 import numpy as np

@@ -189,8 +189,8 @@ def test_transfers_larger_than_four_gib(route):
 
 
 def test_one_aligned_tensor_larger_than_four_gib():
-    """The route on which the workgroups deal the tiles of one aligned tensor out among themselves, beyond 4 GiB:
-    tile numbers times tile bytes need their upper 32 bits. Destination against source on the device, canaries either
+    """One aligned tensor beyond 4 GiB, whose tiles the workgroups draw from a counter pair: tile numbers times tile bytes
+    need their upper 32 bits. Destination against source on the device, canaries either
     side; a length that leaves a ragged last tile."""
     import torch
     from paper_2411_01830_amd import binding as ft

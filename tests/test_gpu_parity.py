@@ -407,7 +407,8 @@ def test_small_jobs_take_the_launch_argument_path(gpu):
 def test_larger_single_class_jobs_reuse_the_self_resetting_counters(gpu):
     """Single-class jobs with more tickets than workgroups still travel with the launch, on a
     counter pair that the kernel itself sets back to zero: thirty jobs back to back (the same pair
-    again and again), kept jobs holding a pair each meanwhile, all three classes, odd sizes."""
+    again and again), kept jobs holding a pair each meanwhile, all three classes, odd sizes. (Most of the pool->pool jobs
+    here go to the wave kernel, which may need no pair; test_gpu_copy_kernel.py has the copy kernel's.)"""
     binding, _ = gpu
     orc, eng, rng = _pair(gpu, host=1 << 26, pool=3 << 27, slab=1 << 20, seed=79)
     pyr = random.Random(79)
@@ -469,7 +470,8 @@ def test_larger_single_class_jobs_reuse_the_self_resetting_counters(gpu):
 
 def test_one_aligned_tensor_is_dealt_out_without_a_counter(gpu):
     """One contiguous transfer between 16-byte aligned addresses (its length may be anything) which has more tiles than
-    workgroups: the workgroups deal the tiles out round robin, no counter (Sec. 5.1: passing one tensor).
+    workgroups: the tiles are dealt out, no counter (Sec. 5.1: passing one tensor) - among the workgroups of the class's
+    kernel over the host link, among the wavefronts of the wave kernel in the pool (test_gpu_copy_kernel.py has the copy kernel).
     Every class, lengths with a ragged last tile and a ragged last chunk, chunk sizes that are not a
     multiple of the tile, with and without timing; detached, such a job takes the ordinary route instead (it would
     hold the caller's stream); canaries around every destination."""
@@ -576,8 +578,8 @@ def test_detached_pool_to_pool_jobs_back_to_back_and_apart(gpu):
 
 
 def test_short_rows_run_the_light_build_two_workgroups_per_unit(gpu):
-    """A pool->pool job whose payload is mostly pitched rows of at most 2 KiB is launched with two workgroups per
-    compute unit (the kernel's light build); one of long rows or contiguous runs with one. Gather into packed
+    """A pool->pool job of over 16 MiB whose payload is mostly pitched rows of at most 2 KiB is launched with two workgroups
+    of eight wavefronts per compute unit; one of long rows with one of sixteen. Gather into packed
     buffers, scatter out of them and pitched on both sides, row lengths 16 .. 1000 at every alignment, tiles that cut
     rows; bytes and order against the oracle."""
     import torch
@@ -622,8 +624,8 @@ def test_short_rows_run_the_light_build_two_workgroups_per_unit(gpu):
 
 def test_log_names_the_compute_unit_of_every_workgroup(gpu):
     """FT_LOG also records where a workgroup ran. A pool->pool launch of as many workgroups as the device has
-    compute units occupies every unit once (two such workgroups do not fit one unit: a tile lives in registers);
-    the light build for short rows occupies every unit twice."""
+    compute units occupies every unit once (two workgroups of sixteen wavefronts, here of misaligned tensors, do not fit one unit);
+    one of two workgroups of eight wavefronts per unit, of short rows, occupies every unit twice."""
     import torch
     from collections import Counter
     binding, _ = gpu

@@ -1,5 +1,6 @@
 """The kernel that gives every wavefront tiles of its own: pool->pool jobs of at most 16, 48 or 128 MiB and jobs of
-pitched rows, host-link jobs of small pieces, at the sizes where its windows, its tiles and the rule that picks it change. Bit-exact against the oracle."""
+pitched rows, host-link jobs of small pieces, at the sizes where its windows, its tiles and the rule that picks it change;
+each case says by tile size and workgroups which kernel it got. Bit-exact against the oracle or plain strided copies."""
 import os
 
 import numpy as np
@@ -51,14 +52,30 @@ def _rows(rng, n, widths, total, funcs):
     return out
 
 
-# name, pieces(rng), weights, chunk, flags, workgroups of the pool->pool launch (None: not asked)
+def _tile(chunk, want):
+    """Bytes per tile when a chunk is cut into tiles of about `want` bytes."""
+    n = -(-chunk // want)
+    return (-(-chunk // n) + 15) // 16 * 16
+
+
+def _wave_tile(payload, chunk):
+    """The tile of a pool->pool launch of the wave kernel: about 4000 tiles of 2 .. 8 KiB."""
+    t = payload // 4000
+    return _tile(chunk, 2048 if t < 2048 else 8192 if t > 8192 else (t + 15) // 16 * 16)
+
+
+# name, pieces(rng), weights, chunk, flags, kernel and workgroups of the pool->pool launch: the wave kernel with a workgroup per ticket or
+# one or two per compute unit, or the copy kernel. Its tiles of 43 or 64 KiB tell the kernels apart where the chunk lets them,
+# and where it does not its at most one workgroup per compute unit does.
 CASES = [
-    ("bytes around a window", lambda g: _runs(g, 200, [1, 15, 16, 17, 31, 32, 33, 1023, 1024, 1025], 3), [1, 2, 5], 1024, 0, "tickets"),
+    ("bytes around a window", lambda g: _runs(g, 200, [1, 15, 16, 17, 31, 32, 33, 1023, 1024, 1025], 3), [1, 2, 5], 4096, 0, "tickets"),
+    ("bytes around a window, chunks of 1 KiB", lambda g: _runs(g, 900, [1, 15, 16, 17, 1023, 1024, 1025], 3), [1, 2, 5], 1024, 0, "tickets"),
     ("one tile and its edges", lambda g: _runs(g, 40, [2047, 2048, 2049, 8191, 8192, 8193, 8208], 2), [1, 1], 64 * KiB, 0, "tickets"),
     ("5000 descriptors of one function", lambda g: _runs(g, 5000, [1, 60, 300, 700], 1), [1], 256 * KiB, 0, "tickets"),
     ("256 functions", lambda g: _runs(g, 600, [64, 5000, 9000], 256), list(range(1, 257)), 4 * KiB, 0, "tickets"),
-    ("257 functions", lambda g: _runs(g, 600, [64, 5000, 9000], 257), [1] * 257, 4 * KiB, 0, None),
-    ("chunks under 1 KiB", lambda g: _runs(g, 20, [300, 5000], 2), [1, 3], 512, 0, None),
+    ("1024 functions", lambda g: _runs(g, 2100, [64, 5000, 9000], 1024), [1 + f % 5 for f in range(1024)], 4 * KiB, 0, "tickets"),
+    ("1025 functions", lambda g: _runs(g, 2100, [64, 5000, 9000], 1025), [1] * 1025, 4 * KiB, 0, None),
+    ("chunks under 1 KiB", lambda g: _runs(g, 200, [300, 5000], 2), [1, 3], 512, 0, None),
     ("logged", lambda g: _runs(g, 60, [40, 3000, 70000], 4), [1, 2, 3, 4], 64 * KiB, fmt.FT_LOG, "tickets"),
     ("detached", lambda g: _runs(g, 60, [40, 3000, 70000], 4), [1, 2, 3, 4], 64 * KiB, fmt.FT_DETACHED, "tickets"),
     ("over 16 MiB", lambda g: _runs(g, 30, [600 * KiB, 700 * KiB + 5], 3), [1, 2, 4], 256 * KiB, 0, "one a unit"),
@@ -68,6 +85,10 @@ CASES = [
     ("short rows over 16 MiB", lambda g: _rows(g, 24, [20, 100, 2000], 18 * MiB, 2), [3, 1], 256 * KiB, 0, "two a unit"),
     ("long rows over 16 MiB", lambda g: _rows(g, 12, [2100, 5760, 30001], 18 * MiB, 2), [3, 1], 256 * KiB, 0, "one a unit"),
     ("rows between 1 MiB pitches", lambda g: [(100, 9, 1 << 20, 200, 0, 3, 5), (70, 5, 100, 1 << 20, 1, 1, 2), (50, 6, (1 << 20) + 1, 60, 0, 0, 0)],
+     [1, 1], 64 * KiB, 0, "tickets"),
+    ("rows as far apart as a tile's 32 bits allow", lambda g: [(16, 3, ((1 << 32) - 1) // 516, 30, 0, 3, 5), (70, 5, 100, 1 << 20, 1, 1, 2)],
+     [1, 1], 64 * KiB, 0, "tickets"),
+    ("rows further apart", lambda g: [(16, 3, ((1 << 32) - 1) // 516 + 1, 30, 0, 3, 5), (70, 5, 100, 1 << 20, 1, 1, 2)],
      [1, 1], 64 * KiB, 0, None),
 ]
 
@@ -112,9 +133,17 @@ def test_wave_tiles_match_the_oracle(case, beside_host_link):
             assert eng.job_schedule(jg, 2) == orc.job_schedule(jo, 2)
             st = binding.job_stats(eng.pool, jg).cls[2]
             cus = torch.cuda.get_device_properties(0).multi_processor_count
-            want = {"tickets": st.tickets, "two a unit": 2 * cus, "one a unit": cus, None: st.workgroups}
-            if not beside_host_link:
-                assert st.workgroups == want[shape], (st.workgroups, st.tickets)
+            own = [r for r in recs if r["src_space"] == FT_POOL]
+            in_rows = sum(r["row_bytes"] * r["rows"] for r in own if r["rows"] > 1)
+            if shape is None or (beside_host_link and st.payload_bytes > 16 * MiB and 2 * in_rows <= st.payload_bytes):
+                short = sum(r["row_bytes"] * r["rows"] for r in own if r["rows"] > 1 and r["row_bytes"] <= 2048)
+                want = _tile(chunk, 43 * KiB if 2 * short > st.payload_bytes else 64 * KiB), min(cus, st.tickets)
+                assert want[0] != _wave_tile(st.payload_bytes, chunk) or cus < st.tickets     # the wave kernel would be seen
+            else:
+                units = 2 if beside_host_link or shape == "two a unit" else 1
+                want = _wave_tile(st.payload_bytes, chunk), st.tickets if shape == "tickets" else units * cus
+                assert want[0] != _tile(chunk, 64 * KiB) or cus < want[1]                     # and so would the copy kernel
+            assert (st.tile_bytes, st.workgroups) == want, st.tickets
             if flags & fmt.FT_LOG:
                 log = binding.job_log(eng.pool, jg, 2)
                 assert int(log["bytes"].sum()) == st.payload_bytes and len(log["bytes"]) == st.tickets
@@ -124,16 +153,17 @@ def test_wave_tiles_match_the_oracle(case, beside_host_link):
         eng.close()
 
 
-# name, pieces(rng), chunk, flags, in one launch of a workgroup per ticket
+# name, pieces(rng), chunk, flags, the wave kernel with a workgroup per ticket (True), with 64 workgroups (False), or the class's
+# own kernel (None); tiles of 1 and 4 KiB against its 8 and 16 KiB tell them apart
 LINK_CASES = [
-    ("bytes around a window", lambda g: _runs(g, 150, [1, 15, 16, 17, 31, 32, 33, 1023, 1024, 1025], 3), 1024, 0, True),
+    ("bytes around a window", lambda g: _runs(g, 150, [1, 15, 16, 17, 31, 32, 33, 1023, 1024, 1025], 3), 4096, 0, True),
     ("one tensor", lambda g: _runs(g, 1, [65536 + 5], 1), 64 * KiB, 0, True),
-    ("128 KiB and a byte of long pieces", lambda g: _runs(g, 2, [64 * KiB + 1], 2), 64 * KiB, 0, False),
+    ("128 KiB and a byte of long pieces", lambda g: _runs(g, 2, [64 * KiB + 1], 2), 64 * KiB, 0, None),
     ("small pieces under 1 MiB", lambda g: _runs(g, 240, [3000, 4095, 4096], 3), 256 * KiB, fmt.FT_LOG, True),
     ("small pieces over 1 MiB", lambda g: _runs(g, 300, [3000, 4095, 4096, 4097], 3), 256 * KiB, 0, False),
     ("small pieces over 1 MiB, detached", lambda g: _runs(g, 300, [3000, 4095], 3), 256 * KiB, fmt.FT_DETACHED, False),
-    ("rows apart on both sides", lambda g: _rows(g, 12, [16, 33, 100, 500, 2048], 1 * MiB, 2), 100000 // 16 * 16, 0, None),
-    ("narrow gathered rows", lambda g: [(w, 700, w + 40, w, i % 2, 3 * i % 16, 5 * i % 16) for i, w in enumerate([16, 17, 40, 63, 64])], 64 * KiB, 0, None),
+    ("rows apart on both sides", lambda g: _rows(g, 12, [16, 33, 100, 500, 2048], 1 * MiB, 2), 100000 // 16 * 16, 0, "rows"),
+    ("narrow gathered rows", lambda g: [(w, 700, w + 40, w, i % 2, 3 * i % 16, 5 * i % 16) for i, w in enumerate([16, 17, 40, 63, 64])], 64 * KiB, 0, True),
     ("rows under 16 bytes", lambda g: _rows(g, 6, [1, 3, 9, 15], 40 * KiB, 2), 64 * KiB, 0, None),
 ]
 
@@ -183,10 +213,13 @@ def test_wave_tiles_on_the_host_link(case, to_host):
             eng.wait(jg)
             assert eng.job_schedule(jg, cls) == orc.job_schedule(jo, cls)
             st = binding.job_stats(eng.pool, jg).cls[cls]
-            if tickets:
-                assert st.workgroups == st.tickets
-            elif tickets is False:
-                assert st.workgroups == min(64, st.tickets)
+            if tickets is None:
+                own = 8 * KiB if to_host and st.payload_bytes <= 256 * KiB else 16 * KiB
+                assert st.tile_bytes == _tile(chunk, own)
+            else:
+                each = tickets is True or (tickets == "rows" and st.payload_bytes <= 1 * MiB)
+                assert st.tile_bytes == _tile(chunk, 1024 if st.payload_bytes <= 128 * KiB else 4096)
+                assert st.workgroups == (st.tickets if each else min(64, st.tickets))
             if flags & fmt.FT_DETACHED:
                 assert st.in_launch == 0     # it would hold the caller's stream
             if flags & fmt.FT_LOG:
@@ -364,6 +397,16 @@ def test_the_weighted_order_holds_whatever_the_tiles_cost(case):
 
 # name, pieces(rng), beside the host link, chunk, workgroups per compute unit, tile
 LARGE_CASES = [
+    ("tensors over 16 MiB", lambda g: _runs(g, 50, [600 * KiB, 700 * KiB + 5], 3), False, 256 * KiB, 1, "wave"),
+    ("one aligned tensor", lambda g: [(100 * MiB + 16, 1, 0, 0, 0, 0, 0)], False, 2 * MiB, 1, 8192),
+    ("misaligned tensors over 48 MiB", lambda g: [(3 * MiB + i, 1, 0, 0, i % 3, i % 16, (i + 5) % 16) for i in range(20)], False, 2 * MiB, 1, 8192),
+    ("aligned tensors over 48 MiB", lambda g: [(3 * MiB + 16 * i, 1, 0, 0, i % 3, 0, 0) for i in range(20)], False, 2 * MiB, 1, 64 * KiB),
+    ("aligned tensors over 48 MiB, detached", lambda g: [(3 * MiB + 16 * i, 1, 0, 0, i % 3, 0, 0) for i in range(20)], False, 2 * MiB, 1, 64 * KiB),
+    ("one aligned tensor beyond the cache", lambda g: [(150 * MiB + 16, 1, 0, 0, 0, 0, 0)], False, 2 * MiB, 1, 64 * KiB),
+    ("short rows beyond the cache", lambda g: _rows(g, 24, [20, 100, 2000], 140 * MiB, 3), False, 256 * KiB, 2, 8192),
+    ("long rows beyond the cache", lambda g: _rows(g, 12, [2100, 5761, 30001, 65535], 140 * MiB, 3), False, 1 * MiB, 1, 8192),
+    ("rows of 64 KiB beyond the cache", lambda g: _rows(g, 12, [65536, 70001], 140 * MiB, 3), False, 1 * MiB, 1, 64 * KiB),
+    ("misaligned tensors over 48 MiB beside the host link", lambda g: [(3 * MiB + i, 1, 0, 0, i % 3, i % 16, (i + 5) % 16) for i in range(20)], True, 2 * MiB, 1, 64 * KiB),
     ("rows beside the host link", lambda g: _rows(g, 12, [300, 5761, 30000], 40 * MiB, 3), True, 256 * KiB, 2, 8192),
     ("rows beyond the cache beside the host link", lambda g: _rows(g, 12, [300, 5761, 30000], 150 * MiB, 3), True, 1 * MiB, 1, 8192),
 ]
@@ -400,10 +443,12 @@ def test_large_jobs_against_plain_copies(case):
             _move_with_torch(want, eng.host, r)
         torch.cuda.synchronize()
         weights = [1 + f for f in range(1 + max(r["func"] for r in recs))]
+        flags = fmt.FT_KEEP | (fmt.FT_DETACHED if "detached" in name else 0)
         for _ in range(2):
-            jg = eng.submit(make_descs(recs), weights, chunk, fmt.FT_KEEP)
+            jg = eng.submit(make_descs(recs), weights, chunk, flags)
             eng.wait(jg)
             st = binding.job_stats(eng.pool, jg).cls[2]
+            tile = _wave_tile(st.payload_bytes, chunk) if tile == "wave" else tile
             assert (st.tile_bytes, st.workgroups) == (tile, per_unit * torch.cuda.get_device_properties(0).multi_processor_count)
             binding.job_release(eng.pool, jg)
             assert torch.equal(mem, want)
