@@ -571,7 +571,9 @@ int ft_job_schedule(ft_pool *p, ft_job_t job, int link_class, uint32_t *func_out
  * gave - the function, the chunk of the function's stream, the offset of the tile's first
  * byte in that stream and the bytes moved (Sec. 6.1: chunks of different functions are
  * triggered in proportion; this is the order the device really followed). Host arrays of
- * `cap` entries each (any may be NULL); *n_out receives the ticket count.
+ * `cap` entries each (any may be NULL); *n_out receives the ticket count. The record costs 48 bytes
+ * of device and of host memory a ticket: a ticket is 43 to 64 KiB of a long pool->pool job, 8 or 16 KiB
+ * over the host link, but 1 to 8 KiB where a wavefront moves one.
  */
 int ft_job_log(ft_pool *p, ft_job_t job, int link_class, uint64_t *t_begin_ns, uint64_t *t_end_ns,
                uint32_t *func_out, uint32_t *chunk_out, uint64_t *byte_off_out, uint32_t *bytes_out,

@@ -107,11 +107,6 @@ __device__ __forceinline__ u32x4 ld16(uint64_t addr) {
 // 16 bytes from any address (the hardware splits an access that straddles aligned granules).
 typedef uint32_t u32x4_any __attribute__((ext_vector_type(4), aligned(1)));
 template <int NT>
-__device__ __forceinline__ u32x4 ld16_any(uint64_t addr) {
-  if (NT) return __builtin_nontemporal_load(reinterpret_cast<const u32x4_any FT_GLOBAL *>(addr));
-  return *reinterpret_cast<const u32x4_any FT_GLOBAL *>(addr);
-}
-template <int NT>
 __device__ __forceinline__ void st16(uint64_t addr, u32x4 v) {
   if (NT == kToHost) asm volatile("global_store_dwordx4 %0, %1, off sc1\n\ts_nop 1" ::"v"(addr), "v"(v) : "memory");
   else if (NT) __builtin_nontemporal_store(v, reinterpret_cast<GVecP>(addr));
@@ -516,12 +511,6 @@ __device__ __forceinline__ void copy_rows_packed_pairs(const Xfer &X, uint64_t p
 }
 
 // 16 bytes to any address.
-template <int NT>
-__device__ __forceinline__ void st16_any(uint64_t addr, u32x4 v) {
-  if (NT) __builtin_nontemporal_store(v, reinterpret_cast<u32x4_any FT_GLOBAL *>(addr));
-  else *reinterpret_cast<u32x4_any FT_GLOBAL *>(addr) = v;
-}
-
 // N lanes' share of one pass over the windows of a pitched piece (ft_windows.h): R windows of W bytes per lane from
 // window `blk` on, at whatever addresses they have (the memory pipeline splits an access that straddles aligned
 // granules). All loads before the first store; no load is predicated (a lane past the last window repeats it).
@@ -530,11 +519,7 @@ struct Window;
 template <>
 struct Window<16> { typedef u32x4_any type; };
 template <>
-struct Window<8> { typedef uint64_t type __attribute__((aligned(1))); };
-template <>
 struct Window<4> { typedef uint32_t type __attribute__((aligned(1))); };
-template <>
-struct Window<2> { typedef uint16_t type __attribute__((aligned(1))); };
 template <>
 struct Window<1> { typedef uint8_t type; };
 
@@ -1437,8 +1422,10 @@ template <int NT>
 static hipError_t launch_wave(int form, dim3 grid, uint32_t waves, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop,
                               const ClassTable &T, const InlineBlob &B) {
   const dim3 block(waves * 64);
-  if (form == kOneTicket) hipExtLaunchKernelGGL((ft_wave_kernel<NT, kOneTicket>), grid, block, 0, stream, ev_start, ev_stop, 0, T, B);
-  else if (form == kDealt) hipExtLaunchKernelGGL((ft_wave_kernel<NT, kDealt>), grid, block, 0, stream, ev_start, ev_stop, 0, T, B);
+  if (form == kOneTicket) {
+    if constexpr (NT == kStream) return hipErrorInvalidValue;  // a job that streams is never that small
+    else hipExtLaunchKernelGGL((ft_wave_kernel<NT, kOneTicket>), grid, block, 0, stream, ev_start, ev_stop, 0, T, B);
+  } else if (form == kDealt) hipExtLaunchKernelGGL((ft_wave_kernel<NT, kDealt>), grid, block, 0, stream, ev_start, ev_stop, 0, T, B);
   else hipExtLaunchKernelGGL((ft_wave_kernel<NT, kShared>), grid, block, 0, stream, ev_start, ev_stop, 0, T, B);
   return hipGetLastError();
 }
