@@ -39,7 +39,7 @@ HBM_PEAK_GBS = 8000.0
 TRAFFIC_PER_ALGO_BYTE = {
     "large_mixed": (1.0077, "profiles/pmc_hbm_traffic_pool_to_pool_large_mixed.md"),
     "feature": (1.0010, "profiles/pmc_hbm_traffic_pool_to_pool_feature.md"),
-    "traffic_crops": (1.4064, "profiles/pmc_hbm_traffic_pool_to_pool_traffic_crops.md"),
+    "traffic_crops": (1.4067, "profiles/pmc_hbm_traffic_pool_to_pool_traffic_crops.md"),
 }
 EXTRA_BLOCKS = ("share_error_pool_to_pool", "share_error_pool_to_host", "batched_triggering", "pinned_ring",
                 "single_transfers", "elastic_store", "path_planner")
