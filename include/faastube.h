@@ -67,7 +67,8 @@ enum {
   FT_LOG = 1 << 1,      /* the kernel records, per ticket, begin/end device time and what its
                            decode of the ticket gave (ft_job_log) */
   FT_PATH_DMA = 1 << 2, /* run the same schedule with hipMemcpyAsync / hipMemcpy2DAsync per
-                           chunk piece instead of the copy kernel (comparison path); no kernel is launched */
+                           chunk piece instead of the copy kernel (comparison path); the library launches no
+                           kernel of its own for it */
   FT_TIMING = 1 << 3,   /* bracket each class's work with timing events */
   FT_DETACHED = 1 << 4, /* do not make the caller's stream wait for the job */
   FT_KEEP = 1 << 5,     /* keep the job record after ft_wait until ft_job_release;

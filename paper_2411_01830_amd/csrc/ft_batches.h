@@ -64,4 +64,12 @@ FT_HD bool wave_counts(uint64_t workgroups, uint32_t waves, uint64_t ntickets) {
   return wave_shares(workgroups * waves, ntickets) && ntickets > workgroups * (waves + wave_batch(waves));
 }
 
+// The last of the launch's draws (they count from 0). A workgroup draws once for every batch that it takes into use before the
+// end - one from the start and those that the counter handed it - and so exactly once beyond the end: all draws together
+// are the counter's batches and one per workgroup, and who makes the last one may set the counter back.
+FT_HD uint32_t wave_last_draw(uint32_t workgroups, uint32_t waves, uint32_t ntickets) {
+  const uint32_t batch = wave_batch(waves), left = ntickets - workgroups * (waves + batch);
+  return (left + batch - 1) / batch + workgroups - 1;
+}
+
 }  // namespace ft

@@ -1287,20 +1287,47 @@ __device__ __forceinline__ void wave_move(const ClassTable &T, const ConstTables
   }
 }
 
-// A workgroup's batches of tickets (ft_batches.h), in LDS.
+// A workgroup's batches of tickets (ft_batches.h), in LDS, with what their draws need: kept in registers across a tile's code
+// it would have others spilled.
 struct WaveBatches {
   unsigned long long taken;
+  unsigned long long counter;  // its address
   uint32_t next;
+  uint32_t batch;      // tickets per batch
+  uint32_t end;        // the launch's tickets
+  uint32_t drawn0;     // first ticket of the batches that the counter hands out; the end: it hands out none
+  uint32_t last_draw;  // the draw after which the counter is set back: the launch's last, or none
+  template <class V>
+  static __device__ V get(const V *p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
   __device__ uint64_t add_taken() { return __hip_atomic_fetch_add(&taken, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
-  __device__ uint64_t word() { return __hip_atomic_load(&taken, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+  __device__ uint64_t word() { return get(&taken); }
   __device__ void set_word(uint64_t v) { __hip_atomic_store(&taken, (unsigned long long)v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
-  __device__ uint32_t ahead() { return __hip_atomic_load(&next, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP); }
+  __device__ uint32_t ahead() { return get(&next); }
   __device__ void set_ahead(uint32_t t) {
     __hip_atomic_store(&next, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
     asm volatile("" ::: "memory");  // a wavefront's LDS operations complete in their order; here it is the compiler's too
   }
   __device__ void pause() { __builtin_amdgcn_s_sleep(1); }
 };
+
+// The next ticket, and the draw that taking it may call for; one lane's work.
+__device__ __forceinline__ uint32_t next_ticket(WaveBatches &B) {
+  bool owes;
+  const uint32_t t = take_ticket(B, WaveBatches::get(&B.batch), WaveBatches::get(&B.end), &owes);
+  if (owes) {
+    uint32_t first = WaveBatches::get(&B.drawn0);
+    if (first < WaveBatches::get(&B.end)) {
+      typedef unsigned long long FT_GLOBAL *CounterP;
+      const CounterP counter = reinterpret_cast<CounterP>(WaveBatches::get(&B.counter));
+      const uint32_t drawn = (uint32_t)__hip_atomic_fetch_add(counter, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      // nobody draws any more: the counter is set back here, not by workgroups that count themselves out one after the other
+      if (drawn == WaveBatches::get(&B.last_draw)) __hip_atomic_store(counter, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      first += drawn * WaveBatches::get(&B.batch);
+    }
+    B.set_ahead(first);
+  }
+  return t;
+}
 
 // Every wavefront starts on a ticket of its own; how it comes to others:
 //   kOneTicket  not at all: a launch of as many workgroups of one wavefront as there are tickets
@@ -1311,14 +1338,14 @@ struct WaveBatches {
 // other forms' code in its kernel 1024 tensors of 10 KB 7.8 us, with that of kShared too 8.3, alone 7.4.
 // With every ticket of long launches dealt out the order was what equal speeds made of it: of two functions of equal weight with
 // alternating tiles, rows of 16 and of 2000 bytes, 200 MB each, the slow one had 21 % of the tiles begun at half time, now
-// 50 %. Kernel time, us, dealt out -> in the order: rows of 256 bytes 63 MB 18.4 -> 19.2, 419 MB 147 -> 147, of 5760 bytes 110 MB
-// 32 -> 32, 1.6 GB 588 -> 531; 64 misaligned tensors 105 MB 35 -> 35; host->pool 20 000 pieces of 4000 bytes 1574 -> 1467 (a
+// 50 %. Kernel time, us, dealt out -> in the order: rows of 256 bytes 63 MB 18.4 -> 19.0, 419 MB 147 -> 144, of 5760 bytes 110 MB
+// 31.1 -> 31.8, 1.6 GB 588 -> 531; 64 misaligned tensors 105 MB 32 -> 34; host->pool 20 000 pieces of 4000 bytes 1574 -> 1466 (a
 // wavefront that the link serves late keeps none of the others' work).
 constexpr int kOneTicket = 0, kDealt = 1, kShared = 2;
 template <int NT, int FORM>
 __global__ __launch_bounds__(FORM == kOneTicket ? 64 : 1024) __attribute__((amdgpu_waves_per_eu(7))) void ft_wave_kernel(ClassTable T, InlineBlob) {
   const ConstTables CT = const_tables(T);
-  const uint32_t lane = threadIdx.x & 63;
+  const uint32_t lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));  // (keeps no register for threadIdx.x)
   uint64_t t_begin = 0;
   if (T.log) t_begin = wall_clock64();
   if (T.log && threadIdx.x == 0) {
@@ -1331,39 +1358,37 @@ __global__ __launch_bounds__(FORM == kOneTicket ? 64 : 1024) __attribute__((amdg
     return;
   }
   __shared__ WaveBatches s_batches;
-  const uint32_t waves = blockDim.x >> 6, round = gridDim.x * waves;
-  const uint32_t batch = wave_batch(waves);
-  const bool counts = wave_counts(gridDim.x, waves, T.ntickets);
+  const uint32_t waves = blockDim.x >> 6;
   if (FORM == kShared) {
     if (threadIdx.x == 0) {
+      const uint32_t batch = wave_batch(waves), round = gridDim.x * waves;
+      const bool counts = wave_counts(gridDim.x, waves, T.ntickets);
       s_batches.taken = batch;
       s_batches.next = round + blockIdx.x * batch;
+      s_batches.batch = batch;
+      s_batches.end = (uint32_t)T.ntickets;
+      s_batches.drawn0 = counts ? round + gridDim.x * batch : (uint32_t)T.ntickets;
+      s_batches.last_draw = T.self_reset ? wave_last_draw(gridDim.x, waves, (uint32_t)T.ntickets) : ~0u;
+      s_batches.counter = reinterpret_cast<unsigned long long>(T.ticket);
     }
     __syncthreads();
   }
   // neighbouring tickets of the first round go to different compute units
   uint32_t t = uniform32(threadIdx.x >> 6) * gridDim.x + blockIdx.x;
-  bool draw = false;
   while (t < (uint32_t)T.ntickets) {
     if (T.log) t_begin = wall_clock64();
-    unsigned long long drawn = 0;
-    if (FORM == kShared && draw && counts && lane == 0) drawn = atomicAdd(T.ticket, 1ull);  // answered while the tables are read
-    const Work w = decode_ticket_wave(T, CT, t, lane);
-    if (FORM == kShared && draw && lane == 0)
-      s_batches.set_ahead(counts ? round + (gridDim.x + (uint32_t)drawn) * batch : (uint32_t)T.ntickets);
-    wave_move<NT>(T, CT, t, w, t_begin, lane);
-    t += round;
+    wave_move<NT>(T, CT, t, decode_ticket_wave(T, CT, t, lane), t_begin, lane);
+    if (FORM == kDealt) t += gridDim.x * waves;
     if (FORM == kShared) {
       uint32_t taken = 0;
-      bool owes = false;
-      if (lane == 0) taken = take_ticket(s_batches, batch, (uint32_t)T.ntickets, &owes);
+      if (lane == 0) taken = next_ticket(s_batches);
       t = uniform32(taken);
-      draw = uniform32(owes ? 1u : 0u) != 0;
     }
   }
-  if (T.log || T.self_reset) __syncthreads();
-  if (T.log && threadIdx.x == 0) T.wg_log[blockIdx.x].t_exit = wall_clock64();
-  if (FORM == kShared && T.self_reset && threadIdx.x == 0) reset_counters_after_last(T);
+  if (T.log) {
+    __syncthreads();
+    if (threadIdx.x == 0) T.wg_log[blockIdx.x].t_exit = wall_clock64();
+  }
 }
 
 __global__ void ft_decode_kernel(ClassTable T, InlineBlob, uint32_t *func_out, uint32_t *chunk_out, uint64_t cap) {

@@ -164,7 +164,7 @@ struct ClassTable {
   uint32_t inline_tables;
   // 1: ticket[0] is the counter and ticket[1] counts the workgroups that have finished; the
   // last one to finish sets both back to zero, so the pair serves the next launch that
-  // gets it without anybody clearing it in between
+  // gets it without anybody clearing it in between (the wave kernel knows its last draw and leaves ticket[1] alone)
   uint32_t self_reset;
   // 1: one function with one descriptor (xfers[0]) and no chunks triggered before: tile v
   // is stream bytes [v / tiles_per_chunk * chunk_bytes + v % tiles_per_chunk * tile_bytes, ...)

@@ -31,6 +31,7 @@ static void launch(uint32_t groups, uint32_t waves, uint32_t tickets, uint32_t s
   std::fprintf(stderr, "%u workgroups of %u, %u tickets, slow %u\n", groups, waves, tickets, slow);  // the last line names a case that hangs
   for (auto &h : hits) h = 0;
   std::atomic<uint32_t> counter{0}, done{0}, latest{0};
+  std::atomic<bool> reset{false};
   for (uint32_t b = 0; b < groups; ++b) {
     wg[b].taken = batch;
     wg[b].next = round + b * batch;
@@ -43,7 +44,18 @@ static void launch(uint32_t groups, uint32_t waves, uint32_t tickets, uint32_t s
         uint32_t t = w * groups + b;
         bool draw = false;
         while (t < tickets) {
-          if (draw) g.set_ahead(wave_counts(groups, waves, tickets) ? round + (groups + counter.fetch_add(1)) * batch : tickets);
+          if (draw) {
+            uint32_t first = tickets;
+            if (wave_counts(groups, waves, tickets)) {
+              const uint32_t drawn = counter.fetch_add(1);
+              first = round + (groups + drawn) * batch;
+              if (drawn == wave_last_draw(groups, waves, tickets)) {
+                CHECK(!reset.exchange(true));
+                counter = 0;  // a draw after this would find a batch that was handed out already
+              }
+            }
+            g.set_ahead(first);
+          }
           hits[t].fetch_add(1);
           uint32_t was = latest.load();
           while (was < t && !latest.compare_exchange_weak(was, t)) {}
@@ -56,6 +68,7 @@ static void launch(uint32_t groups, uint32_t waves, uint32_t tickets, uint32_t s
   for (auto &t : ts) t.join();
   for (auto &h : hits) CHECK(h == 1);
   CHECK(latest == tickets - 1);
+  CHECK(counter == 0 && reset == wave_counts(groups, waves, tickets));
 }
 
 int main(int argc, char **argv) {
