@@ -7,7 +7,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfaastube.so")
-SOURCES = ["ft_pool.cpp", "ft_plan.cpp", "ft_api.cpp", "ft_open.cpp", "ft_policy.cpp", "ft_store.cpp", "ft_paths.cpp", "ft_kernels.hip", "ft_static.hip"]
+SOURCES = ["ft_pool.cpp", "ft_plan.cpp", "ft_api.cpp", "ft_open.cpp", "ft_policy.cpp", "ft_store.cpp", "ft_paths.cpp", "ft_kernels.hip", "ft_pieces.hip", "ft_static.hip"]
 # packed fp32 code generation is switched off for every translation unit
 FLAGS = ["-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "-Wall", "-Wno-unused-result",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
@@ -27,14 +27,8 @@ def hipcc():
     return exe
 
 
-def check_registers(remarks):
-    """A host-link workgroup and a pool->pool workgroup must fit on one CU together
-    (one wavefront of each per SIMD, 512 registers per lane, allocated in eights):
-    a job with both kinds of traffic runs the two kernels side by side, and a
-    host-link workgroup that took a CU for itself would idle that CU's share of HBM.
-    The limit checked is 480, not 512: builds whose two kernels added up to 488 and 496
-    registers measured 1.2 % less of the host link beside pool->pool launches (large_mixed:
-    99.6 -> 98.3 % of the measured peak), the build at 480 does not.
+def kernel_registers(remarks):
+    """Registers per lane of every kernel, from the compiler's remarks.
     No kernel may use scratch memory: every dispatch of one that does needs its queue's."""
     import re
     regs = {}
@@ -50,6 +44,19 @@ def check_registers(remarks):
         m = re.search(r"ScratchSize \[bytes/lane\]: (\d+)", line)
         if m and int(m.group(1)) != 0:
             raise RuntimeError(f"{name} uses {m.group(1)} bytes of scratch memory a lane")
+    return regs
+
+
+def check_registers(remarks):
+    """A host-link workgroup and a pool->pool workgroup must fit on one CU together
+    (one wavefront of each per SIMD, 512 registers per lane, allocated in eights):
+    a job with both kinds of traffic runs the two kernels side by side, and a
+    host-link workgroup that took a CU for itself would idle that CU's share of HBM.
+    The limit checked is 480, not 512: builds whose two kernels added up to 488 and 496
+    registers measured 1.2 % less of the host link beside pool->pool launches (large_mixed:
+    99.6 -> 98.3 % of the measured peak), the build at 480 does not."""
+    import re
+    regs = kernel_registers(remarks)
     up8 = lambda v: (v + 7) // 8 * 8
     per_class = {}
     for k, v in regs.items():
@@ -77,7 +84,7 @@ def build(verbose=False):
     for src in SOURCES:
         obj = os.path.join(out_dir, os.path.splitext(src)[0] + ".o")
         cmd = [hipcc(), "-x", "hip", *FLAGS, "-c", os.path.join(CSRC, src), "-o", obj]
-        if src == "ft_kernels.hip":
+        if src in ("ft_kernels.hip", "ft_pieces.hip"):
             cmd.insert(-4, "-Rpass-analysis=kernel-resource-usage")
         if verbose:
             print(" ".join(cmd), flush=True)
@@ -89,6 +96,8 @@ def build(verbose=False):
             per_class = check_registers(res.stderr)
             if verbose:
                 print("registers per lane (host->pool, pool->host, pool->pool, pool->pool by wavefronts):", per_class, flush=True)
+        elif src == "ft_pieces.hip":
+            kernel_registers(res.stderr)
         else:
             sys.stderr.write(res.stderr)
         objs.append(obj)

@@ -753,6 +753,66 @@ int launch_with_uploaded_tables(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t
   return FT_OK;
 }
 
+// A job of one link class that is short as a list of pieces (ft_pieces.h) is launched as that list on the caller's stream: tables in the
+// launch where they fit, else uploaded in front of it. Not a job whose schedule or log may be asked for (FT_KEEP, FT_LOG): the pieces do not
+// hold the schedule. Nor a detached one that would hold the caller's stream for long. *launched says whether the job went this way.
+int launch_as_pieces(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_bytes, uint32_t flags, hipStream_t user, bool *launched) {
+  *launched = false;
+  if (launch_pieces == nullptr || (flags & (FT_KEEP | FT_LOG | FT_PATH_DMA))) return FT_OK;
+  int only = -1;
+  for (int c = 0; c < FT_NCLASS; ++c)
+    if (plan.cls[c].nchunks > 0) only = only == -1 ? c : -2;
+  if (only < 0 || p->tuning[only].workgroups != 0 || p->tuning[only].tile_bytes != 0) return FT_OK;
+  const ClassPlan &cp = plan.cls[only];
+  if ((flags & FT_DETACHED) && cp.payload > kWaveTilesBytes) return FT_OK;
+  const PieceRoom room = job_pieces(cp, only, chunk_bytes);
+  if (room.pieces == 0) return FT_OK;
+  const uint64_t bytes = align_up(piece_bytes(room), 256);
+  uint64_t few[448];  // the tables of most jobs that take them along
+  char *h = reinterpret_cast<char *>(few);
+  if (bytes > sizeof(few)) {
+    const int rc = get_blob(p, bytes, true, &job->tables);
+    if (rc != FT_OK) return rc;
+    h = job->tables.host;
+  }
+  PieceTables t = piece_places(h, room);
+  build_pieces(cp, chunk_bytes, piece_tile(only, cp.payload), only == FT_H2P, &t);
+  const bool with_launch = pieces_go_along(t);
+  if (!with_launch && job->tables.dev == nullptr) {
+    const int rc = get_blob(p, bytes, true, &job->tables);
+    if (rc != FT_OK) return rc;
+    std::memcpy(job->tables.host, few, bytes);
+  }
+  ClassRun &r = job->run[only];
+  r.used = true;
+  r.pieces = true;
+  r.tile_bytes = t.tile;
+  r.table.ntickets = t.ntiles;
+  r.workgroups = t.ntiles;
+  r.on_user_stream = with_launch;
+  r.stream = user;
+  const bool timing = (flags & FT_TIMING) != 0;
+  int rc = get_event(p, false, &r.ev_done);
+  if (rc == FT_OK && timing) rc = get_event(p, true, &r.ev_begin);
+  if (rc == FT_OK && timing) rc = get_event(p, true, &r.ev_end);
+  if (rc != FT_OK) return fail_submit(p, job, rc);
+  hipError_t e = hipSuccess;
+  if (!with_launch) {
+    e = upload_tables(job->tables, bytes, false, p->ctx->idle_counter, user);
+    t = pieces_at(job->tables.dev, room, t);
+  }
+  // without timing the done event is bound to the dispatch itself, which spares a marker behind it
+  if (e == hipSuccess) e = launch_pieces(t, only, with_launch, user, r.ev_begin, timing ? r.ev_end : r.ev_done);
+  if (e == hipSuccess && timing) e = hipEventRecord(r.ev_done, user);
+  if (e != hipSuccess) {
+    p->hip_error = std::string("launch of pieces: ") + hipGetErrorString(e);
+    (void)hipDeviceSynchronize();
+    return fail_submit(p, job, FT_EHIP);
+  }
+  *launched = true;
+  return FT_OK;
+}
+
 }  // namespace ft
 
 using namespace ft;
@@ -896,9 +956,12 @@ int ft_submit_transfers(ft_pool *p, const ft_desc *descs, uint32_t ndesc, const 
       rc = stage_closed_job(p, job.get(), plan);
       if (rc != FT_OK) return fail_submit(p, job.get(), rc);
     }
-    shape_classes(p, job.get(), plan, chunk_bytes);
     bool launched = false;
-    rc = launch_with_the_launch(p, job.get(), plan, chunk_bytes, flags, user, &launched);
+    rc = launch_as_pieces(p, job.get(), plan, chunk_bytes, flags, user, &launched);
+    if (rc == FT_OK && !launched) {
+      shape_classes(p, job.get(), plan, chunk_bytes);
+      rc = launch_with_the_launch(p, job.get(), plan, chunk_bytes, flags, user, &launched);
+    }
     if (rc == FT_OK && !launched) rc = launch_with_uploaded_tables(p, job.get(), plan, chunk_bytes, flags, user);
     if (rc != FT_OK) return rc;
   }
@@ -1146,11 +1209,26 @@ int ft_job_schedule(ft_pool *p, ft_job_t id, int link_class, uint32_t *func_out,
   uint32_t *dev = reinterpret_cast<uint32_t *>(out.dev);
   // ordered after the job's own kernel and table upload (a job that went with its launch carries its tables along)
   hipStream_t s = r.stream != nullptr ? r.stream : p->ctx->streams[link_class];
-  hipError_t e = launch_decode(r.table, dev, dev + n, n, s, job->inline_tables.get());
+  ClassTable T = r.table;
+  Blob schedule;
+  hipError_t e = hipSuccess;
+  if (r.pieces) {  // its launch had no use for the schedule's tables
+    s = p->ctx->streams[link_class];
+    const Layout lay = layout_of(r.plan, 0, 1);
+    rc = get_blob(p, lay.end, true, &schedule);
+    if (rc != FT_OK) {
+      put_blob(p, out);
+      return rc;
+    }
+    fill_tables(r.plan, lay, schedule.host, schedule.dev, &T);
+    e = hipMemcpyAsync(schedule.dev, schedule.host, lay.end, hipMemcpyHostToDevice, s);
+  }
+  if (e == hipSuccess) e = launch_decode(T, dev, dev + n, n, s, job->inline_tables.get());
   if (e == hipSuccess) e = hipStreamSynchronize(s);
   if (e == hipSuccess) e = hipMemcpy(func_out, dev, n * sizeof(uint32_t), hipMemcpyDeviceToHost);
   if (e == hipSuccess) e = hipMemcpy(chunk_out, dev + n, n * sizeof(uint32_t), hipMemcpyDeviceToHost);
   if (e != hipSuccess) (void)hipDeviceSynchronize();  // the decode may still be writing
+  put_blob(p, schedule);
   put_blob(p, out);
   if (e != hipSuccess) {
     p->hip_error = std::string("ft_job_schedule: ") + hipGetErrorString(e);

@@ -35,6 +35,7 @@ struct ClassRun {
   uint32_t tiles_per_chunk = 0;
   uint32_t workgroups = 0;
   int code = 0;             // what launch_copy is given: the link class, or a launch code of the wave kernel
+  bool pieces = false;      // launched as a list of pieces (ft_pieces.h): the table holds its number of tiles alone
   bool on_user_stream = false;  // launched on the caller's stream, tables in the launch
   hipStream_t stream = nullptr; // the library's stream it runs on otherwise
   int counter_pair = -1;        // its self-resetting counter pair, if it needed a counter

@@ -1,0 +1,108 @@
+// A class of a job as the list of its pieces: what the proportional chunk order of Sec. 6.1 comes to when it is written
+// out, for jobs in which that is short. A piece is a run of bytes that lie together on both sides, or whole rows of one
+// pitched descriptor; pieces follow each other in the order of the chunks that they come from, and every piece is cut into
+// tiles of its own. Tile t of the launch is found by searching one table (the first tile of each piece) and its bytes by
+// reading one record, where the general tables (ft_tables.h) take five dependent reads and several divisions.
+#pragma once
+#include <stdint.h>
+
+#include "ft_plan.h"
+#include "ft_tables.h"
+#include "ft_windows.h"
+
+namespace ft {
+
+struct PieceSides {
+  uint64_t src, dst;
+};
+
+// What pieces of whole rows have beyond their sides (those of their first row). Most jobs have few shapes.
+struct PieceRows {
+  uint32_t row_bytes, src_pitch, dst_pitch;
+  uint32_t per;    // rows of a tile; or kPartsOfRow | tiles of a row
+  uint32_t magic;  // g / windows of a row = mulhi(g, magic) or one less; 0: a row is one window (ft_windows.h)
+  uint32_t part;   // bytes of a tile that is part of a row
+};
+constexpr uint32_t kPartsOfRow = 1u << 31;
+
+// The tables as arrays of `n` entries each, in host or in device memory.
+struct PieceTables {
+  PieceSides *at = nullptr;
+  uint32_t *first = nullptr;    // the piece's first tile; ascending, no piece is without one
+  uint32_t *len = nullptr;      // bytes of a run, rows of a piece of rows
+  uint32_t *shape = nullptr;    // 0: a run; else 1 + index into the shapes. Null: all are runs
+  PieceRows *shapes = nullptr;  // null if shape is
+  uint32_t n = 0, nshapes = 0, ntiles = 0;
+  uint32_t tile = 0;  // bytes of a tile, a power of two
+};
+
+// A run's tiles begin and end where this many bytes of the side that is dearer to cut (the destination; host memory where
+// that is the source) do, so that no line is written by two wavefronts: shared lines cost a misaligned job 4-12 %.
+constexpr uint32_t kPieceLine = 128;
+// Pieces of one job at most, and at most as many as travel with a launch, with as many shapes: kernel arguments end at 4 KiB.
+constexpr uint32_t kMaxPieces = 16384;
+inline bool pieces_go_along(const PieceTables &t) {
+  return t.shape == nullptr ? t.n <= 128 : (t.n <= 64 && t.nshapes <= 64) || (t.n <= 144 && t.nshapes <= 8);
+}
+
+// An upper bound for the pieces of a class and their shapes, 0 if it is no job for them: too many, or rows that the kernels do not
+// cover (under 16 bytes, or so far apart that a tile's distances leave 32 bits).
+struct PieceRoom {
+  uint64_t pieces = 0, shapes = 0;
+};
+PieceRoom piece_room(const ClassPlan &cp, uint64_t chunk_bytes);
+// Bytes of the tables, and their places from `base` (a multiple of 8) on.
+uint64_t piece_bytes(const PieceRoom &room);
+PieceTables piece_places(char *base, const PieceRoom &room);
+// t's tables where a copy of them lies.
+inline PieceTables pieces_at(char *base, const PieceRoom &room, const PieceTables &t) {
+  PieceTables c = piece_places(base, room);
+  c.n = t.n;
+  c.nshapes = t.nshapes;
+  c.ntiles = t.ntiles;
+  c.tile = t.tile;
+  return c;
+}
+// Fills t with the pieces of a class in its order, cut into tiles of `tile` bytes, a power of two from kPieceLine to 8 KiB.
+// by_source: the source's lines are the ones not to be cut.
+void build_pieces(const ClassPlan &cp, uint64_t chunk_bytes, uint32_t tile, bool by_source, PieceTables *t);
+
+// The room for a class of a job that is to be launched as pieces, none if it is not; and the tile.
+PieceRoom job_pieces(const ClassPlan &cp, int cls, uint64_t chunk_bytes);
+uint32_t piece_tile(int cls, uint64_t payload);
+
+// ---- what a tile covers: the arithmetic of the kernels, so that it can be checked without a GPU
+
+// Bytes [begin, begin + n) of a run of len bytes, one of whose sides (the one not to be cut) begins at `side`.
+FT_HD void run_tile(uint64_t side, uint32_t len, uint32_t tile, uint32_t no, uint32_t *begin, uint32_t *n) {
+  const uint32_t before = (uint32_t)side & (kPieceLine - 1);
+  const uint32_t b = no == 0 ? 0u : no * tile - before, e = (no + 1) * tile - before;
+  *begin = b;
+  *n = (e < len ? e : len) - b;
+}
+
+// A tile of whole rows: rows [r0, r0 + n) of a piece of len rows.
+FT_HD void rows_tile(const PieceRows &r, uint32_t len, uint32_t no, uint32_t *r0, uint32_t *n) {
+  *r0 = no * r.per;
+  *n = len - *r0 < r.per ? len - *r0 : r.per;
+}
+
+// Window g of a tile of whole rows, per_row of which a row has: 16 bytes of row *row from column *col on.
+FT_HD uint32_t windows_of_row(uint32_t row_bytes) { return row_bytes / 16 + (row_bytes % 16 != 0 ? 1u : 0u); }
+FT_HD void row_window_of(const PieceRows &r, uint32_t per_row, uint32_t g, uint32_t *row, uint32_t *col) {
+  uint32_t q = r.magic == 0 ? g : mul_hi32(g, r.magic);
+  q -= q * per_row > g ? 1u : 0u;
+  const uint32_t c = (g - q * per_row) * 16, last = r.row_bytes - 16;
+  *row = q;
+  *col = c < last ? c : last;
+}
+
+// A tile that is part of a row: n bytes from column *begin of row *row on.
+FT_HD void row_part(const PieceRows &r, uint32_t no, uint32_t *row, uint32_t *begin, uint32_t *n) {
+  const uint32_t parts = r.per & ~kPartsOfRow;
+  *row = no / parts;
+  *begin = (no - *row * parts) * r.part;
+  *n = r.row_bytes - *begin < r.part ? r.row_bytes - *begin : r.part;
+}
+
+}  // namespace ft

@@ -1,0 +1,230 @@
+// Kernels for a class that is written out as pieces (ft_pieces.h): a workgroup of one wavefront per tile, dispatched in
+// the order of the pieces.
+//
+// What bounds them is what bounds a launch of some MiB: the fetch of its arguments and instructions, the reads that lead
+// from a tile's number to its bytes, one round trip for the bytes, and HBM or the last-level cache. So the tables are
+// small (28 bytes a piece of a run, in the launch itself up to kInlineRuns pieces), a tile is found by one compare of 64
+// entries and one record, and the code is a few hundred instructions. No counter and no persistent workgroups: the hardware
+// starts the workgroups in order as others end.
+#include <hip/hip_runtime.h>
+#include <hip/hip_ext.h>
+
+#include <cstring>
+
+#include "ft_kernels.h"
+#include "ft_moves.h"
+#include "ft_pieces.h"
+
+namespace ft {
+
+// Tables that travel with the launch: the first kernel argument. A launch call costs the host 4.1 us with some bytes of arguments and
+// 5.8 us with 3 KiB, so there are several sizes.
+template <uint32_t CAP, uint32_t SHAPES>
+struct PieceArgs {
+  static constexpr bool kRows = SHAPES != 0;
+  uint32_t n, tile;
+  PieceSides at[CAP];
+  uint32_t first[CAP], len[CAP];
+  uint32_t shape[kRows ? (CAP + 3) / 4 : 1];  // a byte each
+  PieceRows shapes[kRows ? SHAPES : 1];
+};
+// and tables in device memory
+template <bool ROWS>
+struct PieceRefs {
+  static constexpr bool kRows = ROWS;
+  uint32_t n, tile;
+  const PieceSides *at;
+  const uint32_t *first, *len, *shape;
+  const PieceRows *shapes;
+};
+
+struct Piece {
+  uint64_t src, dst;
+  uint32_t len, tile_no;  // tile within the piece
+  uint32_t tile;          // bytes of a tile
+  PieceRows rows;         // row_bytes 0: a run
+};
+
+// The last of n ascending entries (the first of which is 0) at or before t.
+__device__ __forceinline__ uint32_t last_at_or_before(const FT_CONST uint32_t *first, uint32_t n, uint32_t t, uint32_t lane) {
+  uint32_t x = 0;
+  while (n > 1) {
+    const uint32_t step = (n + 63) / 64;
+    const uint32_t j = lane * step;
+    const uint32_t at = (wave_count(j < n && first[x + (j < n ? j : 0u)] <= t) - 1) * step;
+    x += at;
+    n = step < n - at ? step : n - at;
+  }
+  return uniform32(x);
+}
+
+__device__ __forceinline__ PieceRows read_shape(const FT_CONST PieceRows *shapes, uint32_t shape) {
+  PieceRows r;
+  r.row_bytes = 0;
+  if (shape != 0) {
+    const FT_CONST PieceRows &s = shapes[shape - 1];
+    r.row_bytes = s.row_bytes;
+    r.src_pitch = s.src_pitch;
+    r.dst_pitch = s.dst_pitch;
+    r.per = s.per;
+    r.magic = s.magic;
+    r.part = s.part;
+  }
+  return r;
+}
+
+template <uint32_t CAP, uint32_t SHAPES>
+__device__ __forceinline__ Piece find_piece(const PieceArgs<CAP, SHAPES> &, uint32_t t, uint32_t lane) {
+  const FT_CONST PieceArgs<CAP, SHAPES> &a =
+      *reinterpret_cast<const FT_CONST PieceArgs<CAP, SHAPES> *>(reinterpret_cast<uintptr_t>(__builtin_amdgcn_kernarg_segment_ptr()));
+  uint32_t x = 0;
+  if (CAP > 1) {
+    uint32_t before = 0;  // every compare's load is on its way before the first is counted
+#pragma unroll
+    for (uint32_t j0 = 0; j0 < CAP; j0 += 64) {
+      const uint32_t j = j0 + lane;
+      before += wave_count(a.first[j < CAP ? j : 0u] <= t && j < a.n);
+    }
+    x = uniform32(before - 1);
+  }
+  Piece p;
+  p.src = a.at[x].src;
+  p.dst = a.at[x].dst;
+  p.len = a.len[x];
+  p.tile_no = t - a.first[x];
+  p.tile = a.tile;
+  if (SHAPES != 0) p.rows = read_shape(a.shapes, a.shape[x / 4] >> x % 4 * 8 & 255);
+  return p;
+}
+
+template <class T>
+__device__ __forceinline__ const FT_CONST T *constant(const T *p) { return reinterpret_cast<const FT_CONST T *>(reinterpret_cast<uintptr_t>(p)); }
+
+template <bool ROWS>
+__device__ __forceinline__ Piece find_piece(const PieceRefs<ROWS> &r, uint32_t t, uint32_t lane) {
+  const uint32_t x = last_at_or_before(constant(r.first), r.n, t, lane);
+  Piece p;
+  p.src = constant(r.at)[x].src;
+  p.dst = constant(r.at)[x].dst;
+  p.len = constant(r.len)[x];
+  p.tile_no = t - constant(r.first)[x];
+  p.tile = r.tile;
+  if (ROWS) p.rows = read_shape(constant(r.shapes), constant(r.shape)[x]);
+  return p;
+}
+
+// n bytes of a run, at most 512 windows.
+template <int NT>
+__device__ __forceinline__ void move_run(uint64_t d, uint64_t s, uint32_t n, uint32_t lane) {
+  if (n < 16) {
+    if (lane < n) st_off<uint8_t, 0>(d, lane, ld_off<uint8_t, 0>(s, lane));
+    return;
+  }
+  const RunWindows w = run_windows(NT == kFromHost ? s : d, n);  // whole granules on the side that is dearer
+  // no deeper than need be: a lane's load beyond the last window costs as much as any other
+  if (w.count <= 128) wave_run_pass<NT, 2>(d, s, w, 0, lane);
+  else if (w.count <= 256) wave_run_pass<NT, 4>(d, s, w, 0, lane);
+  else wave_run_pass<NT, 8>(d, s, w, 0, lane);
+}
+
+// R * 64 windows of whole rows, `per_row` of which a row has. All loads before the first store; a lane past the last window
+// loads the first one and stores nothing.
+template <int NT, uint32_t R>
+__device__ __forceinline__ void move_windows(uint64_t d, uint64_t s, const PieceRows &r, uint32_t per_row, uint32_t count, uint32_t lane) {
+  u32x4_any v[R];
+  uint32_t to[R];
+#pragma unroll
+  for (uint32_t i = 0; i < R; ++i) {
+    const uint32_t g = lane + i * 64;
+    uint32_t row, col;
+    row_window_of(r, per_row, g < count ? g : 0u, &row, &col);
+    v[i] = ld_off<u32x4_any, NT>(s, row * r.src_pitch + col);
+    to[i] = row * r.dst_pitch + col;
+  }
+#pragma unroll
+  for (uint32_t i = 0; i < R; ++i)
+    if (lane + i * 64 < count) st_off<u32x4_any, NT>(d, to[i], v[i]);
+}
+
+template <int NT, bool ROWS>
+__device__ __forceinline__ void move_tile(const Piece &p, uint32_t lane) {
+  uint64_t d = p.dst, s = p.src;
+  uint32_t begin, n;
+  if (ROWS && p.rows.row_bytes != 0) {
+    const PieceRows &r = p.rows;
+    uint32_t row;
+    if (!(r.per & kPartsOfRow)) {
+      rows_tile(r, p.len, p.tile_no, &row, &n);
+      const uint32_t per_row = windows_of_row(r.row_bytes), count = n * per_row;
+      d += (uint64_t)row * r.dst_pitch;
+      s += (uint64_t)row * r.src_pitch;
+      if (count <= 256) move_windows<NT, 4>(d, s, r, per_row, count, lane);
+      else move_windows<NT, 8>(d, s, r, per_row, count, lane);
+      return;
+    }
+    row_part(r, p.tile_no, &row, &begin, &n);
+    row = uniform32(row);
+    begin = uniform32(begin);
+    d += (uint64_t)row * r.dst_pitch;
+    s += (uint64_t)row * r.src_pitch;
+  } else {
+    run_tile(NT == kFromHost ? p.src : p.dst, p.len, p.tile, p.tile_no, &begin, &n);
+  }
+  move_run<NT>(d + begin, s + begin, n, lane);
+}
+
+template <int NT, class A>
+__global__ __launch_bounds__(64) void ft_piece_kernel(A args) {
+  move_tile<NT, A::kRows>(find_piece(args, blockIdx.x, threadIdx.x), threadIdx.x);
+}
+
+namespace {
+
+template <int NT, class A>
+hipError_t launch(const A &a, uint32_t ntiles, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  static_assert(sizeof(A) <= 4096, "kernel arguments end at 4 KiB");
+  hipExtLaunchKernelGGL((ft_piece_kernel<NT, A>), dim3(ntiles), dim3(64), 0, stream, ev_start, ev_stop, 0, a);
+  return hipGetLastError();
+}
+
+template <uint32_t CAP, uint32_t SHAPES>
+hipError_t launch_along(const PieceTables &t, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  if (t.n > CAP || t.nshapes > SHAPES) return hipErrorInvalidValue;
+  PieceArgs<CAP, SHAPES> a;
+  a.n = t.n;
+  a.tile = t.tile;
+  std::memcpy(static_cast<void *>(a.at), t.at, t.n * sizeof(PieceSides));
+  std::memcpy(a.first, t.first, t.n * sizeof(uint32_t));
+  std::memcpy(a.len, t.len, t.n * sizeof(uint32_t));
+  if (SHAPES != 0) {
+    uint8_t *shape = reinterpret_cast<uint8_t *>(a.shape);
+    for (uint32_t i = 0; i < t.n; ++i) shape[i] = (uint8_t)t.shape[i];
+    std::memcpy(static_cast<void *>(a.shapes), t.shapes, t.nshapes * sizeof(PieceRows));
+  }
+  return launch<0>(a, t.ntiles, stream, ev_start, ev_stop);
+}
+
+template <bool ROWS>
+hipError_t launch_from_memory(const PieceTables &t, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  const PieceRefs<ROWS> r = {t.n, t.tile, t.at, t.first, t.len, t.shape, t.shapes};
+  return launch<0>(r, t.ntiles, stream, ev_start, ev_stop);
+}
+
+}  // namespace
+
+hipError_t launch_pieces(const PieceTables &t, int cls, bool on_host, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
+  if (t.n == 0 || t.ntiles == 0 || cls != 2 || (on_host && !pieces_go_along(t))) return hipErrorInvalidValue;
+  const bool rows = t.shape != nullptr;
+  if (!on_host) return rows ? launch_from_memory<true>(t, stream, ev_start, ev_stop) : launch_from_memory<false>(t, stream, ev_start, ev_stop);
+  if (rows) {
+    if (t.n <= 16 && t.nshapes <= 16) return launch_along<16, 16>(t, stream, ev_start, ev_stop);
+    if (t.n <= 64) return launch_along<64, 64>(t, stream, ev_start, ev_stop);
+    return launch_along<144, 8>(t, stream, ev_start, ev_stop);
+  }
+  if (t.n == 1) return launch_along<1, 0>(t, stream, ev_start, ev_stop);
+  if (t.n <= 16) return launch_along<16, 0>(t, stream, ev_start, ev_stop);
+  if (t.n <= 48) return launch_along<48, 0>(t, stream, ev_start, ev_stop);
+  return launch_along<128, 0>(t, stream, ev_start, ev_stop);
+}
+
+}  // namespace ft

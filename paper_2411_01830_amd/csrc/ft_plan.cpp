@@ -1,6 +1,7 @@
 #include "ft_plan.h"
 
 #include "ft_batches.h"
+#include "ft_pieces.h"
 
 #include <algorithm>
 #include <numeric>
@@ -91,6 +92,15 @@ bool mostly_short_rows(const ClassPlan &cp) {
   return 2 * short_bytes > cp.payload;
 }
 
+// Pitched rows that 32-bit arithmetic covers: the descriptor's payload, and the distance from a tile's first row to the end
+// of its last (a tile is little more than 8 KiB at most).
+static bool rows_fit(const Xfer &x) {
+  if (x.row_bytes < 16 || (x.rows | x.row_bytes) >> 32 != 0 || x.rows * x.row_bytes >> 32 != 0) return false;
+  const uint64_t pitch = x.src_pitch > x.dst_pitch ? x.src_pitch : x.dst_pitch;
+  // (a division for the rare descriptor alone: one for each of 1536 took 4 us of planning)
+  return pitch <= 1u << 20 || pitch <= ((1ull << 32) - 1) / (8208 / x.row_bytes + 3);
+}
+
 // Whether the wave kernel's 32-bit arithmetic covers a job (see ft_kernels.hip): tile and chunk numbers, the payload of
 // every pitched descriptor, and the distance from a tile's first row to the end of its last (a tile is little more than 8 KiB at
 // most). Up to 1024 functions a wavefront's search of the phases and of the runs of empty tiles, 64 entries at a time, costs less
@@ -100,13 +110,8 @@ bool mostly_short_rows(const ClassPlan &cp) {
 static bool wave_tiles_fit(const ClassPlan &cp, uint64_t chunk_bytes) {
   if (chunk_bytes < 1024 || chunk_bytes > (1ull << 29) || cp.funcs.size() > 1024) return false;
   if (cp.nchunks > (1ull << 31) / (chunk_bytes / 1024 + 1)) return false;
-  for (const Xfer &x : cp.xfers) {
-    if (x.rows <= 1) continue;
-    if (x.row_bytes < 16 || (x.rows | x.row_bytes) >> 32 != 0 || x.rows * x.row_bytes >> 32 != 0) return false;
-    const uint64_t pitch = x.src_pitch > x.dst_pitch ? x.src_pitch : x.dst_pitch;
-    // (a division for the rare descriptor alone: one for each of 1536 took 4 us of planning)
-    if (pitch > 1u << 20 && pitch > ((1ull << 32) - 1) / (8208 / x.row_bytes + 3)) return false;
-  }
+  for (const Xfer &x : cp.xfers)
+    if (x.rows > 1 && !rows_fit(x)) return false;
   return true;
 }
 
@@ -170,6 +175,227 @@ int launch_code(const ClassPlan &cp, int cls, uint64_t chunk_bytes, bool tuned, 
   }
   if (!alone || streams) return cls;
   return cp.payload <= kWaveAnyBytes || cp.xfers.size() == 1 || 2 * (misaligned + rows) > cp.payload ? kWaveOnePerUnit : cls;
+}
+
+// ---- a class written out as pieces (ft_pieces.h)
+
+PieceRoom piece_room(const ClassPlan &cp, uint64_t chunk_bytes) {
+  PieceRoom room;
+  if (chunk_bytes < 1024) return room;
+  uint64_t pitched = 0;
+  for (const Xfer &x : cp.xfers) {
+    if (x.rows <= 1) continue;
+    if (!rows_fit(x)) return room;
+    ++pitched;
+  }
+  // a chunk's end cuts a run in two, and pitched rows into whole rows and the two parts of the row that it falls into; with one
+  // function the chunks follow each other and nothing is cut
+  const uint64_t cuts = cp.funcs.size() == 1 ? 0 : cp.nchunks;
+  const uint64_t n = cp.xfers.size() + cuts * (pitched != 0 ? 3 : 1) + (cp.payload >> 30);
+  if (n > kMaxPieces) return room;
+  room.pieces = n;
+  room.shapes = pitched;
+  return room;
+}
+
+uint64_t piece_bytes(const PieceRoom &r) {
+  return r.pieces * (sizeof(PieceSides) + (r.shapes != 0 ? 3 : 2) * sizeof(uint32_t)) + r.shapes * sizeof(PieceRows);
+}
+
+PieceTables piece_places(char *base, const PieceRoom &r) {
+  PieceTables t;
+  t.at = reinterpret_cast<PieceSides *>(base);
+  t.first = reinterpret_cast<uint32_t *>(base + r.pieces * sizeof(PieceSides));
+  t.len = t.first + r.pieces;
+  if (r.shapes != 0) {
+    t.shape = t.len + r.pieces;
+    t.shapes = reinterpret_cast<PieceRows *>(t.shape + r.pieces);
+  }
+  return t;
+}
+
+namespace {
+
+// g / d by a multiplication, d <= 512 windows: a job of 1536 descriptors has as many divisions by the windows of its rows and
+// by the rows of its tiles.
+struct Reciprocals {
+  uint32_t magic[513];
+  constexpr Reciprocals() : magic{} {
+    for (uint32_t d = 1; d <= 512; ++d) magic[d] = 0xffffffffu / d + 1;  // 2^32 / d rounded up; of 1: 0
+  }
+  uint32_t divide(uint32_t g, uint32_t d) const {
+    if (d == 1) return g;
+    const uint32_t q = mul_hi32(g, magic[d]);
+    return q - ((uint64_t)q * d > g ? 1u : 0u);
+  }
+};
+constexpr Reciprocals kReciprocals;
+
+// (The table's pointers are copied: what is written through them could otherwise be the table itself, and every store would be
+// followed by loads of them.)
+struct PieceWriter {
+  PieceSides *const at;
+  uint32_t *const len, *const shape;
+  PieceRows *const shapes;
+  const uint32_t tile;
+  uint32_t n = 0, nshapes = 0, last_shape = 0;
+
+  explicit PieceWriter(const PieceTables &t) : at(t.at), len(t.len), shape(t.shape), shapes(t.shapes), tile(t.tile) {}
+  void add(uint64_t src, uint64_t dst, uint32_t bytes_or_rows, uint32_t of_shape) {
+    at[n] = PieceSides{src, dst};
+    len[n] = bytes_or_rows;
+    if (shape != nullptr) shape[n] = of_shape;
+    last_shape = of_shape;
+    n += 1;
+  }
+  // n bytes that lie together on both sides; they go on with the last piece if they lie behind it
+  void run(uint64_t src, uint64_t dst, uint64_t bytes) {
+    constexpr uint64_t most = 1ull << 30;
+    if (n != 0 && last_shape == 0) {
+      const uint64_t had = len[n - 1];
+      if (at[n - 1].src + had == src && at[n - 1].dst + had == dst) {
+        const uint64_t m = std::min(bytes, most - had);
+        len[n - 1] = (uint32_t)(had + m);
+        src += m;
+        dst += m;
+        bytes -= m;
+      }
+    }
+    for (; bytes > 0; src += most, dst += most, bytes -= std::min(bytes, most)) add(src, dst, (uint32_t)std::min(bytes, most), 0);
+  }
+  // known: the shape that x has been given, 0 as yet
+  void whole_rows(const Xfer &x, uint64_t r, uint64_t rows, uint32_t *known) {
+    const uint64_t src = x.src + r * x.src_pitch, dst = x.dst + r * x.dst_pitch;
+    if (rows == 1) return run(src, dst, x.row_bytes);
+    if (*known == 0) {
+      const PieceRows *same = nshapes != 0 ? &shapes[nshapes - 1] : nullptr;
+      if (same == nullptr || same->row_bytes != x.row_bytes || same->src_pitch != x.src_pitch || same->dst_pitch != x.dst_pitch)
+        shapes[nshapes++] = shape_of((uint32_t)x.row_bytes, (uint32_t)x.src_pitch, (uint32_t)x.dst_pitch);
+      *known = nshapes;
+    }
+    if (n != 0 && last_shape == *known) {
+      const uint64_t had = len[n - 1];
+      if (at[n - 1].src + had * x.src_pitch == src && at[n - 1].dst + had * x.dst_pitch == dst && had + rows < 1ull << 32) {
+        len[n - 1] = (uint32_t)(had + rows);
+        return;
+      }
+    }
+    add(src, dst, (uint32_t)rows, *known);
+  }
+  // payload bytes [p, p + n) of a pitched descriptor, all of which rows_fit has found to be less than 2^32
+  void part(const Xfer &x, uint32_t p, uint32_t n, uint32_t *known) {
+    const uint32_t rb = (uint32_t)x.row_bytes;
+    uint32_t r = p / rb;
+    const uint32_t c = p - r * rb;
+    if (c != 0) {
+      const uint32_t m = std::min(n, rb - c);
+      run(x.src + r * x.src_pitch + c, x.dst + r * x.dst_pitch + c, m);
+      n -= m;
+      r += 1;
+    }
+    const uint32_t whole = n / rb;
+    if (whole != 0) whole_rows(x, r, whole, known);
+    n -= whole * rb;
+    r += whole;
+    if (n != 0) run(x.src + r * x.src_pitch, x.dst + r * x.dst_pitch, n);
+  }
+  // A tile is at most tile / 16 windows of 16 bytes (ft_windows.h).
+  PieceRows shape_of(uint32_t row_bytes, uint32_t src_pitch, uint32_t dst_pitch) const {
+    PieceRows r;
+    r.row_bytes = row_bytes;
+    r.src_pitch = src_pitch;
+    r.dst_pitch = dst_pitch;
+    const uint32_t windows = windows_of_row(row_bytes);
+    r.magic = r.part = 0;
+    if (windows <= tile / 16) {
+      r.magic = kReciprocals.magic[windows];
+      r.per = kReciprocals.divide(tile / 16, windows);
+      return r;
+    }
+    const uint64_t parts = ((uint64_t)row_bytes + tile - 1) / tile;
+    r.part = (uint32_t)(((uint64_t)row_bytes + parts - 1) / parts + 15) / 16 * 16;
+    r.per = kPartsOfRow | (uint32_t)(((uint64_t)row_bytes + r.part - 1) / r.part);
+    return r;
+  }
+};
+
+}  // namespace
+
+void build_pieces(const ClassPlan &cp, uint64_t chunk_bytes, uint32_t tile, bool by_source, PieceTables *t) {
+  t->tile = tile;
+  PieceWriter w(*t);
+  const auto all_of = [&w](const Xfer &x) {
+    uint32_t shape = 0;
+    if (x.rows == 1) w.run(x.src, x.dst, x.row_bytes);
+    else w.whole_rows(x, 0, x.rows, &shape);
+  };
+  if (cp.funcs.size() == 1) {
+    for (const Xfer &x : cp.xfers) all_of(x);
+  } else {
+    struct Place {
+      uint64_t left;  // of the function's stream
+      uint64_t pos;   // bytes of descriptor x that are written out
+      uint32_t x, shape;
+    };
+    Place few[16];
+    std::vector<Place> many;
+    Place *at = few;
+    if (cp.funcs.size() > 16) {
+      many.resize(cp.funcs.size());
+      at = many.data();
+    }
+    for (size_t f = 0; f < cp.funcs.size(); ++f) at[f] = Place{cp.funcs[f].stream_bytes, 0, cp.funcs[f].desc_off, 0};
+    for (size_t i = 0; i < cp.phases.size(); ++i) {
+      const Phase &ph = cp.phases[i];
+      uint64_t chunks = (i + 1 < cp.phases.size() ? cp.phases[i + 1].rank_base : cp.nchunks) - ph.rank_base;
+      while (chunks > 0)
+        for (uint32_t s = 0; s < ph.nslots && chunks > 0; ++s, --chunks) {
+          // a function's chunks come in the order of its stream, so the next one begins where the last one ended
+          Place &p = at[cp.slots[ph.slot_off + s].fl];
+          uint64_t take = std::min(chunk_bytes, p.left);
+          p.left -= take;
+          while (take > 0) {
+            const Xfer &x = cp.xfers[p.x];
+            const uint64_t bytes = x.row_bytes * x.rows, n = std::min(bytes - p.pos, take);
+            if (n == bytes) all_of(x);
+            else if (x.rows == 1) w.run(x.src + p.pos, x.dst + p.pos, n);
+            else w.part(x, (uint32_t)p.pos, (uint32_t)n, &p.shape);
+            take -= n;
+            p.pos += n;
+            if (p.pos == bytes) {
+              p.pos = p.shape = 0;
+              p.x += 1;
+            }
+          }
+        }
+    }
+  }
+  t->n = w.n;
+  t->nshapes = w.nshapes;
+  uint32_t shift = 0, tiles = 0;
+  while (tile >> shift != 1) ++shift;
+  for (uint32_t i = 0; i < t->n; ++i) {
+    t->first[i] = tiles;
+    const uint64_t len = t->len[i];
+    if (t->shape == nullptr || t->shape[i] == 0) {
+      const uint32_t before = (uint32_t)(by_source ? t->at[i].src : t->at[i].dst) & (kPieceLine - 1);
+      tiles += (uint32_t)((len + before + tile - 1) >> shift);
+    } else {
+      const uint32_t per = t->shapes[t->shape[i] - 1].per;
+      tiles += per & kPartsOfRow ? (uint32_t)len * (per & ~kPartsOfRow) : kReciprocals.divide((uint32_t)len - 1, per) + 1;
+    }
+  }
+  t->ntiles = tiles;
+}
+
+PieceRoom job_pieces(const ClassPlan &cp, int cls, uint64_t chunk_bytes) {
+  if (cls != FT_P2P || cp.payload > kCacheResidentBytes) return PieceRoom();
+  const PieceRoom room = piece_room(cp, chunk_bytes);
+  return room.shapes == 0 ? room : PieceRoom();
+}
+
+uint32_t piece_tile(int cls, uint64_t payload) {
+  return payload <= 10u << 20 ? 2048 : payload <= 20u << 20 ? 4096 : 8192;
 }
 
 // Tile of a wave-kernel launch. About 4000 tiles, sixteen wavefronts on every compute unit, each with a tile that it can

@@ -63,6 +63,21 @@ __global__ __launch_bounds__(kInlineBytes / 8) void ft_scratch_put_kernel(uint64
   if (zero != nullptr && i < 2) zero[i] = 0ull;
 }
 
+// n bytes of tables (a multiple of 8) to the array at d, in pieces that travel with small launches, the first of which
+// also clears the counter. On one stream these launches and the kernel behind them run one after another.
+hipError_t put_words(char *d, const char *h, uint64_t n, unsigned long long *counter, hipStream_t stream) {
+  InlineBlob piece;
+  for (uint64_t at = 0; at < n; at += kInlineBytes) {
+    const uint64_t m = n - at < kInlineBytes ? n - at : kInlineBytes;
+    std::memcpy(piece.w, h + at, m);
+    hipLaunchKernelGGL(ft_scratch_put_kernel, dim3(1), dim3(kInlineBytes / 8), 0, stream, reinterpret_cast<uint64_t *>(d + at), piece,
+                       (uint32_t)(m / 8), at == 0 ? counter : nullptr);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 struct StaticClass {
   bool used = false;
   Layout lay;
@@ -70,6 +85,10 @@ struct StaticClass {
   uint64_t ntickets = 0, tile_bytes = 0;
   uint32_t tiles_per_chunk = 0;
   int code = 0;
+  // launched as pieces (ft_pieces.h): the tables at `words`
+  PieceRoom room;
+  PieceTables pieces;
+  std::vector<uint64_t> words;
 };
 
 // What the class's tables would take with the descriptor table that the copy kernel proper needs and the wave kernel does
@@ -108,6 +127,14 @@ extern "C" int ft_submit_static(ft_pool *p, const ft_desc *descs, uint32_t ndesc
     if (cp.nchunks == 0) continue;
     StaticClass &s = sc[c];
     s.used = any = true;
+    s.room = job_pieces(cp, c, chunk_bytes);
+    if (s.room.pieces != 0 && piece_bytes(s.room) <= kStaticTableBytes) {
+      if (tables_with_descriptor_table(cp, c, with_p2p, chunk_bytes) > kStaticClassBytes) return FT_E2BIG;
+      s.words.resize((piece_bytes(s.room) + 7) / 8);
+      s.pieces = piece_places(reinterpret_cast<char *>(s.words.data()), s.room);
+      build_pieces(cp, chunk_bytes, piece_tile(c, cp.payload), c == FT_H2P, &s.pieces);
+      continue;
+    }
     s.code = launch_code(cp, c, chunk_bytes, false, true);  // the classes run one after another
     if (s.code >= kWaveTiles) {
       tile_shape(chunk_bytes, wave_tile(s.code, cp.payload), &s.tile_bytes, &s.tiles_per_chunk);
@@ -134,12 +161,22 @@ extern "C" int ft_submit_static(ft_pool *p, const ft_desc *descs, uint32_t ndesc
   if (rc != FT_OK) return rc;
   hipStream_t stream = static_cast<hipStream_t>(hip_stream);
   std::vector<char> h;
-  InlineBlob piece;
+  InlineBlob piece;  // tables that go with their launch
   for (int c = 0; c < FT_NCLASS; ++c) {
     const StaticClass &s = sc[c];
     if (!s.used) continue;
     const ClassPlan &cp = plan.cls[c];
     char *d = reinterpret_cast<char *>(sd.ptr) + (uint64_t)c * kStaticClassBytes;
+    if (s.pieces.n != 0) {
+      const bool with_launch = pieces_go_along(s.pieces);
+      PieceTables t = s.pieces;
+      if (!with_launch) {
+        FT_HIP(p, put_words(d + 256, reinterpret_cast<const char *>(s.words.data()), s.words.size() * 8, nullptr, stream));
+        t = pieces_at(d + 256, s.room, s.pieces);
+      }
+      FT_HIP(p, launch_pieces(t, c, with_launch, stream, nullptr, nullptr));
+      continue;
+    }
     uint64_t wg = s.code >= kWaveTiles ? wave_workgroups(sd.cu_count, s.code, s.ntickets)
                   : c == FT_P2P ? (uint64_t)sd.cu_count : (with_p2p || c == FT_P2H) ? 32u : 64u;
     if (wg > s.ntickets) wg = s.ntickets;
@@ -158,19 +195,8 @@ extern "C" int ft_submit_static(ft_pool *p, const ft_desc *descs, uint32_t ndesc
     h.assign(s.lay.end, 0);
     ClassTable T{};
     fill_class_table(cp, s.lay, h.data(), d, s.skips, s.ntickets, chunk_bytes, s.tile_bytes, s.tiles_per_chunk, &T);
-    // the tables reach the array in pieces that travel with small launches; the first one also
-    // clears the counter. On one stream these launches and the copy kernel run one after another.
-    const uint64_t first = s.lay.phases, last = s.lay.end;  // the counter line is not uploaded
-    bool zeroed = false;
-    for (uint64_t at = first; at < last || !zeroed; at += kInlineBytes) {
-      const uint64_t n = at < last ? (last - at < kInlineBytes ? last - at : kInlineBytes) : 0;
-      std::memcpy(piece.w, h.data() + at, n);
-      hipLaunchKernelGGL(ft_scratch_put_kernel, dim3(1), dim3(kInlineBytes / 8), 0, stream,
-                         reinterpret_cast<uint64_t *>(d + at), piece, (uint32_t)((n + 7) / 8),
-                         zeroed ? nullptr : T.ticket);
-      FT_HIP(p, hipGetLastError());
-      zeroed = true;
-    }
+    // the counter line is not uploaded
+    FT_HIP(p, put_words(d + s.lay.phases, h.data() + s.lay.phases, s.lay.end - s.lay.phases, T.ticket, stream));
     FT_HIP(p, launch_copy(T, s.code, (uint32_t)wg, stream, nullptr, nullptr));
   }
   return FT_OK;

@@ -1,0 +1,246 @@
+// A class written out as pieces (ft_pieces.h) against the general walk over its tables: the same bytes in the same order,
+// and the kernels' tile and window arithmetic carried out here moves each byte to its place, touches nothing outside the
+// ranges of the descriptors and keeps to the windows that the kernels hold in registers. Random jobs of runs and pitched rows
+// of every width, pitch and alignment, one to thirty functions, chunks of 1 KiB and more.
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <random>
+#include <vector>
+
+#include "../../include/faastube.h"
+#include "../../paper_2411_01830_amd/csrc/ft_pieces.h"
+#include "../../paper_2411_01830_amd/csrc/ft_plan.h"
+
+using namespace ft;
+
+static uint64_t g_seed;
+#define CHECK(x)                                                                                   \
+  do {                                                                                             \
+    if (!(x)) {                                                                                    \
+      std::fprintf(stderr, "%s:%d seed %llu: %s\n", __FILE__, __LINE__, (unsigned long long)g_seed, #x); \
+      std::exit(1);                                                                                \
+    }                                                                                              \
+  } while (0)
+
+static uint64_t n_tiles, n_rows, n_parts, n_merged;
+
+static void move(uint64_t d, uint64_t s, uint32_t n) { std::memcpy(reinterpret_cast<void *>(d), reinterpret_cast<const void *>(s), n); }
+
+static void move_run(uint64_t d, uint64_t s, uint32_t n, bool by_source) {
+  if (n < 16) return move(d, s, n);
+  const RunWindows w = run_windows(by_source ? s : d, n);
+  CHECK(w.count <= 512);
+  for (uint32_t j = 0; j < w.count; ++j) {
+    const uint32_t at = run_window_at(w, j);
+    CHECK(at + 16 <= n);
+    move(d + at, s + at, 16);
+  }
+}
+
+// the tiles of piece i, moved as the kernels do
+static void move_piece(const PieceTables &t, uint32_t i, bool by_source) {
+  const uint32_t ntiles = (i + 1 < t.n ? t.first[i + 1] : t.ntiles) - t.first[i];
+  CHECK(ntiles > 0);
+  uint64_t moved = 0;
+  for (uint32_t no = 0; no < ntiles; ++no, ++n_tiles) {
+    uint64_t d = t.at[i].dst, s = t.at[i].src;
+    uint32_t row, begin, n;
+    if (t.shape == nullptr || t.shape[i] == 0) {
+      const uint64_t side = by_source ? s : d;
+      run_tile(side, t.len[i], t.tile, no, &begin, &n);
+      CHECK(n > 0 && n <= t.tile && begin + n <= t.len[i] && begin == moved);
+      CHECK(no == 0 || (side + begin) % kPieceLine == 0);
+      move_run(d + begin, s + begin, n, by_source);
+      moved += n;
+      continue;
+    }
+    const PieceRows &r = t.shapes[t.shape[i] - 1];
+    const uint32_t per_row = windows_of_row(r.row_bytes);
+    if (!(r.per & kPartsOfRow)) {
+      rows_tile(r, t.len[i], no, &row, &n);
+      CHECK(n > 0 && row == moved && row + n <= t.len[i] && n * per_row <= 512 && n * per_row * 16 <= t.tile);
+      for (uint32_t g = 0; g < n * per_row; ++g) {
+        uint32_t wr, col;
+        row_window_of(r, per_row, g, &wr, &col);
+        CHECK(wr == g / per_row && col + 16 <= r.row_bytes);
+        // distances of 32 bits
+        CHECK((uint64_t)wr * r.src_pitch + col + 16 < 1ull << 32 && (uint64_t)wr * r.dst_pitch + col + 16 < 1ull << 32);
+        move(d + (uint64_t)(row + wr) * r.dst_pitch + col, s + (uint64_t)(row + wr) * r.src_pitch + col, 16);
+      }
+      moved += n;
+      ++n_rows;
+    } else {
+      row_part(r, no, &row, &begin, &n);
+      CHECK(row < t.len[i] && n > 0 && n <= t.tile && begin + n <= r.row_bytes);
+      CHECK((uint64_t)row * r.row_bytes + begin == moved);
+      move_run(d + (uint64_t)row * r.dst_pitch + begin, s + (uint64_t)row * r.src_pitch + begin, n, by_source);
+      moved += n;
+      ++n_parts;
+    }
+  }
+  const PieceRows *r = t.shape != nullptr && t.shape[i] != 0 ? &t.shapes[t.shape[i] - 1] : nullptr;
+  CHECK(moved == (r && (r->per & kPartsOfRow) ? (uint64_t)t.len[i] * r->row_bytes : t.len[i]));
+}
+
+struct Byte {
+  uint64_t src, dst;
+  bool operator==(const Byte &o) const { return src == o.src && dst == o.dst; }
+};
+
+static void bytes_of(std::vector<Byte> &out, const Xfer &x, uint64_t p, uint64_t n) {
+  for (; n > 0; ++p, --n)
+    out.push_back(Byte{x.src + p / x.row_bytes * x.src_pitch + p % x.row_bytes, x.dst + p / x.row_bytes * x.dst_pitch + p % x.row_bytes});
+}
+
+static void job(std::mt19937_64 &r) {
+  auto U = [&](uint64_t a, uint64_t b) { return a + r() % (b - a + 1); };
+  const uint64_t C = U(0, 3) == 0 ? 16 * U(64, 200) : 1024ull << U(0, 7);
+  const uint32_t F = (uint32_t)(U(0, 3) == 0 ? 1 : U(0, 4) == 0 ? U(17, 30) : U(2, 9));
+  const int kind = (int)U(0, 3);  // 0: runs, 1: also rows, 2: rows, 3: runs that touch each other
+  std::vector<uint8_t> src(1 << 20), dst(1 << 20, 0xA5), want;
+  for (size_t i = 0; i < src.size(); ++i) src[i] = (uint8_t)r();
+  uint64_t sa = U(0, 200), da = U(0, 200);
+  ClassPlan cp;
+  for (uint32_t f = 0; f < F; ++f) {
+    Func fn{};
+    fn.desc_off = (uint32_t)cp.xfers.size();
+    fn.func = f;
+    fn.weight = (uint32_t)U(1, 9);
+    const uint32_t nd = (uint32_t)U(1, F == 1 ? 60 : 6);
+    for (uint32_t i = 0; i < nd; ++i) {
+      Xfer x{};
+      x.rows = kind == 2 || (kind == 1 && U(0, 1)) ? U(2, 40) : 1;
+      x.row_bytes = x.rows == 1 ? U(1, U(0, 5) == 0 ? 20000 : 900) : U(16, U(0, 9) == 0 ? 11000 : U(0, 1) ? 40 : 400);
+      x.src_pitch = x.row_bytes + (x.rows > 1 ? U(0, 90) : 0);
+      x.dst_pitch = x.row_bytes + (x.rows > 1 ? U(x.src_pitch == x.row_bytes ? 1 : 0, 90) : 0);
+      const uint64_t es = (x.rows - 1) * x.src_pitch + x.row_bytes, ed = (x.rows - 1) * x.dst_pitch + x.row_bytes;
+      if (sa + es > src.size() || da + ed > dst.size()) break;
+      x.src = reinterpret_cast<uint64_t>(src.data()) + sa;
+      x.dst = reinterpret_cast<uint64_t>(dst.data()) + da;
+      sa += es + (kind == 3 ? 0 : U(0, 33));
+      da += ed + (kind == 3 ? 0 : U(0, 33));
+      x.stream_off = fn.stream_bytes;
+      fn.stream_bytes += x.row_bytes * x.rows;
+      cp.xfers.push_back(x);
+      ++fn.ndesc;
+    }
+    if (fn.ndesc == 0) continue;
+    fn.nchunks = (fn.stream_bytes + C - 1) / C;
+    cp.payload += fn.stream_bytes;
+    cp.funcs.push_back(fn);
+  }
+  CHECK(build_phases(cp.funcs, cp.phases, cp.slots, &cp.nchunks) == FT_OK);
+
+  // the general walk, chunk by chunk
+  std::vector<Byte> order;
+  for (uint64_t rank = 0; rank < cp.nchunks; ++rank) {
+    const ChunkId id = decode_rank(cp.phases.data(), (uint32_t)cp.phases.size(), cp.slots.data(), rank);
+    const Func &fn = cp.funcs[id.fl];
+    uint64_t pos = id.k * C;
+    const uint64_t end = pos + C < fn.stream_bytes ? pos + C : fn.stream_bytes;
+    uint32_t x = find_xfer(cp.xfers.data(), fn.desc_off, fn.desc_off + fn.ndesc - 1, pos);
+    while (pos < end) {
+      const Xfer &X = cp.xfers[x++];
+      const uint64_t q = pos - X.stream_off, left = X.row_bytes * X.rows - q, n = left < end - pos ? left : end - pos;
+      bytes_of(order, X, q, n);
+      pos += n;
+    }
+  }
+  CHECK(order.size() == cp.payload);
+  want = dst;
+  for (const Byte &b : order) want[b.dst - reinterpret_cast<uint64_t>(dst.data())] = *reinterpret_cast<const uint8_t *>(b.src);
+
+  for (int by_source = 0; by_source < 2; ++by_source)
+    for (uint32_t tile : {128u, 2048u, 8192u}) {
+      const PieceRoom room = piece_room(cp, C);
+      if (room.pieces == 0) continue;
+      std::vector<uint32_t> words(piece_bytes(room) / 4);  // no more than that: the sanitizer sees a write beyond
+      PieceTables t = piece_places(reinterpret_cast<char *>(words.data()), room);
+      build_pieces(cp, C, tile, by_source != 0, &t);
+      CHECK(t.n > 0 && t.n <= room.pieces && t.nshapes <= room.shapes && t.tile == tile && t.first[0] == 0);
+      std::vector<Byte> got;
+      std::memset(dst.data(), 0xA5, dst.size());
+      for (uint32_t i = 0; i < t.n; ++i) {
+        Xfer x{};
+        const PieceRows *r = t.shape != nullptr && t.shape[i] != 0 ? &t.shapes[t.shape[i] - 1] : nullptr;
+        x.src = t.at[i].src;
+        x.dst = t.at[i].dst;
+        x.row_bytes = r ? r->row_bytes : t.len[i];
+        x.src_pitch = r ? r->src_pitch : t.len[i];
+        x.dst_pitch = r ? r->dst_pitch : t.len[i];
+        bytes_of(got, x, 0, x.row_bytes * (r ? t.len[i] : 1));
+        move_piece(t, i, by_source != 0);
+      }
+      CHECK(got == order);
+      CHECK(dst == want);
+      n_merged += t.n < cp.xfers.size();
+    }
+}
+
+// A run beyond 2^30 bytes becomes several pieces, and no table entry is exceeded.
+static void long_run() {
+  ClassPlan cp;
+  Func fn{};
+  fn.weight = 1;
+  fn.ndesc = 2;
+  for (uint64_t n : {(5ull << 30) + 77, 3ull << 30}) {
+    Xfer x{};
+    x.src = 0x100000000000ull + fn.stream_bytes;
+    x.dst = 0x200000000005ull + fn.stream_bytes;
+    x.row_bytes = n;
+    x.rows = 1;
+    x.stream_off = fn.stream_bytes;
+    fn.stream_bytes += n;
+    cp.xfers.push_back(x);
+  }
+  fn.nchunks = (fn.stream_bytes + (2 << 20) - 1) / (2 << 20);
+  cp.payload = fn.stream_bytes;
+  cp.funcs.push_back(fn);
+  CHECK(build_phases(cp.funcs, cp.phases, cp.slots, &cp.nchunks) == FT_OK);
+  const PieceRoom room = piece_room(cp, 2 << 20);
+  CHECK(room.pieces >= 9 && room.shapes == 0);
+  std::vector<uint32_t> words(piece_bytes(room) / 4);
+  PieceTables t = piece_places(reinterpret_cast<char *>(words.data()), room);
+  build_pieces(cp, 2 << 20, 4096, false, &t);
+  uint64_t at = 0;
+  for (uint32_t i = 0; i < t.n; ++i) {
+    CHECK(t.at[i].src == cp.xfers[0].src + at && t.at[i].dst == cp.xfers[0].dst + at && t.len[i] <= 1u << 30);
+    at += t.len[i];
+  }
+  CHECK(at == cp.payload && t.n == 9);
+}
+
+// What no list of pieces is made for.
+static void refused() {
+  auto with = [](uint64_t rb, uint64_t rows, uint64_t pitch, uint64_t chunk, uint64_t nchunks) {
+    ClassPlan cp;
+    cp.funcs.resize(2);
+    cp.nchunks = nchunks;
+    Xfer x{};
+    x.row_bytes = rb;
+    x.rows = rows;
+    x.src_pitch = x.dst_pitch = pitch;
+    cp.xfers.push_back(x);
+    return piece_room(cp, chunk).pieces;
+  };
+  CHECK(with(16, 3, 20, 1024, 5) != 0 && with(15, 3, 20, 1024, 5) == 0);
+  CHECK(with(16, 3, 20, 512, 5) == 0);
+  CHECK(with(100, 1, 100, 1024, kMaxPieces - 1) != 0 && with(100, 1, 100, 1024, kMaxPieces) == 0);
+  CHECK(with(16, 3, ((1ull << 32) - 1) / 516, 1024, 5) != 0 && with(16, 3, ((1ull << 32) - 1) / 516 + 1, 1024, 5) == 0);
+}
+
+int main(int argc, char **argv) {
+  const uint64_t first = argc > 1 ? strtoull(argv[1], 0, 10) : 1, count = argc > 2 ? strtoull(argv[2], 0, 10) : 50;
+  refused();
+  long_run();
+  for (g_seed = first; g_seed < first + count; ++g_seed) {
+    std::mt19937_64 r(g_seed);
+    for (int i = 0; i < 6; ++i) job(r);
+  }
+  CHECK(n_rows > 0 && n_parts > 0 && n_merged > 0);
+  std::printf("tiles %llu, of rows %llu, of parts of rows %llu, lists with merged tensors %llu\n", (unsigned long long)n_tiles,
+              (unsigned long long)n_rows, (unsigned long long)n_parts, (unsigned long long)n_merged);
+  std::printf("done %llu..%llu\n", (unsigned long long)first, (unsigned long long)(first + count - 1));
+  return 0;
+}

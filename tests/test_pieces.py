@@ -1,0 +1,150 @@
+"""Jobs that are launched as a list of pieces: pool->pool jobs of at most 128 MiB whose schedule nobody may ask for. Bit-exact
+against the oracle at the sizes where tiles, windows, the forms of the tables and the rule change."""
+import numpy as np
+import pytest
+
+from oracle import OracleEngine
+from workloads import make_descs, FT_POOL
+from workloads import format as fmt
+from test_host_logic import _host_sanitizer_run
+
+KiB, MiB = 1 << 10, 1 << 20
+
+
+def test_pieces_are_the_general_order_written_out(tmp_path):
+    """tests/host/piece_tables.cpp: the pieces hold the bytes of the general walk in its order, and the kernels' arithmetic moves each
+    byte once and nothing else."""
+    _host_sanitizer_run(tmp_path, "piece_tables", ["ft_plan.cpp", "ft_pool.cpp"], ["1", "40"], "done 1..40")
+
+
+def _runs(rng, n, sizes, funcs, odd=True):
+    shift = (lambda: int(rng.integers(0, 16))) if odd else (lambda: 0)
+    return [(int(sizes[i % len(sizes)] if len(sizes) >= n else rng.choice(sizes)), 1, 0, 0, i % funcs, shift(), shift()) for i in range(n)]
+
+
+def _tile(payload):
+    return 2 * KiB if payload <= 10 * MiB else 4 * KiB if payload <= 20 * MiB else 8 * KiB
+
+
+# name, pieces(rng): (row bytes, rows, src pitch, dst pitch, function, src shift, dst shift), weights, chunk, travels with its launch
+# (None: not launched as pieces)
+CASES = [
+    ("one byte", lambda g: [(1, 1, 0, 0, 0, 3, 9)], [1], 2 * MiB, True),
+    *[(f"one tensor of {n}", lambda g, n=n: [(n, 1, 0, 0, 0, 7, 4)], [1], 2 * MiB, True) for n in (15, 16, 17, 2047, 2048, 2049, 65536, 10 * MiB, 10 * MiB + 1, 20 * MiB + 1)],
+    ("one aligned tensor", lambda g: [(64 * KiB, 1, 0, 0, 0, 0, 0)], [1], 2 * MiB, True),
+    *[(f"{n} tensors of one function", lambda g, n=n: _runs(g, n, [1, 15, 16, 17, 127, 128, 129, 2047, 2048, 2049, 5000], 1), [1], 4 * KiB, n <= 128)
+      for n in (2, 16, 17, 48, 49, 63, 64, 65, 128, 129)],
+    ("lengths around a tile, aligned", lambda g: _runs(g, 60, [2032, 2048, 2064, 4096, 8176, 8192, 8208], 2, odd=False), [1, 1], 64 * KiB, True),
+    ("chunks of 1 KiB", lambda g: _runs(g, 900, [1, 15, 16, 17, 1023, 1024, 1025], 3), [1, 2, 5], 1024, False),
+    ("30 functions", lambda g: _runs(g, 70, [64, 5000, 9000], 30), list(range(1, 31)), 16 * KiB, True),
+    ("1025 functions", lambda g: _runs(g, 2100, [64, 5000, 9000], 1025), [1] * 1025, 4 * KiB, False),
+    ("5000 tensors", lambda g: _runs(g, 5000, [1, 60, 300, 700], 1), [1], 256 * KiB, False),
+    ("tiles of 4 KiB", lambda g: _runs(g, 30, [400 * KiB, 500 * KiB + 5], 3), [1, 2, 4], 256 * KiB, True),
+    ("tiles of 8 KiB", lambda g: _runs(g, 30, [800 * KiB + 3, 1000 * KiB], 3), [1, 2, 4], 128 * KiB, False),
+    ("over 20 MiB", lambda g: _runs(g, 30, [800 * KiB + 3, 1000 * KiB], 3), [1, 2, 4], 2 * MiB, True),
+    ("chunks under 1 KiB", lambda g: _runs(g, 200, [300, 5000], 2), [1, 3], 512, None),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", CASES, ids=[c[0] for c in CASES])
+def test_pieces_match_the_oracle(case):
+    import torch
+    from paper_2411_01830_amd import binding, harness
+    name, pieces, weights, chunk, along = case
+    print(f"case pieces: {name}", flush=True)
+    rng = np.random.default_rng(len(name))
+    orc, eng = OracleEngine(), harness.GpuEngine()
+    try:
+        for e in (orc, eng):
+            e.host_arena(1 << 20)
+            e.pool_create(96 * MiB, 4 * KiB)
+        recs = []
+        for rb, rows, sp, dp, f, ss, ds in pieces(rng):
+            es, ed = (rows - 1) * sp + rb, (rows - 1) * dp + rb
+            a, b = orc.slab_alloc(es + 16), orc.slab_alloc(ed + 16)
+            assert eng.slab_alloc(es + 16) == a and eng.slab_alloc(ed + 16) == b
+            fill = rng.integers(0, 256, es + 16, dtype=np.uint8)
+            orc.write_pool(a, fill)
+            eng.write_pool(a, fill)
+            recs.append(dict(func=f, src_space=FT_POOL, dst_space=FT_POOL, src=a + ss, dst=b + ds, row_bytes=rb, rows=rows,
+                             src_pitch=sp if rows > 1 else rb, dst_pitch=dp if rows > 1 else rb))
+        before = torch.cat([t for t, _ in eng.segments]).clone()
+        d = make_descs(recs)
+        jo = orc.submit(d, weights, chunk)
+        orc.wait(jo)
+        payload = sum(r["row_bytes"] * r["rows"] for r in recs)
+
+        def check(what):
+            assert np.array_equal(torch.cat([t for t, _ in eng.segments]).cpu().numpy(), orc.pool_mem), what
+            at = 0
+            for t, _ in eng.segments:
+                t.copy_(before[at:at + t.numel()])
+                at += t.numel()
+            torch.cuda.synchronize()
+
+        for flags in (0, 0, fmt.FT_DETACHED, fmt.FT_TIMING):
+            jg = eng.submit(d, weights, chunk, flags | fmt.FT_VALIDATE)
+            eng.wait(jg)
+            if flags & fmt.FT_TIMING:
+                st = binding.job_stats(eng.pool, jg).cls[2]
+                own = st.tile_bytes == _tile(payload) and st.workgroups == st.tickets
+                if along is None:
+                    assert not own
+                else:
+                    assert own and st.in_launch == (1 if along else 0) and st.device_ms > 0, (st.tile_bytes, st.tickets, st.in_launch)
+                assert eng.job_schedule(jg, 2) == orc.job_schedule(jo, 2)
+                binding.job_release(eng.pool, jg)
+            check(flags)
+        torch.cuda.synchronize()
+        if len(recs) < 600:
+            eng.submit_static(d, weights, chunk, fmt.FT_VALIDATE)
+            torch.cuda.synchronize()
+            check("static")
+    finally:
+        eng.close()
+
+
+@pytest.mark.gpu
+def test_the_largest_job_of_pieces_and_the_next():
+    """128 MiB goes as pieces, 16 bytes more by the copy kernel; a static submit captured into a graph is replayed on new bytes."""
+    import torch
+    from paper_2411_01830_amd import binding, harness
+    print("case the largest job of pieces", flush=True)
+    eng = harness.GpuEngine()
+    try:
+        eng.host_arena(1 << 20)
+        eng.pool_create(320 * MiB, 4 * KiB)
+        mem = eng.segments[0][0]
+        g = torch.Generator("cuda").manual_seed(5)
+        mem.random_(0, 256, generator=g)
+        n = 64 * MiB
+        src, dst = [eng.slab_alloc(n + 4096) for _ in range(2)], [eng.slab_alloc(n + 4096) for _ in range(2)]
+        for more in (0, 16):
+            recs = [dict(func=f, src_space=FT_POOL, dst_space=FT_POOL, src=src[f] + 3 * f, dst=dst[f] + 5 * f, row_bytes=n + more * f) for f in range(2)]
+            want = mem.clone()
+            for r in recs:
+                want[r["dst"]:r["dst"] + r["row_bytes"]] = mem[r["src"]:r["src"] + r["row_bytes"]]
+            jg = eng.submit(make_descs(recs), [1, 2], 2 * MiB, fmt.FT_TIMING)
+            eng.wait(jg)
+            st = binding.job_stats(eng.pool, jg).cls[2]
+            assert (st.tile_bytes, st.workgroups == st.tickets) == ((8 * KiB, True) if more == 0 else (64 * KiB, False))
+            binding.job_release(eng.pool, jg)
+            assert torch.equal(mem, want)
+            mem.random_(0, 256, generator=g)
+        recs = [dict(func=f, src_space=FT_POOL, dst_space=FT_POOL, src=src[f], dst=dst[f] + f, row_bytes=3 * MiB + f) for f in range(2)]
+        d = make_descs(recs)
+        s = torch.cuda.Stream()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            binding.submit_static(eng.pool, d, [1, 2], 256 * KiB, 0, torch.cuda.current_stream().cuda_stream)
+        for _ in range(3):
+            mem.random_(0, 256, generator=g)
+            want = mem.clone()
+            for r in recs:
+                want[r["dst"]:r["dst"] + r["row_bytes"]] = mem[r["src"]:r["src"] + r["row_bytes"]]
+            graph.replay()
+            torch.cuda.synchronize()
+            assert torch.equal(mem, want)
+    finally:
+        eng.close()
