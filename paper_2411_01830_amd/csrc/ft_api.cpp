@@ -764,11 +764,11 @@ int launch_as_pieces(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_byte
     if (plan.cls[c].nchunks > 0) only = only == -1 ? c : -2;
   if (only < 0 || p->tuning[only].workgroups != 0 || p->tuning[only].tile_bytes != 0) return FT_OK;
   const ClassPlan &cp = plan.cls[only];
-  if ((flags & FT_DETACHED) && cp.payload > kWaveTilesBytes) return FT_OK;
+  if ((flags & FT_DETACHED) && cp.payload > (only == FT_P2P ? kWaveTilesBytes : kWaveLinkTilesBytes)) return FT_OK;
   const PieceRoom room = job_pieces(cp, only, chunk_bytes);
   if (room.pieces == 0) return FT_OK;
   const uint64_t bytes = align_up(piece_bytes(room), 256);
-  uint64_t few[448];  // the tables of most jobs that take them along
+  uint64_t few[3 * kRunsAlong];  // the tables of most jobs that take them along
   char *h = reinterpret_cast<char *>(few);
   if (bytes > sizeof(few)) {
     const int rc = get_blob(p, bytes, true, &job->tables);
@@ -784,13 +784,26 @@ int launch_as_pieces(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_byte
     std::memcpy(job->tables.host, few, bytes);
   }
   ClassRun &r = job->run[only];
+  const bool draws = piece_draws(only, t);
+  if (draws) {
+    std::lock_guard<std::mutex> ctx_lock(p->ctx->mu);
+    if (!p->ctx->free_pairs.empty()) {
+      r.counter_pair = (int)p->ctx->free_pairs.back();
+      p->ctx->free_pairs.pop_back();
+    }
+  }
+  if (draws && r.counter_pair < 0) {
+    put_blob(p, job->tables);
+    return FT_OK;
+  }
   r.used = true;
   r.pieces = true;
   r.tile_bytes = t.tile;
   r.table.ntickets = t.ntiles;
-  r.workgroups = t.ntiles;
+  r.workgroups = piece_workgroups(only, t.ntiles);
   r.on_user_stream = with_launch;
   r.stream = user;
+  unsigned long long *counter = draws ? p->ctx->counter_pairs + 2 * r.counter_pair : p->ctx->idle_counter;
   const bool timing = (flags & FT_TIMING) != 0;
   int rc = get_event(p, false, &r.ev_done);
   if (rc == FT_OK && timing) rc = get_event(p, true, &r.ev_begin);
@@ -802,7 +815,7 @@ int launch_as_pieces(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_byte
     t = pieces_at(job->tables.dev, room, t);
   }
   // without timing the done event is bound to the dispatch itself, which spares a marker behind it
-  if (e == hipSuccess) e = launch_pieces(t, only, with_launch, user, r.ev_begin, timing ? r.ev_end : r.ev_done);
+  if (e == hipSuccess) e = launch_pieces(t, only, with_launch, counter, user, r.ev_begin, timing ? r.ev_end : r.ev_done);
   if (e == hipSuccess && timing) e = hipEventRecord(r.ev_done, user);
   if (e != hipSuccess) {
     p->hip_error = std::string("launch of pieces: ") + hipGetErrorString(e);

@@ -70,16 +70,24 @@ __device__ __forceinline__ void st_off(uint64_t base, uint32_t off, V v) {
   __builtin_nontemporal_store(v, reinterpret_cast<V FT_GLOBAL *>(reinterpret_cast<char FT_GLOBAL *>(base) + off));
 }
 
-// Up to R * 64 windows of a contiguous run, from window `blk` on. All loads before the first store; no load is
+// Up to R * 64 windows of a contiguous run, from window `blk` on, loaded and stored. All loads before the first store; no load is
 // predicated (a lane past the last window repeats it and stores nothing).
 template <int NT, uint32_t R>
-__device__ __forceinline__ void wave_run_pass(uint64_t d, uint64_t s, const RunWindows &w, uint32_t blk, uint32_t lane) {
-  u32x4_any v[R];
+__device__ __forceinline__ void wave_run_loads(u32x4_any (&v)[R], uint64_t s, const RunWindows &w, uint32_t blk, uint32_t lane) {
 #pragma unroll
   for (uint32_t i = 0; i < R; ++i) v[i] = ld_off<u32x4_any, NT>(s, run_window_at(w, blk + lane + i * 64));
+}
+template <int NT, uint32_t R>
+__device__ __forceinline__ void wave_run_stores(const u32x4_any (&v)[R], uint64_t d, const RunWindows &w, uint32_t blk, uint32_t lane) {
 #pragma unroll
   for (uint32_t i = 0; i < R; ++i)
     if (blk + lane + i * 64 < w.count) st_off<u32x4_any, NT>(d, run_window_at(w, blk + lane + i * 64), v[i]);
+}
+template <int NT, uint32_t R>
+__device__ __forceinline__ void wave_run_pass(uint64_t d, uint64_t s, const RunWindows &w, uint32_t blk, uint32_t lane) {
+  u32x4_any v[R];
+  wave_run_loads<NT, R>(v, s, w, blk, lane);
+  wave_run_stores<NT, R>(v, d, w, blk, lane);
 }
 
 }  // namespace ft

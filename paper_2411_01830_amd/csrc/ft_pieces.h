@@ -33,16 +33,19 @@ struct PieceTables {
   uint32_t *shape = nullptr;    // 0: a run; else 1 + index into the shapes. Null: all are runs
   PieceRows *shapes = nullptr;  // null if shape is
   uint32_t n = 0, nshapes = 0, ntiles = 0;
-  uint32_t tile = 0;  // bytes of a tile, a power of two
+  uint32_t tile = 0;              // bytes of a tile, a power of two
+  uint64_t src0 = 0, dst0 = 0;    // the lowest addresses of the sides,
+  bool close = false;             // from which every side is less than 2^32 bytes away
 };
 
 // A run's tiles begin and end where this many bytes of the side that is dearer to cut (the destination; host memory where
 // that is the source) do, so that no line is written by two wavefronts: shared lines cost a misaligned job 4-12 %.
 constexpr uint32_t kPieceLine = 128;
-// Pieces of one job at most, and at most as many as travel with a launch, with as many shapes: kernel arguments end at 4 KiB.
-constexpr uint32_t kMaxPieces = 16384;
+// Pieces of one job at most, and at most as many as travel with a launch, with as many shapes: kernel arguments end at 4 KiB, and
+// hold sides as 32-bit distances from the lowest.
+constexpr uint32_t kMaxPieces = 16384, kRunsAlong = 240;
 inline bool pieces_go_along(const PieceTables &t) {
-  return t.shape == nullptr ? t.n <= 128 : (t.n <= 64 && t.nshapes <= 64) || (t.n <= 144 && t.nshapes <= 8);
+  return t.close && (t.shape == nullptr ? t.n <= kRunsAlong : (t.n <= 64 && t.nshapes <= 64) || (t.n <= 200 && t.nshapes <= 16));
 }
 
 // An upper bound for the pieces of a class and their shapes, 0 if it is no job for them: too many, or rows that the kernels do not
@@ -56,12 +59,14 @@ uint64_t piece_bytes(const PieceRoom &room);
 PieceTables piece_places(char *base, const PieceRoom &room);
 // t's tables where a copy of them lies.
 inline PieceTables pieces_at(char *base, const PieceRoom &room, const PieceTables &t) {
-  PieceTables c = piece_places(base, room);
-  c.n = t.n;
-  c.nshapes = t.nshapes;
-  c.ntiles = t.ntiles;
-  c.tile = t.tile;
-  return c;
+  const PieceTables c = piece_places(base, room);
+  PieceTables moved = t;
+  moved.at = c.at;
+  moved.first = c.first;
+  moved.len = c.len;
+  moved.shape = c.shape;
+  moved.shapes = c.shapes;
+  return moved;
 }
 // Fills t with the pieces of a class in its order, cut into tiles of `tile` bytes, a power of two from kPieceLine to 8 KiB.
 // by_source: the source's lines are the ones not to be cut.
@@ -70,6 +75,9 @@ void build_pieces(const ClassPlan &cp, uint64_t chunk_bytes, uint32_t tile, bool
 // The room for a class of a job that is to be launched as pieces, none if it is not; and the tile.
 PieceRoom job_pieces(const ClassPlan &cp, int cls, uint64_t chunk_bytes);
 uint32_t piece_tile(int cls, uint64_t payload);
+// Workgroups, of one wavefront each, of a launch of that many tiles; and whether they draw tiles beyond their first from a counter.
+uint32_t piece_workgroups(int cls, uint32_t ntiles);
+inline bool piece_draws(int cls, const PieceTables &t) { return t.n > 1 && piece_workgroups(cls, t.ntiles) < t.ntiles; }
 
 // ---- what a tile covers: the arithmetic of the kernels, so that it can be checked without a GPU
 

@@ -21,9 +21,12 @@ namespace ft {
 // 5.8 us with 3 KiB, so there are several sizes.
 template <uint32_t CAP, uint32_t SHAPES>
 struct PieceArgs {
-  static constexpr bool kRows = SHAPES != 0;
+  static constexpr bool kRows = SHAPES != 0, kOne = CAP == 1;
   uint32_t n, tile;
-  PieceSides at[CAP];
+  uint64_t src0, dst0;
+  struct {
+    uint32_t src, dst;  // bytes from src0 and dst0
+  } at[CAP];
   uint32_t first[CAP], len[CAP];
   uint32_t shape[kRows ? (CAP + 3) / 4 : 1];  // a byte each
   PieceRows shapes[kRows ? SHAPES : 1];
@@ -31,7 +34,7 @@ struct PieceArgs {
 // and tables in device memory
 template <bool ROWS>
 struct PieceRefs {
-  static constexpr bool kRows = ROWS;
+  static constexpr bool kRows = ROWS, kOne = false;
   uint32_t n, tile;
   const PieceSides *at;
   const uint32_t *first, *len, *shape;
@@ -88,8 +91,8 @@ __device__ __forceinline__ Piece find_piece(const PieceArgs<CAP, SHAPES> &, uint
     x = uniform32(before - 1);
   }
   Piece p;
-  p.src = a.at[x].src;
-  p.dst = a.at[x].dst;
+  p.src = a.src0 + a.at[x].src;
+  p.dst = a.dst0 + a.at[x].dst;
   p.len = a.len[x];
   p.tile_no = t - a.first[x];
   p.tile = a.tile;
@@ -178,22 +181,85 @@ __global__ __launch_bounds__(64) void ft_piece_kernel(A args) {
   move_tile<NT, A::kRows>(find_piece(args, blockIdx.x, threadIdx.x), threadIdx.x);
 }
 
-namespace {
+// The same over the host link, which has to be full but not crowded: 64 wavefronts with 4 KiB of loads from host memory each, one on
+// a compute unit, or 128 with 4 KiB of stores, and each goes on to further tiles. Time beyond what the link takes for
+// the bytes, us: 4 MiB in 32 tensors from the host 2.5 (the class's own kernel, 64 workgroups of 16 KiB, 9.5), to the host 2.4 (6.5);
+// 128 or 256 wavefronts from the host 5.8, four a workgroup 10, every tile at once 39.
+//
+// A wavefront's first two tiles are given, the others are drawn from the counter, in the order of the pieces (of one piece they are
+// dealt out). A tile costs one draw, so the draws of a launch are as many as its tiles, and who has made the last one sets the
+// counter back. (Where no wavefront has a second tile the answers are not looked at, and the counter may be any.) A tile's loads, the draw
+// in front of them and the search for the next tile's piece are waited for together, and the next tile's loads follow the
+// stores at once.
+struct LinkTiles {
+  unsigned long long *counter;
+  uint32_t ntiles;
+};
 
 template <int NT, class A>
-hipError_t launch(const A &a, uint32_t ntiles, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
-  static_assert(sizeof(A) <= 4096, "kernel arguments end at 4 KiB");
-  hipExtLaunchKernelGGL((ft_piece_kernel<NT, A>), dim3(ntiles), dim3(64), 0, stream, ev_start, ev_stop, 0, a);
+__global__ __launch_bounds__(64) void ft_link_piece_kernel(A args, LinkTiles l) {
+  // (its low half: tiles are numbered in 32 bits, and of a 64-bit answer the compiler would use the unwanted register for an address of
+  // the loads, which then wait for the answer)
+  typedef uint32_t FT_GLOBAL *CounterP;
+  const CounterP counter = reinterpret_cast<CounterP>(reinterpret_cast<uintptr_t>(l.counter));
+  const uint32_t lane = threadIdx.x;
+  uint32_t t = blockIdx.x, next = t + gridDim.x;
+  Piece p = find_piece(args, t, lane);
+  while (t < l.ntiles) {
+    uint32_t begin, n, drawn = 0;
+    run_tile(NT == kFromHost ? p.src : p.dst, p.len, p.tile, p.tile_no, &begin, &n);
+    const uint64_t d = p.dst + begin, s = p.src + begin;
+    const RunWindows w = run_windows(NT == kFromHost ? s : d, n < 16 ? 16u : n);  // at most 256: tiles are of 4 KiB at most
+    if (!A::kOne && lane == 0) drawn = __hip_atomic_fetch_add(counter, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    u32x4_any v[4];
+    if (n >= 16) wave_run_loads<NT, 4>(v, s, w, 0, lane);
+    else if (lane < n) st_off<uint8_t, 0>(d, lane, ld_off<uint8_t, 0>(s, lane));
+    p = find_piece(args, next < l.ntiles ? next : t, lane);  // (found again where there is no next)
+    t = next;
+    next += gridDim.x;
+    if (!A::kOne) {
+      drawn = uniform32(drawn);
+      if (drawn == l.ntiles - 1 && lane == 0) __hip_atomic_store(counter, 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      next = 2 * gridDim.x + drawn;
+    }
+    if (n >= 16) wave_run_stores<NT, 4>(v, d, w, 0, lane);
+  }
+}
+
+namespace {
+
+struct Launch {
+  int cls;
+  uint32_t ntiles;
+  unsigned long long *counter;
+  hipStream_t stream;
+  hipEvent_t ev_start, ev_stop;
+};
+
+template <class A>
+hipError_t launch(const A &a, const Launch &l) {
+  static_assert(sizeof(A) + sizeof(LinkTiles) <= 4096, "kernel arguments end at 4 KiB");
+  const dim3 grid(piece_workgroups(l.cls, l.ntiles)), block(64);
+  const LinkTiles tiles = {l.counter, l.ntiles};
+  if (l.cls == 2) hipExtLaunchKernelGGL((ft_piece_kernel<0, A>), grid, block, 0, l.stream, l.ev_start, l.ev_stop, 0, a);
+  else if constexpr (A::kRows) return hipErrorInvalidValue;
+  else if (l.cls == 0) hipExtLaunchKernelGGL((ft_link_piece_kernel<kFromHost, A>), grid, block, 0, l.stream, l.ev_start, l.ev_stop, 0, a, tiles);
+  else hipExtLaunchKernelGGL((ft_link_piece_kernel<kToHost, A>), grid, block, 0, l.stream, l.ev_start, l.ev_stop, 0, a, tiles);
   return hipGetLastError();
 }
 
 template <uint32_t CAP, uint32_t SHAPES>
-hipError_t launch_along(const PieceTables &t, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
+hipError_t launch_along(const PieceTables &t, const Launch &l) {
   if (t.n > CAP || t.nshapes > SHAPES) return hipErrorInvalidValue;
   PieceArgs<CAP, SHAPES> a;
   a.n = t.n;
   a.tile = t.tile;
-  std::memcpy(static_cast<void *>(a.at), t.at, t.n * sizeof(PieceSides));
+  a.src0 = t.src0;
+  a.dst0 = t.dst0;
+  for (uint32_t i = 0; i < t.n; ++i) {
+    a.at[i].src = (uint32_t)(t.at[i].src - t.src0);
+    a.at[i].dst = (uint32_t)(t.at[i].dst - t.dst0);
+  }
   std::memcpy(a.first, t.first, t.n * sizeof(uint32_t));
   std::memcpy(a.len, t.len, t.n * sizeof(uint32_t));
   if (SHAPES != 0) {
@@ -201,30 +267,32 @@ hipError_t launch_along(const PieceTables &t, hipStream_t stream, hipEvent_t ev_
     for (uint32_t i = 0; i < t.n; ++i) shape[i] = (uint8_t)t.shape[i];
     std::memcpy(static_cast<void *>(a.shapes), t.shapes, t.nshapes * sizeof(PieceRows));
   }
-  return launch<0>(a, t.ntiles, stream, ev_start, ev_stop);
+  return launch(a, l);
 }
 
 template <bool ROWS>
-hipError_t launch_from_memory(const PieceTables &t, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
-  const PieceRefs<ROWS> r = {t.n, t.tile, t.at, t.first, t.len, t.shape, t.shapes};
-  return launch<0>(r, t.ntiles, stream, ev_start, ev_stop);
+hipError_t launch_from_memory(const PieceTables &t, const Launch &l) {
+  return launch(PieceRefs<ROWS>{t.n, t.tile, t.at, t.first, t.len, t.shape, t.shapes}, l);
 }
 
 }  // namespace
 
-hipError_t launch_pieces(const PieceTables &t, int cls, bool on_host, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop) {
-  if (t.n == 0 || t.ntiles == 0 || cls != 2 || (on_host && !pieces_go_along(t))) return hipErrorInvalidValue;
+hipError_t launch_pieces(const PieceTables &t, int cls, bool on_host, unsigned long long *counter, hipStream_t stream, hipEvent_t ev_start,
+                         hipEvent_t ev_stop) {
+  if (t.n == 0 || t.ntiles == 0 || cls < 0 || cls > 2 || (on_host && !pieces_go_along(t)) || (cls != 2 && t.tile > 4096)) return hipErrorInvalidValue;
+  const Launch l = {cls, t.ntiles, counter, stream, ev_start, ev_stop};
   const bool rows = t.shape != nullptr;
-  if (!on_host) return rows ? launch_from_memory<true>(t, stream, ev_start, ev_stop) : launch_from_memory<false>(t, stream, ev_start, ev_stop);
+  if (!on_host) return rows ? launch_from_memory<true>(t, l) : launch_from_memory<false>(t, l);
   if (rows) {
-    if (t.n <= 16 && t.nshapes <= 16) return launch_along<16, 16>(t, stream, ev_start, ev_stop);
-    if (t.n <= 64) return launch_along<64, 64>(t, stream, ev_start, ev_stop);
-    return launch_along<144, 8>(t, stream, ev_start, ev_stop);
+    if (t.n <= 16 && t.nshapes <= 16) return launch_along<16, 16>(t, l);
+    if (t.n <= 64) return launch_along<64, 64>(t, l);
+    return launch_along<200, 16>(t, l);
   }
-  if (t.n == 1) return launch_along<1, 0>(t, stream, ev_start, ev_stop);
-  if (t.n <= 16) return launch_along<16, 0>(t, stream, ev_start, ev_stop);
-  if (t.n <= 48) return launch_along<48, 0>(t, stream, ev_start, ev_stop);
-  return launch_along<128, 0>(t, stream, ev_start, ev_stop);
+  if (t.n == 1) return launch_along<1, 0>(t, l);
+  if (t.n <= 16) return launch_along<16, 0>(t, l);
+  if (t.n <= 48) return launch_along<48, 0>(t, l);
+  if (t.n <= 128) return launch_along<128, 0>(t, l);
+  return launch_along<kRunsAlong, 0>(t, l);
 }
 
 }  // namespace ft

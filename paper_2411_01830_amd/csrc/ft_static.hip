@@ -127,12 +127,12 @@ extern "C" int ft_submit_static(ft_pool *p, const ft_desc *descs, uint32_t ndesc
     if (cp.nchunks == 0) continue;
     StaticClass &s = sc[c];
     s.used = any = true;
-    s.room = job_pieces(cp, c, chunk_bytes);
+    if (c == FT_P2P) s.room = job_pieces(cp, c, chunk_bytes);  // (there is no counter pair here for the host link's)
     if (s.room.pieces != 0 && piece_bytes(s.room) <= kStaticTableBytes) {
       if (tables_with_descriptor_table(cp, c, with_p2p, chunk_bytes) > kStaticClassBytes) return FT_E2BIG;
       s.words.resize((piece_bytes(s.room) + 7) / 8);
       s.pieces = piece_places(reinterpret_cast<char *>(s.words.data()), s.room);
-      build_pieces(cp, chunk_bytes, piece_tile(c, cp.payload), c == FT_H2P, &s.pieces);
+      build_pieces(cp, chunk_bytes, piece_tile(c, cp.payload), false, &s.pieces);
       continue;
     }
     s.code = launch_code(cp, c, chunk_bytes, false, true);  // the classes run one after another
@@ -174,7 +174,7 @@ extern "C" int ft_submit_static(ft_pool *p, const ft_desc *descs, uint32_t ndesc
         FT_HIP(p, put_words(d + 256, reinterpret_cast<const char *>(s.words.data()), s.words.size() * 8, nullptr, stream));
         t = pieces_at(d + 256, s.room, s.pieces);
       }
-      FT_HIP(p, launch_pieces(t, c, with_launch, stream, nullptr, nullptr));
+      FT_HIP(p, launch_pieces(t, c, with_launch, nullptr, stream, nullptr, nullptr));
       continue;
     }
     uint64_t wg = s.code >= kWaveTiles ? wave_workgroups(sd.cu_count, s.code, s.ntickets)

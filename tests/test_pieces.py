@@ -32,15 +32,15 @@ CASES = [
     ("one byte", lambda g: [(1, 1, 0, 0, 0, 3, 9)], [1], 2 * MiB, True),
     *[(f"one tensor of {n}", lambda g, n=n: [(n, 1, 0, 0, 0, 7, 4)], [1], 2 * MiB, True) for n in (15, 16, 17, 2047, 2048, 2049, 65536, 10 * MiB, 10 * MiB + 1, 20 * MiB + 1)],
     ("one aligned tensor", lambda g: [(64 * KiB, 1, 0, 0, 0, 0, 0)], [1], 2 * MiB, True),
-    *[(f"{n} tensors of one function", lambda g, n=n: _runs(g, n, [1, 15, 16, 17, 127, 128, 129, 2047, 2048, 2049, 5000], 1), [1], 4 * KiB, n <= 128)
-      for n in (2, 16, 17, 48, 49, 63, 64, 65, 128, 129)],
+    *[(f"{n} tensors of one function", lambda g, n=n: _runs(g, n, [1, 15, 16, 17, 127, 128, 129, 2047, 2048, 2049, 5000], 1), [1], 4 * KiB, n <= 240)
+      for n in (2, 16, 17, 48, 49, 63, 64, 65, 128, 129, 192, 193, 240, 241)],
     ("lengths around a tile, aligned", lambda g: _runs(g, 60, [2032, 2048, 2064, 4096, 8176, 8192, 8208], 2, odd=False), [1, 1], 64 * KiB, True),
     ("chunks of 1 KiB", lambda g: _runs(g, 900, [1, 15, 16, 17, 1023, 1024, 1025], 3), [1, 2, 5], 1024, False),
     ("30 functions", lambda g: _runs(g, 70, [64, 5000, 9000], 30), list(range(1, 31)), 16 * KiB, True),
     ("1025 functions", lambda g: _runs(g, 2100, [64, 5000, 9000], 1025), [1] * 1025, 4 * KiB, False),
     ("5000 tensors", lambda g: _runs(g, 5000, [1, 60, 300, 700], 1), [1], 256 * KiB, False),
     ("tiles of 4 KiB", lambda g: _runs(g, 30, [400 * KiB, 500 * KiB + 5], 3), [1, 2, 4], 256 * KiB, True),
-    ("tiles of 8 KiB", lambda g: _runs(g, 30, [800 * KiB + 3, 1000 * KiB], 3), [1, 2, 4], 128 * KiB, False),
+    ("tiles of 8 KiB", lambda g: _runs(g, 30, [800 * KiB + 3, 1000 * KiB], 3), [1, 2, 4], 32 * KiB, False),
     ("over 20 MiB", lambda g: _runs(g, 30, [800 * KiB + 3, 1000 * KiB], 3), [1, 2, 4], 2 * MiB, True),
     ("chunks under 1 KiB", lambda g: _runs(g, 200, [300, 5000], 2), [1, 3], 512, None),
 ]
@@ -148,3 +148,94 @@ def test_the_largest_job_of_pieces_and_the_next():
             assert torch.equal(mem, want)
     finally:
         eng.close()
+
+
+# as above; the tiles are 1, 2 or 4 KiB, the workgroups at most 64 from the host and 128 towards it
+LINK_CASES = [
+    ("one byte", lambda g: [(1, 1, 0, 0, 0, 3, 9)], [1], 2 * MiB, True),
+    *[(f"one tensor of {n}", lambda g, n=n: [(n, 1, 0, 0, 0, 7, 4)], [1], 2 * MiB, True) for n in (15, 17, 1025, 32 * KiB, 32 * KiB + 1, 128 * KiB, 128 * KiB + 1, 3 * MiB)],
+    ("one aligned tensor", lambda g: [(3 * MiB + 16, 1, 0, 0, 0, 0, 0)], [1], 2 * MiB, "to the host"),
+    *[(f"{n} tensors of one function", lambda g, n=n: _runs(g, n, [1, 15, 16, 17, 127, 4095, 4096, 4097, 9000], 1), [1], 4 * KiB, n <= 240) for n in (16, 48, 128, 129, 240, 241)],
+    ("65 tiles of three functions", lambda g: [(4096, 1, 0, 0, i % 3, 0, 0) for i in range(65)], [1, 2, 5], 4 * KiB, True),
+    ("129 tiles of three functions", lambda g: [(4096, 1, 0, 0, i % 3, 0, 0) for i in range(129)], [1, 2, 5], 4 * KiB, True),
+    ("260 tiles of three functions", lambda g: [(4096, 1, 0, 0, i % 3, 0, 0) for i in range(260)], [1, 2, 5], 4 * KiB, False),
+    ("tensors around 64 KiB", lambda g: _runs(g, 60, [60000, 65536, 70001, 100], 4), [1, 2, 5, 1], 64 * KiB, None),
+    ("chunks of 1 KiB", lambda g: _runs(g, 900, [1, 15, 16, 17, 1023, 1024, 1025], 3), [1, 2, 5], 1024, False),
+    ("chunks under 1 KiB", lambda g: _runs(g, 100, [300, 5000], 2), [1, 3], 512, "general"),
+]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("case", LINK_CASES, ids=[c[0] for c in LINK_CASES])
+@pytest.mark.parametrize("to_host", [False, True])
+def test_pieces_over_the_host_link(case, to_host):
+    import torch
+    from paper_2411_01830_amd import binding, harness
+    name, pieces, weights, chunk, along = case
+    print(f"case pieces over the host link: {name}, to the host: {to_host}", flush=True)
+    rng = np.random.default_rng(len(name) + to_host)
+    orc, eng = OracleEngine(), harness.GpuEngine()
+    cls = 1 if to_host else 0
+    try:
+        host = 8 * MiB
+        for e in (orc, eng):
+            e.host_arena(host)
+            e.pool_create(16 * MiB, 4 * KiB)
+        data = rng.integers(0, 256, host, dtype=np.uint8)
+        if not to_host:
+            orc.write_host(0, data)
+            eng.write_host(0, data)
+        recs, at = [], 0
+        for rb, rows, sp, dp, f, ss, ds in pieces(rng):
+            a = orc.slab_alloc(rb + 16)
+            assert eng.slab_alloc(rb + 16) == a
+            if to_host:
+                orc.write_pool(a, data[at:at + rb + 16])
+                eng.write_pool(a, data[at:at + rb + 16])
+            src, dst = (a + ss, at + ds) if to_host else (at + ss, a + ds)
+            recs.append(dict(func=f, src_space=1 if to_host else 0, dst_space=0 if to_host else 1, src=src, dst=dst, row_bytes=rb))
+            at += rb + 32
+            assert at < host
+        pool_before, host_before = torch.cat([t for t, _ in eng.segments]).clone(), eng.host_np.copy()
+        d = make_descs(recs)
+        jo = orc.submit(d, weights, chunk)
+        orc.wait(jo)
+        payload = sum(r["row_bytes"] for r in recs)
+        for flags in (0, 0, fmt.FT_DETACHED, fmt.FT_TIMING, fmt.FT_TIMING):     # a counter has to be back at zero for the next launch
+            jg = eng.submit(d, weights, chunk, flags | fmt.FT_VALIDATE)
+            eng.wait(jg)
+            if flags & fmt.FT_TIMING:
+                st = binding.job_stats(eng.pool, jg).cls[cls]
+                own = st.tile_bytes == (1024 if payload <= 32 * KiB else 2048 if payload <= 128 * KiB else 4096) and st.workgroups == min(st.tickets, 128 if to_host else 64)
+                assert own == (along != "general" and (to_host or along != "to the host")), (st.tile_bytes, st.workgroups, st.tickets)
+                assert along not in (True, False) or st.in_launch == (1 if along else 0)
+                assert eng.job_schedule(jg, cls) == orc.job_schedule(jo, cls)
+                binding.job_release(eng.pool, jg)
+            assert np.array_equal(torch.cat([t for t, _ in eng.segments]).cpu().numpy(), orc.pool_mem), flags
+            assert np.array_equal(eng.host_np[:len(orc.host_mem)], orc.host_mem), flags
+            at = 0
+            for t, _ in eng.segments:
+                t.copy_(pool_before[at:at + t.numel()])
+                at += t.numel()
+            torch.cuda.synchronize()
+            eng.host_np[:] = host_before
+    finally:
+        eng.close()
+
+
+def test_inline_assembly_stores_of_the_piece_kernels_leave_no_hazard(tmp_path):
+    """As for the other kernels: two wait states behind each store that is written through to the host, its address in vector registers."""
+    import os
+    import re
+    import subprocess
+    from paper_2411_01830_amd import build
+    out = tmp_path / "pieces.s"
+    subprocess.run([build.hipcc(), "-x", "hip", *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, "ft_pieces.hip"), "-o", str(out)],
+                   check=True, capture_output=True)
+    lines = [re.sub(r"\s+", " ", l.split("//")[0]).strip() for l in open(out)]
+    stores = [i for i, l in enumerate(lines) if l.startswith("global_store_dwordx4") and l.endswith(" sc1")]
+    kernels = [l for l in lines if re.match(r"_ZN2ft20ft_link_piece_kernelILi2E\S*:", l)]
+    assert len(kernels) >= 6 and len(stores) >= 4 * len(kernels)
+    for i in stores:
+        assert re.fullmatch(r"global_store_dwordx4 v\[\d+:\d+\], [va]\[\d+:\d+\], off sc1", lines[i]), lines[i]
+        assert lines[i + 1] == "s_nop 1", lines[i:i + 2]
