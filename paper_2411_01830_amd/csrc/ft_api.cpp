@@ -287,29 +287,17 @@ int run_dma(ft_pool *p, const ClassPlan &cp, uint64_t C, int cls, hipStream_t st
   return FT_OK;
 }
 
-void retire(ft_pool *p, Job *job) {
-  SlabPool::Place near = p->slabs.begin();
-  for (size_t i = 0; i < job->allocs.size(); ++i) {
-    Allocation *al = p->slabs.at(job->allocs[i], &near);
-    // (the allocation may have been returned in stream order meanwhile and its offset handed out again)
-    if (al && al->serial == job->alloc_serials[i] && al->busy > 0) al->busy -= 1;
-  }
+void retire(Job *job) {
+  for (const Held &h : job->allocs)
+    // (the allocation may have been returned in stream order meanwhile and its record handed out again)
+    if (h.al->serial == h.serial && h.al->busy > 0) h.al->busy -= 1;
   job->allocs.clear();
-  job->alloc_serials.clear();
 }
 
 // The allocations a job refers to stay busy until it has been waited for.
-void hold_allocations(ft_pool *p, Job *job, const std::vector<uint64_t> &allocs) {
-  job->allocs = allocs;
-  job->alloc_serials.assign(allocs.size(), 0);
-  SlabPool::Place near = p->slabs.begin();
-  for (size_t i = 0; i < allocs.size(); ++i) {
-    Allocation *al = p->slabs.at(allocs[i], &near);
-    if (al) {
-      al->busy += 1;
-      job->alloc_serials[i] = al->serial;
-    }
-  }
+void hold_allocations(Job *job, std::vector<Held> &&allocs) {
+  job->allocs = std::move(allocs);
+  for (const Held &h : job->allocs) h.al->busy += 1;
 }
 
 uint32_t slab_busy(ft_pool *p, uint64_t off) {
@@ -374,7 +362,7 @@ int wait_locked(ft_pool *p, Job *job) {
     }
   }
   job->waited = true;
-  retire(p, job);
+  retire(job);
   return FT_OK;
 }
 
@@ -875,7 +863,7 @@ int ft_pool_destroy(ft_pool *p) {
       Job *job = kv.second.get();
       if (job->open) {
         if (open_wait(p, job->open, job->id) != FT_OK) rc = FT_EHIP;
-        retire(p, job);
+        retire(job);
       } else if (!job->waited) {
         if (wait_locked(p, job) != FT_OK) rc = FT_EHIP;
         else finish_staging(p, job);
@@ -980,7 +968,7 @@ int ft_submit_transfers(ft_pool *p, const ft_desc *descs, uint32_t ndesc, const 
   }
 
   for (int c = 0; c < FT_NCLASS; ++c) job->run[c].plan = std::move(plan.cls[c]);
-  hold_allocations(p, job.get(), plan.allocs);
+  hold_allocations(job.get(), std::move(plan.allocs));
   p->next_job += 1;
   *job_out = job->id;
   job->host_submit_us =
@@ -1019,7 +1007,7 @@ int ft_submit_merge(ft_pool *p, ft_job_t open_id, const ft_desc *descs, uint32_t
     rc = open_merge(p, open_job, job.get(), plan, weights, static_cast<hipStream_t>(hip_stream));
     if (rc != FT_OK) return rc;
   }
-  hold_allocations(p, job.get(), plan.allocs);
+  hold_allocations(job.get(), std::move(plan.allocs));
   p->next_job += 1;
   *job_out = job->id;
   job->host_submit_us =
@@ -1113,7 +1101,7 @@ int ft_wait(ft_pool *p, ft_job_t id) {
     lock.unlock();
     rc = open_wait(p, st, id);
     lock.lock();
-    retire(p, job);  // also after a failure: nothing of the job is in flight any more
+    retire(job);  // also after a failure: nothing of the job is in flight any more
   } else {
     hipEvent_t done[FT_NCLASS];
     for (int c = 0; c < FT_NCLASS; ++c) done[c] = job->run[c].used ? job->run[c].ev_done : nullptr;

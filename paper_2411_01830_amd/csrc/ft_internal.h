@@ -67,8 +67,7 @@ struct Job {
   ClassRun run[FT_NCLASS];
   Blob tables;
   std::unique_ptr<InlineBlob> inline_tables;  // a small job's tables, passed with the launch instead
-  std::vector<uint64_t> allocs;         // offsets of the pool allocations the job refers to,
-  std::vector<uint64_t> alloc_serials;  // and which allocation at that offset it was
+  std::vector<Held> allocs;  // the pool allocations the job refers to
   uint64_t chunk_bytes = 0;
   uint32_t nfunc = 0;    // functions the job was submitted with
   double host_submit_us = 0;

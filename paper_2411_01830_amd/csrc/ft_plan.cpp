@@ -660,6 +660,20 @@ int plan_submit(SlabPool &pool, const std::vector<HostWindow> &windows, const ft
   for (uint32_t f = 0; f < nfunc; ++f)
     if (weights[f] == 0) return FT_EINVAL;
   if (chunk_bytes == 0 || chunk_bytes % 16 != 0) return FT_EINVAL;
+  // how many descriptors each function has in each class says where each one goes, so that it is resolved into its place;
+  // caller's function -> index into the class's table, up to 16 functions without an allocation
+  auto class_of = [](const ft_desc &d) {
+    return d.src_space != FT_POOL ? FT_H2P : (d.dst_space != FT_POOL ? FT_P2H : FT_P2P);
+  };
+  uint32_t small[FT_NCLASS][16];
+  std::vector<uint32_t> large;
+  uint32_t *fn_of[FT_NCLASS] = {small[0], small[1], small[2]};
+  if (nfunc > 16) {
+    large.resize((uint64_t)FT_NCLASS * nfunc);
+    for (int c = 0; c < FT_NCLASS; ++c) fn_of[c] = large.data() + (uint64_t)c * nfunc;
+  } else {
+    for (int c = 0; c < FT_NCLASS; ++c) std::fill(fn_of[c], fn_of[c] + nfunc, 0u);
+  }
   for (uint32_t i = 0; i < ndesc; ++i) {
     const ft_desc &d = descs[i];
     if (d.func >= nfunc || d.flags != 0) return FT_EINVAL;
@@ -667,36 +681,14 @@ int plan_submit(SlabPool &pool, const std::vector<HostWindow> &windows, const ft
     if (d.src_space != FT_POOL && d.dst_space != FT_POOL) return FT_EINVAL;  // host to host
     if (d.row_bytes == 0 || d.rows == 0) return FT_EINVAL;
     if (d.rows > 1 && (d.src_pitch < d.row_bytes || d.dst_pitch < d.row_bytes)) return FT_EINVAL;
+    fn_of[class_of(d)][d.func] += 1;
   }
 
-  // ---- split by class, per-function streams in submission order: how many descriptors each function has in each class
-  // says where each one goes, so that it is resolved into its place
-  auto class_of = [](const ft_desc &d) {
-    return d.src_space != FT_POOL ? FT_H2P : (d.dst_space != FT_POOL ? FT_P2H : FT_P2P);
-  };
-  uint32_t in_class[FT_NCLASS] = {0, 0, 0};
-  for (uint32_t i = 0; i < ndesc; ++i) in_class[class_of(descs[i])] += 1;
-  // Caller's function -> index into the class's table; up to 16 functions without an allocation.
-  uint32_t small[FT_NCLASS][16];
-  std::vector<uint32_t> large[FT_NCLASS];
-  uint32_t *fn_of[FT_NCLASS];
+  // ---- split by class, per-function streams in submission order
   for (int c = 0; c < FT_NCLASS; ++c) {
     ClassPlan &cp = out->cls[c];
     cp = ClassPlan();
-    if (in_class[c] == 0) continue;  // a class without traffic costs no allocation (passing one tensor: two of three)
-    uint32_t *count = small[c];
-    if (nfunc > 16) {
-      large[c].resize(nfunc);
-      count = large[c].data();
-    }
-    std::fill(count, count + nfunc, 0u);
-    fn_of[c] = count;
-    if (in_class[c] == ndesc) {
-      for (uint32_t i = 0; i < ndesc; ++i) count[descs[i].func] += 1;
-    } else {
-      for (uint32_t i = 0; i < ndesc; ++i)
-        if (class_of(descs[i]) == c) count[descs[i].func] += 1;
-    }
+    uint32_t *count = fn_of[c];
     uint32_t off = 0;
     for (uint32_t f = 0; f < nfunc; ++f) {
       if (count[f] == 0) continue;
@@ -714,22 +706,20 @@ int plan_submit(SlabPool &pool, const std::vector<HostWindow> &windows, const ft
       count[f] = (uint32_t)cp.funcs.size();  // from here on: its place in the table
       cp.funcs.push_back(fn);
     }
-    cp.xfers.resize(off);
+    cp.xfers.resize(off);  // (a class without traffic costs no allocation)
   }
   bool stream_overflow = false;
 
   // ---- pass 2: ranges; resolve both sides to device-visible addresses
   std::vector<const Xfer *> resolved(flags & FT_VALIDATE ? ndesc : 0);  // for pass 3: descriptor i, resolved
-  std::vector<uint64_t> used[2];
+  out->allocs.clear();
+  out->allocs.reserve(std::min(2 * ndesc, 64u));
   SlabPool::Place near[2] = {pool.begin(), pool.begin()};
-  // The allocations met last, most recent first: descriptors of one submit mostly name the
-  // same few (the crops of a frame, the packed buffer of a consumer), and a hit spares the
-  // search of the allocation map, the search of the segment list and an entry in `used`.
-  struct Recent {
-    uint64_t lo = 1, hi = 0;  // offsets of the allocation, [lo, hi)
-    uint64_t dev = 0;         // device address of its first byte
-  };
-  Recent recent[4];
+  // The allocation that each side met last, and the four met before: descriptors of one submit mostly name the same few (the
+  // crops of a frame, the packed buffer of a consumer), and a hit spares the search of the pool's index and a reference of its own.
+  static const SlabPool::Entry kNone = {1, 0, 0, nullptr};
+  const SlabPool::Entry *last[2] = {&kNone, &kNone}, *recent[4] = {&kNone, &kNone, &kNone, &kNone};
+  uint32_t oldest = 0;
   for (uint32_t i = 0; i < ndesc; ++i) {
     const ft_desc &d = descs[i];
     const int c = class_of(d);
@@ -753,28 +743,24 @@ int plan_submit(SlabPool &pool, const std::vector<HostWindow> &windows, const ft
       if (add_overflow(off, ext, &end)) return FT_ERANGE;
       uint64_t addr;
       if (space == FT_POOL) {
-        int hit = -1;
-        for (int k = 0; k < 4; ++k)
-          if (off >= recent[k].lo && off < recent[k].hi && ext <= recent[k].hi - off) {
-            hit = k;
-            break;
+        const SlabPool::Entry *e = last[side];
+        const auto inside = [off, ext](const SlabPool::Entry *a) { return SlabPool::holds(*a, off) && ext <= a->end - off; };
+        if (!inside(e)) {
+          SlabPool::Place behind = near[side];
+          const SlabPool::Entry *before = nullptr;
+          e = pool.step(&behind);
+          if (e != nullptr && inside(e)) {  // tensor after tensor
+            near[side] = behind;
+          } else {
+            for (const SlabPool::Entry *r : recent) before = inside(r) ? r : before;
+            recent[oldest++ % 4] = last[side];
+            e = before != nullptr ? before : pool.find(off, ext, &near[side]);
+            if (e == nullptr) return FT_ERANGE;
           }
-        if (hit < 0) {
-          uint64_t start;
-          const Allocation *al = pool.owner(off, ext, &start, &near[side]);
-          if (al == nullptr) return FT_ERANGE;
-          used[side].push_back(start);
-          Recent r;
-          r.lo = start;
-          r.hi = start + al->nslabs * pool.slab_bytes();
-          r.dev = reinterpret_cast<uint64_t>(pool.ptr(start));  // an allocation lies in one segment
-          recent[3] = recent[2];
-          recent[2] = recent[1];
-          recent[1] = recent[0];
-          recent[0] = r;
-          hit = 0;
+          if (before == nullptr) out->allocs.push_back(Held{e->al, e->al->serial});
+          last[side] = e;
         }
-        addr = recent[hit].dev + (off - recent[hit].lo);
+        addr = e->dev + (off - e->start);
       } else if (space == FT_PAGEABLE) {
         // read or written by the library's own threads: only memory the caller has vouched for
         bool inside = false;
@@ -855,17 +841,6 @@ int plan_submit(SlabPool &pool, const std::vector<HostWindow> &windows, const ft
     }
   }
 
-  // the allocations in ascending order, each once; usually either side names them in that order already
-  for (int side = 0; side < 2; ++side)
-    if (!std::is_sorted(used[side].begin(), used[side].end())) std::sort(used[side].begin(), used[side].end());
-  if (used[0].empty() || used[1].empty() || used[0].back() <= used[1].front()) {
-    out->allocs.swap(used[0]);
-    out->allocs.insert(out->allocs.end(), used[1].begin(), used[1].end());
-  } else {
-    out->allocs.resize(used[0].size() + used[1].size());
-    std::merge(used[0].begin(), used[0].end(), used[1].begin(), used[1].end(), out->allocs.begin());
-  }
-  out->allocs.erase(std::unique(out->allocs.begin(), out->allocs.end()), out->allocs.end());
   if (stream_overflow) return FT_ERANGE;
   for (ClassPlan &cp : out->cls) {
     for (Func &fn : cp.funcs) {

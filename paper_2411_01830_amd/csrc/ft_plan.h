@@ -30,7 +30,7 @@ struct ClassPlan {
 
 struct SubmitPlan {
   ClassPlan cls[FT_NCLASS];
-  std::vector<uint64_t> allocs;  // start offsets of the pool allocations referred to (unique)
+  std::vector<Held> allocs;  // the pool allocations referred to (some may be there more than once)
   bool has_pageable = false;     // some source or destination is pageable host memory: needs the staging ring
 };
 

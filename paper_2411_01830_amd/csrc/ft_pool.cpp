@@ -1,5 +1,6 @@
 #include "ft_pool.h"
 
+#include <algorithm>
 #include <cstddef>
 
 #include "../../include/faastube.h"
@@ -44,7 +45,8 @@ int SlabPool::drop_last_segment(void **base_out, uint64_t *bytes_out) {
 
 uint64_t SlabPool::live_bytes() const {
   uint64_t n = 0;
-  for (const auto &kv : allocs_) n += kv.second.nslabs;
+  for (const auto &b : blocks_)
+    for (uint32_t i = 0; i < b->n; ++i) n += b->e[i].al->nslabs;
   return n * slab_;
 }
 
@@ -68,11 +70,16 @@ int SlabPool::alloc(uint64_t nbytes, uint64_t *off_out) {
     uint64_t start = it->first, len = it->second;
     free_runs_.erase(it);
     if (len > need) free_runs_[start + need] = len - need;
-    Allocation a;
-    a.nslabs = need;
-    a.busy = 0;
-    a.serial = next_serial_++;
-    allocs_[start * slab_] = a;
+    if (free_records_.empty()) {
+      records_.emplace_back();
+      free_records_.push_back(&records_.back());
+    }
+    Allocation *a = free_records_.back();
+    free_records_.pop_back();
+    a->nslabs = need;
+    a->busy = 0;
+    a->serial = next_serial_++;
+    insert(Entry{start * slab_, (start + need) * slab_, reinterpret_cast<uint64_t>(ptr(start * slab_)), a});
     *off_out = start * slab_;
     return FT_OK;
   }
@@ -80,11 +87,14 @@ int SlabPool::alloc(uint64_t nbytes, uint64_t *off_out) {
 }
 
 int SlabPool::free(uint64_t off, bool ordered) {
-  auto it = allocs_.find(off);
-  if (it == allocs_.end()) return FT_EINVAL;
-  if (it->second.busy != 0 && !ordered) return FT_EBUSY;
-  uint64_t start = off / slab_, len = it->second.nslabs;
-  allocs_.erase(it);
+  Place at;
+  if (!last_at_or_before(off, &at) || entry(at)->start != off) return FT_EINVAL;
+  Allocation *al = entry(at)->al;
+  if (al->busy != 0 && !ordered) return FT_EBUSY;
+  uint64_t start = off / slab_, len = al->nslabs;
+  erase(at);
+  al->serial = 0;
+  free_records_.push_back(al);
   const Segment *seg = segment_of_slab(start);
   // merge with the free neighbours that lie in the same segment
   auto next = free_runs_.find(start + len);
@@ -104,43 +114,71 @@ int SlabPool::free(uint64_t off, bool ordered) {
   return FT_OK;
 }
 
+// The last allocation that starts at or before `off`.
+bool SlabPool::last_at_or_before(uint64_t off, Place *p) const {
+  uint32_t lo = 0, hi = (uint32_t)blocks_.size();  // blocks that start at or before off
+  while (lo < hi) {
+    const uint32_t mid = (lo + hi) / 2;
+    if (blocks_[mid]->e[0].start <= off) lo = mid + 1; else hi = mid;
+  }
+  if (lo == 0) return false;
+  const Block &b = *blocks_[lo - 1];
+  uint32_t i = 1, n = b.n;
+  while (i < n) {
+    const uint32_t mid = (i + n) / 2;
+    if (b.e[mid].start <= off) i = mid + 1; else n = mid;
+  }
+  p->block = lo - 1;
+  p->pos = i - 1;
+  return true;
+}
+
+void SlabPool::insert(const Entry &e) {
+  Place at;
+  if (last_at_or_before(e.start, &at)) at.pos += 1;  // else: in front of the first
+  else if (blocks_.empty()) blocks_.push_back(std::make_unique<Block>());
+  Block *b = blocks_[at.block].get();
+  if (b->n == kBlock) {
+    // A full block is halved; where allocations come in ascending order the new one is begun with the newcomer alone.
+    auto next = std::make_unique<Block>();
+    const uint32_t keep = at.pos == kBlock ? kBlock : kBlock / 2;
+    next->n = kBlock - keep;
+    std::copy(b->e + keep, b->e + kBlock, next->e);
+    b->n = keep;
+    Block *n = next.get();
+    blocks_.insert(blocks_.begin() + at.block + 1, std::move(next));
+    if (at.pos > keep || keep == kBlock) {
+      at.pos -= keep;
+      b = n;
+    }
+  }
+  std::copy_backward(b->e + at.pos, b->e + b->n, b->e + b->n + 1);
+  b->e[at.pos] = e;
+  b->n += 1;
+}
+
+void SlabPool::erase(const Place &p) {
+  Block &b = *blocks_[p.block];
+  std::copy(b.e + p.pos + 1, b.e + b.n, b.e + p.pos);
+  b.n -= 1;
+  if (b.n == 0) blocks_.erase(blocks_.begin() + p.block);
+}
+
 Allocation *SlabPool::at(uint64_t start) {
-  auto it = allocs_.find(start);
-  return it == allocs_.end() ? nullptr : &it->second;
+  Place p;
+  return last_at_or_before(start, &p) && entry(p)->start == start ? entry(p)->al : nullptr;
 }
 
 Allocation *SlabPool::owner(uint64_t off, uint64_t extent, uint64_t *start_out, Place *near) {
-  Place it = *near;
-  for (int step = 0; step < 2 && it != allocs_.end(); ++step, ++it) {
-    const uint64_t a0 = it->first, a1 = a0 + it->second.nslabs * slab_;
-    if (off < a0) break;
-    if (off >= a1) continue;
-    if (extent > a1 - off) return nullptr;  // allocations do not overlap: no other one holds `off`
-    *near = it;
-    if (start_out) *start_out = a0;
-    return &it->second;
-  }
-  it = allocs_.upper_bound(off);
-  if (it == allocs_.begin()) return nullptr;
-  --it;
-  const uint64_t a0 = it->first, a1 = a0 + it->second.nslabs * slab_;
-  if (off >= a1 || extent > a1 - off) return nullptr;
-  *near = it;
-  if (start_out) *start_out = a0;
-  return &it->second;
+  const Entry *e = find(off, extent, near);
+  if (e == nullptr) return nullptr;
+  if (start_out) *start_out = e->start;
+  return e->al;
 }
 
 Allocation *SlabPool::at(uint64_t start, Place *near) {
-  Place it = *near;
-  for (int step = 0; step < 2 && it != allocs_.end(); ++step, ++it)
-    if (it->first == start) {
-      *near = it;
-      return &it->second;
-    }
-  it = allocs_.find(start);
-  if (it == allocs_.end()) return nullptr;
-  *near = it;
-  return &it->second;
+  const Entry *e = find(start, 1, near);
+  return e != nullptr && e->start == start ? e->al : nullptr;
 }
 
 void *SlabPool::ptr(uint64_t off) const {
