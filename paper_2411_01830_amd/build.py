@@ -62,7 +62,7 @@ def check_registers(remarks):
     for k, v in regs.items():
         m = re.search(r"ft_copy_kernelILb1ELi(\d)E", k)
         if m:
-            per_class[int(m.group(1))] = up8(v)
+            per_class[int(m.group(1))] = max(per_class.get(int(m.group(1)), 0), up8(v))
         elif "ft_wave_kernel" in k:
             per_class[3] = max(per_class.get(3, 0), up8(v))
     if sorted(per_class) != [0, 1, 2, 3]:

@@ -580,29 +580,30 @@ int launch_with_the_launch(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chun
   return FT_OK;
 }
 
-// Tables of `bytes` bytes (a multiple of 256) from a blob's pinned twin to its device buffer, on `stream`: by the runtime's
-// copy, or as one tensor by the wave kernel, whose loads are then those for host memory (the rule stands with table_fetch_code).
+// Tables from a blob's pinned twin to its device buffer, as one piece from the host: at most 64 tiles of 4 KiB in
+// flight, which is what fills the link (table_fetch_code tells why no more). Below 16 KiB, too, that is no slower than the runtime's
+// copy, which is a launch as well.
+hipError_t upload_pieces(const Blob &b, uint64_t bytes, hipStream_t stream) {
+  PieceSides sides = {reinterpret_cast<uint64_t>(b.host), reinterpret_cast<uint64_t>(b.dev)};
+  uint32_t first = 0, len = (uint32_t)bytes;
+  PieceTables t;
+  t.at = &sides;
+  t.first = &first;
+  t.len = &len;
+  t.n = 1;
+  t.tile = piece_tile(FT_H2P, bytes);
+  t.ntiles = (len + ((uint32_t)sides.src & (kPieceLine - 1)) + t.tile - 1) / t.tile;
+  t.src0 = sides.src;
+  t.dst0 = sides.dst;
+  t.close = true;
+  return launch_pieces(t, FT_H2P, true, nullptr, stream, nullptr, nullptr);
+}
+
+// The same of a job by the general tables, on `stream`: by the runtime's copy, or (the rule stands with table_fetch_code) as above.
 // dma: a job by the copy engines, which does not wait for a free compute unit.
-hipError_t upload_tables(const Blob &b, uint64_t bytes, bool dma, unsigned long long *idle_counter, hipStream_t stream) {
-  const int code = dma ? 0 : table_fetch_code(bytes);
-  if (code == 0) return hipMemcpyAsync(b.dev, b.host, bytes, hipMemcpyHostToDevice, stream);
-  InlineBlob tables;
-  Xfer x{};
-  x.src = reinterpret_cast<uint64_t>(b.host);
-  x.dst = reinterpret_cast<uint64_t>(b.dev);
-  x.row_bytes = bytes;
-  x.rows = 1;
-  x.src_pitch = x.dst_pitch = bytes;
-  std::memcpy(tables.w, &x, sizeof(x));
-  ClassTable T{};
-  T.ticket = idle_counter;
-  T.ntickets = T.nchunks = (bytes + kTableTile - 1) / kTableTile;
-  T.chunk_bytes = T.tile_bytes = kTableTile;
-  T.tiles_per_chunk = 1;
-  T.desc_per = 1;
-  T.inline_tables = 1;
-  T.single = 1;
-  return launch_copy(T, code, (uint32_t)wave_workgroups(0, code, T.ntickets), stream, nullptr, nullptr, &tables);
+hipError_t upload_tables(const Blob &b, uint64_t bytes, bool dma, hipStream_t stream) {
+  if (dma || table_fetch_code(bytes) == 0 || launch_pieces == nullptr) return hipMemcpyAsync(b.dev, b.host, bytes, hipMemcpyHostToDevice, stream);
+  return upload_pieces(b, bytes, stream);
 }
 
 // The general way: the tables of all classes in one blob, copied to the device on the caller's
@@ -657,7 +658,7 @@ int launch_with_uploaded_tables(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t
     put_event(p, false, fork);
     return fail_submit(p, job, FT_EHIP);
   };
-  hipError_t e = upload_tables(job->tables, total, dma, p->ctx->idle_counter, user);
+  hipError_t e = upload_tables(job->tables, total, dma, user);
   if (e != hipSuccess) return hip_fail(e, "upload of the tables");
   if (!straight) {
     e = hipEventRecord(fork, user);
@@ -799,7 +800,7 @@ int launch_as_pieces(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_byte
   if (rc != FT_OK) return fail_submit(p, job, rc);
   hipError_t e = hipSuccess;
   if (!with_launch) {
-    e = upload_tables(job->tables, bytes, false, p->ctx->idle_counter, user);
+    e = upload_pieces(job->tables, bytes, user);
     t = pieces_at(job->tables.dev, room, t);
   }
   // without timing the done event is bound to the dispatch itself, which spares a marker behind it

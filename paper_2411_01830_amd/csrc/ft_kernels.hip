@@ -903,8 +903,12 @@ __device__ __forceinline__ void reset_counters_after_last(const ClassTable &T) {
 //
 // CLS (the link class) selects the block size of the copy routines and gives each class's kernel a
 // name of its own, so that profiles keep host-link launches and pool->pool launches apart.
-template <bool NT, int CLS>
-__global__ __launch_bounds__(kThreads, (CLS == 2 ? 1 : 2)) void ft_copy_kernel(ClassTable T, InlineBlob) {
+//
+// B: the tables that travel with the launch, or NoTables where they are in device memory: a launch call writes its arguments to device
+// memory and costs the host 1.8 us more with 3 KiB of them.
+struct NoTables {};
+template <bool NT, int CLS, class B>
+__global__ __launch_bounds__(kThreads, (CLS == 2 ? 1 : 2)) void ft_copy_kernel(ClassTable T, B) {
   constexpr uint32_t U = UnrollOf<CLS>::value;
   constexpr int MODE = !NT ? 0 : CLS == 1 ? kToHost : kStream;
   __shared__ WorkSlot s_work[2];
@@ -1269,8 +1273,8 @@ __device__ __forceinline__ uint32_t next_ticket(WaveBatches &B) {
 // 31.1 -> 31.8, 1.6 GB 588 -> 531; 64 misaligned tensors 105 MB 32 -> 34; host->pool 20 000 pieces of 4000 bytes 1574 -> 1466 (a
 // wavefront that the link serves late keeps none of the others' work).
 constexpr int kOneTicket = 0, kDealt = 1, kShared = 2;
-template <int NT, int FORM>
-__global__ __launch_bounds__(FORM == kOneTicket ? 64 : 1024) __attribute__((amdgpu_waves_per_eu(7))) void ft_wave_kernel(ClassTable T, InlineBlob) {
+template <int NT, int FORM, class B>
+__global__ __launch_bounds__(FORM == kOneTicket ? 64 : 1024) __attribute__((amdgpu_waves_per_eu(7))) void ft_wave_kernel(ClassTable T, B) {
   const ConstTables CT = const_tables(T);
   const uint32_t lane = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));  // (keeps no register for threadIdx.x)
   uint64_t t_begin = 0;
@@ -1367,46 +1371,49 @@ __global__ __launch_bounds__(kThreads) void ft_plain_fill_kernel(u32x4 *dst, uin
     __builtin_nontemporal_store(v, dst + i);
 }
 
-// What a launch passes as tables when the job's own are in device memory.
-static const InlineBlob kNoTables{};
-
-template <int NT>
+template <int NT, class B>
 static hipError_t launch_wave(int form, dim3 grid, uint32_t waves, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop,
-                              const ClassTable &T, const InlineBlob &B) {
+                              const ClassTable &T, const B &b) {
   const dim3 block(waves * 64);
   if (form == kOneTicket) {
     if constexpr (NT == kStream) return hipErrorInvalidValue;  // a job that streams is never that small
-    else hipExtLaunchKernelGGL((ft_wave_kernel<NT, kOneTicket>), grid, block, 0, stream, ev_start, ev_stop, 0, T, B);
-  } else if (form == kDealt) hipExtLaunchKernelGGL((ft_wave_kernel<NT, kDealt>), grid, block, 0, stream, ev_start, ev_stop, 0, T, B);
-  else hipExtLaunchKernelGGL((ft_wave_kernel<NT, kShared>), grid, block, 0, stream, ev_start, ev_stop, 0, T, B);
+    else hipExtLaunchKernelGGL((ft_wave_kernel<NT, kOneTicket, B>), grid, block, 0, stream, ev_start, ev_stop, 0, T, b);
+  } else if (form == kDealt) hipExtLaunchKernelGGL((ft_wave_kernel<NT, kDealt, B>), grid, block, 0, stream, ev_start, ev_stop, 0, T, b);
+  else hipExtLaunchKernelGGL((ft_wave_kernel<NT, kShared, B>), grid, block, 0, stream, ev_start, ev_stop, 0, T, b);
   return hipGetLastError();
 }
 
-hipError_t launch_copy(const ClassTable &T, int link_class, uint32_t workgroups, hipStream_t stream,
-                       hipEvent_t ev_start, hipEvent_t ev_stop, const InlineBlob *tables) {
-  if (workgroups == 0 || (T.inline_tables != 0) != (tables != nullptr)) return hipErrorInvalidValue;
+template <class B>
+static hipError_t launch_with(const ClassTable &T, int link_class, uint32_t workgroups, hipStream_t stream, hipEvent_t ev_start, hipEvent_t ev_stop,
+                              const B &b) {
   const dim3 grid(workgroups), block(kThreads);
-  const InlineBlob &B = tables ? *tables : kNoTables;
   // with events, they are bound to this dispatch: they read the kernel's own start and end
   if (link_class >= kWaveTiles) {
     const uint32_t waves = wave_code_threads(link_class) / 64;
     const int form = (link_class & 15) == kWaveTiles ? kOneTicket : !T.single && wave_shares(workgroups * waves, T.ntickets) ? kShared : kDealt;
     if (waves == 0 || (form == kOneTicket && workgroups != T.ntickets)) return hipErrorInvalidValue;
     switch (link_class & ~15) {
-      case 0: return launch_wave<0>(form, grid, waves, stream, ev_start, ev_stop, T, B);
-      case kWaveStreams: return launch_wave<kStream>(form, grid, waves, stream, ev_start, ev_stop, T, B);
-      case kWaveFromHost: return launch_wave<kFromHost>(form, grid, waves, stream, ev_start, ev_stop, T, B);
-      case kWaveToHost: return launch_wave<kToHost>(form, grid, waves, stream, ev_start, ev_stop, T, B);
+      case 0: return launch_wave<0>(form, grid, waves, stream, ev_start, ev_stop, T, b);
+      case kWaveStreams: return launch_wave<kStream>(form, grid, waves, stream, ev_start, ev_stop, T, b);
+      case kWaveFromHost: return launch_wave<kFromHost>(form, grid, waves, stream, ev_start, ev_stop, T, b);
+      case kWaveToHost: return launch_wave<kToHost>(form, grid, waves, stream, ev_start, ev_stop, T, b);
       default: return hipErrorInvalidValue;
     }
   }
   switch (link_class) {
-    case 0: hipExtLaunchKernelGGL((ft_copy_kernel<true, 0>), grid, block, 0, stream, ev_start, ev_stop, 0, T, B); break;
-    case 1: hipExtLaunchKernelGGL((ft_copy_kernel<true, 1>), grid, block, 0, stream, ev_start, ev_stop, 0, T, B); break;
-    case 2: hipExtLaunchKernelGGL((ft_copy_kernel<true, 2>), grid, block, 0, stream, ev_start, ev_stop, 0, T, B); break;
+    case 0: hipExtLaunchKernelGGL((ft_copy_kernel<true, 0, B>), grid, block, 0, stream, ev_start, ev_stop, 0, T, b); break;
+    case 1: hipExtLaunchKernelGGL((ft_copy_kernel<true, 1, B>), grid, block, 0, stream, ev_start, ev_stop, 0, T, b); break;
+    case 2: hipExtLaunchKernelGGL((ft_copy_kernel<true, 2, B>), grid, block, 0, stream, ev_start, ev_stop, 0, T, b); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
+}
+
+hipError_t launch_copy(const ClassTable &T, int link_class, uint32_t workgroups, hipStream_t stream,
+                       hipEvent_t ev_start, hipEvent_t ev_stop, const InlineBlob *tables) {
+  if (workgroups == 0 || (T.inline_tables != 0) != (tables != nullptr)) return hipErrorInvalidValue;
+  if (tables != nullptr) return launch_with(T, link_class, workgroups, stream, ev_start, ev_stop, *tables);
+  return launch_with(T, link_class, workgroups, stream, ev_start, ev_stop, NoTables{});
 }
 
 hipError_t launch_decode(const ClassTable &T, uint32_t *func_out, uint32_t *chunk_out, uint64_t cap,
@@ -1415,7 +1422,7 @@ hipError_t launch_decode(const ClassTable &T, uint32_t *func_out, uint32_t *chun
   uint64_t n = T.nchunks < cap ? T.nchunks : cap;
   if (n == 0) return hipSuccess;
   uint32_t blocks = (uint32_t)((n + 255) / 256);
-  hipLaunchKernelGGL(ft_decode_kernel, dim3(blocks), dim3(256), 0, stream, T, tables ? *tables : kNoTables, func_out,
+  hipLaunchKernelGGL(ft_decode_kernel, dim3(blocks), dim3(256), 0, stream, T, tables ? *tables : InlineBlob{}, func_out,
                      chunk_out, cap);
   return hipGetLastError();
 }
