@@ -757,20 +757,18 @@ int launch_as_pieces(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_byte
   const PieceRoom room = job_pieces(cp, only, chunk_bytes);
   if (room.pieces == 0) return FT_OK;
   const uint64_t bytes = align_up(piece_bytes(room), 256);
-  uint64_t few[3 * kRunsAlong];  // the tables of most jobs that take them along
-  char *h = reinterpret_cast<char *>(few);
-  if (bytes > sizeof(few)) {
-    const int rc = get_blob(p, bytes, true, &job->tables);
-    if (rc != FT_OK) return rc;
-    h = job->tables.host;
-  }
+  // (written out in ordinary memory: the blob's lines were last read by the device, and every store to one of them would wait for it)
+  if (p->piece_words.size() * 8 < bytes) p->piece_words.resize(bytes / 8);
+  char *h = reinterpret_cast<char *>(p->piece_words.data());
   PieceTables t = piece_places(h, room);
-  build_pieces(cp, chunk_bytes, piece_tile(only, cp.payload), only == FT_H2P, &t);
+  if (!build_pieces(cp, chunk_bytes, piece_tile(only, cp.payload), only == FT_H2P, &t)) return FT_OK;
   const bool with_launch = pieces_go_along(t);
-  if (!with_launch && job->tables.dev == nullptr) {
+  // Where they do not, the general tables may (few tensors in many chunks); and rows are then better off with them (job_pieces).
+  if (!with_launch && (t.shape != nullptr || inline_layout_of(cp).end <= kInlineBytes)) return FT_OK;
+  if (!with_launch) {
     const int rc = get_blob(p, bytes, true, &job->tables);
     if (rc != FT_OK) return rc;
-    std::memcpy(job->tables.host, few, bytes);
+    std::memcpy(job->tables.host, h, bytes);
   }
   ClassRun &r = job->run[only];
   const bool draws = piece_draws(only, t);

@@ -140,6 +140,7 @@ struct ft_pool {
   ft::DeviceCtx *ctx;
   std::unordered_map<uint64_t, std::unique_ptr<ft::Job>> jobs;
   uint64_t next_job = 1;
+  std::vector<uint64_t> piece_words;  // where a submit writes its pieces out; at most kMaxPieces of them, 393 KB
   ft::Tuning tuning[FT_NCLASS];
   uint32_t batch_chunks = 5;  // chunks per triggered batch of an open job (Sec. 6.1 default)
   uint32_t batch_depth = 3;   // batches an open job keeps queued ahead of the device

@@ -16,26 +16,30 @@ struct PieceSides {
   uint64_t src, dst;
 };
 
-// What pieces of whole rows have beyond their sides (those of their first row). Most jobs have few shapes.
+// What pieces of rows have beyond their sides (those of column 0 of their first row). Most jobs have few shapes.
 struct PieceRows {
   uint32_t row_bytes, src_pitch, dst_pitch;
   uint32_t per;    // rows of a tile; or kPartsOfRow | tiles of a row
   uint32_t magic;  // g / windows of a row = mulhi(g, magic) or one less; 0: a row is one window (ft_windows.h)
   uint32_t part;   // bytes of a tile that is part of a row
 };
-constexpr uint32_t kPartsOfRow = 1u << 31;
+constexpr uint32_t kPartsOfRow = 1u << 31;  // a piece of such rows has whole ones only
+struct PieceEdges {
+  uint32_t from, to;
+};
 
-// The tables as arrays of `n` entries each, in host or in device memory.
+// The tables as arrays of `n` entries each, in host or (of runs) in device memory.
 struct PieceTables {
   PieceSides *at = nullptr;
   uint32_t *first = nullptr;    // the piece's first tile; ascending, no piece is without one
   uint32_t *len = nullptr;      // bytes of a run, rows of a piece of rows
   uint32_t *shape = nullptr;    // 0: a run; else 1 + index into the shapes. Null: all are runs
-  PieceRows *shapes = nullptr;  // null if shape is
+  PieceRows *shapes = nullptr;  // null if shape is, as is
+  PieceEdges *edges = nullptr;  // of rows (of a run nothing): the first row from column `from`, the last one up to `to`
   uint32_t n = 0, nshapes = 0, ntiles = 0;
   uint32_t tile = 0;              // bytes of a tile, a power of two
   uint64_t src0 = 0, dst0 = 0;    // the lowest addresses of the sides,
-  bool close = false;             // from which every side is less than 2^32 bytes away
+  bool close = false;             // from which every side is less than 2^32 bytes away (said of few pieces only)
 };
 
 // A run's tiles begin and end where this many bytes of the side that is dearer to cut (the destination; host memory where
@@ -43,17 +47,16 @@ struct PieceTables {
 constexpr uint32_t kPieceLine = 128;
 // Pieces of one job at most, and at most as many as travel with a launch, with as many shapes: kernel arguments end at 4 KiB, and
 // hold sides as 32-bit distances from the lowest.
-constexpr uint32_t kMaxPieces = 16384, kRunsAlong = 240;
+constexpr uint32_t kMaxPieces = 16384, kRunsAlong = 240, kRowsAlong = 140;
 inline bool pieces_go_along(const PieceTables &t) {
-  return t.close && (t.shape == nullptr ? t.n <= kRunsAlong : (t.n <= 64 && t.nshapes <= 64) || (t.n <= 200 && t.nshapes <= 16));
+  return t.close && (t.shape == nullptr ? t.n <= kRunsAlong : (t.n <= 64 && t.nshapes <= 64) || (t.n <= kRowsAlong && t.nshapes <= 16));
 }
 
-// An upper bound for the pieces of a class and their shapes, 0 if it is no job for them: too many, or rows that the kernels do not
-// cover (under 16 bytes, or so far apart that a tile's distances leave 32 bits).
+// An upper bound for the pieces of a class and their shapes, 0 if it is no job for them.
 struct PieceRoom {
   uint64_t pieces = 0, shapes = 0;
 };
-PieceRoom piece_room(const ClassPlan &cp, uint64_t chunk_bytes);
+PieceRoom piece_room(const ClassPlan &cp, uint64_t chunk_bytes, uint32_t tile);
 // Bytes of the tables, and their places from `base` (a multiple of 8) on.
 uint64_t piece_bytes(const PieceRoom &room);
 PieceTables piece_places(char *base, const PieceRoom &room);
@@ -66,11 +69,13 @@ inline PieceTables pieces_at(char *base, const PieceRoom &room, const PieceTable
   moved.len = c.len;
   moved.shape = c.shape;
   moved.shapes = c.shapes;
+  moved.edges = c.edges;
   return moved;
 }
-// Fills t with the pieces of a class in its order, cut into tiles of `tile` bytes, a power of two from kPieceLine to 8 KiB.
-// by_source: the source's lines are the ones not to be cut.
-void build_pieces(const ClassPlan &cp, uint64_t chunk_bytes, uint32_t tile, bool by_source, PieceTables *t);
+// Fills t with the pieces of a class in its order, cut into tiles of `tile` bytes, a power of two from 1 to 8 KiB.
+// by_source: the source's lines are the ones not to be cut. False: there are rows that the kernels do not cover (under 16
+// bytes, or so far apart that a tile's distances leave 32 bits).
+bool build_pieces(const ClassPlan &cp, uint64_t chunk_bytes, uint32_t tile, bool by_source, PieceTables *t);
 
 // The room for a class of a job that is to be launched as pieces, none if it is not; and the tile.
 PieceRoom job_pieces(const ClassPlan &cp, int cls, uint64_t chunk_bytes);
@@ -89,20 +94,25 @@ FT_HD void run_tile(uint64_t side, uint32_t len, uint32_t tile, uint32_t no, uin
   *n = (e < len ? e : len) - b;
 }
 
-// A tile of whole rows: rows [r0, r0 + n) of a piece of len rows.
-FT_HD void rows_tile(const PieceRows &r, uint32_t len, uint32_t no, uint32_t *r0, uint32_t *n) {
-  *r0 = no * r.per;
-  *n = len - *r0 < r.per ? len - *r0 : r.per;
-}
-
-// Window g of a tile of whole rows, per_row of which a row has: 16 bytes of row *row from column *col on.
+// Windows of a row, and the windows (ft_windows.h) of a tile of rows: those of rows [*r0, ...) of a piece of len rows.
 FT_HD uint32_t windows_of_row(uint32_t row_bytes) { return row_bytes / 16 + (row_bytes % 16 != 0 ? 1u : 0u); }
-FT_HD void row_window_of(const PieceRows &r, uint32_t per_row, uint32_t g, uint32_t *row, uint32_t *col) {
-  uint32_t q = r.magic == 0 ? g : mul_hi32(g, r.magic);
-  q -= q * per_row > g ? 1u : 0u;
-  const uint32_t c = (g - q * per_row) * 16, last = r.row_bytes - 16;
-  *row = q;
-  *col = c < last ? c : last;
+FT_HD RowWindows rows_tile(const PieceRows &r, uint32_t len, const PieceEdges &e, uint32_t no, uint32_t *r0) {
+  const uint32_t begin = no * r.per, n = len - begin < r.per ? len - begin : r.per;
+  *r0 = begin;
+  RowWindows w;
+  w.c0 = begin == 0 ? e.from : 0u;
+  w.more = n - 1;
+  w.row_bytes = r.row_bytes;
+  w.last_end = begin + n == len ? e.to : r.row_bytes;
+  w.per_row = windows_of_row(r.row_bytes);
+  w.magic = r.magic;
+  const uint32_t first_len = (n == 1 ? w.last_end : r.row_bytes) - w.c0;
+  w.short_first = first_len < 16 ? first_len : 0u;
+  w.short_last = n != 1 && w.last_end < 16 ? w.last_end : 0u;
+  w.first = w.short_first != 0 ? w.per_row : w.c0 / 16;
+  const uint32_t last = w.last_end < 16 ? w.more * w.per_row : w.more * w.per_row + (w.last_end + 15) / 16;  // one past it
+  w.count = last > w.first ? last - w.first : 0u;
+  return w;
 }
 
 // A tile that is part of a row: n bytes from column *begin of row *row on.

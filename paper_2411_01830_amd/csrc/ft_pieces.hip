@@ -29,16 +29,15 @@ struct PieceArgs {
   } at[CAP];
   uint32_t first[CAP], len[CAP];
   uint32_t shape[kRows ? (CAP + 3) / 4 : 1];  // a byte each
+  PieceEdges edges[kRows ? CAP : 1];
   PieceRows shapes[kRows ? SHAPES : 1];
 };
-// and tables in device memory
-template <bool ROWS>
+// and tables in device memory, of runs
 struct PieceRefs {
-  static constexpr bool kRows = ROWS, kOne = false;
+  static constexpr bool kRows = false, kOne = false;
   uint32_t n, tile;
   const PieceSides *at;
-  const uint32_t *first, *len, *shape;
-  const PieceRows *shapes;
+  const uint32_t *first, *len;
 };
 
 struct Piece {
@@ -46,6 +45,7 @@ struct Piece {
   uint32_t len, tile_no;  // tile within the piece
   uint32_t tile;          // bytes of a tile
   PieceRows rows;         // row_bytes 0: a run
+  PieceEdges edges;
 };
 
 // The last of n ascending entries (the first of which is 0) at or before t.
@@ -96,15 +96,18 @@ __device__ __forceinline__ Piece find_piece(const PieceArgs<CAP, SHAPES> &, uint
   p.len = a.len[x];
   p.tile_no = t - a.first[x];
   p.tile = a.tile;
-  if (SHAPES != 0) p.rows = read_shape(a.shapes, a.shape[x / 4] >> x % 4 * 8 & 255);
+  if (SHAPES != 0) {
+    p.rows = read_shape(a.shapes, a.shape[x / 4] >> x % 4 * 8 & 255);
+    p.edges.from = a.edges[x].from;
+    p.edges.to = a.edges[x].to;
+  }
   return p;
 }
 
 template <class T>
 __device__ __forceinline__ const FT_CONST T *constant(const T *p) { return reinterpret_cast<const FT_CONST T *>(reinterpret_cast<uintptr_t>(p)); }
 
-template <bool ROWS>
-__device__ __forceinline__ Piece find_piece(const PieceRefs<ROWS> &r, uint32_t t, uint32_t lane) {
+__device__ __forceinline__ Piece find_piece(const PieceRefs &r, uint32_t t, uint32_t lane) {
   const uint32_t x = last_at_or_before(constant(r.first), r.n, t, lane);
   Piece p;
   p.src = constant(r.at)[x].src;
@@ -112,7 +115,6 @@ __device__ __forceinline__ Piece find_piece(const PieceRefs<ROWS> &r, uint32_t t
   p.len = constant(r.len)[x];
   p.tile_no = t - constant(r.first)[x];
   p.tile = r.tile;
-  if (ROWS) p.rows = read_shape(constant(r.shapes), constant(r.shape)[x]);
   return p;
 }
 
@@ -130,23 +132,39 @@ __device__ __forceinline__ void move_run(uint64_t d, uint64_t s, uint32_t n, uin
   else wave_run_pass<NT, 8>(d, s, w, 0, lane);
 }
 
-// R * 64 windows of whole rows, `per_row` of which a row has. All loads before the first store; a lane past the last window
-// loads the first one and stores nothing.
+// Up to R * 64 windows of rows. All loads before the first store; a lane past the last window loads the first one and stores nothing.
 template <int NT, uint32_t R>
-__device__ __forceinline__ void move_windows(uint64_t d, uint64_t s, const PieceRows &r, uint32_t per_row, uint32_t count, uint32_t lane) {
+__device__ __forceinline__ void move_windows(uint64_t d, uint64_t s, const PieceRows &r, const RowWindows &w, uint32_t lane) {
   u32x4_any v[R];
   uint32_t to[R];
 #pragma unroll
   for (uint32_t i = 0; i < R; ++i) {
     const uint32_t g = lane + i * 64;
-    uint32_t row, col;
-    row_window_of(r, per_row, g < count ? g : 0u, &row, &col);
-    v[i] = ld_off<u32x4_any, NT>(s, row * r.src_pitch + col);
-    to[i] = row * r.dst_pitch + col;
+    const RowCursor c = row_window<16>(w, g < w.count ? g : 0u);
+    const uint32_t col = row_window_col<16>(w, c);
+    v[i] = ld_off<u32x4_any, NT>(s, c.row * r.src_pitch + col);
+    to[i] = c.row * r.dst_pitch + col;
   }
 #pragma unroll
   for (uint32_t i = 0; i < R; ++i)
-    if (lane + i * 64 < count) st_off<u32x4_any, NT>(d, to[i], v[i]);
+    if (lane + i * 64 < w.count) st_off<u32x4_any, NT>(d, to[i], v[i]);
+}
+
+// The windows of a tile of rows, and the bytes of a part of its first or last row that is shorter than a window: these are loaded before
+// and stored after them.
+template <int NT>
+__device__ __forceinline__ void move_rows(uint64_t d, uint64_t s, const PieceRows &r, const RowWindows &w, uint32_t lane) {
+  // lanes 0 .. 15: the first part's bytes, lanes 16 .. 31: the last part's
+  const bool edge = lane < 16 ? lane < w.short_first : lane - 16 < w.short_last;
+  const uint32_t es = lane < 16 ? w.c0 + lane : w.more * r.src_pitch + (lane - 16), ed = lane < 16 ? w.c0 + lane : w.more * r.dst_pitch + (lane - 16);
+  uint8_t eb = 0;
+  if (edge) eb = ld_off<uint8_t, 0>(s, es);
+  if (w.count <= 256) {
+    if (w.count != 0) move_windows<NT, 4>(d, s, r, w, lane);
+  } else {
+    move_windows<NT, 8>(d, s, r, w, lane);
+  }
+  if (edge) st_off<uint8_t, 0>(d, ed, eb);
 }
 
 template <int NT, bool ROWS>
@@ -157,12 +175,8 @@ __device__ __forceinline__ void move_tile(const Piece &p, uint32_t lane) {
     const PieceRows &r = p.rows;
     uint32_t row;
     if (!(r.per & kPartsOfRow)) {
-      rows_tile(r, p.len, p.tile_no, &row, &n);
-      const uint32_t per_row = windows_of_row(r.row_bytes), count = n * per_row;
-      d += (uint64_t)row * r.dst_pitch;
-      s += (uint64_t)row * r.src_pitch;
-      if (count <= 256) move_windows<NT, 4>(d, s, r, per_row, count, lane);
-      else move_windows<NT, 8>(d, s, r, per_row, count, lane);
+      const RowWindows w = rows_tile(r, p.len, p.edges, p.tile_no, &row);
+      move_rows<NT>(d + (uint64_t)row * r.dst_pitch, s + (uint64_t)row * r.src_pitch, r, w, lane);
       return;
     }
     row_part(r, p.tile_no, &row, &begin, &n);
@@ -265,14 +279,10 @@ hipError_t launch_along(const PieceTables &t, const Launch &l) {
   if (SHAPES != 0) {
     uint8_t *shape = reinterpret_cast<uint8_t *>(a.shape);
     for (uint32_t i = 0; i < t.n; ++i) shape[i] = (uint8_t)t.shape[i];
+    std::memcpy(static_cast<void *>(a.edges), t.edges, t.n * sizeof(PieceEdges));
     std::memcpy(static_cast<void *>(a.shapes), t.shapes, t.nshapes * sizeof(PieceRows));
   }
   return launch(a, l);
-}
-
-template <bool ROWS>
-hipError_t launch_from_memory(const PieceTables &t, const Launch &l) {
-  return launch(PieceRefs<ROWS>{t.n, t.tile, t.at, t.first, t.len, t.shape, t.shapes}, l);
 }
 
 }  // namespace
@@ -282,11 +292,11 @@ hipError_t launch_pieces(const PieceTables &t, int cls, bool on_host, unsigned l
   if (t.n == 0 || t.ntiles == 0 || cls < 0 || cls > 2 || (on_host && !pieces_go_along(t)) || (cls != 2 && t.tile > 4096)) return hipErrorInvalidValue;
   const Launch l = {cls, t.ntiles, counter, stream, ev_start, ev_stop};
   const bool rows = t.shape != nullptr;
-  if (!on_host) return rows ? launch_from_memory<true>(t, l) : launch_from_memory<false>(t, l);
+  if (!on_host) return rows ? hipErrorInvalidValue : launch(PieceRefs{t.n, t.tile, t.at, t.first, t.len}, l);
   if (rows) {
     if (t.n <= 16 && t.nshapes <= 16) return launch_along<16, 16>(t, l);
     if (t.n <= 64) return launch_along<64, 64>(t, l);
-    return launch_along<200, 16>(t, l);
+    return launch_along<kRowsAlong, 16>(t, l);
   }
   if (t.n == 1) return launch_along<1, 0>(t, l);
   if (t.n <= 16) return launch_along<16, 0>(t, l);

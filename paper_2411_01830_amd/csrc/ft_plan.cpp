@@ -179,27 +179,25 @@ int launch_code(const ClassPlan &cp, int cls, uint64_t chunk_bytes, bool tuned, 
 
 // ---- a class written out as pieces (ft_pieces.h)
 
-PieceRoom piece_room(const ClassPlan &cp, uint64_t chunk_bytes) {
+PieceRoom piece_room(const ClassPlan &cp, uint64_t chunk_bytes, uint32_t tile) {
   PieceRoom room;
   if (chunk_bytes < 1024) return room;
-  uint64_t pitched = 0;
-  for (const Xfer &x : cp.xfers) {
-    if (x.rows <= 1) continue;
-    if (!rows_fit(x)) return room;
-    ++pitched;
-  }
-  // a chunk's end cuts a run in two, and pitched rows into whole rows and the two parts of the row that it falls into; with one
-  // function the chunks follow each other and nothing is cut
+  // a chunk's end cuts a run or rows in two, but rows that a tile holds only a part of into whole rows and the two parts of the row
+  // that it falls into; with one function the chunks follow each other and nothing is cut
+  uint64_t each = 1;
+  if (cp.pitched != 0)
+    for (const Xfer &x : cp.xfers) each = x.rows > 1 && x.row_bytes > tile ? 3 : each;
   const uint64_t cuts = cp.funcs.size() == 1 ? 0 : cp.nchunks;
-  const uint64_t n = cp.xfers.size() + cuts * (pitched != 0 ? 3 : 1) + (cp.payload >> 30);
+  const uint64_t n = cp.xfers.size() + cuts * each + (cp.payload >> 30);
   if (n > kMaxPieces) return room;
   room.pieces = n;
-  room.shapes = pitched;
+  room.shapes = cp.pitched;
   return room;
 }
 
 uint64_t piece_bytes(const PieceRoom &r) {
-  return r.pieces * (sizeof(PieceSides) + (r.shapes != 0 ? 3 : 2) * sizeof(uint32_t)) + r.shapes * sizeof(PieceRows);
+  return r.pieces * (sizeof(PieceSides) + (r.shapes != 0 ? 3 * sizeof(uint32_t) + sizeof(PieceEdges) : 2 * sizeof(uint32_t))) +
+         r.shapes * sizeof(PieceRows);
 }
 
 PieceTables piece_places(char *base, const PieceRoom &r) {
@@ -209,7 +207,8 @@ PieceTables piece_places(char *base, const PieceRoom &r) {
   t.len = t.first + r.pieces;
   if (r.shapes != 0) {
     t.shape = t.len + r.pieces;
-    t.shapes = reinterpret_cast<PieceRows *>(t.shape + r.pieces);
+    t.edges = reinterpret_cast<PieceEdges *>(t.shape + r.pieces);
+    t.shapes = reinterpret_cast<PieceRows *>(t.edges + r.pieces);
   }
   return t;
 }
@@ -231,73 +230,128 @@ struct Reciprocals {
 };
 constexpr Reciprocals kReciprocals;
 
-// (The table's pointers are copied: what is written through them could otherwise be the table itself, and every store would be
-// followed by loads of them.)
-struct PieceWriter {
-  PieceSides *const at;
-  uint32_t *const len, *const shape;
-  PieceRows *const shapes;
-  const uint32_t tile;
-  uint32_t n = 0, nshapes = 0, last_shape = 0;
+// Writes pieces down one after the other. Host time matters here: a thousand tensors are written out in 4 us. So the table's pointers are copied (what is written through them could otherwise be the table itself, and every store
+// would be followed by loads of them), and the last piece is kept aside until it is known not to go on.
+class PieceWriter {
+ public:
+  PieceWriter(const PieceTables &t, uint32_t shift, bool by_source)
+      : at_(t.at), first_(t.first), len_(t.len), shape_(t.shape), shapes_(t.shapes), edges_(t.edges), shift_(shift), by_source_(by_source) {}
 
-  explicit PieceWriter(const PieceTables &t) : at(t.at), len(t.len), shape(t.shape), shapes(t.shapes), tile(t.tile) {}
-  void add(uint64_t src, uint64_t dst, uint32_t bytes_or_rows, uint32_t of_shape) {
-    at[n] = PieceSides{src, dst};
-    len[n] = bytes_or_rows;
-    if (shape != nullptr) shape[n] = of_shape;
-    last_shape = of_shape;
-    n += 1;
-  }
-  // n bytes that lie together on both sides; they go on with the last piece if they lie behind it
-  void run(uint64_t src, uint64_t dst, uint64_t bytes) {
+  // n bytes that lie together on both sides
+  void run(uint64_t src, uint64_t dst, uint64_t n) {
     constexpr uint64_t most = 1ull << 30;
-    if (n != 0 && last_shape == 0) {
-      const uint64_t had = len[n - 1];
-      if (at[n - 1].src + had == src && at[n - 1].dst + had == dst) {
-        const uint64_t m = std::min(bytes, most - had);
-        len[n - 1] = (uint32_t)(had + m);
-        src += m;
-        dst += m;
-        bytes -= m;
-      }
-    }
-    for (; bytes > 0; src += most, dst += most, bytes -= std::min(bytes, most)) add(src, dst, (uint32_t)std::min(bytes, most), 0);
-  }
-  // known: the shape that x has been given, 0 as yet
-  void whole_rows(const Xfer &x, uint64_t r, uint64_t rows, uint32_t *known) {
-    const uint64_t src = x.src + r * x.src_pitch, dst = x.dst + r * x.dst_pitch;
-    if (rows == 1) return run(src, dst, x.row_bytes);
-    if (*known == 0) {
-      const PieceRows *same = nshapes != 0 ? &shapes[nshapes - 1] : nullptr;
-      if (same == nullptr || same->row_bytes != x.row_bytes || same->src_pitch != x.src_pitch || same->dst_pitch != x.dst_pitch)
-        shapes[nshapes++] = shape_of((uint32_t)x.row_bytes, (uint32_t)x.src_pitch, (uint32_t)x.dst_pitch);
-      *known = nshapes;
-    }
-    if (n != 0 && last_shape == *known) {
-      const uint64_t had = len[n - 1];
-      if (at[n - 1].src + had * x.src_pitch == src && at[n - 1].dst + had * x.dst_pitch == dst && had + rows < 1ull << 32) {
-        len[n - 1] = (uint32_t)(had + rows);
-        return;
-      }
-    }
-    add(src, dst, (uint32_t)rows, *known);
-  }
-  // payload bytes [p, p + n) of a pitched descriptor, all of which rows_fit has found to be less than 2^32
-  void part(const Xfer &x, uint32_t p, uint32_t n, uint32_t *known) {
-    const uint32_t rb = (uint32_t)x.row_bytes;
-    uint32_t r = p / rb;
-    const uint32_t c = p - r * rb;
-    if (c != 0) {
-      const uint32_t m = std::min(n, rb - c);
-      run(x.src + r * x.src_pitch + c, x.dst + r * x.dst_pitch + c, m);
+    if (open_ && of_ == 0 && src_ + have_ == src && dst_ + have_ == dst) {
+      const uint64_t m = std::min(n, most - have_);
+      have_ += m;
+      src += m;
+      dst += m;
       n -= m;
-      r += 1;
     }
-    const uint32_t whole = n / rb;
-    if (whole != 0) whole_rows(x, r, whole, known);
-    n -= whole * rb;
-    r += whole;
-    if (n != 0) run(x.src + r * x.src_pitch, x.dst + r * x.dst_pitch, n);
+    for (; n > 0; src += most, dst += most, n -= std::min(n, most)) begin(src, dst, std::min(n, most), 0);
+  }
+  // column `from` of row r up to column `to` of row r + rows - 1 of x, rows > 1. False: not rows that the kernels cover.
+  // known: the shape that x has been given, 0 as yet
+  bool rows(const Xfer &x, uint64_t r, uint64_t rows, uint32_t from, uint32_t to, uint32_t *known) {
+    if (*known == 0) {
+      if (nshapes_ == 0 || last_.row_bytes != x.row_bytes || last_.src_pitch != x.src_pitch || last_.dst_pitch != x.dst_pitch) {
+        if (!rows_fit(x)) return false;
+        last_ = shape_of((uint32_t)x.row_bytes, (uint32_t)x.src_pitch, (uint32_t)x.dst_pitch);
+        shapes_[nshapes_++] = last_;
+      } else if (x.rows * x.row_bytes >> 32 != 0) {
+        return false;
+      }
+      *known = nshapes_;
+    }
+    const uint64_t src = x.src + r * x.src_pitch, dst = x.dst + r * x.dst_pitch;
+    // goes on with the last piece if that ends in front of it: in the row before, or in this one
+    if (open_ && of_ == *known) {
+      const uint64_t common = from != 0 ? 1 : 0, had = have_ - common;
+      if (to_ == (common ? from : x.row_bytes) && src_ + had * x.src_pitch == src && dst_ + had * x.dst_pitch == dst && had + rows < 1ull << 32) {
+        have_ = had + rows;
+        to_ = to;
+        return true;
+      }
+    }
+    begin(src, dst, rows, *known);
+    edges_[n_].from = from;
+    to_ = to;
+    return true;
+  }
+  bool all_of(const Xfer &x) {
+    if (x.rows == 1) {
+      run(x.src, x.dst, x.row_bytes);
+      return true;
+    }
+    uint32_t known = 0;
+    return rows(x, 0, x.rows, 0, (uint32_t)x.row_bytes, &known);
+  }
+  // payload bytes [p, p + bytes) of a descriptor, not all of them
+  bool part(const Xfer &x, uint64_t p, uint64_t bytes, uint32_t *known) {
+    if (x.rows == 1) {
+      run(x.src + p, x.dst + p, bytes);
+      return true;
+    }
+    if (*known == 0 && !rows_fit(x)) return false;
+    const uint32_t rb = (uint32_t)x.row_bytes, first = (uint32_t)p, end = (uint32_t)(p + bytes);  // rows_fit: less than 2^32
+    uint32_t r = first / rb, from = first - r * rb;
+    const uint32_t last = (end - 1) / rb, to = end - last * rb;
+    const auto in_row = [&](uint32_t row, uint32_t a, uint32_t b) { run(x.src + row * x.src_pitch + a, x.dst + row * x.dst_pitch + a, b - a); };
+    if (r == last) {
+      in_row(r, from, to);
+      return true;
+    }
+    if (windows_of_row(rb) <= 1u << shift_ >> 4) return rows(x, r, last - r + 1, from, to, known);
+    if (from != 0) in_row(r++, from, rb);
+    const uint32_t whole = last - r + (to == rb ? 1 : 0);
+    if (whole == 1) in_row(r, 0, rb);
+    else if (whole != 0 && !rows(x, r, whole, 0, rb, known)) return false;
+    if (to != rb) in_row(last, 0, to);
+    return true;
+  }
+  void end(PieceTables *t) {
+    if (open_) close();
+    t->n = n_;
+    t->nshapes = nshapes_;
+    t->ntiles = tiles_;
+  }
+
+ private:
+  PieceSides *const at_;
+  uint32_t *const first_, *const len_, *const shape_;
+  PieceRows *const shapes_;
+  PieceEdges *const edges_;
+  const uint32_t shift_;
+  const bool by_source_;
+  bool open_ = false;
+  uint32_t n_ = 0, nshapes_ = 0, tiles_ = 0;
+  // the last piece: its sides, shape, bytes or rows, and end
+  uint64_t src_ = 0, dst_ = 0, have_ = 0;
+  uint32_t of_ = 0, to_ = 0;
+  PieceRows last_{};  // the last shape
+
+  void begin(uint64_t src, uint64_t dst, uint64_t bytes_or_rows, uint32_t of) {
+    if (open_) close();
+    open_ = true;
+    src_ = src;
+    dst_ = dst;
+    have_ = bytes_or_rows;
+    of_ = of;
+  }
+  void close() {
+    at_[n_] = PieceSides{src_, dst_};
+    first_[n_] = tiles_;
+    len_[n_] = (uint32_t)have_;
+    if (of_ == 0) {
+      if (shape_ != nullptr) shape_[n_] = 0;
+      const uint32_t before = (uint32_t)(by_source_ ? src_ : dst_) & (kPieceLine - 1);
+      tiles_ += (uint32_t)((have_ + before + (1u << shift_) - 1) >> shift_);
+    } else {
+      shape_[n_] = of_;
+      edges_[n_].to = to_;
+      const uint32_t per = of_ == nshapes_ ? last_.per : shapes_[of_ - 1].per;
+      tiles_ += per & kPartsOfRow ? (uint32_t)have_ * (per & ~kPartsOfRow) : kReciprocals.divide((uint32_t)have_ - 1, per) + 1;
+    }
+    n_ += 1;
   }
   // A tile is at most tile / 16 windows of 16 bytes (ft_windows.h).
   PieceRows shape_of(uint32_t row_bytes, uint32_t src_pitch, uint32_t dst_pitch) const {
@@ -305,95 +359,88 @@ struct PieceWriter {
     r.row_bytes = row_bytes;
     r.src_pitch = src_pitch;
     r.dst_pitch = dst_pitch;
-    const uint32_t windows = windows_of_row(row_bytes);
+    const uint32_t windows = windows_of_row(row_bytes), tile = 1u << shift_;
     r.magic = r.part = 0;
     if (windows <= tile / 16) {
       r.magic = kReciprocals.magic[windows];
       r.per = kReciprocals.divide(tile / 16, windows);
       return r;
     }
-    const uint64_t parts = ((uint64_t)row_bytes + tile - 1) / tile;
+    // a part may begin anywhere, so that one of tile - 15 bytes and more could be a window more than a tile has
+    const uint64_t parts = ((uint64_t)row_bytes + tile - 17) / (tile - 16);
     r.part = (uint32_t)(((uint64_t)row_bytes + parts - 1) / parts + 15) / 16 * 16;
     r.per = kPartsOfRow | (uint32_t)(((uint64_t)row_bytes + r.part - 1) / r.part);
     return r;
   }
 };
 
-}  // namespace
-
-void build_pieces(const ClassPlan &cp, uint64_t chunk_bytes, uint32_t tile, bool by_source, PieceTables *t) {
-  t->tile = tile;
-  PieceWriter w(*t);
-  const auto all_of = [&w](const Xfer &x) {
-    uint32_t shape = 0;
-    if (x.rows == 1) w.run(x.src, x.dst, x.row_bytes);
-    else w.whole_rows(x, 0, x.rows, &shape);
-  };
+bool write_pieces(const ClassPlan &cp, uint64_t chunk_bytes, PieceWriter &w) {
   if (cp.funcs.size() == 1) {
-    for (const Xfer &x : cp.xfers) all_of(x);
-  } else {
-    struct Place {
-      uint64_t left;  // of the function's stream
-      uint64_t pos;   // bytes of descriptor x that are written out
-      uint32_t x, shape;
-    };
-    Place few[16];
-    std::vector<Place> many;
-    Place *at = few;
-    if (cp.funcs.size() > 16) {
-      many.resize(cp.funcs.size());
-      at = many.data();
-    }
-    for (size_t f = 0; f < cp.funcs.size(); ++f) at[f] = Place{cp.funcs[f].stream_bytes, 0, cp.funcs[f].desc_off, 0};
-    for (size_t i = 0; i < cp.phases.size(); ++i) {
-      const Phase &ph = cp.phases[i];
-      uint64_t chunks = (i + 1 < cp.phases.size() ? cp.phases[i + 1].rank_base : cp.nchunks) - ph.rank_base;
-      while (chunks > 0)
-        for (uint32_t s = 0; s < ph.nslots && chunks > 0; ++s, --chunks) {
-          // a function's chunks come in the order of its stream, so the next one begins where the last one ended
-          Place &p = at[cp.slots[ph.slot_off + s].fl];
-          uint64_t take = std::min(chunk_bytes, p.left);
-          p.left -= take;
-          while (take > 0) {
-            const Xfer &x = cp.xfers[p.x];
-            const uint64_t bytes = x.row_bytes * x.rows, n = std::min(bytes - p.pos, take);
-            if (n == bytes) all_of(x);
-            else if (x.rows == 1) w.run(x.src + p.pos, x.dst + p.pos, n);
-            else w.part(x, (uint32_t)p.pos, (uint32_t)n, &p.shape);
-            take -= n;
-            p.pos += n;
-            if (p.pos == bytes) {
-              p.pos = p.shape = 0;
-              p.x += 1;
-            }
+    for (const Xfer &x : cp.xfers)
+      if (!w.all_of(x)) return false;
+    return true;
+  }
+  struct Place {
+    uint64_t left;  // of the function's stream
+    uint64_t pos;   // bytes of descriptor x that are written out
+    uint32_t x, shape;
+  };
+  Place few[16];
+  std::vector<Place> many;
+  Place *at = few;
+  if (cp.funcs.size() > 16) {
+    many.resize(cp.funcs.size());
+    at = many.data();
+  }
+  for (size_t f = 0; f < cp.funcs.size(); ++f) at[f] = Place{cp.funcs[f].stream_bytes, 0, cp.funcs[f].desc_off, 0};
+  for (size_t i = 0; i < cp.phases.size(); ++i) {
+    const Phase &ph = cp.phases[i];
+    uint64_t chunks = (i + 1 < cp.phases.size() ? cp.phases[i + 1].rank_base : cp.nchunks) - ph.rank_base;
+    while (chunks > 0)
+      for (uint32_t s = 0; s < ph.nslots && chunks > 0; ++s, --chunks) {
+        // a function's chunks come in the order of its stream, so the next one begins where the last one ended
+        Place &p = at[cp.slots[ph.slot_off + s].fl];
+        uint64_t take = std::min(chunk_bytes, p.left);
+        p.left -= take;
+        while (take > 0) {
+          const Xfer &x = cp.xfers[p.x];
+          const uint64_t bytes = x.row_bytes * x.rows, n = std::min(bytes - p.pos, take);
+          if (!(n == bytes ? w.all_of(x) : w.part(x, p.pos, n, &p.shape))) return false;
+          take -= n;
+          p.pos += n;
+          if (p.pos == bytes) {
+            p.pos = 0;
+            p.shape = 0;
+            p.x += 1;
           }
         }
-    }
+      }
   }
-  t->n = w.n;
-  t->nshapes = w.nshapes;
-  uint32_t shift = 0, tiles = 0;
+  return true;
+}
+
+}  // namespace
+
+bool build_pieces(const ClassPlan &cp, uint64_t chunk_bytes, uint32_t tile, bool by_source, PieceTables *t) {
+  uint32_t shift = 0;
   while (tile >> shift != 1) ++shift;
+  PieceWriter w(*t, shift, by_source);
+  if (!write_pieces(cp, chunk_bytes, w)) return false;
+  w.end(t);
+  t->tile = tile;
+  t->close = t->n <= kRunsAlong;
+  if (!t->close) return true;  // too many to go along in any case
   uint64_t low[2] = {~0ull, ~0ull}, high[2] = {0, 0};
   for (uint32_t i = 0; i < t->n; ++i) {
-    t->first[i] = tiles;
     low[0] = std::min(low[0], t->at[i].src);
     high[0] = std::max(high[0], t->at[i].src);
     low[1] = std::min(low[1], t->at[i].dst);
     high[1] = std::max(high[1], t->at[i].dst);
-    const uint64_t len = t->len[i];
-    if (t->shape == nullptr || t->shape[i] == 0) {
-      const uint32_t before = (uint32_t)(by_source ? t->at[i].src : t->at[i].dst) & (kPieceLine - 1);
-      tiles += (uint32_t)((len + before + tile - 1) >> shift);
-    } else {
-      const uint32_t per = t->shapes[t->shape[i] - 1].per;
-      tiles += per & kPartsOfRow ? (uint32_t)len * (per & ~kPartsOfRow) : kReciprocals.divide((uint32_t)len - 1, per) + 1;
-    }
   }
-  t->ntiles = tiles;
   t->src0 = low[0];
   t->dst0 = low[1];
   t->close = (high[0] - low[0]) >> 32 == 0 && (high[1] - low[1]) >> 32 == 0;
+  return true;
 }
 
 // Pool->pool up to what the last-level cache holds: kernel time, us, general tables -> pieces, sources not in the cache: 64 maps of batch 1,
@@ -403,20 +450,22 @@ void build_pieces(const ClassPlan &cp, uint64_t chunk_bytes, uint32_t tile, bool
 // at odd addresses 4713 -> 4663; to the host 298.3 -> 295.4, 1179.0 -> 1175.8, 128 MiB with odd ones 2400 -> 2349. All but one aligned
 // tensor from the host (64 KiB 4.5 -> 4.2, but 256 KiB 7.5 -> 8.0, 1 MiB 21.0 -> 22.2, 64 MiB 1167.8 -> 1169.6), and aligned jobs beyond
 // 64 MiB, whose pieces take the host longer to write out than the kernel gains (1 GiB in 2064 pieces 18663 -> 18683 a pass).
+// Rows go as pieces where these go along with the launch (quadrants of 4K frames, 16 descriptors, 99.5 MB, 48 -> 44 a pass,
+// kernel 38.6 -> 35.5); where they would be uploaded, writing them out costs more than the kernel gains (1536 crops 56.0 by the general
+// tables, 63.0 by pieces, kernels 24.4 and 19.8).
 PieceRoom job_pieces(const ClassPlan &cp, int cls, uint64_t chunk_bytes) {
   if (cls == FT_P2P && cp.payload > kCacheResidentBytes) return PieceRoom();
   if (cls == FT_H2P && cp.xfers.size() == 1 && cp.payload > 128u << 10 && ((cp.xfers[0].src | cp.xfers[0].dst) & 15) == 0) return PieceRoom();
+  if (cp.pitched != 0 && (cls != FT_P2P || cp.xfers.size() > kRowsAlong)) return PieceRoom();
   if (cls != FT_P2P && cp.payload > 64u << 20) {
     uint64_t odd = 0;
-    for (const Xfer &x : cp.xfers) odd += ((x.src ^ x.dst) & 15) != 0 ? x.row_bytes * x.rows : 0;
+    for (const Xfer &x : cp.xfers) odd += ((x.src ^ x.dst) & 15) != 0 ? x.row_bytes : 0;
     if (odd < cp.payload / 8) return PieceRoom();
   }
-  const PieceRoom room = piece_room(cp, chunk_bytes);
-  return room.shapes == 0 ? room : PieceRoom();
+  const PieceRoom room = piece_room(cp, chunk_bytes, piece_tile(cls, cp.payload));
+  return cp.pitched != 0 && room.pieces > 2 * kRowsAlong ? PieceRoom() : room;
 }
 
-// Pool->pool: some thousand tiles, sixteen wavefronts on every compute unit, and no more than a lane holds in eight vectors. Host
-// link: see ft_link_piece_kernel; less where that leaves compute units without a tile.
 uint32_t piece_tile(int cls, uint64_t payload) {
   if (cls != FT_P2P) return payload <= 32u << 10 ? 1024 : payload <= 128u << 10 ? 2048 : 4096;
   return payload <= 10u << 20 ? 2048 : payload <= 20u << 20 ? 4096 : 8192;
@@ -785,6 +834,7 @@ int plan_submit(SlabPool &pool, const std::vector<HostWindow> &windows, const ft
       x.row_bytes = x.src_pitch = x.dst_pitch = payload;  // rows that touch are one contiguous run
       x.rows = 1;
     }
+    cp.pitched += x.rows > 1 ? 1 : 0;
     x.stream_off = fn.stream_bytes;
     if (add_overflow(fn.stream_bytes, payload, &fn.stream_bytes)) stream_overflow = true;
   }

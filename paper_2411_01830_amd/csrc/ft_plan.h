@@ -26,6 +26,7 @@ struct ClassPlan {
   uint32_t desc_per = 1;             // entries per chunk in chunk_desc: 1, or tiles per chunk
   uint64_t nchunks = 0;
   uint64_t payload = 0;
+  uint64_t pitched = 0;  // descriptors of more than one row
 };
 
 struct SubmitPlan {

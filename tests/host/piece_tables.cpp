@@ -23,7 +23,7 @@ static uint64_t g_seed;
     }                                                                                              \
   } while (0)
 
-static uint64_t n_tiles, n_rows, n_parts, n_merged;
+static uint64_t n_tiles, n_rows, n_parts, n_merged, n_edges;
 
 static void move(uint64_t d, uint64_t s, uint32_t n) { std::memcpy(reinterpret_cast<void *>(d), reinterpret_cast<const void *>(s), n); }
 
@@ -56,21 +56,27 @@ static void move_piece(const PieceTables &t, uint32_t i, bool by_source) {
       continue;
     }
     const PieceRows &r = t.shapes[t.shape[i] - 1];
-    const uint32_t per_row = windows_of_row(r.row_bytes);
+    const PieceEdges &e = t.edges[i];
     if (!(r.per & kPartsOfRow)) {
-      rows_tile(r, t.len[i], no, &row, &n);
-      CHECK(n > 0 && row == moved && row + n <= t.len[i] && n * per_row <= 512 && n * per_row * 16 <= t.tile);
-      for (uint32_t g = 0; g < n * per_row; ++g) {
-        uint32_t wr, col;
-        row_window_of(r, per_row, g, &wr, &col);
-        CHECK(wr == g / per_row && col + 16 <= r.row_bytes);
+      const RowWindows w = rows_tile(r, t.len[i], e, no, &row);
+      n = w.more + 1;
+      CHECK(row == moved && row + n <= t.len[i] && w.per_row == windows_of_row(r.row_bytes) && w.count <= 512 && w.count * 16 <= t.tile);
+      for (uint32_t g = 0; g < w.count; ++g) {
+        const RowCursor c = row_window<16>(w, g);
+        const uint32_t col = row_window_col<16>(w, c);
+        CHECK(c.row <= w.more && col + 16 <= (row + c.row + 1 == t.len[i] ? e.to : r.row_bytes) && col >= (row + c.row == 0 ? e.from : 0));
         // distances of 32 bits
-        CHECK((uint64_t)wr * r.src_pitch + col + 16 < 1ull << 32 && (uint64_t)wr * r.dst_pitch + col + 16 < 1ull << 32);
-        move(d + (uint64_t)(row + wr) * r.dst_pitch + col, s + (uint64_t)(row + wr) * r.src_pitch + col, 16);
+        CHECK((uint64_t)c.row * r.src_pitch + col + 16 < 1ull << 32 && (uint64_t)c.row * r.dst_pitch + col + 16 < 1ull << 32);
+        move(d + (uint64_t)(row + c.row) * r.dst_pitch + col, s + (uint64_t)(row + c.row) * r.src_pitch + col, 16);
       }
+      CHECK(w.short_first < 16 && w.short_last < 16);
+      move(d + (uint64_t)row * r.dst_pitch + w.c0, s + (uint64_t)row * r.src_pitch + w.c0, w.short_first);
+      move(d + (uint64_t)(row + w.more) * r.dst_pitch, s + (uint64_t)(row + w.more) * r.src_pitch, w.short_last);
+      n_edges += w.short_first != 0 || w.short_last != 0;
       moved += n;
       ++n_rows;
     } else {
+      CHECK(e.from == 0 && e.to == r.row_bytes);
       row_part(r, no, &row, &begin, &n);
       CHECK(row < t.len[i] && n > 0 && n <= t.tile && begin + n <= r.row_bytes);
       CHECK((uint64_t)row * r.row_bytes + begin == moved);
@@ -112,6 +118,10 @@ static void job(std::mt19937_64 &r) {
       Xfer x{};
       x.rows = kind == 2 || (kind == 1 && U(0, 1)) ? U(2, 40) : 1;
       x.row_bytes = x.rows == 1 ? U(1, U(0, 5) == 0 ? 20000 : 900) : U(16, U(0, 9) == 0 ? 11000 : U(0, 1) ? 40 : 400);
+      if (x.rows > 1 && U(0, 9) == 0) {  // about a whole number of tiles
+        x.row_bytes = (1024ull << U(0, 3)) * U(1, 3) - 20 + U(0, 40);
+        x.rows = U(2, 5);
+      }
       x.src_pitch = x.row_bytes + (x.rows > 1 ? U(0, 90) : 0);
       x.dst_pitch = x.row_bytes + (x.rows > 1 ? U(x.src_pitch == x.row_bytes ? 1 : 0, 90) : 0);
       const uint64_t es = (x.rows - 1) * x.src_pitch + x.row_bytes, ed = (x.rows - 1) * x.dst_pitch + x.row_bytes;
@@ -123,6 +133,7 @@ static void job(std::mt19937_64 &r) {
       x.stream_off = fn.stream_bytes;
       fn.stream_bytes += x.row_bytes * x.rows;
       cp.xfers.push_back(x);
+      cp.pitched += x.rows > 1;
       ++fn.ndesc;
     }
     if (fn.ndesc == 0) continue;
@@ -152,12 +163,12 @@ static void job(std::mt19937_64 &r) {
   for (const Byte &b : order) want[b.dst - reinterpret_cast<uint64_t>(dst.data())] = *reinterpret_cast<const uint8_t *>(b.src);
 
   for (int by_source = 0; by_source < 2; ++by_source)
-    for (uint32_t tile : {128u, 2048u, 8192u}) {
-      const PieceRoom room = piece_room(cp, C);
+    for (uint32_t tile : {1024u, 2048u, 8192u}) {
+      const PieceRoom room = piece_room(cp, C, tile);
       if (room.pieces == 0) continue;
       std::vector<uint32_t> words(piece_bytes(room) / 4);  // no more than that: the sanitizer sees a write beyond
       PieceTables t = piece_places(reinterpret_cast<char *>(words.data()), room);
-      build_pieces(cp, C, tile, by_source != 0, &t);
+      CHECK(build_pieces(cp, C, tile, by_source != 0, &t));
       CHECK(t.n > 0 && t.n <= room.pieces && t.nshapes <= room.shapes && t.tile == tile && t.first[0] == 0);
       std::vector<Byte> got;
       std::memset(dst.data(), 0xA5, dst.size());
@@ -169,7 +180,8 @@ static void job(std::mt19937_64 &r) {
         x.row_bytes = r ? r->row_bytes : t.len[i];
         x.src_pitch = r ? r->src_pitch : t.len[i];
         x.dst_pitch = r ? r->dst_pitch : t.len[i];
-        bytes_of(got, x, 0, x.row_bytes * (r ? t.len[i] : 1));
+        if (r) bytes_of(got, x, t.edges[i].from, (t.len[i] - 1) * x.row_bytes + t.edges[i].to - t.edges[i].from);
+        else bytes_of(got, x, 0, x.row_bytes);
         move_piece(t, i, by_source != 0);
       }
       CHECK(got == order);
@@ -198,11 +210,11 @@ static void long_run() {
   cp.payload = fn.stream_bytes;
   cp.funcs.push_back(fn);
   CHECK(build_phases(cp.funcs, cp.phases, cp.slots, &cp.nchunks) == FT_OK);
-  const PieceRoom room = piece_room(cp, 2 << 20);
+  const PieceRoom room = piece_room(cp, 2 << 20, 4096);
   CHECK(room.pieces >= 9 && room.shapes == 0);
   std::vector<uint32_t> words(piece_bytes(room) / 4);
   PieceTables t = piece_places(reinterpret_cast<char *>(words.data()), room);
-  build_pieces(cp, 2 << 20, 4096, false, &t);
+  CHECK(build_pieces(cp, 2 << 20, 4096, false, &t));
   uint64_t at = 0;
   for (uint32_t i = 0; i < t.n; ++i) {
     CHECK(t.at[i].src == cp.xfers[0].src + at && t.at[i].dst == cp.xfers[0].dst + at && t.len[i] <= 1u << 30);
@@ -213,21 +225,40 @@ static void long_run() {
 
 // What no list of pieces is made for.
 static void refused() {
-  auto with = [](uint64_t rb, uint64_t rows, uint64_t pitch, uint64_t chunk, uint64_t nchunks) {
+  auto with = [](uint64_t rb, uint64_t rows, uint64_t pitch, uint64_t chunk, uint64_t more_chunks) {
     ClassPlan cp;
-    cp.funcs.resize(2);
-    cp.nchunks = nchunks;
     Xfer x{};
     x.row_bytes = rb;
     x.rows = rows;
     x.src_pitch = x.dst_pitch = pitch;
-    cp.xfers.push_back(x);
-    return piece_room(cp, chunk).pieces;
+    for (uint32_t f = 0; f < 2; ++f) {
+      Func fn{};
+      fn.weight = fn.ndesc = 1;
+      fn.desc_off = f;
+      fn.stream_bytes = rb * rows;
+      fn.nchunks = (fn.stream_bytes + chunk - 1) / chunk;
+      cp.xfers.push_back(x);
+      cp.funcs.push_back(fn);
+      cp.pitched += rows > 1;
+    }
+    CHECK(build_phases(cp.funcs, cp.phases, cp.slots, &cp.nchunks) == FT_OK);
+    PieceRoom room = piece_room(cp, chunk, 2048);
+    if (more_chunks != 0) {
+      cp.nchunks = more_chunks;
+      return piece_room(cp, chunk, 2048).pieces != 0;
+    }
+    if (room.pieces == 0) return false;
+    std::vector<uint32_t> words(piece_bytes(room) / 4);
+    PieceTables t = piece_places(reinterpret_cast<char *>(words.data()), room);
+    return build_pieces(cp, chunk, 2048, false, &t);
   };
-  CHECK(with(16, 3, 20, 1024, 5) != 0 && with(15, 3, 20, 1024, 5) == 0);
-  CHECK(with(16, 3, 20, 512, 5) == 0);
-  CHECK(with(100, 1, 100, 1024, kMaxPieces - 1) != 0 && with(100, 1, 100, 1024, kMaxPieces) == 0);
-  CHECK(with(16, 3, ((1ull << 32) - 1) / 516, 1024, 5) != 0 && with(16, 3, ((1ull << 32) - 1) / 516 + 1, 1024, 5) == 0);
+  for (uint64_t chunk : {1024, 1 << 20}) {
+    CHECK(with(16, 3, 20, chunk, 0) && !with(15, 3, 20, chunk, 0));
+    CHECK(with(16, 3, ((1ull << 32) - 1) / 516, chunk, 0) && !with(16, 3, ((1ull << 32) - 1) / 516 + 1, chunk, 0));
+  }
+  CHECK(with(1000, 4000, 1000000, 1 << 20, 0) && !with(1000, 5000000, 1001, 1 << 22, 0) && !with(1ull << 33, 2, 1ull << 33, 1ull << 30, 0));
+  CHECK(!with(16, 3, 20, 512, 0));
+  CHECK(with(100, 1, 100, 1024, kMaxPieces - 2) && !with(100, 1, 100, 1024, kMaxPieces - 1));
 }
 
 int main(int argc, char **argv) {
@@ -238,7 +269,7 @@ int main(int argc, char **argv) {
     std::mt19937_64 r(g_seed);
     for (int i = 0; i < 6; ++i) job(r);
   }
-  CHECK(n_rows > 0 && n_parts > 0 && n_merged > 0);
+  CHECK(n_rows > 0 && n_parts > 0 && n_merged > 0 && n_edges > 0);
   std::printf("tiles %llu, of rows %llu, of parts of rows %llu, lists with merged tensors %llu\n", (unsigned long long)n_tiles,
               (unsigned long long)n_rows, (unsigned long long)n_parts, (unsigned long long)n_merged);
   std::printf("done %llu..%llu\n", (unsigned long long)first, (unsigned long long)(first + count - 1));

@@ -1,4 +1,4 @@
-"""Jobs that are launched as a list of pieces: pool->pool jobs of at most 128 MiB whose schedule nobody may ask for. Bit-exact
+"""Jobs that are launched as a list of pieces: of runs, pool->pool at most 128 MiB, and of few pitched rows; none whose schedule may be asked for. Bit-exact
 against the oracle at the sizes where tiles, windows, the forms of the tables and the rule change."""
 import numpy as np
 import pytest
@@ -22,12 +22,21 @@ def _runs(rng, n, sizes, funcs, odd=True):
     return [(int(sizes[i % len(sizes)] if len(sizes) >= n else rng.choice(sizes)), 1, 0, 0, i % funcs, shift(), shift()) for i in range(n)]
 
 
+def _rows(rng, n, widths, total, funcs):
+    out = []
+    for i in range(n):
+        rb = int(widths[i % len(widths)])
+        out.append((rb, max(2, total // n // rb), rb + int(rng.integers(0, 50)), rb + int(rng.integers(0, 3)) * 7, i % funcs,
+                    int(rng.integers(0, 16)), int(rng.integers(0, 16))))
+    return out
+
+
 def _tile(payload):
     return 2 * KiB if payload <= 10 * MiB else 4 * KiB if payload <= 20 * MiB else 8 * KiB
 
 
 # name, pieces(rng): (row bytes, rows, src pitch, dst pitch, function, src shift, dst shift), weights, chunk, travels with its launch
-# (None: not launched as pieces)
+# ("any": it may; None: not launched as pieces; "either": nor this, by a kernel of the same shape)
 CASES = [
     ("one byte", lambda g: [(1, 1, 0, 0, 0, 3, 9)], [1], 2 * MiB, True),
     *[(f"one tensor of {n}", lambda g, n=n: [(n, 1, 0, 0, 0, 7, 4)], [1], 2 * MiB, True) for n in (15, 16, 17, 2047, 2048, 2049, 65536, 10 * MiB, 10 * MiB + 1, 20 * MiB + 1)],
@@ -40,9 +49,23 @@ CASES = [
     ("1025 functions", lambda g: _runs(g, 2100, [64, 5000, 9000], 1025), [1] * 1025, 4 * KiB, False),
     ("5000 tensors", lambda g: _runs(g, 5000, [1, 60, 300, 700], 1), [1], 256 * KiB, False),
     ("tiles of 4 KiB", lambda g: _runs(g, 30, [400 * KiB, 500 * KiB + 5], 3), [1, 2, 4], 256 * KiB, True),
-    ("tiles of 8 KiB", lambda g: _runs(g, 30, [800 * KiB + 3, 1000 * KiB], 3), [1, 2, 4], 32 * KiB, False),
+    ("tiles of 8 KiB", lambda g: _runs(g, 300, [80 * KiB + 3, 100 * KiB], 3), [1, 2, 4], 256 * KiB, False),
+    ("few tensors in many chunks", lambda g: _runs(g, 20, [100 * KiB + 3, 100 * KiB], 4), [1, 2, 4, 1], 4 * KiB, "either"),
     ("over 20 MiB", lambda g: _runs(g, 30, [800 * KiB + 3, 1000 * KiB], 3), [1, 2, 4], 2 * MiB, True),
     ("chunks under 1 KiB", lambda g: _runs(g, 200, [300, 5000], 2), [1, 3], 512, None),
+    ("rows of 16 bytes and a bit", lambda g: _rows(g, 14, [16, 17, 31, 32, 33, 47, 48], 2 * MiB, 2), [1, 2], 1 * MiB, True),
+    ("rows cut by every chunk", lambda g: _rows(g, 10, [16, 17, 40, 100, 255, 2047, 2048], 400 * KiB, 3), [1, 2, 5], 1024, "either"),
+    ("rows cut by every chunk, one function", lambda g: _rows(g, 16, [16, 17, 40, 100, 255, 2047, 2048], 200 * KiB, 1), [1], 1024, True),
+    ("rows longer than a tile", lambda g: _rows(g, 6, [2049, 8193, 20000, 66000], 1 * MiB, 2), [3, 1], 1 * MiB, "any"),
+    ("rows around a tile of 8 KiB", lambda g: _rows(g, 8, [4096, 4097, 8191, 8192, 8193, 8208], 22 * MiB, 2), [3, 1], 2 * MiB, "any"),
+    ("rows and runs", lambda g: _rows(g, 20, [16, 100, 3000], 600 * KiB, 2) + _runs(g, 20, [1, 16, 5000, 70000], 2), [1, 2], 64 * KiB, "any"),
+    ("100 pieces of few shapes", lambda g: [(100, 20, 160, 100, i % 2, i % 7, i % 5) for i in range(100)], [1, 1], 64 * KiB, True),
+    ("200 pieces of few shapes", lambda g: [(100, 20, 160, 100, i % 2, i % 7, i % 5) for i in range(200)], [1, 1], 64 * KiB, "either"),
+    ("70 shapes", lambda g: _rows(g, 70, list(range(16, 86)), 300 * KiB, 1), [1], 64 * KiB, "either"),
+    ("single rows", lambda g: [(100, 2, 160, 100, i % 2, i % 7, i % 5) for i in range(30)], [1, 1], 1024, "any"),
+    ("rows under 16 bytes", lambda g: _rows(g, 20, [1, 2, 3, 5, 8, 15], 100 * KiB, 2), [1, 2], 64 * KiB, None),
+    ("rows between 1 MiB pitches", lambda g: [(100, 9, 1 << 20, 200, 0, 3, 5), (70, 5, 100, 1 << 20, 1, 1, 2), (50, 6, (1 << 20) + 1, 60, 0, 0, 0)],
+     [1, 1], 64 * KiB, True),
 ]
 
 
@@ -91,8 +114,8 @@ def test_pieces_match_the_oracle(case):
                 own = st.tile_bytes == _tile(payload) and st.workgroups == st.tickets
                 if along is None:
                     assert not own
-                else:
-                    assert own and st.in_launch == (1 if along else 0) and st.device_ms > 0, (st.tile_bytes, st.tickets, st.in_launch)
+                elif along != "either":
+                    assert own and (along == "any" or st.in_launch == along) and st.device_ms > 0, (st.tile_bytes, st.tickets, st.in_launch)
                 assert eng.job_schedule(jg, 2) == orc.job_schedule(jo, 2)
                 binding.job_release(eng.pool, jg)
             check(flags)
