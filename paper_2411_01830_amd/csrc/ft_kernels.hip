@@ -5,6 +5,7 @@
 // of a chunk, chunks are numbered in the proportional order of Sec. 6.1, so the
 // counter hands the link's bandwidth out to functions by weight at tile granularity.
 // ft_wave_kernel does the same for jobs that latency bounds, one tile per wavefront.
+// Jobs whose order is a short list do not come here: ft_pieces.hip.
 // Bytes move as 16-byte vectors, one per lane, consecutive lanes on consecutive
 // vectors, so every wavefront load/store covers 1 KiB of contiguous memory.
 #include <hip/hip_runtime.h>

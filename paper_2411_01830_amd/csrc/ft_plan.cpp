@@ -500,7 +500,8 @@ uint64_t wave_workgroups(int cu_count, int code, uint64_t ntickets) {
 // 55.0 us; 128 of them (12 KiB, which the runtime copies with a kernel too) 24.5 us either way. Every wavefront has a tile
 // of host memory in flight: with a workgroup per KiB of any amount 1 GiB pool->pool beside a submit of 16 384 descriptors took
 // 341 us instead of 325, a host->pool job 1199 instead of 1193. So beyond the 256 KiB of reads that fill the link the
-// tiles are dealt out to 256 wavefronts.
+// tiles are dealt out to 256 wavefronts. As one piece, 64 wavefronts of 4 KiB, the fetch itself is shorter still: 64 KiB 4.9 -> 3.8 us of
+// kernel time, 97 KiB 5.7 -> 5.1.
 int table_fetch_code(uint64_t bytes) {
   if (bytes < 16 * 1024) return 0;
   return (bytes <= 256 * 1024 ? kWaveTiles : kWaveLink) | kWaveFromHost;

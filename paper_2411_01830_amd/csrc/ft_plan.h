@@ -79,8 +79,8 @@ uint64_t wave_workgroups(int cu_count, int code, uint64_t ntickets);
 // Whether a wave-kernel launch draws tickets from its counter; single: its table says one function with one descriptor.
 bool wave_draws(int code, uint64_t workgroups, uint64_t ntickets, bool single);
 
-// How a job's tables of this many bytes reach the device: 0 by the runtime's copy, otherwise by a wave-kernel launch of this
-// code as one tensor in tiles of kTableTile.
+// How a job's tables of this many bytes reach the device: 0 by the runtime's copy, otherwise by the engine's own kernel:
+// as one piece from the host (ft_pieces.h). The code and kTableTile are the wave kernel's shape within the same bound on reads in flight.
 constexpr uint64_t kTableTile = 1024;
 int table_fetch_code(uint64_t bytes);
 
