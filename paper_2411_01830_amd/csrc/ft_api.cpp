@@ -580,23 +580,17 @@ int launch_with_the_launch(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chun
   return FT_OK;
 }
 
-// Tables from a blob's pinned twin to its device buffer, as one piece from the host: at most 64 tiles of 4 KiB in
-// flight, which is what fills the link (table_fetch_code tells why no more). Below 16 KiB, too, that is no slower than the runtime's
+// Tables from a blob's pinned twin to its device buffer, as one piece from the host (beyond 1 GiB of them, sixteen million descriptors, as
+// several, one behind the other): at most 64 tiles of 4 KiB in flight, which is what fills the link (table_fetch_code tells why no more). Below 16 KiB, too, that is no slower than the runtime's
 // copy, which is a launch as well.
 hipError_t upload_pieces(const Blob &b, uint64_t bytes, hipStream_t stream) {
-  PieceSides sides = {reinterpret_cast<uint64_t>(b.host), reinterpret_cast<uint64_t>(b.dev)};
-  uint32_t first = 0, len = (uint32_t)bytes;
-  PieceTables t;
-  t.at = &sides;
-  t.first = &first;
-  t.len = &len;
-  t.n = 1;
-  t.tile = piece_tile(FT_H2P, bytes);
-  t.ntiles = (len + ((uint32_t)sides.src & (kPieceLine - 1)) + t.tile - 1) / t.tile;
-  t.src0 = sides.src;
-  t.dst0 = sides.dst;
-  t.close = true;
-  return launch_pieces(t, FT_H2P, true, nullptr, stream, nullptr, nullptr);
+  for (uint64_t at = 0; at < bytes;) {
+    const OneRun part(reinterpret_cast<uint64_t>(b.host) + at, reinterpret_cast<uint64_t>(b.dev) + at, bytes - at, piece_tile(FT_H2P, bytes), true);
+    const hipError_t e = launch_pieces(part.tables, FT_H2P, true, nullptr, stream, nullptr, nullptr);
+    if (e != hipSuccess) return e;
+    at += part.len;
+  }
+  return hipSuccess;
 }
 
 // The same of a job by the general tables, on `stream`: by the runtime's copy, or (the rule stands with table_fetch_code) as above.

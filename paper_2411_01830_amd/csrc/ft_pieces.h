@@ -77,6 +77,33 @@ inline PieceTables pieces_at(char *base, const PieceRoom &room, const PieceTable
 // bytes, or so far apart that a tile's distances leave 32 bits).
 bool build_pieces(const ClassPlan &cp, uint64_t chunk_bytes, uint32_t tile, bool by_source, PieceTables *t);
 
+// A run longer than this is several pieces: tiles are found by 32-bit arithmetic.
+constexpr uint64_t kLongestRun = 1ull << 30;
+
+// One run on its own, without a list: the tables are its members. The first kLongestRun bytes of it at most; a longer one is launched
+// in several parts.
+struct OneRun {
+  PieceSides at;
+  uint32_t first, len;
+  PieceTables tables;
+  OneRun(uint64_t src, uint64_t dst, uint64_t bytes, uint32_t tile, bool by_source) {
+    at = PieceSides{src, dst};
+    first = 0;
+    len = (uint32_t)(bytes < kLongestRun ? bytes : kLongestRun);
+    tables.at = &at;
+    tables.first = &first;
+    tables.len = &len;
+    tables.n = 1;
+    tables.tile = tile;
+    tables.ntiles = (len + ((uint32_t)(by_source ? src : dst) & (kPieceLine - 1)) + tile - 1) / tile;
+    tables.src0 = src;
+    tables.dst0 = dst;
+    tables.close = true;
+  }
+  OneRun(const OneRun &) = delete;
+  OneRun &operator=(const OneRun &) = delete;
+};
+
 // The room for a class of a job that is to be launched as pieces, none if it is not; and the tile.
 PieceRoom job_pieces(const ClassPlan &cp, int cls, uint64_t chunk_bytes);
 uint32_t piece_tile(int cls, uint64_t payload);

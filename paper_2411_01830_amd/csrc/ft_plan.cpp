@@ -239,7 +239,7 @@ class PieceWriter {
 
   // n bytes that lie together on both sides
   void run(uint64_t src, uint64_t dst, uint64_t n) {
-    constexpr uint64_t most = 1ull << 30;
+    constexpr uint64_t most = kLongestRun;
     if (open_ && of_ == 0 && src_ + have_ == src && dst_ + have_ == dst) {
       const uint64_t m = std::min(n, most - have_);
       have_ += m;

@@ -223,6 +223,34 @@ static void long_run() {
   CHECK(at == cp.payload && t.n == 9);
 }
 
+// Tables on their way to the device, up to what 2^32 descriptors take: the parts follow each other and their tiles cover every byte once.
+static void table_uploads() {
+  const uint64_t g = kLongestRun;
+  for (uint64_t bytes : {(uint64_t)256, (uint64_t)16384, (uint64_t)393216, g - 256, g, g + 256, 4 * g - 256, 4 * g, 4 * g + 768, 256 * g + 512})
+    for (uint64_t host : {(uint64_t)1 << 44, ((uint64_t)1 << 44) + 16, ((uint64_t)1 << 44) + 0xfffff000u}) {
+      const uint64_t dev = (uint64_t)1 << 45;
+      uint64_t at = 0, parts = 0;
+      for (; at < bytes; ++parts) {
+        const OneRun part(host + at, dev + at, bytes - at, piece_tile(FT_H2P, bytes), true);
+        const PieceTables &t = part.tables;
+        CHECK(t.n == 1 && pieces_go_along(t) && t.shape == nullptr && t.first[0] == 0 && t.at[0].src == host + at && t.at[0].dst == dev + at);
+        CHECK(t.src0 == t.at[0].src && t.dst0 == t.at[0].dst && t.len[0] > 0 && t.len[0] <= kLongestRun && t.tile <= 4096);
+        CHECK((uint64_t)piece_workgroups(FT_H2P, t.ntiles) * t.tile <= 256 * 1024);  // no more asked of host memory at once than fills the link
+        uint64_t moved = 0;
+        const uint32_t step = parts == 0 || t.ntiles < 1000 ? 1 : t.ntiles / 1000;
+        for (uint32_t no = 0; no < t.ntiles; no += no + step < t.ntiles || no + 1 == t.ntiles ? step : t.ntiles - 1 - no) {
+          uint32_t begin, n;
+          run_tile(t.at[0].src, t.len[0], t.tile, no, &begin, &n);
+          CHECK(n > 0 && n <= t.tile && (uint64_t)begin + n <= t.len[0] && (step > 1 || begin == moved));
+          moved = (uint64_t)begin + n;
+        }
+        CHECK(moved == t.len[0]);
+        at += t.len[0];
+      }
+      CHECK(at == bytes && parts == (bytes + kLongestRun - 1) / kLongestRun);
+    }
+}
+
 // What no list of pieces is made for.
 static void refused() {
   auto with = [](uint64_t rb, uint64_t rows, uint64_t pitch, uint64_t chunk, uint64_t more_chunks) {
@@ -265,6 +293,7 @@ int main(int argc, char **argv) {
   const uint64_t first = argc > 1 ? strtoull(argv[1], 0, 10) : 1, count = argc > 2 ? strtoull(argv[2], 0, 10) : 50;
   refused();
   long_run();
+  table_uploads();
   for (g_seed = first; g_seed < first + count; ++g_seed) {
     std::mt19937_64 r(g_seed);
     for (int i = 0; i < 6; ++i) job(r);
