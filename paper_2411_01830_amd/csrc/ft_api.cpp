@@ -596,7 +596,7 @@ hipError_t upload_pieces(const Blob &b, uint64_t bytes, hipStream_t stream) {
 // The same of a job by the general tables, on `stream`: by the runtime's copy, or (the rule stands with table_fetch_code) as above.
 // dma: a job by the copy engines, which does not wait for a free compute unit.
 hipError_t upload_tables(const Blob &b, uint64_t bytes, bool dma, hipStream_t stream) {
-  if (dma || table_fetch_code(bytes) == 0 || launch_pieces == nullptr) return hipMemcpyAsync(b.dev, b.host, bytes, hipMemcpyHostToDevice, stream);
+  if (dma || table_fetch_code(bytes) == 0) return hipMemcpyAsync(b.dev, b.host, bytes, hipMemcpyHostToDevice, stream);
   return upload_pieces(b, bytes, stream);
 }
 
@@ -741,7 +741,7 @@ int launch_with_uploaded_tables(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t
 // hold the schedule. Nor a detached one that would hold the caller's stream for long. *launched says whether the job went this way.
 int launch_as_pieces(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_bytes, uint32_t flags, hipStream_t user, bool *launched) {
   *launched = false;
-  if (launch_pieces == nullptr || (flags & (FT_KEEP | FT_LOG | FT_PATH_DMA))) return FT_OK;
+  if (flags & (FT_KEEP | FT_LOG | FT_PATH_DMA)) return FT_OK;
   int only = -1;
   for (int c = 0; c < FT_NCLASS; ++c)
     if (plan.cls[c].nchunks > 0) only = only == -1 ? c : -2;

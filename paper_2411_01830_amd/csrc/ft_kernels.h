@@ -17,9 +17,8 @@ hipError_t launch_copy(const ClassTable &T, int link_class, uint32_t workgroups,
                        hipEvent_t ev_start, hipEvent_t ev_stop, const InlineBlob *tables = nullptr);
 // The pieces of a class (ft_pieces.h), whose tables lie in device memory or (on_host) are to travel with the launch. counter: on
 // the host link a word in device memory, of launches of which piece_draws says so one that is zero and will be zero again.
-// Weak: a host build without the kernels has none, and its jobs go by the general tables.
 hipError_t launch_pieces(const PieceTables &t, int cls, bool on_host, unsigned long long *counter, hipStream_t stream, hipEvent_t ev_start,
-                         hipEvent_t ev_stop) __attribute__((weak));
+                         hipEvent_t ev_stop);
 // Decode every chunk rank with the device function the copy kernel uses (test hook).
 hipError_t launch_decode(const ClassTable &T, uint32_t *func_out, uint32_t *chunk_out, uint64_t cap,
                          hipStream_t stream, const InlineBlob *tables = nullptr);

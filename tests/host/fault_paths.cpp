@@ -8,6 +8,7 @@
 // Usage: fault_paths
 #include <hip/hip_runtime_api.h>
 
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -16,6 +17,7 @@
 #include "../../include/faastube.h"
 
 extern "C" int stand_in_fail(const char *name, int nth);
+extern "C" int stand_in_calls(const char *name);
 
 #define CHECK(c) do { if (!(c)) { std::fprintf(stderr, "FAIL %s line %d (point %s, n %d)\n", #c, __LINE__, g_point, g_n); std::abort(); } } while (0)
 static const char *g_point = "-";
@@ -26,7 +28,7 @@ static const uint64_t KiB = 1024, MiB = 1024 * 1024;
 struct World {
   char *dev = nullptr, *host = nullptr;
   uint64_t pool_bytes = 64 * MiB, host_bytes = 32 * MiB;
-  std::vector<char> expect;
+  std::vector<char> expect, host_expect;
   std::vector<char> pageable, pageable_expect;  // ordinary host memory for the jobs that stage
   ft_pool *pool = nullptr;
   std::vector<ft_off_t> allocs;
@@ -72,17 +74,41 @@ static JobSpec make_job(World &w, uint32_t nfunc, uint64_t bytes, bool mixed, ui
   return j;
 }
 
+// One job of n runs of `bytes` bytes or so, on both sides of one allocation each (so 300 of them cost two).
+static JobSpec make_runs(World &w, int cls, uint32_t nfunc, uint32_t n, uint64_t bytes, uint64_t salt) {
+  JobSpec j;
+  const uint64_t step = bytes + 40;
+  const ft_off_t a = alloc(w, n * step), b = cls == 2 ? alloc(w, n * step) : 0;
+  char *host = w.host + (cls == 1 ? w.host_bytes / 2 + salt * 1 * MiB : salt * 8191);
+  for (uint64_t i = 0; i < n * step; ++i)
+    if (cls != 0) w.dev[a + i] = w.expect[a + i] = (char)(i * salt >> 5);
+  for (uint32_t i = 0; i < n; ++i) {
+    ft_desc d{};
+    d.func = i % nfunc;
+    d.rows = 1;
+    d.row_bytes = bytes + i % 7;
+    d.src_space = cls == 0 ? FT_HOST : FT_POOL;
+    d.dst_space = cls == 1 ? FT_HOST : FT_POOL;
+    d.src = cls == 0 ? reinterpret_cast<uint64_t>(host + i * step) : a + i * step + i % 3;
+    d.dst = cls == 1 ? reinterpret_cast<uint64_t>(host + i * step) : (cls == 0 ? a : b) + i * step + i % 5;
+    j.d.push_back(d);
+  }
+  for (uint32_t f = 0; f < nfunc; ++f) j.wts.push_back(1 + f % 3);
+  return j;
+}
+
 static void expect_job(World &w, const JobSpec &j) {
   for (const ft_desc &d : j.d) {
     const char *src = d.src_space == FT_POOL ? w.expect.data() + d.src : reinterpret_cast<const char *>(d.src);
-    std::memmove(w.expect.data() + d.dst, src, d.row_bytes);
+    char *dst = d.dst_space == FT_POOL ? w.expect.data() + d.dst : w.host_expect.data() + (d.dst - reinterpret_cast<uint64_t>(w.host));
+    std::memmove(dst, src, d.row_bytes);
   }
 }
 
 // One pass over all kinds of job. inject: arm the failure before the pass.
 static int pass(World &w, bool inject, const char *point, int n) {
   int failures = 0;
-  std::vector<ft_job_t> to_wait;
+  std::vector<ft_job_t> to_wait, once;  // once: not kept, dead after a wait that succeeds
   auto outcome = [&](int rc, const JobSpec &j, ft_job_t id) {
     CHECK(rc <= 0);
     if (rc == FT_OK) {
@@ -100,6 +126,39 @@ static int pass(World &w, bool inject, const char *point, int n) {
     const int rj = ft_submit_transfers(w.pool, j.d.data(), (uint32_t)j.d.size(), j.wts.data(), (uint32_t)j.wts.size(),
                                        256 * KiB, FT_KEEP, nullptr, &id);
     outcome(rj, j, id);
+  }
+  // closed jobs as pieces: with the launch, uploaded; each link class, with and without a counter; rows; asked for their schedule
+  for (int kind = 0; kind < 8; ++kind) {
+    const int cls = kind < 3 ? 2 : kind % 2;
+    JobSpec j = make_runs(w, cls, 1 + kind % 4, kind == 0 ? 20 : kind >= 5 ? 10 : 300, kind == 7 ? 100 : 3000, 3 + kind);
+    if (kind == 2)
+      for (ft_desc &d : j.d) {  // the same bytes as rows of 100
+        d.rows = 30;
+        d.row_bytes = 100;
+        d.src_pitch = 100;
+        d.dst_pitch = 101;
+      }
+    ft_job_t id = 0;
+    const int rj = ft_submit_transfers(w.pool, j.d.data(), (uint32_t)j.d.size(), j.wts.data(), (uint32_t)j.wts.size(), 16 * KiB,
+                                       kind % 3 == 1 ? FT_TIMING : kind == 6 ? FT_DETACHED : 0, nullptr, &id);
+    if (kind == 2 && rj == FT_OK) {
+      for (const ft_desc &d : j.d)
+        for (uint64_t r = 0; r < d.rows; ++r) std::memcpy(w.expect.data() + d.dst + r * d.dst_pitch, w.expect.data() + d.src + r * d.src_pitch, d.row_bytes);
+      to_wait.push_back(id);
+      once.push_back(id);
+      continue;
+    }
+    outcome(rj, j, id);
+    if (rj == FT_OK && kind % 3 == 1) {
+      uint64_t chunks = 0;
+      std::vector<uint32_t> func(4096), chunk(4096);
+      const int rs = ft_job_schedule(w.pool, id, cls, func.data(), chunk.data(), 4096, &chunks);
+      CHECK(rs <= 0);
+      if (rs != FT_OK) failures += 1;
+      else CHECK(chunks > 0 && func[0] < j.wts.size() && chunk[0] == 0);
+    } else if (rj == FT_OK) {
+      once.push_back(id);
+    }
   }
   // a closed job with pageable memory on both sides (a pinned buffer of its own, copies in ft_wait)
   {
@@ -155,6 +214,10 @@ static int pass(World &w, bool inject, const char *point, int n) {
       failures += 1;
       data_defined = false;  // some chunks of that sequence were never moved
     }
+    if (rw == FT_OK && std::find(once.begin(), once.end(), id) != once.end()) {
+      CHECK(ft_wait(w.pool, id) == FT_EINVAL);
+      continue;
+    }
     const int rl = ft_job_release(w.pool, id);
     if (rl != FT_OK) std::fprintf(stderr, "release of job %llu -> %d (wait gave %d)\n", (unsigned long long)id, rl, rw);
     CHECK(rl == FT_OK);
@@ -166,9 +229,11 @@ static int pass(World &w, bool inject, const char *point, int n) {
   CHECK(ft_pool_usage(w.pool, &total, &live) == FT_OK && live == 0);
   if (data_defined) {
     CHECK(std::memcmp(w.dev, w.expect.data(), w.pool_bytes) == 0);
+    CHECK(std::memcmp(w.host, w.host_expect.data(), w.host_bytes) == 0);
     CHECK(w.pageable == w.pageable_expect);
   } else {
     std::memcpy(w.expect.data(), w.dev, w.pool_bytes);  // start the next pass from what is there
+    std::memcpy(w.host_expect.data(), w.host, w.host_bytes);
     w.pageable_expect = w.pageable;
   }
   return failures;
@@ -199,11 +264,32 @@ static void copy_engines_alone(World &w) {
   std::memcpy(w.expect.data(), w.dev, w.pool_bytes);
 }
 
+// More jobs at once than there are counters: those that find none take the general route, and the counters come back.
+static void counters_run_out(World &w) {
+  for (int round = 0; round < 2; ++round) {
+    std::vector<ft_job_t> jobs;
+    JobSpec j = make_runs(w, 0, 2, 4, 100 * KiB, 17);
+    const int before = stand_in_calls("launch_copy"), pieces = stand_in_calls("launch_pieces");
+    for (int i = 0; i < 300; ++i) {
+      ft_job_t id = 0;
+      CHECK(ft_submit_transfers(w.pool, j.d.data(), (uint32_t)j.d.size(), j.wts.data(), (uint32_t)j.wts.size(), 64 * KiB, 0, nullptr, &id) == FT_OK);
+      jobs.push_back(id);
+    }
+    CHECK(stand_in_calls("launch_pieces") - pieces == 256 && stand_in_calls("launch_copy") - before == 44);
+    for (ft_job_t id : jobs) CHECK(ft_wait(w.pool, id) == FT_OK);
+    expect_job(w, j);
+    for (ft_off_t off : w.allocs) CHECK(ft_slab_free(w.pool, off) == FT_OK);
+    w.allocs.clear();
+  }
+  CHECK(std::memcmp(w.dev, w.expect.data(), w.pool_bytes) == 0);
+}
+
 int main() {
   World w;
   CHECK(hipMalloc(reinterpret_cast<void **>(&w.dev), w.pool_bytes) == hipSuccess);
   CHECK(hipHostMalloc(reinterpret_cast<void **>(&w.host), w.host_bytes, 0) == hipSuccess);
   for (uint64_t i = 0; i < w.host_bytes; ++i) w.host[i] = (char)(i * 2654435761u >> 13);
+  w.host_expect.assign(w.host, w.host + w.host_bytes);
   std::memset(w.dev, 0, w.pool_bytes);
   w.expect.assign(w.pool_bytes, 0);
   CHECK(ft_pool_create(&w.pool, w.dev, w.pool_bytes, 64 * KiB, 0) == FT_OK);
@@ -214,11 +300,12 @@ int main() {
   CHECK(ft_pageable_window_add(w.pool, w.pageable.data(), w.pageable.size()) == FT_OK);
   CHECK(pass(w, false, "-", 0) == 0);  // also creates the per-device resources
   copy_engines_alone(w);
+  counters_run_out(w);
   const char *points[] = {"hipMemcpyAsync", "hipEventRecord", "hipStreamWaitEvent", "hipEventCreateWithFlags",
-                          "hipMalloc",      "hipHostMalloc",  "hipEventSynchronize", "launch_copy"};
+                          "hipMalloc",      "hipHostMalloc",  "hipEventSynchronize", "launch_copy", "launch_pieces"};
   int hit = 0;
   for (const char *point : points)
-    for (int n = 1; n <= 12; ++n) {
+    for (int n = 1; n <= 20; ++n) {
       g_point = point;
       g_n = n;
       const int failures = pass(w, true, point, n);
@@ -226,8 +313,8 @@ int main() {
       g_point = "-";
       CHECK(pass(w, false, "-", 0) == 0);  // and everything works again afterwards
     }
-  std::fprintf(stderr, "%d of %d injected failures were met by a call\n", hit, (int)(sizeof(points) / sizeof(points[0])) * 12);
-  CHECK(hit >= 30);
+  std::fprintf(stderr, "%d of %d injected failures were met by a call\n", hit, (int)(sizeof(points) / sizeof(points[0])) * 20);
+  CHECK(hit >= 60);
   CHECK(ft_pool_destroy(w.pool) == FT_OK);
   std::printf("fault_paths done\n");
   return 0;

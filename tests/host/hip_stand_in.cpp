@@ -8,10 +8,12 @@
 // thread: copies are memcpy, events are always complete, and a kernel launch walks the launch's
 // tickets one after the other - ticket -> tile -> (function, chunk) -> descriptor -> pieces, read
 // from the same tables the GPU kernel reads - and moves the bytes with memcpy. The order in which
-// tickets move bytes does not matter for a valid job, so the result is the GPU's.
+// tickets move bytes does not matter for a valid job, so the result is the GPU's. A launch of pieces walks
+// its tiles with the kernels' own arithmetic (ft_pieces.h).
 #include <hip/hip_runtime_api.h>
 
 #include <atomic>
+#include <cstdio>
 #include <cstdlib>
 #include <cstring>
 
@@ -20,17 +22,19 @@
 
 // Failure injection for tests of the error paths: stand_in_fail("hipMemcpyAsync", 3) makes the
 // third call from now of that function fail once (0 clears it). Names: the HIP calls below that
-// say FAIL_POINT, and "launch_copy".
+// say FAIL_POINT, "launch_copy" and "launch_pieces". stand_in_calls says how often one of them has been called.
 namespace {
 struct FailPoint {
   const char *name;
-  std::atomic<int> countdown{0};
+  std::atomic<int> countdown{0}, calls{0};
 };
 FailPoint g_fail[] = {{"hipMemcpyAsync"}, {"hipEventRecord"}, {"hipStreamWaitEvent"}, {"hipEventCreateWithFlags"},
-                      {"hipMalloc"},      {"hipHostMalloc"},  {"hipEventSynchronize"}, {"launch_copy"}};
+                      {"hipMalloc"},      {"hipHostMalloc"},  {"hipEventSynchronize"}, {"launch_copy"},
+                      {"launch_pieces"}};
 bool fails_now(const char *name) {
   for (FailPoint &f : g_fail)
     if (std::strcmp(f.name, name) == 0) {
+      f.calls += 1;
       int c = f.countdown.load();
       while (c > 0 && !f.countdown.compare_exchange_weak(c, c - 1)) {
       }
@@ -48,6 +52,12 @@ extern "C" int stand_in_fail(const char *name, int nth) {
       f.countdown.store(nth);
       return 0;
     }
+  return -1;
+}
+
+extern "C" int stand_in_calls(const char *name) {
+  for (FailPoint &f : g_fail)
+    if (std::strcmp(f.name, name) == 0) return f.calls.load();
   return -1;
 }
 
@@ -242,6 +252,46 @@ hipError_t launch_copy(const ClassTable &T, int, uint32_t workgroups, hipStream_
   }
   if (T.log)
     for (uint32_t g = 0; g < workgroups; ++g) T.wg_log[g].t_exit = g_clock++;
+  return hipSuccess;
+}
+
+// A tile of piece i, with the kernels' arithmetic.
+static void move_tile(const PieceTables &t, uint32_t i, uint32_t no, bool by_source) {
+  const uint64_t s = t.at[i].src, d = t.at[i].dst;
+  const auto move = [](uint64_t to, uint64_t from, uint32_t n) { std::memcpy(reinterpret_cast<void *>(to), reinterpret_cast<const void *>(from), n); };
+  uint32_t row, begin, n;
+  if (t.shape == nullptr || t.shape[i] == 0) {
+    run_tile(by_source ? s : d, t.len[i], t.tile, no, &begin, &n);
+    move(d + begin, s + begin, n);
+    return;
+  }
+  const PieceRows &r = t.shapes[t.shape[i] - 1];
+  if (r.per & kPartsOfRow) {
+    row_part(r, no, &row, &begin, &n);
+    move(d + (uint64_t)row * r.dst_pitch + begin, s + (uint64_t)row * r.src_pitch + begin, n);
+    return;
+  }
+  const RowWindows w = rows_tile(r, t.len[i], t.edges[i], no, &row);
+  const uint64_t s0 = s + (uint64_t)row * r.src_pitch, d0 = d + (uint64_t)row * r.dst_pitch;
+  for (uint32_t g = 0; g < w.count; ++g) {
+    const RowCursor c = row_window<16>(w, g);
+    const uint32_t col = row_window_col<16>(w, c);
+    move(d0 + (uint64_t)c.row * r.dst_pitch + col, s0 + (uint64_t)c.row * r.src_pitch + col, 16);
+  }
+  move(d0 + w.c0, s0 + w.c0, w.short_first);
+  move(d0 + (uint64_t)w.more * r.dst_pitch, s0 + (uint64_t)w.more * r.src_pitch, w.short_last);
+}
+
+hipError_t launch_pieces(const PieceTables &t, int cls, bool on_host, unsigned long long *counter, hipStream_t, hipEvent_t, hipEvent_t) {
+  if (t.n == 0 || t.ntiles == 0 || cls < 0 || cls > 2 || (on_host && !pieces_go_along(t)) || (cls != 2 && (t.tile > 4096 || t.shape != nullptr))) return hipErrorInvalidValue;
+  FAIL_POINT("launch_pieces", hipErrorLaunchFailure);
+  // the device's counter says which tile is next; it has to be zero for every launch that asks it
+  if (cls != 2 && piece_draws(cls, t) && (counter == nullptr || *reinterpret_cast<uint32_t *>(counter) != 0)) {
+    std::fprintf(stderr, "launch_pieces: a counter that is not zero\n");
+    std::abort();
+  }
+  for (uint32_t i = 0; i < t.n; ++i)
+    for (uint32_t no = 0; no < (i + 1 < t.n ? t.first[i + 1] : t.ntiles) - t.first[i]; ++no) move_tile(t, i, no, cls == 0);
   return hipSuccess;
 }
 
