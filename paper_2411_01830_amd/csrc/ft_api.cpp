@@ -761,7 +761,7 @@ int launch_as_pieces(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_byte
   if (!with_launch && (t.shape != nullptr || inline_layout_of(cp).end <= kInlineBytes)) return FT_OK;
   if (!with_launch) {
     const int rc = get_blob(p, bytes, true, &job->tables);
-    if (rc != FT_OK) return rc;
+    if (rc != FT_OK) return fail_submit(p, job, rc);
     std::memcpy(job->tables.host, h, bytes);
   }
   ClassRun &r = job->run[only];

@@ -284,6 +284,25 @@ static void counters_run_out(World &w) {
   CHECK(std::memcmp(w.dev, w.expect.data(), w.pool_bytes) == 0);
 }
 
+// A job out of pageable memory that fails for want of a table buffer gives its pinned buffer back: the next attempt takes the same one.
+static void pinned_buffer_comes_back(World &w) {
+  JobSpec j = make_runs(w, 0, 1, 8000, 100, 23);  // tables beyond every buffer that is there
+  for (size_t i = 0; i < j.d.size(); ++i) {
+    j.d[i].src_space = FT_PAGEABLE;
+    j.d[i].src = reinterpret_cast<uint64_t>(w.pageable.data() + i * 120);
+  }
+  const int before = stand_in_calls("hipHostMalloc");
+  for (int i = 0; i < 5; ++i) {
+    ft_job_t id = 0;
+    CHECK(stand_in_fail("hipMalloc", 1) == 0);
+    CHECK(ft_submit_transfers(w.pool, j.d.data(), (uint32_t)j.d.size(), j.wts.data(), 1, 2 * MiB, 0, nullptr, &id) == FT_EHIP);
+  }
+  CHECK(stand_in_fail("hipMalloc", 0) == 0);
+  CHECK(stand_in_calls("hipHostMalloc") - before <= 1);
+  for (ft_off_t off : w.allocs) CHECK(ft_slab_free(w.pool, off) == FT_OK);
+  w.allocs.clear();
+}
+
 int main() {
   World w;
   CHECK(hipMalloc(reinterpret_cast<void **>(&w.dev), w.pool_bytes) == hipSuccess);
@@ -301,6 +320,7 @@ int main() {
   CHECK(pass(w, false, "-", 0) == 0);  // also creates the per-device resources
   copy_engines_alone(w);
   counters_run_out(w);
+  pinned_buffer_comes_back(w);
   const char *points[] = {"hipMemcpyAsync", "hipEventRecord", "hipStreamWaitEvent", "hipEventCreateWithFlags",
                           "hipMalloc",      "hipHostMalloc",  "hipEventSynchronize", "launch_copy", "launch_pieces"};
   int hit = 0;
