@@ -738,7 +738,9 @@ int launch_with_uploaded_tables(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t
 
 // A job of one link class that is short as a list of pieces (ft_pieces.h) is launched as that list on the caller's stream: tables in the
 // launch where they fit, else uploaded in front of it. Not a job whose schedule or log may be asked for (FT_KEEP, FT_LOG): the pieces do not
-// hold the schedule. Nor a detached one that would hold the caller's stream for long. *launched says whether the job went this way.
+// hold the schedule. Nor a detached one that would hold the caller's stream for long, or whose general tables would not go with a launch:
+// it belongs on the library's streams, where detached jobs overlap and pool->pool launches are told of the host link's. *launched says
+// whether the job went this way.
 int launch_as_pieces(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_bytes, uint32_t flags, hipStream_t user, bool *launched) {
   *launched = false;
   if (flags & (FT_KEEP | FT_LOG | FT_PATH_DMA)) return FT_OK;
@@ -747,7 +749,8 @@ int launch_as_pieces(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_byte
     if (plan.cls[c].nchunks > 0) only = only == -1 ? c : -2;
   if (only < 0 || p->tuning[only].workgroups != 0 || p->tuning[only].tile_bytes != 0) return FT_OK;
   const ClassPlan &cp = plan.cls[only];
-  if ((flags & FT_DETACHED) && cp.payload > (only == FT_P2P ? kWaveTilesBytes : kWaveLinkTilesBytes)) return FT_OK;
+  const bool detached = (flags & FT_DETACHED) != 0, tables_fit = inline_layout_of(cp).end <= kInlineBytes;
+  if (detached && (cp.payload > (only == FT_P2P ? kWaveTilesBytes : kWaveLinkTilesBytes) || !tables_fit)) return FT_OK;
   const PieceRoom room = job_pieces(cp, only, chunk_bytes);
   if (room.pieces == 0) return FT_OK;
   const uint64_t bytes = align_up(piece_bytes(room), 256);
@@ -758,7 +761,7 @@ int launch_as_pieces(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_byte
   if (!build_pieces(cp, chunk_bytes, piece_tile(only, cp.payload), only == FT_H2P, &t)) return FT_OK;
   const bool with_launch = pieces_go_along(t);
   // Where they do not, the general tables may (few tensors in many chunks); and rows are then better off with them (job_pieces).
-  if (!with_launch && (t.shape != nullptr || inline_layout_of(cp).end <= kInlineBytes)) return FT_OK;
+  if (!with_launch && (t.shape != nullptr || tables_fit)) return FT_OK;
   if (!with_launch) {
     const int rc = get_blob(p, bytes, true, &job->tables);
     if (rc != FT_OK) return fail_submit(p, job, rc);

@@ -18,6 +18,7 @@
 
 extern "C" int stand_in_fail(const char *name, int nth);
 extern "C" int stand_in_calls(const char *name);
+extern "C" hipStream_t stand_in_stream(void);
 
 #define CHECK(c) do { if (!(c)) { std::fprintf(stderr, "FAIL %s line %d (point %s, n %d)\n", #c, __LINE__, g_point, g_n); std::abort(); } } while (0)
 static const char *g_point = "-";
@@ -303,6 +304,36 @@ static void pinned_buffer_comes_back(World &w) {
   w.allocs.clear();
 }
 
+// A detached job leaves the caller's stream alone unless it is small enough to go along with its launch, whatever it is launched as.
+static void detached_jobs(World &w) {
+  hipStream_t mine;
+  CHECK(hipStreamCreate(&mine) == hipSuccess);
+  struct {
+    int cls;
+    uint32_t n;
+    uint64_t bytes;
+    bool on_mine, as_pieces;
+  } cases[] = {{2, 20, 3000, true, true},   {2, 200, 3000, false, false}, {2, 300, 3000, false, false}, {0, 20, 3000, true, true}, {0, 20, 30000, true, true},
+               {0, 300, 1000, false, false}, {1, 20, 30000, true, true},   {1, 300, 1000, false, false}, {0, 20, 100000, false, false}};
+  for (auto &c : cases)
+    for (uint32_t flags : {0u, (uint32_t)FT_DETACHED}) {
+      JobSpec j = make_runs(w, c.cls, 2, c.n, c.bytes, 5);
+      const int pieces = stand_in_calls("launch_pieces"), copies = stand_in_calls("launch_copy");
+      ft_job_t id = 0;
+      CHECK(ft_submit_transfers(w.pool, j.d.data(), (uint32_t)j.d.size(), j.wts.data(), (uint32_t)j.wts.size(), 64 * KiB, flags, mine, &id) == FT_OK);
+      const bool on_mine = flags == 0 || c.on_mine, as_pieces = flags == 0 || c.as_pieces;
+      CHECK((stand_in_stream() == mine) == on_mine);
+      CHECK((stand_in_calls("launch_copy") == copies) == as_pieces && (as_pieces ? stand_in_calls("launch_pieces") > pieces : true));
+      CHECK(ft_wait(w.pool, id) == FT_OK);
+      expect_job(w, j);
+      for (ft_off_t off : w.allocs) CHECK(ft_slab_free(w.pool, off) == FT_OK);
+      w.allocs.clear();
+    }
+  CHECK(std::memcmp(w.dev, w.expect.data(), w.pool_bytes) == 0);
+  CHECK(std::memcmp(w.host, w.host_expect.data(), w.host_bytes) == 0);
+  CHECK(hipStreamDestroy(mine) == hipSuccess);
+}
+
 int main() {
   World w;
   CHECK(hipMalloc(reinterpret_cast<void **>(&w.dev), w.pool_bytes) == hipSuccess);
@@ -321,6 +352,7 @@ int main() {
   copy_engines_alone(w);
   counters_run_out(w);
   pinned_buffer_comes_back(w);
+  detached_jobs(w);
   const char *points[] = {"hipMemcpyAsync", "hipEventRecord", "hipStreamWaitEvent", "hipEventCreateWithFlags",
                           "hipMalloc",      "hipHostMalloc",  "hipEventSynchronize", "launch_copy", "launch_pieces"};
   int hit = 0;

@@ -55,6 +55,10 @@ extern "C" int stand_in_fail(const char *name, int nth) {
   return -1;
 }
 
+// The stream of the last launch.
+static std::atomic<hipStream_t> g_stream{nullptr};
+extern "C" hipStream_t stand_in_stream(void) { return g_stream.load(); }
+
 extern "C" int stand_in_calls(const char *name) {
   for (FailPoint &f : g_fail)
     if (std::strcmp(f.name, name) == 0) return f.calls.load();
@@ -167,10 +171,11 @@ std::atomic<uint64_t> g_clock{1};
 
 }  // namespace
 
-hipError_t launch_copy(const ClassTable &T, int, uint32_t workgroups, hipStream_t, hipEvent_t, hipEvent_t,
+hipError_t launch_copy(const ClassTable &T, int, uint32_t workgroups, hipStream_t stream, hipEvent_t, hipEvent_t,
                        const InlineBlob *blob) {
   if (workgroups == 0 || (T.inline_tables != 0) != (blob != nullptr)) return hipErrorInvalidValue;
   FAIL_POINT("launch_copy", hipErrorLaunchFailure);
+  g_stream = stream;
   const Tables tb = tables_of(T, blob);
   if (T.log)
     for (uint32_t g = 0; g < workgroups; ++g) {
@@ -282,9 +287,10 @@ static void move_tile(const PieceTables &t, uint32_t i, uint32_t no, bool by_sou
   move(d0 + (uint64_t)w.more * r.dst_pitch, s0 + (uint64_t)w.more * r.src_pitch, w.short_last);
 }
 
-hipError_t launch_pieces(const PieceTables &t, int cls, bool on_host, unsigned long long *counter, hipStream_t, hipEvent_t, hipEvent_t) {
+hipError_t launch_pieces(const PieceTables &t, int cls, bool on_host, unsigned long long *counter, hipStream_t stream, hipEvent_t, hipEvent_t) {
   if (t.n == 0 || t.ntiles == 0 || cls < 0 || cls > 2 || (on_host && !pieces_go_along(t)) || (cls != 2 && (t.tile > 4096 || t.shape != nullptr))) return hipErrorInvalidValue;
   FAIL_POINT("launch_pieces", hipErrorLaunchFailure);
+  g_stream = stream;
   // the device's counter says which tile is next; it has to be zero for every launch that asks it
   if (cls != 2 && piece_draws(cls, t) && (counter == nullptr || *reinterpret_cast<uint32_t *>(counter) != 0)) {
     std::fprintf(stderr, "launch_pieces: a counter that is not zero\n");
