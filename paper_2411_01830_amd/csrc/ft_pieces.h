@@ -104,8 +104,9 @@ struct OneRun {
   OneRun &operator=(const OneRun &) = delete;
 };
 
-// The room for a class of a job that is to be launched as pieces, none if it is not; and the tile.
-PieceRoom job_pieces(const ClassPlan &cp, int cls, uint64_t chunk_bytes);
+// The room for a class of a job that is to be launched as pieces, none if it is not; and the tile. tables_fit: the general tables
+// would travel with the launch.
+PieceRoom job_pieces(const ClassPlan &cp, int cls, uint64_t chunk_bytes, bool tables_fit);
 uint32_t piece_tile(int cls, uint64_t payload);
 // Workgroups, of one wavefront each, of a launch of that many tiles; and whether they draw tiles beyond their first from a counter.
 uint32_t piece_workgroups(int cls, uint32_t ntiles);

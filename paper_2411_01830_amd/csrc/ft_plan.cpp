@@ -179,16 +179,43 @@ int launch_code(const ClassPlan &cp, int cls, uint64_t chunk_bytes, bool tuned, 
 
 // ---- a class written out as pieces (ft_pieces.h)
 
+// How often the order goes from one function to another, and once for its begin.
+static uint64_t stretches(const ClassPlan &cp) {
+  uint64_t n = 0;
+  uint32_t last = ~0u;
+  for (size_t i = 0; i < cp.phases.size(); ++i) {
+    const Phase &ph = cp.phases[i];
+    const uint64_t chunks = (i + 1 < cp.phases.size() ? cp.phases[i + 1].rank_base : cp.nchunks) - ph.rank_base;
+    const uint64_t rounds = chunks / ph.nslots, rest = chunks % ph.nslots;
+    // round after round of the same slots: changes within one, and from one to the next
+    const Slot *s = cp.slots.data() + ph.slot_off;
+    uint64_t in_rest = 0, in_round = 0;
+    for (uint32_t k = 1; k < ph.nslots; ++k) {
+      if (k == rest) in_rest = in_round;
+      in_round += s[k].fl != s[k - 1].fl ? 1 : 0;
+    }
+    n += s[0].fl != last ? 1 : 0;
+    n += rounds * in_round + (rest != 0 ? in_rest : 0) + ((chunks - 1) / ph.nslots) * (s[0].fl != s[ph.nslots - 1].fl ? 1 : 0);
+    last = s[rest != 0 ? rest - 1 : ph.nslots - 1].fl;
+  }
+  return n;
+}
+
 PieceRoom piece_room(const ClassPlan &cp, uint64_t chunk_bytes, uint32_t tile) {
   PieceRoom room;
   if (chunk_bytes < 1024) return room;
-  // a chunk's end cuts a run or rows in two, but rows that a tile holds only a part of into whole rows and the two parts of the row
-  // that it falls into; with one function the chunks follow each other and nothing is cut
-  uint64_t each = 1;
-  if (cp.pitched != 0)
+  uint64_t cuts = 0;  // with one function the chunks follow each other and nothing is cut
+  if (cp.funcs.size() > 1 && cp.pitched == 0) {
+    // a function's chunks that follow each other are as good as one
+    cuts = stretches(cp);
+  } else if (cp.funcs.size() > 1) {
+    // a chunk's end cuts rows in two, but rows that a tile holds only a part of into whole rows and the two parts of the row that it
+    // falls into
+    uint64_t each = 1;
     for (const Xfer &x : cp.xfers) each = x.rows > 1 && x.row_bytes > tile ? 3 : each;
-  const uint64_t cuts = cp.funcs.size() == 1 ? 0 : cp.nchunks;
-  const uint64_t n = cp.xfers.size() + cuts * each + (cp.payload >> 30);
+    cuts = cp.nchunks * each;
+  }
+  const uint64_t n = cp.xfers.size() + cuts + (cp.payload >> 30);
   if (n > kMaxPieces) return room;
   room.pieces = n;
   room.shapes = cp.pitched;
@@ -453,7 +480,19 @@ bool build_pieces(const ClassPlan &cp, uint64_t chunk_bytes, uint32_t tile, bool
 // Rows go as pieces where these go along with the launch (quadrants of 4K frames, 16 descriptors, 99.5 MB, 48 -> 44 a pass,
 // kernel 38.6 -> 35.5); where they would be uploaded, writing them out costs more than the kernel gains (1536 crops 56.0 by the general
 // tables, 63.0 by pieces, kernels 24.4 and 19.8).
-PieceRoom job_pieces(const ClassPlan &cp, int cls, uint64_t chunk_bytes) {
+// Every place where the order goes from one function to another costs the host a piece to write out, 5.5 ns, and beyond kRunsAlong of them
+// the list has to be uploaded too. Passes (submit and wait), us, general tables -> pieces:
+//   general tables that travel with the launch, 8 tensors: 16 MiB 256 places 16.2 -> 17.9, 2048 places 18.0 -> 29.5; 64 MiB 256 places 39.2 ->
+//     40.9, 8192 places 131 -> 171
+//   uploaded ones, pool->pool by the wave kernel: 64 tensors, 16 MiB 256 places 24.4 -> 25.2, 1024 places 24.1 -> 29.3; 300 tensors, 16 MiB 64
+//     places 34.1 -> 32.8, 256 places 31.4 -> 31.3, 1024 places 30.6 -> 35.5
+//   by the copy kernel, whose tiles no chunk's end may cut: 40 tensors, 64 MiB 256 places 44.6 -> 37.0, 8192 places 137 -> 92
+//   host link: 64 tensors, 4 MiB 256 places 95.7 -> 93.1, 1024 places 95.2 -> 96.8; 16 MiB 256 places 312.9 -> 312.8, 1024 places
+//     314.7 -> 316.8; 300 tensors, 60 MiB 960 places 1147 -> 1130, 15 360 places 1172 -> 1222; 1000 tensors, 4 MiB 1024 places 130.9 -> 113.5
+// so the places are counted before anything is written: kRunsAlong of them where the general tables travel along and for the wave
+// kernel's jobs, over the link 256 and one for every 64 KiB; and where there are many tensors, which the general tables have to hold too, one
+// for every two of them, over the link two for each.
+PieceRoom job_pieces(const ClassPlan &cp, int cls, uint64_t chunk_bytes, bool tables_fit) {
   if (cls == FT_P2P && cp.payload > kCacheResidentBytes) return PieceRoom();
   if (cls == FT_H2P && cp.xfers.size() == 1 && cp.payload > 128u << 10 && ((cp.xfers[0].src | cp.xfers[0].dst) & 15) == 0) return PieceRoom();
   if (cp.pitched != 0 && (cls != FT_P2P || cp.xfers.size() > kRowsAlong)) return PieceRoom();
@@ -463,7 +502,12 @@ PieceRoom job_pieces(const ClassPlan &cp, int cls, uint64_t chunk_bytes) {
     if (odd < cp.payload / 8) return PieceRoom();
   }
   const PieceRoom room = piece_room(cp, chunk_bytes, piece_tile(cls, cp.payload));
-  return cp.pitched != 0 && room.pieces > 2 * kRowsAlong ? PieceRoom() : room;
+  if (room.pieces == 0 || cp.pitched != 0) return room.pieces > 2 * kRowsAlong ? PieceRoom() : room;
+  const uint64_t places = room.pieces - cp.xfers.size();
+  if (places <= kRunsAlong) return room;
+  if (tables_fit) return PieceRoom();
+  if (cls != FT_P2P) return places <= 256 + (cp.payload >> 16) || places <= 2 * cp.xfers.size() ? room : PieceRoom();
+  return places <= cp.xfers.size() / 2 || launch_code(cp, cls, chunk_bytes, false, true) < kWaveTiles ? room : PieceRoom();
 }
 
 uint32_t piece_tile(int cls, uint64_t payload) {

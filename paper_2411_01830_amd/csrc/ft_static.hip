@@ -127,19 +127,20 @@ extern "C" int ft_submit_static(ft_pool *p, const ft_desc *descs, uint32_t ndesc
     if (cp.nchunks == 0) continue;
     StaticClass &s = sc[c];
     s.used = any = true;
-    if (c == FT_P2P) s.room = job_pieces(cp, c, chunk_bytes);  // (there is no counter pair here for the host link's)
+    if (c == FT_P2P) s.room = job_pieces(cp, c, chunk_bytes, false);  // (there is no counter pair here for the host link's)
     // Pieces that do not go along with their launch take a small launch for every 3 KiB, and so do the general tables: few tensors in
     // many chunks are shorter by these (20 tensors of 10 functions in chunks of 64 KiB, 40 MB: 18.4 us, by 640 pieces 26.9).
     const auto launches = [](uint64_t bytes) { return (bytes + kInlineBytes - 1) / kInlineBytes; };
     const Layout general = layout_of(cp, 0, 1);
     if (s.room.pieces != 0 && piece_bytes(s.room) <= kStaticTableBytes) {
       if (tables_with_descriptor_table(cp, c, with_p2p, chunk_bytes) > kStaticClassBytes) return FT_E2BIG;
-      s.words.resize((piece_bytes(s.room) + 7) / 8);
-      s.pieces = piece_places(reinterpret_cast<char *>(s.words.data()), s.room);
-      if (build_pieces(cp, chunk_bytes, piece_tile(c, cp.payload), false, &s.pieces) &&
-          (pieces_go_along(s.pieces) || (s.room.shapes == 0 && launches(piece_bytes(s.room)) < launches(general.end - general.phases))))
-        continue;
-      s.pieces = PieceTables();
+      const bool shorter = s.room.shapes == 0 && launches(piece_bytes(s.room)) < launches(general.end - general.phases);
+      if (shorter || s.room.shapes != 0 || s.room.pieces - cp.xfers.size() <= kRunsAlong) {  // (else they can't go along: nothing is written out)
+        s.words.resize((piece_bytes(s.room) + 7) / 8);
+        s.pieces = piece_places(reinterpret_cast<char *>(s.words.data()), s.room);
+        if (build_pieces(cp, chunk_bytes, piece_tile(c, cp.payload), false, &s.pieces) && (pieces_go_along(s.pieces) || shorter)) continue;
+        s.pieces = PieceTables();
+      }
     }
     s.code = launch_code(cp, c, chunk_bytes, false, true);  // the classes run one after another
     if (s.code >= kWaveTiles) {

@@ -145,9 +145,13 @@ static void job(std::mt19937_64 &r) {
 
   // the general walk, chunk by chunk
   std::vector<Byte> order;
+  uint64_t places = 0;  // where it goes from one function to another
+  uint32_t before = ~0u;
   for (uint64_t rank = 0; rank < cp.nchunks; ++rank) {
     const ChunkId id = decode_rank(cp.phases.data(), (uint32_t)cp.phases.size(), cp.slots.data(), rank);
     const Func &fn = cp.funcs[id.fl];
+    places += id.fl != before;
+    before = id.fl;
     uint64_t pos = id.k * C;
     const uint64_t end = pos + C < fn.stream_bytes ? pos + C : fn.stream_bytes;
     uint32_t x = find_xfer(cp.xfers.data(), fn.desc_off, fn.desc_off + fn.ndesc - 1, pos);
@@ -166,6 +170,7 @@ static void job(std::mt19937_64 &r) {
     for (uint32_t tile : {1024u, 2048u, 8192u}) {
       const PieceRoom room = piece_room(cp, C, tile);
       if (room.pieces == 0) continue;
+      if (cp.pitched == 0) CHECK(room.pieces == cp.xfers.size() + (cp.funcs.size() == 1 ? 0 : places));
       std::vector<uint32_t> words(piece_bytes(room) / 4);  // no more than that: the sanitizer sees a write beyond
       PieceTables t = piece_places(reinterpret_cast<char *>(words.data()), room);
       CHECK(build_pieces(cp, C, tile, by_source != 0, &t));
@@ -289,11 +294,55 @@ static void refused() {
   CHECK(with(100, 1, 100, 1024, kMaxPieces - 2) && !with(100, 1, 100, 1024, kMaxPieces - 1));
 }
 
+// What a list would cost the host is known before it is written: `n` tensors of equal size, `total` MiB of `nf` functions in chunks of `chunk`
+// KiB.
+static void priced() {
+  auto takes = [](int cls, uint32_t n, uint64_t total, uint32_t nf, uint64_t chunk, bool odd, bool tables_fit) {
+    ClassPlan cp;
+    const uint64_t size = (total << 20) / n / 16 * 16;
+    for (uint32_t f = 0; f < nf; ++f) {
+      Func fn{};
+      fn.func = f;
+      fn.weight = 1;
+      fn.desc_off = (uint32_t)cp.xfers.size();
+      for (uint32_t i = f; i < n; i += nf) {
+        Xfer x{};
+        x.src = 0x100000000000ull + i * (size + 4096) + (odd ? 3 : 0);
+        x.dst = 0x200000000000ull + i * (size + 4096);
+        x.row_bytes = x.src_pitch = x.dst_pitch = size;
+        x.rows = 1;
+        x.stream_off = fn.stream_bytes;
+        fn.stream_bytes += size;
+        fn.ndesc += 1;
+        cp.xfers.push_back(x);
+      }
+      fn.nchunks = (fn.stream_bytes + (chunk << 10) - 1) / (chunk << 10);
+      cp.payload += fn.stream_bytes;
+      cp.funcs.push_back(fn);
+    }
+    CHECK(build_phases(cp.funcs, cp.phases, cp.slots, &cp.nchunks) == FT_OK);
+    return job_pieces(cp, cls, chunk << 10, tables_fit).pieces != 0;
+  };
+  // few large tensors whose general tables travel along
+  CHECK(takes(FT_P2P, 8, 64, 8, 2048, false, true) && takes(FT_P2P, 8, 64, 1, 8, false, true));
+  CHECK(!takes(FT_P2P, 8, 64, 8, 64, false, true) && !takes(FT_P2P, 8, 64, 8, 8, false, true) && !takes(FT_P2P, 8, 16, 8, 8, false, true));
+  CHECK(!takes(FT_P2P, 40, 60, 8, 8, true, true) && takes(FT_P2P, 40, 40, 4, 512, true, true));
+  // uploaded: beside the copy kernel any number, beside the wave kernel what a launch could hold
+  CHECK(takes(FT_P2P, 64, 64, 8, 8, false, false) && !takes(FT_P2P, 64, 64, 8, 8, true, false) && !takes(FT_P2P, 64, 32, 8, 64, false, false));
+  CHECK(takes(FT_P2P, 1024, 16, 4, 256, false, false) && !takes(FT_P2P, 300, 16, 4, 16, false, false) &&
+        takes(FT_P2P, 2048, 16, 4, 16, false, false));
+  for (int cls : {(int)FT_H2P, (int)FT_P2H})
+    CHECK(takes(cls, 64, 4, 4, 16, false, false) && !takes(cls, 64, 4, 4, 4, false, false) && takes(cls, 300, 60, 4, 64, false, false) &&
+          !takes(cls, 300, 60, 4, 16, false, false) && !takes(cls, 8, 60, 4, 64, false, true) && takes(cls, 8, 16, 4, 256, false, true) &&
+          takes(cls, 1000, 4, 4, 4, false, false) && !takes(cls, 1000, 16, 4, 4, false, false));
+}
+
 int main(int argc, char **argv) {
   const uint64_t first = argc > 1 ? strtoull(argv[1], 0, 10) : 1, count = argc > 2 ? strtoull(argv[2], 0, 10) : 50;
   refused();
   long_run();
   table_uploads();
+  priced();
   for (g_seed = first; g_seed < first + count; ++g_seed) {
     std::mt19937_64 r(g_seed);
     for (int i = 0; i < 6; ++i) job(r);
