@@ -22,7 +22,7 @@ namespace ft {
 template <uint32_t CAP, uint32_t SHAPES>
 struct PieceArgs {
   static constexpr bool kRows = SHAPES != 0, kOne = CAP == 1;
-  uint32_t n, tile;
+  uint32_t n, tile, ntiles;
   uint64_t src0, dst0;
   struct {
     uint32_t src, dst;  // bytes from src0 and dst0
@@ -35,7 +35,7 @@ struct PieceArgs {
 // and tables in device memory, of runs
 struct PieceRefs {
   static constexpr bool kRows = false, kOne = false;
-  uint32_t n, tile;
+  uint32_t n, tile, ntiles;
   const PieceSides *at;
   const uint32_t *first, *len;
 };
@@ -192,7 +192,8 @@ __device__ __forceinline__ void move_tile(const Piece &p, uint32_t lane) {
 
 template <int NT, class A>
 __global__ __launch_bounds__(64) void ft_piece_kernel(A args) {
-  move_tile<NT, A::kRows>(find_piece(args, blockIdx.x, threadIdx.x), threadIdx.x);
+  const uint32_t t = A::kOne ? blockIdx.x : tile_of_workgroup(blockIdx.x, args.ntiles);
+  move_tile<NT, A::kRows>(find_piece(args, t, threadIdx.x), threadIdx.x);
 }
 
 // The same over the host link, which has to be full but not crowded: 64 wavefronts with 4 KiB of loads from host memory each, one on
@@ -268,6 +269,7 @@ hipError_t launch_along(const PieceTables &t, const Launch &l) {
   PieceArgs<CAP, SHAPES> a;
   a.n = t.n;
   a.tile = t.tile;
+  a.ntiles = t.ntiles;
   a.src0 = t.src0;
   a.dst0 = t.dst0;
   for (uint32_t i = 0; i < t.n; ++i) {
@@ -292,7 +294,7 @@ hipError_t launch_pieces(const PieceTables &t, int cls, bool on_host, unsigned l
   if (t.n == 0 || t.ntiles == 0 || cls < 0 || cls > 2 || (on_host && !pieces_go_along(t)) || (cls != 2 && t.tile > 4096)) return hipErrorInvalidValue;
   const Launch l = {cls, t.ntiles, counter, stream, ev_start, ev_stop};
   const bool rows = t.shape != nullptr;
-  if (!on_host) return rows ? hipErrorInvalidValue : launch(PieceRefs{t.n, t.tile, t.at, t.first, t.len}, l);
+  if (!on_host) return rows ? hipErrorInvalidValue : launch(PieceRefs{t.n, t.tile, t.ntiles, t.at, t.first, t.len}, l);
   if (rows) {
     if (t.n <= 16 && t.nshapes <= 16) return launch_along<16, 16>(t, l);
     if (t.n <= 64) return launch_along<64, 64>(t, l);

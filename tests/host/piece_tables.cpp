@@ -337,12 +337,30 @@ static void priced() {
           takes(cls, 1000, 4, 4, 4, false, false) && !takes(cls, 1000, 16, 4, 4, false, false));
 }
 
+// Every tile is some workgroup's, no more than seven places from its own; and of tiles that repeat after 2, 4 or 8 every die (b % 8) has as
+// many of one kind as of another in 64 workgroups.
+static void tiles_over_dies() {
+  for (uint32_t ntiles = 1; ntiles < 700; ++ntiles) {
+    std::vector<uint32_t> seen(ntiles, 0), kinds(64, 0);
+    for (uint32_t b = 0; b < ntiles; ++b) {
+      const uint32_t t = tile_of_workgroup(b, ntiles);
+      CHECK(t < ntiles && t / 8 == b / 8);
+      seen[t] += 1;
+      kinds[b % 8 * 8 + t % 8] += 1;
+      if ((b + 1) % 64 == 0)
+        for (uint32_t k : kinds) CHECK(k == (b + 1) / 64);
+    }
+    for (uint32_t s : seen) CHECK(s == 1);
+  }
+}
+
 int main(int argc, char **argv) {
   const uint64_t first = argc > 1 ? strtoull(argv[1], 0, 10) : 1, count = argc > 2 ? strtoull(argv[2], 0, 10) : 50;
   refused();
   long_run();
   table_uploads();
   priced();
+  tiles_over_dies();
   for (g_seed = first; g_seed < first + count; ++g_seed) {
     std::mt19937_64 r(g_seed);
     for (int i = 0; i < 6; ++i) job(r);
