@@ -108,9 +108,13 @@ struct OneRun {
 // would travel with the launch.
 PieceRoom job_pieces(const ClassPlan &cp, int cls, uint64_t chunk_bytes, bool tables_fit);
 uint32_t piece_tile(int cls, uint64_t payload);
-// Workgroups, of one wavefront each, of a launch of that many tiles; and whether they draw tiles beyond their first from a counter.
+// Workgroups, of one wavefront each, of a launch of that many tiles; and whether they draw tiles beyond their first from a counter: those
+// of one piece, which has no order to keep, are dealt out, unless their number would leave some wavefronts a round more than others.
 uint32_t piece_workgroups(int cls, uint32_t ntiles);
-inline bool piece_draws(int cls, const PieceTables &t) { return t.n > 1 && piece_workgroups(cls, t.ntiles) < t.ntiles; }
+inline bool piece_draws(int cls, const PieceTables &t) {
+  const uint32_t workgroups = piece_workgroups(cls, t.ntiles);
+  return workgroups < t.ntiles && (t.n > 1 || (workgroups & (workgroups - 1)) != 0);
+}
 
 // ---- what a tile covers: the arithmetic of the kernels, so that it can be checked without a GPU
 

@@ -197,12 +197,12 @@ __global__ __launch_bounds__(64) void ft_piece_kernel(A args) {
 }
 
 // The same over the host link, which has to be full but not crowded: 64 wavefronts with 4 KiB of loads from host memory each, one on
-// a compute unit, or 128 with 4 KiB of stores, and each goes on to further tiles. Time beyond what the link takes for
+// a compute unit, or 48 (in short jobs 128) with 4 KiB of stores, and each goes on to further tiles. Time beyond what the link takes for
 // the bytes, us: 4 MiB in 32 tensors from the host 2.5 (the class's own kernel, 64 workgroups of 16 KiB, 9.5), to the host 2.4 (6.5);
 // 128 or 256 wavefronts from the host 5.8, four a workgroup 10, every tile at once 39.
 //
 // A wavefront's first two tiles are given, the others are drawn from the counter, in the order of the pieces (of one piece they are
-// dealt out). A tile costs one draw, so the draws of a launch are as many as its tiles, and who has made the last one sets the
+// dealt out where all wavefronts get as many). A tile costs one draw, so the draws of a launch are as many as its tiles, and who has made the last one sets the
 // counter back. (Where no wavefront has a second tile the answers are not looked at, and the counter may be any.) A tile's loads, the draw
 // in front of them and the search for the next tile's piece are waited for together, and the next tile's loads follow the
 // stores at once.
@@ -300,7 +300,7 @@ hipError_t launch_pieces(const PieceTables &t, int cls, bool on_host, unsigned l
     if (t.n <= 64) return launch_along<64, 64>(t, l);
     return launch_along<kRowsAlong, 16>(t, l);
   }
-  if (t.n == 1) return launch_along<1, 0>(t, l);
+  if (t.n == 1 && (cls == 2 || !piece_draws(cls, t))) return launch_along<1, 0>(t, l);
   if (t.n <= 16) return launch_along<16, 0>(t, l);
   if (t.n <= 48) return launch_along<48, 0>(t, l);
   if (t.n <= 128) return launch_along<128, 0>(t, l);

@@ -517,7 +517,12 @@ uint32_t piece_tile(int cls, uint64_t payload) {
 
 uint32_t piece_workgroups(int cls, uint32_t ntiles) {
   if (cls == FT_P2P) return ntiles;
-  return std::min(ntiles, cls == FT_H2P ? 64u : 128u);
+  if (cls == FT_H2P) return std::min(ntiles, 64u);
+  // Towards the host 48 fill the link as well as 128 do, whose stores, queued on their way to it, hold up every other kernel's: pool->pool
+  // jobs of 64 MiB on another stream, us each, beside 60 MiB to the host by 128, 96, 64, 48, 32 wavefronts 375, 281, 141, 62, 26 (beside
+  // the class's own kernel 186), the job itself 1103.5, 1103.5, 1104.7, 1104.9, 1135.9, alone 1102 with any of them. Short jobs, which
+  // are over in 20 us, keep 128: one tensor of 256 KiB 6.2, 6.6 with 48, of 1 MiB 20.0, 20.8.
+  return ntiles <= 256 ? std::min(ntiles, 128u) : 48u;
 }
 
 // Tile of a wave-kernel launch. About 4000 tiles, sixteen wavefronts on every compute unit, each with a tile that it can

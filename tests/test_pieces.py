@@ -173,7 +173,7 @@ def test_the_largest_job_of_pieces_and_the_next():
         eng.close()
 
 
-# as above; the tiles are 1, 2 or 4 KiB, the workgroups at most 64 from the host and 128 towards it
+# as above; the tiles are 1, 2 or 4 KiB, the workgroups at most 64 from the host and towards it 128, of more than 256 tiles 48
 LINK_CASES = [
     ("one byte", lambda g: [(1, 1, 0, 0, 0, 3, 9)], [1], 2 * MiB, True),
     *[(f"one tensor of {n}", lambda g, n=n: [(n, 1, 0, 0, 0, 7, 4)], [1], 2 * MiB, True) for n in (15, 17, 1025, 32 * KiB, 32 * KiB + 1, 128 * KiB, 128 * KiB + 1, 3 * MiB)],
@@ -229,7 +229,7 @@ def test_pieces_over_the_host_link(case, to_host):
             eng.wait(jg)
             if flags & fmt.FT_TIMING:
                 st = binding.job_stats(eng.pool, jg).cls[cls]
-                own = st.tile_bytes == (1024 if payload <= 32 * KiB else 2048 if payload <= 128 * KiB else 4096) and st.workgroups == min(st.tickets, 128 if to_host else 64)
+                own = st.tile_bytes == (1024 if payload <= 32 * KiB else 2048 if payload <= 128 * KiB else 4096) and st.workgroups == min(st.tickets, (48 if st.tickets > 256 else 128) if to_host else 64)
                 assert own == (along != "general" and (to_host or along != "to the host")), (st.tile_bytes, st.workgroups, st.tickets)
                 assert along not in (True, False) or st.in_launch == (1 if along else 0)
                 assert eng.job_schedule(jg, cls) == orc.job_schedule(jo, cls)
