@@ -116,6 +116,9 @@ inline bool piece_draws(int cls, const PieceTables &t) {
   return workgroups < t.ntiles && (t.n > 1 || (workgroups & (workgroups - 1)) != 0);
 }
 
+// LDS that a workgroup asks for without using it, so that a compute unit of 160 KiB takes no more of them at once.
+uint32_t piece_lds(int cls, const PieceTables &t);
+
 // ---- what a tile covers: the arithmetic of the kernels, so that it can be checked without a GPU
 
 // The tile of workgroup b where every tile has one. The eight dies take the workgroups in turn, b % 8 says which, and each begins its own in

@@ -245,7 +245,7 @@ namespace {
 
 struct Launch {
   int cls;
-  uint32_t ntiles;
+  uint32_t ntiles, lds;
   unsigned long long *counter;
   hipStream_t stream;
   hipEvent_t ev_start, ev_stop;
@@ -256,7 +256,7 @@ hipError_t launch(const A &a, const Launch &l) {
   static_assert(sizeof(A) + sizeof(LinkTiles) <= 4096, "kernel arguments end at 4 KiB");
   const dim3 grid(piece_workgroups(l.cls, l.ntiles)), block(64);
   const LinkTiles tiles = {l.counter, l.ntiles};
-  if (l.cls == 2) hipExtLaunchKernelGGL((ft_piece_kernel<0, A>), grid, block, 0, l.stream, l.ev_start, l.ev_stop, 0, a);
+  if (l.cls == 2) hipExtLaunchKernelGGL((ft_piece_kernel<0, A>), grid, block, l.lds, l.stream, l.ev_start, l.ev_stop, 0, a);
   else if constexpr (A::kRows) return hipErrorInvalidValue;
   else if (l.cls == 0) hipExtLaunchKernelGGL((ft_link_piece_kernel<kFromHost, A>), grid, block, 0, l.stream, l.ev_start, l.ev_stop, 0, a, tiles);
   else hipExtLaunchKernelGGL((ft_link_piece_kernel<kToHost, A>), grid, block, 0, l.stream, l.ev_start, l.ev_stop, 0, a, tiles);
@@ -292,7 +292,7 @@ hipError_t launch_along(const PieceTables &t, const Launch &l) {
 hipError_t launch_pieces(const PieceTables &t, int cls, bool on_host, unsigned long long *counter, hipStream_t stream, hipEvent_t ev_start,
                          hipEvent_t ev_stop) {
   if (t.n == 0 || t.ntiles == 0 || cls < 0 || cls > 2 || (on_host && !pieces_go_along(t)) || (cls != 2 && t.tile > 4096)) return hipErrorInvalidValue;
-  const Launch l = {cls, t.ntiles, counter, stream, ev_start, ev_stop};
+  const Launch l = {cls, t.ntiles, piece_lds(cls, t), counter, stream, ev_start, ev_stop};
   const bool rows = t.shape != nullptr;
   if (!on_host) return rows ? hipErrorInvalidValue : launch(PieceRefs{t.n, t.tile, t.ntiles, t.at, t.first, t.len}, l);
   if (rows) {

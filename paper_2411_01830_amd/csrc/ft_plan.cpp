@@ -525,6 +525,17 @@ uint32_t piece_workgroups(int cls, uint32_t ntiles) {
   return ntiles <= 256 ? std::min(ntiles, 128u) : 48u;
 }
 
+// Lists of runs of more than 48 MiB that go with their launch: eight wavefronts on a compute unit, 16 MiB under way, as much as the class's
+// own kernel has. That is enough for them, and all 32 that a unit could take are too many beside the host link. us, 32 -> 8 a unit: alone
+// 64.5 MB 20.1 -> 20.0, 56 MiB 18.0 -> 17.9, 96 MiB 34.7 -> 34.8, 124 MiB 45.8 -> 45.9, 64 MiB at odd addresses 20.7 -> 20.9; beside one
+// tensor of 128 MiB from the host on another stream 64 MiB 46.7 -> 34.1 a job, the tensor 2405..2425 -> 2366 (beside the class's own
+// kernel 40.6 and 2379), 100 MiB 49.0 -> 39.0, 2424 -> 2390 (51.3 and 2374), 64 MiB at odd addresses 52 -> 37, 2380 -> 2360.
+// Not uploaded lists, whose wavefronts have more to wait for (600 tensors 100 MiB 39.7 -> 40.3 alone, 1000 of 50 MiB 18.3 -> 18.8; 300 of
+// 60 MiB beside the tensor 63 -> 49, it 2395 -> 2374), nor rows (99.5 MB 36 -> 38 alone; beside the tensor 39 -> 38, it 2440 -> 2362).
+uint32_t piece_lds(int cls, const PieceTables &t) {
+  return cls == FT_P2P && t.shape == nullptr && t.n <= kRunsAlong && t.ntiles > (48u << 20) / 8192 ? 160u * 1024 / 8 : 0u;
+}
+
 // Tile of a wave-kernel launch. About 4000 tiles, sixteen wavefronts on every compute unit, each with a tile that it can
 // hold in registers: more tiles cost more decodes than they hide (15.6 MB in 1024 tensors: 4000 tiles 11.0 us, 7000
 // 12.2, 2000 11.7), fewer leave compute units idle. 2 KiB is two loads per lane. Host link: see link_code; up to 128 KiB

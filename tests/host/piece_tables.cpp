@@ -354,6 +354,31 @@ static void tiles_over_dies() {
   }
 }
 
+// Which launches keep compute units free for others: lists that go along with more tiles than 48 MiB has, no rows, nothing over the link.
+static void units_kept_free() {
+  PieceRows rows{};
+  uint32_t shape = 1;
+  for (int cls = 0; cls < 3; ++cls)
+    for (uint32_t n : {1u, kRunsAlong, kRunsAlong + 1})
+      for (uint32_t ntiles : {1u, 6144u, 6145u, 16384u}) {
+        PieceTables t;
+        t.n = n;
+        t.ntiles = ntiles;
+        t.tile = 8192;
+        const uint32_t lds = piece_lds(cls, t);
+        CHECK((lds != 0) == (cls == 2 && n <= kRunsAlong && ntiles > 6144) && (lds == 0 || (160u << 10) / lds == 8));
+        t.shape = &shape;
+        t.shapes = &rows;
+        CHECK(piece_lds(cls, t) == 0);
+      }
+  PieceTables t;  // jobs of up to 20 MiB have small tiles, and not too many of them
+  for (uint64_t payload : {10u << 20, 20u << 20, 48u << 20}) {
+    t.n = kRunsAlong;
+    t.ntiles = (uint32_t)(payload / piece_tile(FT_P2P, payload)) + (payload < 48u << 20 ? t.n : 0);
+    CHECK(piece_lds(FT_P2P, t) == 0);
+  }
+}
+
 int main(int argc, char **argv) {
   const uint64_t first = argc > 1 ? strtoull(argv[1], 0, 10) : 1, count = argc > 2 ? strtoull(argv[2], 0, 10) : 50;
   refused();
@@ -361,6 +386,7 @@ int main(int argc, char **argv) {
   table_uploads();
   priced();
   tiles_over_dies();
+  units_kept_free();
   for (g_seed = first; g_seed < first + count; ++g_seed) {
     std::mt19937_64 r(g_seed);
     for (int i = 0; i < 6; ++i) job(r);
