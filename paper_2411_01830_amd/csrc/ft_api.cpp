@@ -581,8 +581,8 @@ int launch_with_the_launch(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chun
 }
 
 // Tables from a blob's pinned twin to its device buffer, as one piece from the host (beyond 1 GiB of them, sixteen million descriptors, as
-// several, one behind the other): at most 64 tiles of 4 KiB in flight, which is what fills the link (table_fetch_code tells why no more). Below 16 KiB, too, that is no slower than the runtime's
-// copy, which is a launch as well.
+// several, one behind the other): at most 64 tiles of 4 KiB in flight, which is what fills the link (tables_by_kernel tells why no
+// more). Below 16 KiB, too, that is no slower than the runtime's copy, which is a launch as well.
 hipError_t upload_pieces(const Blob &b, uint64_t bytes, hipStream_t stream) {
   for (uint64_t at = 0; at < bytes;) {
     const OneRun part(reinterpret_cast<uint64_t>(b.host) + at, reinterpret_cast<uint64_t>(b.dev) + at, bytes - at, piece_tile(FT_H2P, bytes), true);
@@ -593,10 +593,10 @@ hipError_t upload_pieces(const Blob &b, uint64_t bytes, hipStream_t stream) {
   return hipSuccess;
 }
 
-// The same of a job by the general tables, on `stream`: by the runtime's copy, or (the rule stands with table_fetch_code) as above.
+// The same of a job by the general tables, on `stream`: by the runtime's copy, or (the rule stands with tables_by_kernel) as above.
 // dma: a job by the copy engines, which does not wait for a free compute unit.
 hipError_t upload_tables(const Blob &b, uint64_t bytes, bool dma, hipStream_t stream) {
-  if (dma || table_fetch_code(bytes) == 0) return hipMemcpyAsync(b.dev, b.host, bytes, hipMemcpyHostToDevice, stream);
+  if (dma || !tables_by_kernel(bytes)) return hipMemcpyAsync(b.dev, b.host, bytes, hipMemcpyHostToDevice, stream);
   return upload_pieces(b, bytes, stream);
 }
 

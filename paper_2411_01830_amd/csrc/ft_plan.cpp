@@ -556,16 +556,11 @@ uint64_t wave_workgroups(int cu_count, int code, uint64_t ntickets) {
 
 // From 16 KiB on the runtime hands its copy to the copy engine, whose start and whose completion signal the kernel behind it
 // waits for (10 us in front of the launch), and what it wrote comes from HBM (2000 functions, 600 KB: kernel behind it 287 us, behind a
-// launch 258). Submit to end of wait, 8 KB tensors, runtime's copy -> wave kernel: 256 of them 38.5 -> 28.7 us, 1024 63.5 ->
-// 55.0 us; 128 of them (12 KiB, which the runtime copies with a kernel too) 24.5 us either way. Every wavefront has a tile
-// of host memory in flight: with a workgroup per KiB of any amount 1 GiB pool->pool beside a submit of 16 384 descriptors took
-// 341 us instead of 325, a host->pool job 1199 instead of 1193. So beyond the 256 KiB of reads that fill the link the
-// tiles are dealt out to 256 wavefronts. As one piece, 64 wavefronts of 4 KiB, the fetch itself is shorter still: 64 KiB 4.9 -> 3.8 us of
-// kernel time, 97 KiB 5.7 -> 5.1.
-int table_fetch_code(uint64_t bytes) {
-  if (bytes < 16 * 1024) return 0;
-  return (bytes <= 256 * 1024 ? kWaveTiles : kWaveLink) | kWaveFromHost;
-}
+// launch 258). Submit to end of wait, 8 KB tensors, runtime's copy -> a kernel: 256 of them 38.5 -> 28.7 us, 1024 63.5 -> 55.0 us;
+// 128 of them (12 KiB, which the runtime copies with a kernel too) 24.5 us either way. The kernel has at most 256 KiB of host
+// memory in flight, 64 wavefronts of 4 KiB, which fills the link: with a wavefront per KiB of any amount 1 GiB pool->pool beside a
+// submit of 16 384 descriptors took 341 us instead of 325, a host->pool job 1199 instead of 1193.
+bool tables_by_kernel(uint64_t bytes) { return bytes >= 16 * 1024; }
 
 bool wave_draws(int code, uint64_t workgroups, uint64_t ntickets, bool single) {
   return !single && wave_counts(workgroups, wave_code_threads(code) / 64, ntickets);

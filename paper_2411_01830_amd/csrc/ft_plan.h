@@ -79,10 +79,9 @@ uint64_t wave_workgroups(int cu_count, int code, uint64_t ntickets);
 // Whether a wave-kernel launch draws tickets from its counter; single: its table says one function with one descriptor.
 bool wave_draws(int code, uint64_t workgroups, uint64_t ntickets, bool single);
 
-// How a job's tables of this many bytes reach the device: 0 by the runtime's copy, otherwise by the engine's own kernel:
-// as one piece from the host (ft_pieces.h). The code and kTableTile are the wave kernel's shape within the same bound on reads in flight.
-constexpr uint64_t kTableTile = 1024;
-int table_fetch_code(uint64_t bytes);
+// Whether a job's tables of this many bytes reach the device by the engine's own kernel, as one piece from the host (ft_pieces.h), or
+// by the runtime's copy.
+bool tables_by_kernel(uint64_t bytes);
 
 // Bytes per ticket and tickets per chunk for a chunk size and a wanted tile size.
 void tile_shape(uint64_t chunk_bytes, uint64_t want_tile, uint64_t *tile_bytes, uint32_t *tiles_per_chunk);

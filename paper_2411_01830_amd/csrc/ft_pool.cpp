@@ -169,18 +169,6 @@ Allocation *SlabPool::at(uint64_t start) {
   return last_at_or_before(start, &p) && entry(p)->start == start ? entry(p)->al : nullptr;
 }
 
-Allocation *SlabPool::owner(uint64_t off, uint64_t extent, uint64_t *start_out, Place *near) {
-  const Entry *e = find(off, extent, near);
-  if (e == nullptr) return nullptr;
-  if (start_out) *start_out = e->start;
-  return e->al;
-}
-
-Allocation *SlabPool::at(uint64_t start, Place *near) {
-  const Entry *e = find(start, 1, near);
-  return e != nullptr && e->start == start ? e->al : nullptr;
-}
-
 void *SlabPool::ptr(uint64_t off) const {
   const Segment *seg = segment_of_slab(off / slab_);
   if (!seg) return nullptr;

@@ -81,9 +81,6 @@ class SlabPool {
     return entry(*near);
   }
   static bool holds(const Entry &e, uint64_t off) { return off >= e.start && off < e.end; }
-  // The same, as the record, with the allocation's offset; and the one at `start`.
-  Allocation *owner(uint64_t off, uint64_t extent, uint64_t *start_out, Place *near);
-  Allocation *at(uint64_t start, Place *near);
   void *ptr(uint64_t off) const;
   uint64_t slab_bytes() const { return slab_; }
   uint64_t total_bytes() const { return total_slabs_ * slab_; }

@@ -230,6 +230,7 @@ static void long_run() {
 
 // Tables on their way to the device, up to what 2^32 descriptors take: the parts follow each other and their tiles cover every byte once.
 static void table_uploads() {
+  CHECK(!tables_by_kernel(256) && !tables_by_kernel(16 * 1024 - 1) && tables_by_kernel(16 * 1024) && tables_by_kernel(1ull << 33));
   const uint64_t g = kLongestRun;
   for (uint64_t bytes : {(uint64_t)256, (uint64_t)16384, (uint64_t)393216, g - 256, g, g + 256, 4 * g - 256, 4 * g, 4 * g + 768, 256 * g + 512})
     for (uint64_t host : {(uint64_t)1 << 44, ((uint64_t)1 << 44) + 16, ((uint64_t)1 << 44) + 0xfffff000u}) {

@@ -278,18 +278,6 @@ static void far_rows() {
           }
 }
 
-// A launch that fetches tables asks host memory for no more than fills the link, and with the loads meant for it.
-static void table_fetches() {
-  for (uint64_t n = 256; n < 64u << 20; n += n < 1u << 20 ? 256 : 65536) {
-    const int code = table_fetch_code(n);
-    if (code == 0) continue;
-    const uint64_t nt = (n + kTableTile - 1) / kTableTile, wg = wave_workgroups(0, code, nt);
-    CHECK(wg > 0 && wg * (wave_code_threads(code) / 64) * kTableTile <= 256 * 1024);
-    CHECK((code & kWaveFromHost) != 0 && ((code & 15) != kWaveTiles || wg == nt) && !wave_draws(code, wg, nt, true));
-  }
-  CHECK(table_fetch_code(256) == 0 && table_fetch_code(100096) != 0);
-}
-
 int main(int argc, char **argv) {
   const uint64_t first = argc > 1 ? strtoull(argv[1], 0, 10) : 1, count = argc > 2 ? strtoull(argv[2], 0, 10) : 50;
   largest_launches();
@@ -298,7 +286,6 @@ int main(int argc, char **argv) {
                    kWaveTiles | kWaveFromHost, kWaveTiles | kWaveToHost, kWaveLink | kWaveFromHost, kWaveLink | kWaveToHost, (int)FT_P2P, (int)FT_H2P, (int)FT_P2H})
     CHECK(n_jobs[code] > 0);
   far_rows();
-  table_fetches();
   for (uint32_t d = 0; d < 16; ++d)
     for (uint32_t n = 16; n < 9000; n += n < 200 ? 1 : 61) run(d, n);
   for (g_seed = first; g_seed < first + count; ++g_seed) {
