@@ -533,7 +533,7 @@ uint32_t piece_workgroups(int cls, uint32_t ntiles) {
 // Not uploaded lists, whose wavefronts have more to wait for (600 tensors 100 MiB 39.7 -> 40.3 alone, 1000 of 50 MiB 18.3 -> 18.8; 300 of
 // 60 MiB beside the tensor 63 -> 49, it 2395 -> 2374), nor rows (99.5 MB 36 -> 38 alone; beside the tensor 39 -> 38, it 2440 -> 2362).
 uint32_t piece_lds(int cls, const PieceTables &t) {
-  return cls == FT_P2P && t.shape == nullptr && t.n <= kRunsAlong && t.ntiles > (48u << 20) / 8192 ? 160u * 1024 / 8 : 0u;
+  return cls == FT_P2P && t.shape == nullptr && pieces_go_along(t) && t.ntiles > (48u << 20) / 8192 ? 160u * 1024 / 8 : 0u;
 }
 
 // Tile of a wave-kernel launch. About 4000 tiles, sixteen wavefronts on every compute unit, each with a tile that it can

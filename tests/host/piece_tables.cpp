@@ -366,6 +366,8 @@ static void units_kept_free() {
         t.n = n;
         t.ntiles = ntiles;
         t.tile = 8192;
+        CHECK(piece_lds(cls, t) == 0);  // sides too far apart for a launch
+        t.close = true;
         const uint32_t lds = piece_lds(cls, t);
         CHECK((lds != 0) == (cls == 2 && n <= kRunsAlong && ntiles > 6144) && (lds == 0 || (160u << 10) / lds == 8));
         t.shape = &shape;
@@ -375,6 +377,7 @@ static void units_kept_free() {
   PieceTables t;  // jobs of up to 20 MiB have small tiles, and not too many of them
   for (uint64_t payload : {10u << 20, 20u << 20, 48u << 20}) {
     t.n = kRunsAlong;
+    t.close = true;
     t.ntiles = (uint32_t)(payload / piece_tile(FT_P2P, payload)) + (payload < 48u << 20 ? t.n : 0);
     CHECK(piece_lds(FT_P2P, t) == 0);
   }
