@@ -106,10 +106,10 @@ typedef struct ft_desc {
 typedef struct ft_class_stats {
   uint64_t payload_bytes; /* sum of rows*row_bytes of the class's descriptors */
   uint64_t chunks;        /* N = sum over functions of ceil(S_f / chunk_bytes) */
-  uint64_t tickets;       /* tiles that hold bytes: what the device counter runs to */
+  uint64_t tickets;       /* tiles that hold bytes */
   uint64_t tile_bytes;    /* bytes one ticket moves (last tile of a chunk may be shorter) */
-  uint32_t workgroups;    /* persistent workgroups launched (0 on the DMA path) */
-  uint32_t in_launch;     /* 1: a small job - tables passed with the launch, run on the caller's stream */
+  uint32_t workgroups;    /* workgroups launched: one a tile, or fewer that go on to further tiles (0 on the DMA path) */
+  uint32_t in_launch;     /* 1: tables passed with the launch, run on the caller's stream */
   float device_ms;        /* FT_TIMING: duration of the class's kernel (events bound to its dispatch;
                              on the FT_PATH_DMA path: events around its copy calls), else -1 */
   float begin_ms, end_ms; /* FT_TIMING after ft_timing_epoch: when that kernel began and ended, in ms since
@@ -233,7 +233,8 @@ int ft_set_stage_threads(ft_pool *p, uint32_t threads);
  *                   the job, so two jobs on one stream run in submit order. Nothing orders
  *                   two FT_DETACHED jobs with respect to each other: their launches of one
  *                   link class overlap (the head of one fills the compute units that the
- *                   tail of the other leaves idle); a job that reads what a detached job
+ *                   tail of the other leaves idle), except small ones, up to 16 MiB pool->pool or
+ *                   1 MiB on the host link with tables of up to 3 KiB, which run on hip_stream; a job that reads what a detached job
  *                   writes is submitted after ft_wait for that one.
  *
  * Per link class (host->pool, pool->host, pool->pool) and function, the payloads of
@@ -241,7 +242,22 @@ int ft_set_stage_threads(ft_pool *p, uint32_t threads);
  * chunk k is stream bytes [k*C, min((k+1)*C, S_f)). All chunks of a class are put in
  * one total order: chunk j of function f carries the finish tag (j+1)/w_f, smaller
  * tags first, equal tags by lower f - i.e. always serve the unfinished function with
- * the smallest (served+1)/weight. Persistent workgroups draw tickets from a device
+ * the smallest (served+1)/weight.
+ *
+ * A job of one link class whose order comes to a short list of pieces is launched as that list, on hip_stream
+ * itself: pool->pool up to 128 MiB, pitched rows among them of up to 140 descriptors if their pieces fit a launch; over
+ * the host link contiguous transfers (not one of more than 128 KiB between 16-byte aligned addresses from the host,
+ * nor mostly aligned ones of more than 64 MiB); chunks of 1 KiB or more; up to 16384 pieces, and no more than save
+ * time. Not with FT_KEEP, FT_LOG, FT_OPEN, FT_PATH_DMA or a tuned launch shape, nor a job with FT_DETACHED other than
+ * the small ones above. The tables travel with the launch (up to 240 contiguous pieces) or are copied ahead of it.
+ *  - Pool->pool every tile of 2 to 8 KiB has a wavefront of its own, begun in the order but for seven places: the
+ *    dies of the chip take the tiles in turn, and the eight tiles of a group one further round in each group,
+ *    so that all have the same mixture. As many are under way as the chip holds; 16 MiB of those contiguous
+ *    jobs of more than 48 MiB whose tables travel with the launch.
+ *  - On the host link 64 wavefronts from the host and 48 towards it (128 up to 1 MiB) draw tiles of up to 4 KiB in
+ *    the order from a counter.
+ *
+ * In all other jobs persistent workgroups draw tickets from a device
  * counter in that order; the classes run concurrently on streams of their own. Jobs that latency
  * bounds (pool->pool up to 48 MiB, one tensor or mostly misaligned ones up to 128 MiB, pitched rows
  * under 64 KiB of any amount; host-link jobs of small pieces) give every ticket to a single wavefront:
@@ -315,7 +331,8 @@ int ft_job_stats(ft_pool *p, ft_job_t job, ft_job_stats_t *out);
  * plus one 256-byte counter line per link class, 197 376 bytes on every GPU the library runs on,
  * held until the process ends).
  *   Arguments as for ft_submit_transfers; flags: 0 or FT_VALIDATE. Sides: FT_HOST and FT_POOL only.
- *   Same validation, same chunk order, same copy kernel and tile shapes, same bytes afterwards.
+ *   Same validation, same chunk order, same kernels, same bytes afterwards (host-link classes never as a list
+ *   of pieces, which needs a counter that this call has not; pool->pool as one only where that takes no more small launches).
  *   Everything is launched on hip_stream (table pieces travel with small launches, or the whole tables with the
  *   copy kernel itself if they fit; then one copy kernel per link class in use, one after the other). There is no job handle and nothing to
  *   wait for but the stream: the transfers are complete when the work queued on hip_stream by

@@ -737,8 +737,8 @@ int launch_with_uploaded_tables(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t
 }
 
 // A job of one link class that is short as a list of pieces (ft_pieces.h) is launched as that list on the caller's stream: tables in the
-// launch where they fit, else uploaded in front of it. Not a job whose schedule or log may be asked for (FT_KEEP, FT_LOG): the pieces do not
-// hold the schedule. Nor a detached one that would hold the caller's stream for long, or whose general tables would not go with a launch:
+// launch where they fit, else uploaded in front of it. Not a job with a log (FT_LOG), which is one of tickets, nor one that is kept for its
+// schedule (FT_KEEP), whose tables ft_job_schedule finds on the device; those of a timed job are uploaded when they are asked for. Nor a detached one that would hold the caller's stream for long, or whose general tables would not go with a launch:
 // it belongs on the library's streams, where detached jobs overlap and pool->pool launches are told of the host link's. *launched says
 // whether the job went this way.
 int launch_as_pieces(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_bytes, uint32_t flags, hipStream_t user, bool *launched) {
@@ -1209,7 +1209,7 @@ int ft_job_schedule(ft_pool *p, ft_job_t id, int link_class, uint32_t *func_out,
   ClassTable T = r.table;
   Blob schedule;
   hipError_t e = hipSuccess;
-  if (r.pieces) {  // its launch had no use for the schedule's tables
+  if (r.pieces) {  // its launch had no use for the schedule's tables: what is decoded here is the order that the pieces were written out in
     s = p->ctx->streams[link_class];
     const Layout lay = layout_of(r.plan, 0, 1);
     rc = get_blob(p, lay.end, true, &schedule);

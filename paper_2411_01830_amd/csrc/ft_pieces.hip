@@ -1,11 +1,11 @@
-// Kernels for a class that is written out as pieces (ft_pieces.h): a workgroup of one wavefront per tile, dispatched in
-// the order of the pieces.
+// Kernels for a class that is written out as pieces (ft_pieces.h): pool->pool a workgroup of one wavefront per tile, dispatched in
+// the order of the pieces; over the host link few wavefronts, which draw their tiles (ft_link_piece_kernel).
 //
 // What bounds them is what bounds a launch of some MiB: the fetch of its arguments and instructions, the reads that lead
 // from a tile's number to its bytes, one round trip for the bytes, and HBM or the last-level cache. So the tables are
-// small (28 bytes a piece of a run, in the launch itself up to kInlineRuns pieces), a tile is found by one compare of 64
-// entries and one record, and the code is a few hundred instructions. No counter and no persistent workgroups: the hardware
-// starts the workgroups in order as others end.
+// small (16 bytes a run in the launch itself, up to kRunsAlong runs; 24 in device memory), a tile is found by one compare of 64
+// entries and one record, and the code is a few hundred instructions. Pool->pool needs no counter and no persistent
+// workgroups: the hardware starts the workgroups in order as others end.
 #include <hip/hip_runtime.h>
 #include <hip/hip_ext.h>
 
@@ -202,8 +202,8 @@ __global__ __launch_bounds__(64) void ft_piece_kernel(A args) {
 // 128 or 256 wavefronts from the host 5.8, four a workgroup 10, every tile at once 39.
 //
 // A wavefront's first two tiles are given, the others are drawn from the counter, in the order of the pieces (of one piece they are
-// dealt out where all wavefronts get as many). A tile costs one draw, so the draws of a launch are as many as its tiles, and who has made the last one sets the
-// counter back. (Where no wavefront has a second tile the answers are not looked at, and the counter may be any.) A tile's loads, the draw
+// dealt out where all wavefronts get as many). A tile costs one draw, so the draws of a launch are as many as its tiles, and who
+// has made the last one sets the counter back. (Where no wavefront has a second tile the answers are not looked at, and the counter may be any.) A tile's loads, the draw
 // in front of them and the search for the next tile's piece are waited for together, and the next tile's loads follow the
 // stores at once.
 struct LinkTiles {

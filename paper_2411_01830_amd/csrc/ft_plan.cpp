@@ -470,15 +470,15 @@ bool build_pieces(const ClassPlan &cp, uint64_t chunk_bytes, uint32_t tile, bool
   return true;
 }
 
-// Pool->pool up to what the last-level cache holds: kernel time, us, general tables -> pieces, sources not in the cache: 64 maps of batch 1,
-// 64.5 MB 27.7 -> 20.3; 48 tensors, 30 MB 14.3 -> 10.4; 1024 tensors, 15.6 MB 11.1 -> 7.7; one of 64 KiB 4.0 either way, as an
-// empty kernel. Beyond it 64 KiB tiles in the order of a counter are faster (382 MB: 127 against 135).
+// Pool->pool up to what the last-level cache holds: kernel time by events bound to the dispatch (which say 3.9 us of an empty kernel; a kernel
+// trace says 1.5 us less of a short one), three jobs in turn, us, general tables -> pieces: 64 maps of batch 1, 64.5 MB 27.7 -> 20.0;
+// 48 tensors, 30 MB 14.3 -> 10.4; 1024 tensors, 15.6 MB 11.1 -> 7.7; one of 64 KiB 4.0 either way. Beyond it 64 KiB tiles in the order of a counter are faster (382 MB: 127 against 135).
 // Host link, 16 tensors of 8 functions: from the host 16 MiB 298.6 -> 295.7, 64 MiB 1172.8 -> 1169.2, 256 MiB with half of them
 // at odd addresses 4713 -> 4663; to the host 298.3 -> 295.4, 1179.0 -> 1175.8, 128 MiB with odd ones 2400 -> 2349. All but one aligned
 // tensor from the host (64 KiB 4.5 -> 4.2, but 256 KiB 7.5 -> 8.0, 1 MiB 21.0 -> 22.2, 64 MiB 1167.8 -> 1169.6), and aligned jobs beyond
 // 64 MiB, whose pieces take the host longer to write out than the kernel gains (1 GiB in 2064 pieces 18663 -> 18683 a pass).
 // Rows go as pieces where these go along with the launch (quadrants of 4K frames, 16 descriptors, 99.5 MB, 48 -> 44 a pass,
-// kernel 38.6 -> 35.5); where they would be uploaded, writing them out costs more than the kernel gains (1536 crops 56.0 by the general
+// kernel 38.0 -> 35.7); where they would be uploaded, writing them out costs more than the kernel gains (1536 crops 56.0 by the general
 // tables, 63.0 by pieces, kernels 24.4 and 19.8).
 // Every place where the order goes from one function to another costs the host a piece to write out, 5.5 ns, and beyond kRunsAlong of them
 // the list has to be uploaded too. Passes (submit and wait), us, general tables -> pieces:

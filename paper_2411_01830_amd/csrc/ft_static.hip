@@ -1,6 +1,6 @@
 // ft_submit_static: the submit for callers that cannot allocate (code under HIP graph capture,
 // tight serving loops, harnesses that forbid hipMalloc). It does what ft_submit_transfers does for
-// a job of pinned-host and pool sides - same validation, same chunk order, same copy kernel - but
+// a job of pinned-host and pool sides - same validation, same chunk order, same kernels - but
 // takes nothing from the runtime: no device buffer, no pinned buffer, no event, no stream. What the
 // kernels need beyond the caller's memory (the schedule tables and the ticket counter of each link
 // class) lies in one fixed array in device memory that belongs to this library, and everything is

@@ -344,7 +344,8 @@ ORDER_CASES = [
 @pytest.mark.gpu
 @pytest.mark.parametrize("case", ORDER_CASES, ids=[c[0] for c in ORDER_CASES])
 def test_the_weighted_order_holds_whatever_the_tiles_cost(case):
-    """Two functions of equal weight whose tiles alternate, one of them of slow tiles: when half of the tickets have been
+    """Tickets drawn from the counter (kept jobs; others of that size may go as lists of pieces, whose order over the dies
+    tests/host/piece_tables.cpp checks). Two functions of equal weight whose tiles alternate, one of them of slow tiles: when half of the tickets have been
     begun, half of those are the slow function's. A workgroup has at most the rest of one batch to begin, of which one
     function has at most one ticket more than the other: |A - B| <= workgroups, so the share is off by at most
     workgroups / tickets (and one per cent for tickets taken but not yet logged). Bytes against plain strided copies."""
