@@ -766,19 +766,21 @@ int plan_submit(SlabPool &pool, const std::vector<HostWindow> &windows, const ft
     if (weights[f] == 0) return FT_EINVAL;
   if (chunk_bytes == 0 || chunk_bytes % 16 != 0) return FT_EINVAL;
   // how many descriptors each function has in each class says where each one goes, so that it is resolved into its place;
-  // caller's function -> index into the class's table, up to 16 functions without an allocation
+  // caller's function -> index into the class's table, for the classes that there are, up to 16 functions without an allocation
   auto class_of = [](const ft_desc &d) {
     return d.src_space != FT_POOL ? FT_H2P : (d.dst_space != FT_POOL ? FT_P2H : FT_P2P);
   };
   uint32_t small[FT_NCLASS][16];
-  std::vector<uint32_t> large;
-  uint32_t *fn_of[FT_NCLASS] = {small[0], small[1], small[2]};
-  if (nfunc > 16) {
-    large.resize((uint64_t)FT_NCLASS * nfunc);
-    for (int c = 0; c < FT_NCLASS; ++c) fn_of[c] = large.data() + (uint64_t)c * nfunc;
-  } else {
-    for (int c = 0; c < FT_NCLASS; ++c) std::fill(fn_of[c], fn_of[c] + nfunc, 0u);
-  }
+  std::vector<uint32_t> large[FT_NCLASS];
+  uint32_t *fn_of[FT_NCLASS] = {nullptr, nullptr, nullptr};
+  auto counts_of = [&](int c) {
+    if (nfunc > 16) {
+      large[c].assign(nfunc, 0);
+      return large[c].data();
+    }
+    std::fill(small[c], small[c] + nfunc, 0u);
+    return &small[c][0];
+  };
   for (uint32_t i = 0; i < ndesc; ++i) {
     const ft_desc &d = descs[i];
     if (d.func >= nfunc || d.flags != 0) return FT_EINVAL;
@@ -786,7 +788,9 @@ int plan_submit(SlabPool &pool, const std::vector<HostWindow> &windows, const ft
     if (d.src_space != FT_POOL && d.dst_space != FT_POOL) return FT_EINVAL;  // host to host
     if (d.row_bytes == 0 || d.rows == 0) return FT_EINVAL;
     if (d.rows > 1 && (d.src_pitch < d.row_bytes || d.dst_pitch < d.row_bytes)) return FT_EINVAL;
-    fn_of[class_of(d)][d.func] += 1;
+    const int c = class_of(d);
+    if (fn_of[c] == nullptr) fn_of[c] = counts_of(c);
+    fn_of[c][d.func] += 1;
   }
 
   // ---- split by class, per-function streams in submission order
@@ -794,6 +798,7 @@ int plan_submit(SlabPool &pool, const std::vector<HostWindow> &windows, const ft
     ClassPlan &cp = out->cls[c];
     cp = ClassPlan();
     uint32_t *count = fn_of[c];
+    if (count == nullptr) continue;
     uint32_t off = 0;
     for (uint32_t f = 0; f < nfunc; ++f) {
       if (count[f] == 0) continue;
@@ -811,7 +816,7 @@ int plan_submit(SlabPool &pool, const std::vector<HostWindow> &windows, const ft
       count[f] = (uint32_t)cp.funcs.size();  // from here on: its place in the table
       cp.funcs.push_back(fn);
     }
-    cp.xfers.resize(off);  // (a class without traffic costs no allocation)
+    cp.xfers.resize(off);
   }
   bool stream_overflow = false;
 

@@ -6,6 +6,7 @@
 // Usage: walk_tables <first seed> <count>
 #include <cstdio>
 #include <cstdlib>
+#include <new>
 #include <random>
 #include <vector>
 #include "../../paper_2411_01830_amd/csrc/ft_plan.h"
@@ -73,7 +74,46 @@ static void walk(const ClassPlan &cp, uint64_t C, uint64_t tile, uint32_t tpc, c
   CHECK(total == cp.payload);
 }
 
+static uint64_t g_asked;  // bytes asked of the allocator
+void *operator new(size_t n) {
+  g_asked += n;
+  void *p = std::malloc(n != 0 ? n : 1);
+  if (p == nullptr) throw std::bad_alloc();
+  return p;
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
+
+// A job of many declared functions and few descriptors takes memory, and time to clear it, for the link classes that it has, not for all.
+static void few_of_many_functions() {
+  const uint32_t nf = 100000;
+  SlabPool pool(4096);
+  CHECK(pool.add_segment(reinterpret_cast<void *>(0x7f0000000000ull), 1 << 20) == FT_OK);
+  uint64_t a, b;
+  CHECK(pool.alloc(4096, &a) == FT_OK && pool.alloc(4096, &b) == FT_OK);
+  std::vector<uint32_t> w(nf, 1);
+  std::vector<HostWindow> win(1, HostWindow{0x100000000ull, 1 << 20, false});
+  for (int classes = 1; classes <= 3; ++classes) {
+    std::vector<ft_desc> d((size_t)classes);
+    for (int c = 0; c < classes; ++c) {
+      d[c] = ft_desc{};
+      d[c].func = nf - 1;
+      d[c].src_space = c == 1 ? FT_HOST : FT_POOL;
+      d[c].dst_space = c == 2 ? FT_HOST : FT_POOL;
+      d[c].src = c == 1 ? win[0].base : a;
+      d[c].dst = c == 2 ? win[0].base + 100 : b;
+      d[c].row_bytes = 16;
+      d[c].rows = 1;
+    }
+    const uint64_t before = g_asked;
+    SubmitPlan plan;
+    CHECK(plan_submit(pool, win, d.data(), (uint32_t)classes, w.data(), nf, 4096, 0, &plan) == FT_OK);
+    CHECK(g_asked - before <= (uint64_t)classes * (4 * nf + 4096));
+  }
+}
+
 int main(int argc, char **argv) {
+  few_of_many_functions();
   const uint64_t first = argc > 1 ? strtoull(argv[1], 0, 10) : 1, count = argc > 2 ? strtoull(argv[2], 0, 10) : 200;
   for (g_seed = first; g_seed < first + count; ++g_seed) {
     std::mt19937_64 r(g_seed);
