@@ -749,9 +749,9 @@ int launch_as_pieces(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_byte
     if (plan.cls[c].nchunks > 0) only = only == -1 ? c : -2;
   if (only < 0 || p->tuning[only].workgroups != 0 || p->tuning[only].tile_bytes != 0) return FT_OK;
   const ClassPlan &cp = plan.cls[only];
-  const bool detached = (flags & FT_DETACHED) != 0, tables_fit = inline_layout_of(cp).end <= kInlineBytes;
-  if (detached && (cp.payload > (only == FT_P2P ? kWaveTilesBytes : kWaveLinkTilesBytes) || !tables_fit)) return FT_OK;
-  const PieceRoom room = job_pieces(cp, only, chunk_bytes, tables_fit);
+  const auto tables_fit = [&cp] { return inline_layout_of(cp).end <= kInlineBytes; };
+  if ((flags & FT_DETACHED) && (cp.payload > (only == FT_P2P ? kWaveTilesBytes : kWaveLinkTilesBytes) || !tables_fit())) return FT_OK;
+  const PieceRoom room = job_pieces(cp, only, chunk_bytes, cp.nchunks > kRunsAlong && tables_fit());  // (of fewer chunks it is not asked)
   if (room.pieces == 0) return FT_OK;
   const uint64_t bytes = align_up(piece_bytes(room), 256);
   // (written out in ordinary memory: the blob's lines were last read by the device, and every store to one of them would wait for it)
@@ -761,7 +761,7 @@ int launch_as_pieces(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_byte
   if (!build_pieces(cp, chunk_bytes, piece_tile(only, cp.payload), only == FT_H2P, &t)) return FT_OK;
   const bool with_launch = pieces_go_along(t);
   // Where they do not, the general tables may; and rows are then better off with them (job_pieces).
-  if (!with_launch && (t.shape != nullptr || tables_fit)) return FT_OK;
+  if (!with_launch && (t.shape != nullptr || tables_fit())) return FT_OK;
   if (!with_launch) {
     const int rc = get_blob(p, bytes, true, &job->tables);
     if (rc != FT_OK) return fail_submit(p, job, rc);
