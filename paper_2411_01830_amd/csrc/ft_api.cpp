@@ -737,7 +737,7 @@ int launch_with_uploaded_tables(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t
 }
 
 // A job of one link class that is short as a list of pieces (ft_pieces.h) is launched as that list on the caller's stream: tables in the
-// launch where they fit, else uploaded in front of it. Not a job with a log (FT_LOG), which is one of tickets, nor one that is kept for its
+// launch where they fit, else in memory, uploaded in front of it or read where they are written. Not a job with a log (FT_LOG), which is one of tickets, nor one that is kept for its
 // schedule (FT_KEEP), whose tables ft_job_schedule finds on the device; those of a timed job are uploaded when they are asked for. Nor a detached one that would hold the caller's stream for long, or whose general tables would not go with a launch:
 // it belongs on the library's streams, where detached jobs overlap and pool->pool launches are told of the host link's. *launched says
 // whether the job went this way.
@@ -763,9 +763,10 @@ int launch_as_pieces(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_byte
   // Where they do not, the general tables may; and rows are then better off with them (job_pieces).
   if (!with_launch && (t.shape != nullptr || tables_fit())) return FT_OK;
   if (!with_launch) {
-    const int rc = get_blob(p, bytes, true, &job->tables);
+    find_base(&t);
+    const int rc = get_blob(p, packed_bytes(t), true, &job->tables);
     if (rc != FT_OK) return fail_submit(p, job, rc);
-    std::memcpy(job->tables.host, h, bytes);
+    pack_pieces(t, job->tables.host);
   }
   ClassRun &r = job->run[only];
   const bool draws = piece_draws(only, t);
@@ -795,8 +796,9 @@ int launch_as_pieces(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_byte
   if (rc != FT_OK) return fail_submit(p, job, rc);
   hipError_t e = hipSuccess;
   if (!with_launch) {
-    e = upload_pieces(job->tables, bytes, user);
-    t = pieces_at(job->tables.dev, room, t);
+    const bool in_place = pieces_read_in_place(only, packed_bytes(t));
+    if (!in_place) e = upload_pieces(job->tables, packed_bytes(t), user);
+    t.packed = in_place ? job->tables.host : job->tables.dev;
   }
   // without timing the done event is bound to the dispatch itself, which spares a marker behind it
   if (e == hipSuccess) e = launch_pieces(t, only, with_launch, counter, user, r.ev_begin, timing ? r.ev_end : r.ev_done);

@@ -15,7 +15,7 @@ namespace ft {
 // T.inline_tables is set, else null.
 hipError_t launch_copy(const ClassTable &T, int link_class, uint32_t workgroups, hipStream_t stream,
                        hipEvent_t ev_start, hipEvent_t ev_stop, const InlineBlob *tables = nullptr);
-// The pieces of a class (ft_pieces.h), whose tables lie in device memory or (on_host) are to travel with the launch. counter: on
+// The pieces of a class (ft_pieces.h), whose list lies where t.packed says or (on_host) is to travel with the launch. counter: on
 // the host link a word in device memory, of launches of which piece_draws says so one that is zero and will be zero again.
 hipError_t launch_pieces(const PieceTables &t, int cls, bool on_host, unsigned long long *counter, hipStream_t stream, hipEvent_t ev_start,
                          hipEvent_t ev_stop);

@@ -44,6 +44,23 @@ __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
   return (uint64_t)hi << 32 | lo;
 }
 
+// What one lane has, the same one for all.
+__device__ __forceinline__ uint32_t of_lane32(uint32_t v, uint32_t lane) { return __builtin_amdgcn_readlane(v, lane); }
+__device__ __forceinline__ uint64_t of_lane64(uint64_t v, uint32_t lane) {
+  return (uint64_t)of_lane32((uint32_t)(v >> 32), lane) << 32 | of_lane32((uint32_t)v, lane);
+}
+
+// What each lane has, and all lanes before it.
+__device__ __forceinline__ uint32_t wave_sums(uint32_t v) {
+  v += __builtin_amdgcn_update_dpp(0, v, 0x111, 0xf, 0xf, false);  // within a row of 16: from 1, 2, 4 and 8 lanes before
+  v += __builtin_amdgcn_update_dpp(0, v, 0x112, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x114, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x118, 0xf, 0xf, false);
+  v += __builtin_amdgcn_update_dpp(0, v, 0x142, 0xa, 0xf, false);  // the last of a row to the row after it, of two rows to the two after them
+  v += __builtin_amdgcn_update_dpp(0, v, 0x143, 0xc, 0xf, false);
+  return v;
+}
+
 // How many of the 64 lanes say yes.
 __device__ __forceinline__ uint32_t wave_count(bool yes) { return (uint32_t)__popcll(__ballot(yes)); }
 

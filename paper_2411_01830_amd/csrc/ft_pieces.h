@@ -1,8 +1,8 @@
 // A class of a job as the list of its pieces: what the proportional chunk order of Sec. 6.1 comes to when it is written
 // out, for jobs in which that is short. A piece is a run of bytes that lie together on both sides, or whole rows of one
 // pitched descriptor; pieces follow each other in the order of the chunks that they come from, and every piece is cut into
-// tiles of its own. Tile t of the launch is found by searching one table (the first tile of each piece) and its bytes by
-// reading one record, where the general tables (ft_tables.h) take five dependent reads and several divisions.
+// tiles of its own. Tile t of the launch is found by the first tiles of the pieces, or of blocks of them, in the launch's arguments and then its bytes by
+// one read, where the general tables (ft_tables.h) take five dependent reads and several divisions.
 #pragma once
 #include <stdint.h>
 
@@ -28,7 +28,7 @@ struct PieceEdges {
   uint32_t from, to;
 };
 
-// The tables as arrays of `n` entries each, in host or (of runs) in device memory.
+// The tables as arrays of `n` entries each, in host memory.
 struct PieceTables {
   PieceSides *at = nullptr;
   uint32_t *first = nullptr;    // the piece's first tile; ascending, no piece is without one
@@ -38,8 +38,9 @@ struct PieceTables {
   PieceEdges *edges = nullptr;  // of rows (of a run nothing): the first row from column `from`, the last one up to `to`
   uint32_t n = 0, nshapes = 0, ntiles = 0;
   uint32_t tile = 0;              // bytes of a tile, a power of two
-  uint64_t src0 = 0, dst0 = 0;    // the lowest addresses of the sides,
-  bool close = false;             // from which every side is less than 2^32 bytes away (said of few pieces only)
+  const char *packed = nullptr;   // where the device finds a list of runs (pack_pieces), if it does not go along
+  uint64_t src0 = 0, dst0 = 0;    // addresses not above any side's,
+  bool close = false;             // from which every side is less than 2^32 bytes away (said of few pieces only, of more by find_base)
 };
 
 // A run's tiles begin and end where this many bytes of the side that is dearer to cut (the destination; host memory where
@@ -60,22 +61,22 @@ PieceRoom piece_room(const ClassPlan &cp, uint64_t chunk_bytes, uint32_t tile);
 // Bytes of the tables, and their places from `base` (a multiple of 8) on.
 uint64_t piece_bytes(const PieceRoom &room);
 PieceTables piece_places(char *base, const PieceRoom &room);
-// t's tables where a copy of them lies.
-inline PieceTables pieces_at(char *base, const PieceRoom &room, const PieceTables &t) {
-  const PieceTables c = piece_places(base, room);
-  PieceTables moved = t;
-  moved.at = c.at;
-  moved.first = c.first;
-  moved.len = c.len;
-  moved.shape = c.shape;
-  moved.shapes = c.shapes;
-  moved.edges = c.edges;
-  return moved;
-}
+// Lists of runs that do not go along lie in memory as arrays one behind the other: where no side is 2 GiB or more away from the first
+// piece's, sources and destinations as 32-bit distances from t's src0 and dst0, lengths, 12 bytes a piece; else PieceSides and lengths. What else
+// the kernels need is in their arguments (the first tile of every kPieceBlock-th piece) or follows from the lengths.
+constexpr uint32_t kPieceBlock = 64;  // a lane each
+inline uint64_t packed_bytes(const PieceTables &t) { return (uint64_t)t.n * (t.close ? 12 : 20); }
+// Says whether t's pieces are close, and from where.
+void find_base(PieceTables *t);
+// Writes t, whose base is known, to `to`.
+void pack_pieces(const PieceTables &t, char *to);
 // Fills t with the pieces of a class in its order, cut into tiles of `tile` bytes, a power of two from 1 to 8 KiB.
 // by_source: the source's lines are the ones not to be cut. False: there are rows that the kernels do not cover (under 16
 // bytes, or so far apart that a tile's distances leave 32 bits).
 bool build_pieces(const ClassPlan &cp, uint64_t chunk_bytes, uint32_t tile, bool by_source, PieceTables *t);
+
+// Tiles of a run of len bytes, one of whose sides (the one not to be cut) begins at `side`.
+FT_HD uint32_t run_tiles(uint64_t side, uint32_t len, uint32_t tile) { return (len + ((uint32_t)side & (kPieceLine - 1)) + tile - 1) / tile; }
 
 // A run longer than this is several pieces: tiles are found by 32-bit arithmetic.
 constexpr uint64_t kLongestRun = 1ull << 30;
@@ -95,7 +96,7 @@ struct OneRun {
     tables.len = &len;
     tables.n = 1;
     tables.tile = tile;
-    tables.ntiles = (len + ((uint32_t)(by_source ? src : dst) & (kPieceLine - 1)) + tile - 1) / tile;
+    tables.ntiles = run_tiles(by_source ? src : dst, len, tile);
     tables.src0 = src;
     tables.dst0 = dst;
     tables.close = true;
@@ -115,6 +116,13 @@ inline bool piece_draws(int cls, const PieceTables &t) {
   const uint32_t workgroups = piece_workgroups(cls, t.ntiles);
   return workgroups < t.ntiles && (t.n > 1 || (workgroups & (workgroups - 1)) != 0);
 }
+
+// Whether a list that does not go along is read where the host wrote it, in pinned memory, and not uploaded first: no launch in front of the
+// job's and no gap between the two, but every die has the list over the link for itself, 8 x 12 bytes a piece. Passes, us, uploaded -> in
+// place, 4 functions: 260 pieces 33.1 -> 29.2, 520 38.0 -> 34.2, 1000 47.3 -> 44.9, 2000 67.8 -> 66.6, 4000 109.5 -> 110.4, 8000 196 -> 205. The
+// kernel alone 4.2 -> 4.2, 5.7 (1000), 7.2 (2000), 10.8 (4000). Not over the host link, whose few wavefronts look for a piece for each
+// of their tiles, behind the link's own reads (536 tensors of 10 KB from the host 138 -> 154).
+inline bool pieces_read_in_place(int cls, uint64_t bytes) { return cls == FT_P2P && bytes <= 32u << 10; }
 
 // LDS that a workgroup asks for without using it, so that a compute unit of 160 KiB takes no more of them at once.
 uint32_t piece_lds(int cls, const PieceTables &t);

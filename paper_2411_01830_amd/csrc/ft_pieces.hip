@@ -3,7 +3,7 @@
 //
 // What bounds them is what bounds a launch of some MiB: the fetch of its arguments and instructions, the reads that lead
 // from a tile's number to its bytes, one round trip for the bytes, and HBM or the last-level cache. So the tables are
-// small (16 bytes a run in the launch itself, up to kRunsAlong runs; 24 in device memory), a tile is found by one compare of 64
+// small (16 bytes a run in the launch itself, up to kRunsAlong runs; 12 in memory), a tile is found by one compare of 64
 // entries and one record, and the code is a few hundred instructions. Pool->pool needs no counter and no persistent
 // workgroups: the hardware starts the workgroups in order as others end.
 #include <hip/hip_runtime.h>
@@ -32,12 +32,16 @@ struct PieceArgs {
   PieceEdges edges[kRows ? CAP : 1];
   PieceRows shapes[kRows ? SHAPES : 1];
 };
-// and tables in device memory, of runs
+// and lists of runs in memory (pack_pieces), with the first tile of every block of pieces: a wavefront has its tile's block from the
+// arguments, and the block's entries, one a lane, are one read deep. (A search through all first tiles and then a record were three, each a trip
+// over the link where the list is read in place: 1024 tensors, 15.6 MB, in place 9.5 us with 24 bytes a piece searched, 7.7 so; uploaded 6.2 either way.)
+template <uint32_t BLOCKS, bool CLOSE>
 struct PieceRefs {
   static constexpr bool kRows = false, kOne = false;
   uint32_t n, tile, ntiles;
-  const PieceSides *at;
-  const uint32_t *first, *len;
+  uint64_t src0, dst0;
+  const char *packed;
+  uint32_t block[BLOCKS];
 };
 
 struct Piece {
@@ -47,19 +51,6 @@ struct Piece {
   PieceRows rows;         // row_bytes 0: a run
   PieceEdges edges;
 };
-
-// The last of n ascending entries (the first of which is 0) at or before t.
-__device__ __forceinline__ uint32_t last_at_or_before(const FT_CONST uint32_t *first, uint32_t n, uint32_t t, uint32_t lane) {
-  uint32_t x = 0;
-  while (n > 1) {
-    const uint32_t step = (n + 63) / 64;
-    const uint32_t j = lane * step;
-    const uint32_t at = (wave_count(j < n && first[x + (j < n ? j : 0u)] <= t) - 1) * step;
-    x += at;
-    n = step < n - at ? step : n - at;
-  }
-  return uniform32(x);
-}
 
 __device__ __forceinline__ PieceRows read_shape(const FT_CONST PieceRows *shapes, uint32_t shape) {
   PieceRows r;
@@ -76,7 +67,7 @@ __device__ __forceinline__ PieceRows read_shape(const FT_CONST PieceRows *shapes
   return r;
 }
 
-template <uint32_t CAP, uint32_t SHAPES>
+template <int NT, uint32_t CAP, uint32_t SHAPES>
 __device__ __forceinline__ Piece find_piece(const PieceArgs<CAP, SHAPES> &, uint32_t t, uint32_t lane) {
   const FT_CONST PieceArgs<CAP, SHAPES> &a =
       *reinterpret_cast<const FT_CONST PieceArgs<CAP, SHAPES> *>(reinterpret_cast<uintptr_t>(__builtin_amdgcn_kernarg_segment_ptr()));
@@ -105,15 +96,41 @@ __device__ __forceinline__ Piece find_piece(const PieceArgs<CAP, SHAPES> &, uint
 }
 
 template <class T>
-__device__ __forceinline__ const FT_CONST T *constant(const T *p) { return reinterpret_cast<const FT_CONST T *>(reinterpret_cast<uintptr_t>(p)); }
+__device__ __forceinline__ const FT_CONST T *constant(const char *p) { return reinterpret_cast<const FT_CONST T *>(reinterpret_cast<uintptr_t>(p)); }
 
-__device__ __forceinline__ Piece find_piece(const PieceRefs &r, uint32_t t, uint32_t lane) {
-  const uint32_t x = last_at_or_before(constant(r.first), r.n, t, lane);
+template <int NT, uint32_t BLOCKS, bool CLOSE>
+__device__ __forceinline__ Piece find_piece(const PieceRefs<BLOCKS, CLOSE> &, uint32_t t, uint32_t lane) {
+  typedef PieceRefs<BLOCKS, CLOSE> Refs;
+  const FT_CONST Refs &r = *reinterpret_cast<const FT_CONST Refs *>(reinterpret_cast<uintptr_t>(__builtin_amdgcn_kernarg_segment_ptr()));
+  uint32_t before = 0;
+#pragma unroll
+  for (uint32_t j0 = 0; j0 < BLOCKS; j0 += 64) {
+    const uint32_t j = j0 + lane;
+    before += wave_count(r.block[j < BLOCKS ? j : 0u] <= t && j * kPieceBlock < r.n);
+  }
+  const uint32_t b = uniform32(before - 1), begin = b * kPieceBlock;
+  const bool is = begin + lane < r.n;
+  const uint32_t j = is ? begin + lane : begin;
+  uint64_t src, dst;
+  uint32_t len;
+  if (CLOSE) {
+    src = r.src0 + constant<uint32_t>(r.packed)[j];
+    dst = r.dst0 + constant<uint32_t>(r.packed)[r.n + j];
+    len = constant<uint32_t>(r.packed)[2 * r.n + j];
+  } else {
+    src = constant<PieceSides>(r.packed)[j].src;
+    dst = constant<PieceSides>(r.packed)[j].dst;
+    len = constant<uint32_t>(r.packed + r.n * sizeof(PieceSides))[j];
+  }
+  // the tiles of the block's pieces up to each, which say where each begins
+  const uint32_t tiles = run_tiles(NT == kFromHost ? src : dst, len, r.tile);
+  const uint32_t first = r.block[b] + wave_sums(is ? tiles : 0u) - tiles;
+  const uint32_t x = uniform32(wave_count(is && first <= t) - 1);
   Piece p;
-  p.src = constant(r.at)[x].src;
-  p.dst = constant(r.at)[x].dst;
-  p.len = constant(r.len)[x];
-  p.tile_no = t - constant(r.first)[x];
+  p.src = of_lane64(src, x);
+  p.dst = of_lane64(dst, x);
+  p.len = of_lane32(len, x);
+  p.tile_no = t - of_lane32(first, x);
   p.tile = r.tile;
   return p;
 }
@@ -193,7 +210,7 @@ __device__ __forceinline__ void move_tile(const Piece &p, uint32_t lane) {
 template <int NT, class A>
 __global__ __launch_bounds__(64) void ft_piece_kernel(A args) {
   const uint32_t t = A::kOne ? blockIdx.x : tile_of_workgroup(blockIdx.x, args.ntiles);
-  move_tile<NT, A::kRows>(find_piece(args, t, threadIdx.x), threadIdx.x);
+  move_tile<NT, A::kRows>(find_piece<NT>(args, t, threadIdx.x), threadIdx.x);
 }
 
 // The same over the host link, which has to be full but not crowded: 64 wavefronts with 4 KiB of loads from host memory each, one on
@@ -219,7 +236,7 @@ __global__ __launch_bounds__(64) void ft_link_piece_kernel(A args, LinkTiles l) 
   const CounterP counter = reinterpret_cast<CounterP>(reinterpret_cast<uintptr_t>(l.counter));
   const uint32_t lane = threadIdx.x;
   uint32_t t = blockIdx.x, next = t + gridDim.x;
-  Piece p = find_piece(args, t, lane);
+  Piece p = find_piece<NT>(args, t, lane);
   while (t < l.ntiles) {
     uint32_t begin, n, drawn = 0;
     run_tile(NT == kFromHost ? p.src : p.dst, p.len, p.tile, p.tile_no, &begin, &n);
@@ -229,7 +246,7 @@ __global__ __launch_bounds__(64) void ft_link_piece_kernel(A args, LinkTiles l) 
     u32x4_any v[4];
     if (n >= 16) wave_run_loads<NT, 4>(v, s, w, 0, lane);
     else if (lane < n) st_off<uint8_t, 0>(d, lane, ld_off<uint8_t, 0>(s, lane));
-    p = find_piece(args, next < l.ntiles ? next : t, lane);  // (found again where there is no next)
+    p = find_piece<NT>(args, next < l.ntiles ? next : t, lane);  // (found again where there is no next)
     t = next;
     next += gridDim.x;
     if (!A::kOne) {
@@ -287,6 +304,21 @@ hipError_t launch_along(const PieceTables &t, const Launch &l) {
   return launch(a, l);
 }
 
+template <uint32_t BLOCKS, bool CLOSE>
+hipError_t launch_refs(const PieceTables &t, const Launch &l) {
+  if (t.n > BLOCKS * kPieceBlock) return hipErrorInvalidValue;
+  static_assert(256 * kPieceBlock >= kMaxPieces, "a block for every piece");
+  PieceRefs<BLOCKS, CLOSE> r;
+  r.n = t.n;
+  r.tile = t.tile;
+  r.ntiles = t.ntiles;
+  r.src0 = t.src0;
+  r.dst0 = t.dst0;
+  r.packed = t.packed;
+  for (uint32_t b = 0; b * kPieceBlock < t.n; ++b) r.block[b] = t.first[b * kPieceBlock];
+  return launch(r, l);
+}
+
 }  // namespace
 
 hipError_t launch_pieces(const PieceTables &t, int cls, bool on_host, unsigned long long *counter, hipStream_t stream, hipEvent_t ev_start,
@@ -294,7 +326,12 @@ hipError_t launch_pieces(const PieceTables &t, int cls, bool on_host, unsigned l
   if (t.n == 0 || t.ntiles == 0 || cls < 0 || cls > 2 || (on_host && !pieces_go_along(t)) || (cls != 2 && t.tile > 4096)) return hipErrorInvalidValue;
   const Launch l = {cls, t.ntiles, piece_lds(cls, t), counter, stream, ev_start, ev_stop};
   const bool rows = t.shape != nullptr;
-  if (!on_host) return rows ? hipErrorInvalidValue : launch(PieceRefs{t.n, t.tile, t.ntiles, t.at, t.first, t.len}, l);
+  if (!on_host) {
+    if (rows || t.packed == nullptr) return hipErrorInvalidValue;
+    if (t.n <= 16 * kPieceBlock) return t.close ? launch_refs<16, true>(t, l) : launch_refs<16, false>(t, l);
+    if (t.n <= 64 * kPieceBlock) return t.close ? launch_refs<64, true>(t, l) : launch_refs<64, false>(t, l);
+    return t.close ? launch_refs<256, true>(t, l) : launch_refs<256, false>(t, l);
+  }
   if (rows) {
     if (t.n <= 16 && t.nshapes <= 16) return launch_along<16, 16>(t, l);
     if (t.n <= 64) return launch_along<64, 64>(t, l);

@@ -4,6 +4,7 @@
 #include "ft_pieces.h"
 
 #include <algorithm>
+#include <cstring>
 #include <numeric>
 
 namespace ft {
@@ -468,6 +469,35 @@ bool build_pieces(const ClassPlan &cp, uint64_t chunk_bytes, uint32_t tile, bool
   t->dst0 = low[1];
   t->close = (high[0] - low[0]) >> 32 == 0 && (high[1] - low[1]) >> 32 == 0;
   return true;
+}
+
+void find_base(PieceTables *t) {
+  constexpr uint64_t half = 1ull << 31;
+  const uint64_t s = t->at[0].src - half, d = t->at[0].dst - half;
+  uint64_t far_s = 0, far_d = 0;
+  for (uint32_t i = 0; i < t->n; ++i) {
+    far_s |= t->at[i].src - s;
+    far_d |= t->at[i].dst - d;
+  }
+  t->close = (far_s | far_d) >> 32 == 0;
+  t->src0 = s;
+  t->dst0 = d;
+}
+
+void pack_pieces(const PieceTables &t, char *to) {
+  const uint32_t n = t.n;
+  if (t.close) {
+    uint32_t *src = reinterpret_cast<uint32_t *>(to), *dst = src + n;
+    const PieceSides *at = t.at;
+    const uint32_t s = (uint32_t)t.src0, d = (uint32_t)t.dst0;
+    for (uint32_t i = 0; i < n; ++i) src[i] = (uint32_t)at[i].src - s;
+    for (uint32_t i = 0; i < n; ++i) dst[i] = (uint32_t)at[i].dst - d;
+    to += 8ull * n;
+  } else {
+    std::memcpy(to, t.at, n * sizeof(PieceSides));
+    to += n * sizeof(PieceSides);
+  }
+  std::memcpy(to, t.len, n * sizeof(uint32_t));
 }
 
 // Pool->pool up to what the last-level cache holds: kernel time by events bound to the dispatch (which say 3.9 us of an empty kernel; a kernel

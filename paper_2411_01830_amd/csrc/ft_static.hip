@@ -178,8 +178,11 @@ extern "C" int ft_submit_static(ft_pool *p, const ft_desc *descs, uint32_t ndesc
       const bool with_launch = pieces_go_along(s.pieces);
       PieceTables t = s.pieces;
       if (!with_launch) {
-        FT_HIP(p, put_words(d + 256, reinterpret_cast<const char *>(s.words.data()), s.words.size() * 8, nullptr, stream));
-        t = pieces_at(d + 256, s.room, s.pieces);
+        find_base(&t);
+        h.assign(align_up(packed_bytes(t), 8), 0);
+        pack_pieces(t, h.data());
+        FT_HIP(p, put_words(d + 256, h.data(), h.size(), nullptr, stream));
+        t.packed = d + 256;
       }
       FT_HIP(p, launch_pieces(t, c, with_launch, nullptr, stream, nullptr, nullptr));
       continue;

@@ -173,6 +173,55 @@ def test_the_largest_job_of_pieces_and_the_next():
         eng.close()
 
 
+def test_lists_in_memory_read_back_as_they_were_written(tmp_path):
+    """tests/host/packed_pieces.cpp: both forms of a list in memory, found by blocks and lengths as the kernels find them."""
+    _host_sanitizer_run(tmp_path, "packed_pieces", ["ft_plan.cpp", "ft_pool.cpp"], [], "done")
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("far", [False, True])
+@pytest.mark.parametrize("n", [241, 1024, 1025, 2730, 2731, 4096, 4097, 16384])
+def test_lists_in_memory_of_every_size(n, far):
+    """The blocks in the arguments (16, 64, 256), lists read in place and uploaded, sides close to each other and 4 GiB apart."""
+    import torch
+    from paper_2411_01830_amd import binding
+    print(f"case lists in memory: {n}, far apart: {far}", flush=True)
+    rng = np.random.default_rng(n)
+    half = 16 * MiB
+    mem = torch.empty((4 << 30) + half if far else 2 * half, dtype=torch.uint8, device="cuda")
+    lo, hi = mem[:half], mem[-half:]
+    pool = binding.pool_create(lo.data_ptr(), half, 4 * KiB, 0)
+    try:
+        binding.pool_grow(pool, hi.data_ptr(), half)
+        binding.slab_alloc(pool, half)
+        binding.slab_alloc(pool, half)
+        sizes = rng.integers(1, 900 if n < 10000 else 400, n)
+        # every third tensor from the other side; what one side reads the other's tensors do not write
+        swap = np.arange(n) % 3 == 0
+        at = np.concatenate([[0], np.cumsum(sizes + 17)[:-1]])
+        assert at[-1] + 1000 < half // 2
+        src = np.where(swap, half, 0) + at
+        dst = np.where(swap, 0, half) + half // 2 + at + rng.integers(0, 2, n)
+        d = make_descs([dict(func=0, src_space=FT_POOL, dst_space=FT_POOL, src=int(src[i]), dst=int(dst[i]), row_bytes=int(sizes[i])) for i in range(n)])
+        for call in ("submit", "static"):
+            lo.random_(0, 256)
+            hi.random_(0, 256)
+            before = torch.cat([lo, hi]).cpu().numpy()
+            want = before.copy()
+            for s, t, b in zip(src, dst, sizes):
+                want[t:t + b] = before[s:s + b]
+            if call == "submit":
+                binding.wait(pool, binding.submit_transfers(pool, d, [1], 256 * KiB, 0, torch.cuda.current_stream().cuda_stream))
+            elif n == 241:
+                binding.submit_static(pool, d, [1], 256 * KiB, 0, torch.cuda.current_stream().cuda_stream)
+            else:
+                continue
+            torch.cuda.synchronize()
+            assert np.array_equal(torch.cat([lo, hi]).cpu().numpy(), want), call
+    finally:
+        binding.pool_destroy(pool)
+
+
 # as above; the tiles are 1, 2 or 4 KiB, the workgroups at most 64 from the host and towards it 128, of more than 256 tiles 48
 LINK_CASES = [
     ("one byte", lambda g: [(1, 1, 0, 0, 0, 3, 9)], [1], 2 * MiB, True),
