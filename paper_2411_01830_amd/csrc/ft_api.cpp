@@ -50,6 +50,14 @@ int ensure_device(ft_pool *p) {
     c->counter_pairs = c->idle_counter + 256 / sizeof(unsigned long long);
     for (uint32_t i = 0; i < kPairs; ++i) c->free_pairs.push_back(kPairs - 1 - i);
   }
+  if (c->done_words == nullptr) {
+    constexpr uint32_t kSlots = 64;
+    uint64_t *words = nullptr;
+    FT_HIP(p, hipHostMalloc(reinterpret_cast<void **>(&words), kSlots * kDoneWords * kDoneStride * sizeof(uint64_t), hipHostMallocDefault));
+    std::memset(words, 0, kSlots * kDoneWords * kDoneStride * sizeof(uint64_t));
+    c->done_words = words;
+    for (uint32_t i = 0; i < kSlots; ++i) c->free_done.push_back(kSlots - 1 - i);
+  }
   c->ready = true;
   return FT_OK;
 }
@@ -324,6 +332,11 @@ void release_device_side(ft_pool *p, Job *job) {
       p->ctx->free_pairs.push_back((uint32_t)job->run[c].counter_pair);
       job->run[c].counter_pair = -1;
     }
+    if (job->run[c].done_slot >= 0) {
+      std::lock_guard<std::mutex> lock(p->ctx->mu);
+      p->ctx->free_done.push_back((uint32_t)job->run[c].done_slot);
+      job->run[c].done_slot = -1;
+    }
     put_blob(p, job->run[c].log);
     put_event(p, true, job->run[c].ev_begin);
     put_event(p, true, job->run[c].ev_end);
@@ -331,12 +344,33 @@ void release_device_side(ft_pool *p, Job *job) {
   }
 }
 
+// How many wavefronts of a class whose kernel says itself when it is done have not done so, of the first `left`. The last is asked first: what is written
+// meanwhile are lines that nobody reads.
+uint32_t unsaid(const ft_pool *p, const ClassRun &r, uint32_t left) {
+  const uint64_t *words = p->ctx->done_words + (uint64_t)r.done_slot * kDoneWords * kDoneStride;
+  while (left > 0 && __atomic_load_n(words + kDoneStride * (left - 1), __ATOMIC_ACQUIRE) == r.done_value) --left;
+  return left;
+}
+bool said_done(const ft_pool *p, const ClassRun &r) { return r.done_slot >= 0 && unsaid(p, r, r.workgroups) == 0; }
+
+// Waits for that, but not for long: what the job's event takes longer is little beside a long job (or one behind other work).
+bool wait_until_said(const ft_pool *p, const ClassRun &r) {
+  if (r.done_slot < 0) return false;
+  const auto until = std::chrono::steady_clock::now() + std::chrono::microseconds(200);
+  uint32_t left = r.workgroups;
+  for (uint32_t round = 1; (left = unsaid(p, r, left)) > 0; ++round) {
+    if (round % 64 == 0 && std::chrono::steady_clock::now() > until) return false;
+    __builtin_ia32_pause();
+  }
+  return true;
+}
+
 int wait_locked(ft_pool *p, Job *job) {
   DeviceGuard guard(p->device);
   for (int c = 0; c < FT_NCLASS; ++c) {
     ClassRun &r = job->run[c];
     if (!r.used) continue;
-    FT_HIP(p, hipEventSynchronize(r.ev_done));
+    if (!said_done(p, r)) FT_HIP(p, hipEventSynchronize(r.ev_done));
     if (job->flags & FT_TIMING) {
       FT_HIP(p, hipEventElapsedTime(&r.device_ms, r.ev_begin, r.ev_end));
       hipEvent_t epoch = nullptr;
@@ -586,7 +620,7 @@ int launch_with_the_launch(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chun
 hipError_t upload_pieces(const Blob &b, uint64_t bytes, hipStream_t stream) {
   for (uint64_t at = 0; at < bytes;) {
     const OneRun part(reinterpret_cast<uint64_t>(b.host) + at, reinterpret_cast<uint64_t>(b.dev) + at, bytes - at, piece_tile(FT_H2P, bytes), true);
-    const hipError_t e = launch_pieces(part.tables, FT_H2P, true, nullptr, stream, nullptr, nullptr);
+    const hipError_t e = launch_pieces(part.tables, FT_H2P, true, nullptr, DoneWords(), stream, nullptr, nullptr);
     if (e != hipSuccess) return e;
     at += part.len;
   }
@@ -794,6 +828,17 @@ int launch_as_pieces(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_byte
   if (rc == FT_OK && timing) rc = get_event(p, true, &r.ev_begin);
   if (rc == FT_OK && timing) rc = get_event(p, true, &r.ev_end);
   if (rc != FT_OK) return fail_submit(p, job, rc);
+  DoneWords done;
+  if (!timing && says_done(only, cp.payload, t.ntiles)) {
+    std::lock_guard<std::mutex> ctx_lock(p->ctx->mu);
+    if (!p->ctx->free_done.empty()) {
+      r.done_slot = (int)p->ctx->free_done.back();
+      p->ctx->free_done.pop_back();
+      r.done_value = ++p->ctx->done_value;
+      done.words = p->ctx->done_words + (uint64_t)r.done_slot * kDoneWords * kDoneStride;
+      done.value = r.done_value;
+    }
+  }
   hipError_t e = hipSuccess;
   if (!with_launch) {
     const bool in_place = pieces_read_in_place(only, packed_bytes(t));
@@ -801,7 +846,7 @@ int launch_as_pieces(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_byte
     t.packed = in_place ? job->tables.host : job->tables.dev;
   }
   // without timing the done event is bound to the dispatch itself, which spares a marker behind it
-  if (e == hipSuccess) e = launch_pieces(t, only, with_launch, counter, user, r.ev_begin, timing ? r.ev_end : r.ev_done);
+  if (e == hipSuccess) e = launch_pieces(t, only, with_launch, counter, done, user, r.ev_begin, timing ? r.ev_end : r.ev_done);
   if (e == hipSuccess && timing) e = hipEventRecord(r.ev_done, user);
   if (e != hipSuccess) {
     p->hip_error = std::string("launch of pieces: ") + hipGetErrorString(e);
@@ -1101,14 +1146,12 @@ int ft_wait(ft_pool *p, ft_job_t id) {
     lock.lock();
     retire(job);  // also after a failure: nothing of the job is in flight any more
   } else {
-    hipEvent_t done[FT_NCLASS];
-    for (int c = 0; c < FT_NCLASS; ++c) done[c] = job->run[c].used ? job->run[c].ev_done : nullptr;
     lock.unlock();
     {
       DeviceGuard guard(p->device);
       hipError_t e = hipSuccess;
       for (int c = 0; c < FT_NCLASS; ++c)
-        if (done[c] != nullptr && hipEventSynchronize(done[c]) != hipSuccess) e = hipErrorUnknown;  // shows again below
+        if (job->run[c].used && !wait_until_said(p, job->run[c]) && hipEventSynchronize(job->run[c].ev_done) != hipSuccess) e = hipErrorUnknown;  // shows again below
       if (e == hipSuccess) finish_staging(p, job);  // (`waiting` keeps the record alive meanwhile)
     }
     lock.lock();
@@ -1138,6 +1181,7 @@ int ft_job_done(ft_pool *p, ft_job_t id, int *done_out) {
   DeviceGuard guard(p->device);
   for (int c = 0; c < FT_NCLASS; ++c) {
     if (!job->run[c].used) continue;
+    if (said_done(p, job->run[c])) continue;
     const hipError_t e = hipEventQuery(job->run[c].ev_done);
     if (e == hipErrorNotReady) {
       *done_out = 0;

@@ -39,6 +39,8 @@ struct ClassRun {
   bool on_user_stream = false;  // launched on the caller's stream, tables in the launch
   hipStream_t stream = nullptr; // the library's stream it runs on otherwise
   int counter_pair = -1;        // its self-resetting counter pair, if it needed a counter
+  int done_slot = -1;           // its words in pinned memory, if its kernel says itself when it is done
+  uint64_t done_value = 0;
   // ev_done orders the caller's stream and ft_wait after the class's work. With FT_TIMING,
   // ev_begin / ev_end bracket it: bound to the kernel's dispatch on the kernel path,
   // recorded around the copy calls on the DMA path.
@@ -126,6 +128,10 @@ struct DeviceCtx {
   // travel with the launch: zero whenever no kernel is using them
   unsigned long long *counter_pairs = nullptr;
   std::vector<uint32_t> free_pairs;
+  // lists of kDoneWords words in pinned memory, for kernels that say themselves when they are done (ft_pieces.h), each time with another value
+  uint64_t *done_words = nullptr;
+  uint64_t done_value = 0;
+  std::vector<uint32_t> free_done;
 };
 
 DeviceCtx *device_ctx(int device);

@@ -16,9 +16,10 @@ namespace ft {
 hipError_t launch_copy(const ClassTable &T, int link_class, uint32_t workgroups, hipStream_t stream,
                        hipEvent_t ev_start, hipEvent_t ev_stop, const InlineBlob *tables = nullptr);
 // The pieces of a class (ft_pieces.h), whose list lies where t.packed says or (on_host) is to travel with the launch. counter: on
-// the host link a word in device memory, of launches of which piece_draws says so one that is zero and will be zero again.
-hipError_t launch_pieces(const PieceTables &t, int cls, bool on_host, unsigned long long *counter, hipStream_t stream, hipEvent_t ev_start,
-                         hipEvent_t ev_stop);
+// the host link a word in device memory, of launches of which piece_draws says so one that is zero and will be zero again. done: words for
+// the launch's workgroups, at most kDoneWords, or none.
+hipError_t launch_pieces(const PieceTables &t, int cls, bool on_host, unsigned long long *counter, const DoneWords &done, hipStream_t stream,
+                         hipEvent_t ev_start, hipEvent_t ev_stop);
 // Decode every chunk rank with the device function the copy kernel uses (test hook).
 hipError_t launch_decode(const ClassTable &T, uint32_t *func_out, uint32_t *chunk_out, uint64_t cap,
                          hipStream_t stream, const InlineBlob *tables = nullptr);

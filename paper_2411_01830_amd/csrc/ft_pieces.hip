@@ -139,7 +139,7 @@ __device__ __forceinline__ Piece find_piece(const PieceRefs<BLOCKS, CLOSE> &, ui
 template <int NT>
 __device__ __forceinline__ void move_run(uint64_t d, uint64_t s, uint32_t n, uint32_t lane) {
   if (n < 16) {
-    if (lane < n) st_off<uint8_t, 0>(d, lane, ld_off<uint8_t, 0>(s, lane));
+    if (lane < n) st_off<uint8_t, NT == kThrough ? kThrough : 0>(d, lane, ld_off<uint8_t, 0>(s, lane));
     return;
   }
   const RunWindows w = run_windows(NT == kFromHost ? s : d, n);  // whole granules on the side that is dearer
@@ -181,7 +181,7 @@ __device__ __forceinline__ void move_rows(uint64_t d, uint64_t s, const PieceRow
   } else {
     move_windows<NT, 8>(d, s, r, w, lane);
   }
-  if (edge) st_off<uint8_t, 0>(d, ed, eb);
+  if (edge) st_off<uint8_t, NT == kThrough ? kThrough : 0>(d, ed, eb);
 }
 
 template <int NT, bool ROWS>
@@ -207,10 +207,21 @@ __device__ __forceinline__ void move_tile(const Piece &p, uint32_t lane) {
   move_run<NT>(d + begin, s + begin, n, lane);
 }
 
+// A wavefront's last words: what it stored is in memory, for every die, the copy engines and the host. The wait is spelled out because the
+// compiler does not count the stores of inline assembly.
+template <int NT>
+__device__ __forceinline__ void say_done(const DoneWords &done) {
+  // Written through to memory when the wait is over; what is not is written back here. (64 KiB pool->pool with that instead 9.6 a pass, so 9.25.)
+  if (NT != kThrough) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  if (threadIdx.x == 0) __hip_atomic_store(done.words + kDoneStride * blockIdx.x, done.value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 template <int NT, class A>
-__global__ __launch_bounds__(64) void ft_piece_kernel(A args) {
+__global__ __launch_bounds__(64) void ft_piece_kernel(A args, DoneWords done) {
   const uint32_t t = A::kOne ? blockIdx.x : tile_of_workgroup(blockIdx.x, args.ntiles);
   move_tile<NT, A::kRows>(find_piece<NT>(args, t, threadIdx.x), threadIdx.x);
+  if (NT == kThrough) say_done<NT>(done);
 }
 
 // The same over the host link, which has to be full but not crowded: 64 wavefronts with 4 KiB of loads from host memory each, one on
@@ -226,6 +237,7 @@ __global__ __launch_bounds__(64) void ft_piece_kernel(A args) {
 struct LinkTiles {
   unsigned long long *counter;
   uint32_t ntiles;
+  DoneWords done;
 };
 
 template <int NT, class A>
@@ -256,6 +268,7 @@ __global__ __launch_bounds__(64) void ft_link_piece_kernel(A args, LinkTiles l) 
     }
     if (n >= 16) wave_run_stores<NT, 4>(v, d, w, 0, lane);
   }
+  if (l.done.words != nullptr) say_done<NT>(l.done);
 }
 
 namespace {
@@ -264,6 +277,7 @@ struct Launch {
   int cls;
   uint32_t ntiles, lds;
   unsigned long long *counter;
+  DoneWords done;
   hipStream_t stream;
   hipEvent_t ev_start, ev_stop;
 };
@@ -272,8 +286,10 @@ template <class A>
 hipError_t launch(const A &a, const Launch &l) {
   static_assert(sizeof(A) + sizeof(LinkTiles) <= 4096, "kernel arguments end at 4 KiB");
   const dim3 grid(piece_workgroups(l.cls, l.ntiles)), block(64);
-  const LinkTiles tiles = {l.counter, l.ntiles};
-  if (l.cls == 2) hipExtLaunchKernelGGL((ft_piece_kernel<0, A>), grid, block, l.lds, l.stream, l.ev_start, l.ev_stop, 0, a);
+  const LinkTiles tiles = {l.counter, l.ntiles, l.done};
+  if (l.done.words != nullptr && grid.x > kDoneWords) return hipErrorInvalidValue;
+  if (l.cls == 2 && l.done.words != nullptr) hipExtLaunchKernelGGL((ft_piece_kernel<kThrough, A>), grid, block, l.lds, l.stream, l.ev_start, l.ev_stop, 0, a, l.done);
+  else if (l.cls == 2) hipExtLaunchKernelGGL((ft_piece_kernel<0, A>), grid, block, l.lds, l.stream, l.ev_start, l.ev_stop, 0, a, l.done);
   else if constexpr (A::kRows) return hipErrorInvalidValue;
   else if (l.cls == 0) hipExtLaunchKernelGGL((ft_link_piece_kernel<kFromHost, A>), grid, block, 0, l.stream, l.ev_start, l.ev_stop, 0, a, tiles);
   else hipExtLaunchKernelGGL((ft_link_piece_kernel<kToHost, A>), grid, block, 0, l.stream, l.ev_start, l.ev_stop, 0, a, tiles);
@@ -321,10 +337,10 @@ hipError_t launch_refs(const PieceTables &t, const Launch &l) {
 
 }  // namespace
 
-hipError_t launch_pieces(const PieceTables &t, int cls, bool on_host, unsigned long long *counter, hipStream_t stream, hipEvent_t ev_start,
-                         hipEvent_t ev_stop) {
+hipError_t launch_pieces(const PieceTables &t, int cls, bool on_host, unsigned long long *counter, const DoneWords &done, hipStream_t stream,
+                         hipEvent_t ev_start, hipEvent_t ev_stop) {
   if (t.n == 0 || t.ntiles == 0 || cls < 0 || cls > 2 || (on_host && !pieces_go_along(t)) || (cls != 2 && t.tile > 4096)) return hipErrorInvalidValue;
-  const Launch l = {cls, t.ntiles, piece_lds(cls, t), counter, stream, ev_start, ev_stop};
+  const Launch l = {cls, t.ntiles, piece_lds(cls, t), counter, done, stream, ev_start, ev_stop};
   const bool rows = t.shape != nullptr;
   if (!on_host) {
     if (rows || t.packed == nullptr) return hipErrorInvalidValue;

@@ -184,7 +184,7 @@ extern "C" int ft_submit_static(ft_pool *p, const ft_desc *descs, uint32_t ndesc
         FT_HIP(p, put_words(d + 256, h.data(), h.size(), nullptr, stream));
         t.packed = d + 256;
       }
-      FT_HIP(p, launch_pieces(t, c, with_launch, nullptr, stream, nullptr, nullptr));
+      FT_HIP(p, launch_pieces(t, c, with_launch, nullptr, DoneWords(), stream, nullptr, nullptr));
       continue;
     }
     uint64_t wg = s.code >= kWaveTiles ? wave_workgroups(sd.cu_count, s.code, s.ntickets)

@@ -287,7 +287,7 @@ static void move_tile(const PieceTables &t, uint32_t i, uint32_t no, bool by_sou
   move(d0 + (uint64_t)w.more * r.dst_pitch, s0 + (uint64_t)w.more * r.src_pitch, w.short_last);
 }
 
-hipError_t launch_pieces(const PieceTables &t, int cls, bool on_host, unsigned long long *counter, hipStream_t stream, hipEvent_t, hipEvent_t) {
+hipError_t launch_pieces(const PieceTables &t, int cls, bool on_host, unsigned long long *counter, const DoneWords &done, hipStream_t stream, hipEvent_t, hipEvent_t) {
   if (t.n == 0 || t.ntiles == 0 || cls < 0 || cls > 2 || (on_host && !pieces_go_along(t)) || (cls != 2 && (t.tile > 4096 || t.shape != nullptr))) return hipErrorInvalidValue;
   FAIL_POINT("launch_pieces", hipErrorLaunchFailure);
   g_stream = stream;
@@ -298,6 +298,8 @@ hipError_t launch_pieces(const PieceTables &t, int cls, bool on_host, unsigned l
   }
   for (uint32_t i = 0; i < t.n; ++i)
     for (uint32_t no = 0; no < (i + 1 < t.n ? t.first[i + 1] : t.ntiles) - t.first[i]; ++no) move_tile(t, i, no, cls == 0);
+  if (done.words != nullptr && piece_workgroups(cls, t.ntiles) > kDoneWords) return hipErrorInvalidValue;
+  for (uint32_t i = 0; done.words != nullptr && i < piece_workgroups(cls, t.ntiles); ++i) __atomic_store_n(done.words + kDoneStride * i, done.value, __ATOMIC_RELEASE);
   return hipSuccess;
 }
 

@@ -311,3 +311,71 @@ def test_inline_assembly_stores_of_the_piece_kernels_leave_no_hazard(tmp_path):
     for i in stores:
         assert re.fullmatch(r"global_store_dwordx4 v\[\d+:\d+\], [va]\[\d+:\d+\], off sc1", lines[i]), lines[i]
         assert lines[i + 1] == "s_nop 1", lines[i:i + 2]
+
+
+def test_kernels_that_say_they_are_done_have_waited_for_their_stores(tmp_path):
+    """In front of each word to the host a wait for every store, and nothing stored between the two."""
+    import os
+    import re
+    import subprocess
+    from paper_2411_01830_amd import build
+    out = tmp_path / "pieces.s"
+    subprocess.run([build.hipcc(), "-x", "hip", *build.FLAGS, "--cuda-device-only", "-S", os.path.join(build.CSRC, "ft_pieces.hip"), "-o", str(out)],
+                   check=True, capture_output=True)
+    lines = [re.sub(r"\s+", " ", l.split("//")[0]).strip() for l in open(out)]
+    said = [i for i, l in enumerate(lines) if l.startswith("global_store_dwordx2") and l.endswith(" sc0 sc1")]
+    kernels = [l for l in lines if re.match(r"_ZN2ft(15ft_piece_kernelILi4E|20ft_link_piece_kernel)\S*:", l)]
+    assert len(said) == len(kernels) >= 20
+    for i in said:
+        j = max(k for k in range(i) if lines[k] == "s_waitcnt vmcnt(0)" and lines[k - 1] == ";;#ASMSTART")
+        assert not [l for l in lines[j:i] if re.match(r"(global|flat|buffer|scratch)_(store|atomic)", l)], lines[j:i + 1]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("where", ["pool_to_pool", "host_to_pool", "pool_to_host"])
+@pytest.mark.parametrize("sizes", [[5], [16], [64 * KiB + 3], [640 * 2 * KiB - 128], [640 * 2 * KiB + 1], [31, 700, 5000] * 25, [2 * KiB] * 70],
+                         ids=["5", "16", "64K", "640 tiles", "641 tiles", "75 small", "70 jobs"])
+def test_what_has_been_waited_for_is_there(where, sizes):
+    """After ft_wait, with nothing else waited for, the bytes are read by a kernel on another stream, by the copy engine and by the host."""
+    import torch
+    from paper_2411_01830_amd import binding
+    print(f"case waited for: {where} {len(sizes)} of {sizes[0]}", flush=True)
+    g = torch.Generator("cuda").manual_seed(len(sizes))
+    room = -(-(sum(sizes) + 64 * len(sizes)) // 4096) * 4096
+    mem = torch.zeros(2 * room, dtype=torch.uint8, device="cuda")
+    host = torch.zeros(room, dtype=torch.uint8, pin_memory=True)
+    pool = binding.pool_create(mem.data_ptr(), 2 * room, 4 * KiB, 0)
+    jobs, other = torch.cuda.Stream(), torch.cuda.Stream()
+    try:
+        binding.slab_alloc(pool, 2 * room)
+        binding.host_window_add(pool, host.data_ptr(), room)
+        starts = np.concatenate([[0], np.cumsum([n + 48 for n in sizes])[:-1]])
+        src0, dst0 = (host.data_ptr() if where == "host_to_pool" else 0), (host.data_ptr() if where == "pool_to_host" else room)
+        recs = [dict(func=0, src_space=0 if where == "host_to_pool" else 1, dst_space=0 if where == "pool_to_host" else 1, src=src0 + int(a) + 1,
+                     dst=dst0 + int(a) + 1, row_bytes=n) for a, n in zip(starts, sizes)]
+        lists = [[r] for r in recs] if len(recs) == 70 else [recs]
+        lists = [binding.Transfers(make_descs(l), [1]) for l in lists]
+        mask = torch.zeros(room, dtype=torch.bool, device="cuda")
+        for a, n in zip(starts, sizes):
+            mask[int(a) + 1:int(a) + 1 + n] = True
+        for _ in range(12):
+            data = torch.randint(0, 256, (room,), dtype=torch.uint8, device="cuda", generator=g)
+            want = torch.where(mask, data, torch.zeros_like(data))
+            (host if where == "host_to_pool" else mem[:room]).copy_(data)
+            (host if where == "pool_to_host" else mem[room:]).zero_()
+            torch.cuda.synchronize()
+            handles = [binding.submit_transfers(pool, l, None, 2 * MiB, 0, jobs.cuda_stream) for l in lists]
+            for h in handles:
+                binding.wait(pool, h)
+            if where == "pool_to_host":
+                got = torch.from_numpy(host.numpy().copy()).cuda()
+            else:
+                with torch.cuda.stream(other):
+                    got = mem[room:] + torch.zeros((), dtype=torch.uint8, device="cuda")
+                    copied = mem[room:].cpu()
+                assert torch.equal(copied.cuda(), want)
+            torch.cuda.synchronize()
+            assert torch.equal(got, want)
+    finally:
+        torch.cuda.synchronize()
+        binding.pool_destroy(pool)
