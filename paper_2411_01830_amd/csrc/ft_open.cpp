@@ -62,6 +62,7 @@ struct Generation {
   uint64_t ntickets = 0;
   uint64_t next_rank = 0;           // first rank of this order not yet triggered
   uint32_t next_counter = 0;
+  bool parts = false;               // there are counters for batches in parts
   uint32_t inflight = 0;            // batches launched with these tables and not seen complete
   hipEvent_t uploaded = nullptr;    // each of the class's two streams waits for it before its first batch
   bool waited_upload[2] = {false, false};
@@ -111,8 +112,10 @@ void stage_copy(char *dst, const char *src, uint64_t n) {
   else std::memcpy(dst, src, n);
 }
 
+// A batch in flight, or a part of one (kPartBytes): what is counted of a batch is its last part's.
 struct OpenBatch {
   std::shared_ptr<Generation> gen;
+  bool last = true;
   uint32_t lane = 0;                // which of the class's two streams
   hipEvent_t done = nullptr, t_begin = nullptr, t_end = nullptr;
   std::vector<std::pair<uint64_t, uint64_t>> job_chunks;  // job id, chunks of it in this batch
@@ -314,6 +317,7 @@ struct OpenClass {
   std::vector<OpenFn> fns;
   std::shared_ptr<Generation> gen;  // the order in force
   std::deque<OpenBatch> inflight;
+  uint32_t batches_inflight = 0;    // of them whole or with their last part
   uint64_t batches_triggered = 0;
   uint64_t batches_done = 0;        // of them, seen complete (bytes in place)
   // chunks per batch of this class. The paper's batch (5 chunks of 2 MB) is sized for a PCIe
@@ -415,7 +419,8 @@ int build_generation(ft_pool *p, OpenState *st, int c, hipStream_t user, std::sh
   build_chunk_table(cp, st->chunk_bytes, oc.tile_bytes, oc.tiles_per_chunk);
   build_skips(cp, st->chunk_bytes, oc.tile_bytes, oc.tiles_per_chunk, &g->skips, &g->ntickets);
   const uint64_t ncounters = (cp.nchunks + oc.batch_chunks - 1) / oc.batch_chunks;
-  const Layout lay = layout_of(cp, 0, ncounters);
+  g->parts = oc.ring != nullptr && c == FT_H2P;  // a batch may be launched in as many parts as it has chunks
+  const Layout lay = layout_of(cp, 0, g->parts ? cp.nchunks : ncounters);
   rc = get_blob(p, lay.end, true, &g->blob);
   if (rc != FT_OK) return rc;
   std::memset(g->blob.host, 0, lay.end);
@@ -492,6 +497,13 @@ void retire_generation(ft_pool *p, OpenState *st, int c, Generation *g) {
 constexpr uint64_t kStagePiece = 256 * 1024;  // longest single copy handed to a helper
 constexpr uint32_t kOnDeviceBatchScale = 64;  // see OpenClass::batch_chunks
 
+// A batch of pageable sources that finds nothing in flight is launched in parts of so many bytes (of whole chunks), each as soon as it is in
+// the ring, so that the link does not wait for the whole batch: a chunk of 2 MiB takes four threads 38 us, a batch of five 190. Passes, us, 4
+// tensors in chunks of 2 MiB: 16 MiB 427..437 -> 369..377, 32 MiB 741..747 -> 711..717, 64 MiB 1331 -> 1315, 128 MiB 2528 -> 2523 (the threads are the bound).
+// Not towards pageable memory, where the last batch's parts could leave the ring as they arrive: 16 MiB 455 -> 469, 128 MiB 2622 -> 2634; there the
+// threads are behind by then.
+constexpr uint64_t kPartBytes = 1 << 20;
+
 struct Prepared {
   OpenBatch batch;
   ClassTable T;
@@ -537,88 +549,103 @@ void stage_chunk(const ClassPlan &cp, const Func &f, uint64_t k, uint64_t chunk_
   }
 }
 
-// Decides the next batch of class c and books it (ranks, counter, what it holds).
+// Decides the next batch of class c and books it (ranks, counters, what it holds), as one launch or as parts.
 // Called with st->mu held.
-bool prepare_batch(OpenState *st, int c, Prepared *out) {
+bool prepare_batch(OpenState *st, int c, std::vector<Prepared> *out) {
   ft_pool *p = st->pool;
   OpenClass &oc = st->cls[c];
   Generation &g = *oc.gen;
   const ClassPlan &cp = g.plan;
   const uint64_t r0 = g.next_rank;
   const uint64_t r1 = std::min<uint64_t>(r0 + oc.batch_chunks, cp.nchunks);
-  ClassTable &T = out->T;
-  T = g.table;
-  uint64_t t0, t1, acc1;
-  uint32_t idx1;
-  ticket_of_rank(g, oc.tiles_per_chunk, r0, &t0, &T.skip0, &T.skip_acc0);
-  if (r1 == cp.nchunks) t1 = g.ntickets;
-  else ticket_of_rank(g, oc.tiles_per_chunk, r1, &t1, &idx1, &acc1);
-  T.ticket_base = t0;
-  T.ntickets = t1;
-  T.ticket = g.table.ticket + g.next_counter;
-  {
-    uint32_t lo = 0, hi = (uint32_t)cp.phases.size();
-    while (hi - lo > 1) {
-      const uint32_t mid = (lo + hi) >> 1;
-      if (cp.phases[mid].rank_base <= r0) lo = mid; else hi = mid;
-    }
-    T.phase0 = lo;
-  }
-  set_cursor_start(T, cp.phases.data(), (uint32_t)cp.phases.size(), g.skips.data(), (uint32_t)g.skips.size());
   const uint64_t slot0 = oc.ring_slots ? (oc.batches_triggered % (st->depth + 1)) * oc.batch_chunks : 0;
-  T.stage_base = reinterpret_cast<uint64_t>(oc.ring);
-  T.stage_rank0 = r0;
-  T.stage_slot0 = slot0;
-  if (g.log.dev != nullptr) {
-    T.log = reinterpret_cast<LogEntry *>(g.log.dev);
-    T.wg_log = reinterpret_cast<WgLogEntry *>(g.log.dev + g.ntickets * sizeof(LogEntry)) +
-               (uint64_t)g.next_counter * oc.workgroups;
-  }
-  OpenBatch &b = out->batch;
-  b.gen = oc.gen;
-  b.lane = (uint32_t)(oc.batches_triggered & 1);
   const bool timing = (st->flags & FT_TIMING) != 0;
-  if (get_event(p, false, &b.done) != FT_OK || (timing && (get_event(p, true, &b.t_begin) != FT_OK ||
-                                                           get_event(p, true, &b.t_end) != FT_OK))) {
-    if (st->error == FT_OK) st->error = FT_EHIP, st->error_text = p->hip_error;
-    put_event(p, false, b.done);
-    put_event(p, true, b.t_begin);
-    put_event(p, true, b.t_end);
-    return false;
-  }
-  out->wait_upload = !g.waited_upload[b.lane];
-  g.waited_upload[b.lane] = true;
-  uint64_t wg = oc.workgroups;
-  if (wg > t1 - t0) wg = t1 - t0;
-  out->workgroups = (uint32_t)wg;
-  // what the batch holds, on the host: advances every function's count of triggered chunks
-  const uint32_t batch_no = (uint32_t)oc.batches_triggered;
-  for (uint64_t r = r0; r < r1; ++r) {
-    const ChunkId id = decode_rank(cp.phases.data(), (uint32_t)cp.phases.size(), cp.slots.data(), r);
-    const Func &f = cp.funcs[id.fl];
-    OpenFn &fn = oc.fns[f.func];
-    const uint64_t k = f.chunk_base + id.k;
-    fn.next_chunk = k + 1;
-    bool found = false;
-    for (auto &jc : b.job_chunks)
-      if (jc.first == fn.job) jc.second += 1, found = true;
-    if (!found) b.job_chunks.push_back({fn.job, 1});
-    {
-      const uint64_t c0 = k * st->chunk_bytes;
-      const uint64_t n = std::min(st->chunk_bytes, fn.stream_bytes - c0);
-      if (!b.fn_bytes.empty() && b.fn_bytes.back().first == f.func) b.fn_bytes.back().second += n;
-      else b.fn_bytes.push_back({f.func, n});
+  const bool in_parts = g.parts && !timing && !(st->flags & FT_LOG) && oc.inflight.empty();
+  const uint64_t per = in_parts ? std::max<uint64_t>(1, kPartBytes / st->chunk_bytes) : r1 - r0;
+  out->clear();
+  for (uint64_t r = r0; r < r1; r += per) {
+    out->emplace_back();
+    OpenBatch &b = out->back().batch;
+    if (get_event(p, false, &b.done) != FT_OK || (timing && (get_event(p, true, &b.t_begin) != FT_OK ||
+                                                             get_event(p, true, &b.t_end) != FT_OK))) {
+      if (st->error == FT_OK) st->error = FT_EHIP, st->error_text = p->hip_error;
+      for (Prepared &pr : *out) {
+        put_event(p, false, pr.batch.done);
+        put_event(p, true, pr.batch.t_begin);
+        put_event(p, true, pr.batch.t_end);
+      }
+      return false;
     }
-    if (st->flags & FT_KEEP) oc.order.push_back(BatchRec{fn.job, fn.func, (uint32_t)k, batch_no});
-    if (fn.staged)
-      stage_chunk(cp, f, k, st->chunk_bytes, oc.ring + (slot0 + (r - r0)) * st->chunk_bytes, &out->copies,
-                  &b.unstage, &oc.staged_bytes);
   }
-  if (g.log.dev != nullptr) g.triggered.push_back(Generation::Triggered{t0, t1, batch_no});
+  const uint32_t batch_no = (uint32_t)oc.batches_triggered;
+  OpenBatch &whole = out->back().batch;  // counts for the batch
+  for (size_t i = 0; i < out->size(); ++i) {
+    Prepared &pr = (*out)[i];
+    const uint64_t p0 = r0 + i * per, p1 = std::min(p0 + per, r1);
+    ClassTable &T = pr.T;
+    T = g.table;
+    uint64_t t0, t1, acc1;
+    uint32_t idx1;
+    ticket_of_rank(g, oc.tiles_per_chunk, p0, &t0, &T.skip0, &T.skip_acc0);
+    if (p1 == cp.nchunks) t1 = g.ntickets;
+    else ticket_of_rank(g, oc.tiles_per_chunk, p1, &t1, &idx1, &acc1);
+    T.ticket_base = t0;
+    T.ntickets = t1;
+    T.ticket = g.table.ticket + g.next_counter;
+    {
+      uint32_t lo = 0, hi = (uint32_t)cp.phases.size();
+      while (hi - lo > 1) {
+        const uint32_t mid = (lo + hi) >> 1;
+        if (cp.phases[mid].rank_base <= p0) lo = mid; else hi = mid;
+      }
+      T.phase0 = lo;
+    }
+    set_cursor_start(T, cp.phases.data(), (uint32_t)cp.phases.size(), g.skips.data(), (uint32_t)g.skips.size());
+    T.stage_base = reinterpret_cast<uint64_t>(oc.ring);
+    T.stage_rank0 = r0;
+    T.stage_slot0 = slot0;
+    if (g.log.dev != nullptr) {
+      T.log = reinterpret_cast<LogEntry *>(g.log.dev);
+      T.wg_log = reinterpret_cast<WgLogEntry *>(g.log.dev + g.ntickets * sizeof(LogEntry)) +
+                 (uint64_t)g.next_counter * oc.workgroups;
+    }
+    OpenBatch &b = pr.batch;
+    b.gen = oc.gen;
+    b.last = i + 1 == out->size();
+    b.lane = (uint32_t)((oc.batches_triggered + (out->size() - 1 - i)) & 1);
+    pr.wait_upload = !g.waited_upload[b.lane];
+    g.waited_upload[b.lane] = true;
+    uint64_t wg = oc.workgroups;
+    if (wg > t1 - t0) wg = t1 - t0;
+    pr.workgroups = (uint32_t)wg;
+    // what the batch holds, on the host: advances every function's count of triggered chunks
+    for (uint64_t r = p0; r < p1; ++r) {
+      const ChunkId id = decode_rank(cp.phases.data(), (uint32_t)cp.phases.size(), cp.slots.data(), r);
+      const Func &f = cp.funcs[id.fl];
+      OpenFn &fn = oc.fns[f.func];
+      const uint64_t k = f.chunk_base + id.k;
+      fn.next_chunk = k + 1;
+      bool found = false;
+      for (auto &jc : whole.job_chunks)
+        if (jc.first == fn.job) jc.second += 1, found = true;
+      if (!found) whole.job_chunks.push_back({fn.job, 1});
+      {
+        const uint64_t c0 = k * st->chunk_bytes;
+        const uint64_t n = std::min(st->chunk_bytes, fn.stream_bytes - c0);
+        if (!whole.fn_bytes.empty() && whole.fn_bytes.back().first == f.func) whole.fn_bytes.back().second += n;
+        else whole.fn_bytes.push_back({f.func, n});
+      }
+      if (st->flags & FT_KEEP) oc.order.push_back(BatchRec{fn.job, fn.func, (uint32_t)k, batch_no});
+      if (fn.staged)
+        stage_chunk(cp, f, k, st->chunk_bytes, oc.ring + (slot0 + (r - r0)) * st->chunk_bytes, &pr.copies,
+                    &b.unstage, &oc.staged_bytes);
+    }
+    if (g.log.dev != nullptr) g.triggered.push_back(Generation::Triggered{t0, t1, batch_no});
+    g.next_counter += 1;
+    oc.tickets += t1 - t0;
+  }
   g.next_rank = r1;
-  g.next_counter += 1;
   g.inflight += 1;
-  oc.tickets += t1 - t0;
   oc.batches_triggered += 1;
   return true;
 }
@@ -658,33 +685,46 @@ void feeder_main(OpenState *st, int c) {
   };
   OpenBatch carry;  // complete on the device, its bytes still to be taken out of the ring
   bool have_carry = false;
+  std::vector<Prepared> parts;
   for (;;) {
-    while (st->error == FT_OK && oc.inflight.size() < st->depth && oc.gen->next_rank < oc.gen->plan.nchunks) {
-      Prepared pr;
-      if (!prepare_batch(st, c, &pr)) break;
+    while (st->error == FT_OK && oc.batches_inflight < st->depth && oc.gen->next_rank < oc.gen->plan.nchunks) {
+      if (!prepare_batch(st, c, &parts)) break;
       StagePool *stagers = oc.stagers.get();
-      lock.unlock();
-      // the ring slots of this batch were last used depth + 1 batches ago; at most depth - 1
-      // batches are in flight, so that one is complete
-      if (!pr.copies.empty()) {
-        const auto s0 = std::chrono::steady_clock::now();
-        stagers->run(pr.copies);
-        const double ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - s0).count();
-        lock.lock();
-        oc.stage_ms += ms;
-        lock.unlock();
+      hipError_t e = hipSuccess;
+      for (Prepared &pr : parts) {
+        if (e == hipSuccess) {
+          lock.unlock();
+          // the ring slots of this batch were last used depth + 1 batches ago; at most depth - 1
+          // batches are in flight, so that one is complete
+          double stage_ms = 0;
+          if (!pr.copies.empty()) {
+            const auto s0 = std::chrono::steady_clock::now();
+            stagers->run(pr.copies);
+            stage_ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - s0).count();
+          }
+          e = launch_batch(p, c, pr);
+          lock.lock();
+          oc.stage_ms += stage_ms;
+          if (e != hipSuccess) {
+            set_error(st, e, "open job batch launch");
+            if (&pr == &parts[0]) {
+              pr.batch.gen->inflight -= 1;
+            } else {  // the parts that have been launched are the batch
+              oc.inflight.back().last = true;
+              oc.batches_inflight += 1;
+            }
+          }
+        }
+        if (e != hipSuccess) {
+          put_event(p, false, pr.batch.done);
+          put_event(p, true, pr.batch.t_begin);
+          put_event(p, true, pr.batch.t_end);
+          continue;
+        }
+        oc.batches_inflight += pr.batch.last ? 1 : 0;
+        oc.inflight.push_back(std::move(pr.batch));
       }
-      const hipError_t e = launch_batch(p, c, pr);
-      lock.lock();
-      if (e != hipSuccess) {
-        set_error(st, e, "open job batch launch");
-        put_event(p, false, pr.batch.done);
-        put_event(p, true, pr.batch.t_begin);
-        put_event(p, true, pr.batch.t_end);
-        pr.batch.gen->inflight -= 1;
-        break;
-      }
-      oc.inflight.push_back(std::move(pr.batch));
+      if (e != hipSuccess) break;
     }
     if (have_carry) {
       // A complete batch whose ring slots hold bytes for pageable destinations. The batch
@@ -698,7 +738,7 @@ void feeder_main(OpenState *st, int c) {
       const double ms = std::chrono::duration<double, std::milli>(std::chrono::steady_clock::now() - s0).count();
       lock.lock();
       oc.stage_ms += ms;
-      count_done(carry);
+      if (carry.last) count_done(carry);
       have_carry = false;
       continue;
     }
@@ -725,12 +765,15 @@ void feeder_main(OpenState *st, int c) {
     put_event(p, false, b.done);
     put_event(p, true, b.t_begin);
     put_event(p, true, b.t_end);
-    b.gen->inflight -= 1;
-    if (b.gen->inflight == 0 && b.gen != oc.gen) retire_generation(p, st, c, b.gen.get());
+    if (b.last) {
+      oc.batches_inflight -= 1;
+      b.gen->inflight -= 1;
+      if (b.gen->inflight == 0 && b.gen != oc.gen) retire_generation(p, st, c, b.gen.get());
+    }
     if (st->error == FT_OK && !b.unstage.empty()) {
       carry = std::move(b);
       have_carry = true;
-    } else {
+    } else if (b.last) {
       count_done(b);
     }
   }

@@ -279,6 +279,38 @@ def test_pageable_sources_through_the_ring(gpu, batch, depth, threads):
         eng.close()
 
 
+@pytest.mark.parametrize("chunk,batch,depth", [(512 * 1024, 5, 3), (1 << 20, 7, 1), (3 << 20, 2, 2), (2 << 20, 5, 3)])
+def test_batches_of_pageable_sources_in_parts(gpu, chunk, batch, depth):
+    """The first batch of a job from pageable memory is launched as its parts reach the ring: bytes, and the number of batches, stay what they were."""
+    from workloads import FT_PAGEABLE
+    binding, _ = gpu
+    orc, eng, rng = _engines(gpu, 1 * MiB, 64 * MiB, seed=chunk % 97)
+    try:
+        page = rng.integers(0, 256, 28 * MiB, dtype=np.uint8)
+        for e in (orc, eng):
+            e.pageable_arena(28 * MiB)
+            e.write_pageable(0, page)
+        binding.set_batch(eng.pool, batch, depth)
+        sizes = [11 * MiB + 77, 5 * MiB + 1, 9 * MiB]
+        recs, at = [], 0
+        for i, n in enumerate(sizes):
+            dst = orc.slab_alloc(n + 16)
+            assert eng.slab_alloc(n + 16) == dst
+            recs.append(dict(func=i, src_space=FT_PAGEABLE, dst_space=FT_POOL, src=at + i, dst=dst + 5 * i, row_bytes=n))
+            at += n + 16
+        d = make_descs(recs)
+        orc.wait(orc.submit(d, [1, 2, 4], chunk))
+        print(f"parts chunk={chunk} batch={batch} depth={depth}", flush=True)
+        job = eng.submit(d, [1, 2, 4], chunk, fmt.FT_OPEN | fmt.FT_KEEP)
+        eng.wait(job)
+        _images_equal(orc, eng)
+        done, batches = binding.job_progress(eng.pool, job, 0, 3)
+        assert done == sizes and batches == -(-sum(-(-n // chunk) for n in sizes) // batch)
+        binding.job_release(eng.pool, job)
+    finally:
+        eng.close()
+
+
 def test_merges_from_another_thread_while_the_open_job_is_waited_for(gpu):
     """ft_wait on an open job must not keep the pool's other calls out: one thread waits for the long
     job while this one merges small ones into it and waits for each."""

@@ -460,6 +460,12 @@ def test_error_paths_with_injected_runtime_failures(tmp_path):
     _with_the_stand_in(tmp_path, "address,undefined", 0, program="fault_paths", args=[], expect="fault_paths done")
 
 
+@pytest.mark.parametrize("sanitize", ["address,undefined", "thread"])
+def test_batches_in_parts_with_injected_failures(tmp_path, sanitize):
+    """tests/host/ring_parts.cpp: batches of pageable sources launched in parts, whole and with each launch or event failing in turn."""
+    _with_the_stand_in(tmp_path, sanitize, 0, program="ring_parts", args=[], expect="ring_parts done")
+
+
 def test_rest_of_the_api_under_sanitizers(tmp_path):
     """tests/host/api_tour.cpp: logs with exactly-sized arrays, the device's order against the host planner's, the
     piece-by-piece comparison path, tuned launch shapes, pitched pieces in all classes, pool growth and shrinkage."""
