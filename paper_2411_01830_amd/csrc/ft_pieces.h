@@ -46,6 +46,8 @@ struct PieceTables {
 // A run's tiles begin and end where this many bytes of the side that is dearer to cut (the destination; host memory where
 // that is the source) do, so that no line is written by two wavefronts: shared lines cost a misaligned job 4-12 %.
 constexpr uint32_t kPieceLine = 128;
+// Tiles of a pool->pool job of runs that no cache holds.
+constexpr uint32_t kStreamTile = 16384;
 // Pieces of one job at most, and at most as many as travel with a launch, with as many shapes: kernel arguments end at 4 KiB, and
 // hold sides as 32-bit distances from the lowest.
 constexpr uint32_t kMaxPieces = 16384, kRunsAlong = 240, kRowsAlong = 140;
@@ -70,7 +72,7 @@ inline uint64_t packed_bytes(const PieceTables &t) { return (uint64_t)t.n * (t.c
 void find_base(PieceTables *t);
 // Writes t, whose base is known, to `to`.
 void pack_pieces(const PieceTables &t, char *to);
-// Fills t with the pieces of a class in its order, cut into tiles of `tile` bytes, a power of two from 1 to 8 KiB.
+// Fills t with the pieces of a class in its order, cut into tiles of `tile` bytes, a power of two from 1 to 8 KiB (of runs alone, pool->pool, 16).
 // by_source: the source's lines are the ones not to be cut. False: there are rows that the kernels do not cover (under 16
 // bytes, or so far apart that a tile's distances leave 32 bits).
 bool build_pieces(const ClassPlan &cp, uint64_t chunk_bytes, uint32_t tile, bool by_source, PieceTables *t);

@@ -135,7 +135,7 @@ __device__ __forceinline__ Piece find_piece(const PieceRefs<BLOCKS, CLOSE> &, ui
   return p;
 }
 
-// n bytes of a run, at most 512 windows.
+// n bytes of a run, at most 512 windows, streaming 1024.
 template <int NT>
 __device__ __forceinline__ void move_run(uint64_t d, uint64_t s, uint32_t n, uint32_t lane) {
   if (n < 16) {
@@ -146,7 +146,8 @@ __device__ __forceinline__ void move_run(uint64_t d, uint64_t s, uint32_t n, uin
   // no deeper than need be: a lane's load beyond the last window costs as much as any other
   if (w.count <= 128) wave_run_pass<NT, 2>(d, s, w, 0, lane);
   else if (w.count <= 256) wave_run_pass<NT, 4>(d, s, w, 0, lane);
-  else wave_run_pass<NT, 8>(d, s, w, 0, lane);
+  else if (NT != kStream || w.count <= 512) wave_run_pass<NT, 8>(d, s, w, 0, lane);
+  else wave_run_pass<NT, 16>(d, s, w, 0, lane);
 }
 
 // Up to R * 64 windows of rows. All loads before the first store; a lane past the last window loads the first one and stores nothing.
@@ -289,7 +290,10 @@ hipError_t launch(const A &a, const Launch &l) {
   const LinkTiles tiles = {l.counter, l.ntiles, l.done};
   if (l.done.words != nullptr && grid.x > kDoneWords) return hipErrorInvalidValue;
   if (l.cls == 2 && l.done.words != nullptr) hipExtLaunchKernelGGL((ft_piece_kernel<kThrough, A>), grid, block, l.lds, l.stream, l.ev_start, l.ev_stop, 0, a, l.done);
-  else if (l.cls == 2) hipExtLaunchKernelGGL((ft_piece_kernel<0, A>), grid, block, l.lds, l.stream, l.ev_start, l.ev_stop, 0, a, l.done);
+  else if (l.cls == 2 && a.tile == kStreamTile) {
+    if constexpr (A::kRows) return hipErrorInvalidValue;
+    else hipExtLaunchKernelGGL((ft_piece_kernel<kStream, A>), grid, block, l.lds, l.stream, l.ev_start, l.ev_stop, 0, a, l.done);
+  } else if (l.cls == 2) hipExtLaunchKernelGGL((ft_piece_kernel<0, A>), grid, block, l.lds, l.stream, l.ev_start, l.ev_stop, 0, a, l.done);
   else if constexpr (A::kRows) return hipErrorInvalidValue;
   else if (l.cls == 0) hipExtLaunchKernelGGL((ft_link_piece_kernel<kFromHost, A>), grid, block, 0, l.stream, l.ev_start, l.ev_stop, 0, a, tiles);
   else hipExtLaunchKernelGGL((ft_link_piece_kernel<kToHost, A>), grid, block, 0, l.stream, l.ev_start, l.ev_stop, 0, a, tiles);
@@ -339,7 +343,7 @@ hipError_t launch_refs(const PieceTables &t, const Launch &l) {
 
 hipError_t launch_pieces(const PieceTables &t, int cls, bool on_host, unsigned long long *counter, const DoneWords &done, hipStream_t stream,
                          hipEvent_t ev_start, hipEvent_t ev_stop) {
-  if (t.n == 0 || t.ntiles == 0 || cls < 0 || cls > 2 || (on_host && !pieces_go_along(t)) || (cls != 2 && t.tile > 4096)) return hipErrorInvalidValue;
+  if (t.n == 0 || t.ntiles == 0 || cls < 0 || cls > 2 || (on_host && !pieces_go_along(t)) || (cls != 2 && t.tile > 4096) || t.tile > kStreamTile) return hipErrorInvalidValue;
   const Launch l = {cls, t.ntiles, piece_lds(cls, t), counter, done, stream, ev_start, ev_stop};
   const bool rows = t.shape != nullptr;
   if (!on_host) {

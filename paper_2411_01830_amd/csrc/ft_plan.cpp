@@ -522,8 +522,18 @@ void pack_pieces(const PieceTables &t, char *to) {
 // so the places are counted before anything is written: kRunsAlong of them where the general tables travel along and for the wave
 // kernel's jobs, over the link 256 and one for every 64 KiB; and where there are many tensors, which the general tables have to hold too, one
 // for every two of them, over the link two for each.
+// Pool->pool beyond what the cache holds the general tables' 64 KiB tiles, which four wavefronts move line by line, are the faster ones for sides that are
+// aligned alike (382 MB 143 a pass, by pieces 148), and pieces of 16 KiB for those that are not. Three jobs in turn, us a pass, general tables -> pieces, all
+// tensors at odd addresses: 8 tensors 140 MiB 72.1 -> 62.7, 200 96.1 -> 83.6, 250 111.9 -> 102.0, 400 166.2 -> 156.5; 190 tensors 200 MiB 106.4 -> 93.4,
+// 400 178.4 -> 164.9; one tensor 200 MiB 86.5 -> 77.7, 700 259 -> 250. A quarter of 40 tensors so: 140 MiB 66.9 -> 64.7, 200 87.0 -> 85.2. So from five
+// eighths of the bytes on, up to 1024 places, 6 us of writing out.
 PieceRoom job_pieces(const ClassPlan &cp, int cls, uint64_t chunk_bytes, bool tables_fit) {
-  if (cls == FT_P2P && cp.payload > kCacheResidentBytes) return PieceRoom();
+  const bool streams = cls == FT_P2P && cp.payload > kCacheResidentBytes;
+  if (streams) {
+    uint64_t odd = 0;
+    for (const Xfer &x : cp.xfers) odd += ((x.src ^ x.dst) & 15) != 0 ? x.row_bytes : 0;
+    if (cp.pitched != 0 || odd < cp.payload / 8 * 5) return PieceRoom();
+  }
   if (cls == FT_H2P && cp.xfers.size() == 1 && cp.payload > 128u << 10 && ((cp.xfers[0].src | cp.xfers[0].dst) & 15) == 0) return PieceRoom();
   if (cp.pitched != 0 && (cls != FT_P2P || cp.xfers.size() > kRowsAlong)) return PieceRoom();
   if (cls != FT_P2P && cp.payload > 64u << 20) {
@@ -534,6 +544,7 @@ PieceRoom job_pieces(const ClassPlan &cp, int cls, uint64_t chunk_bytes, bool ta
   const PieceRoom room = piece_room(cp, chunk_bytes, piece_tile(cls, cp.payload));
   if (room.pieces == 0 || cp.pitched != 0) return room.pieces > 2 * kRowsAlong ? PieceRoom() : room;
   const uint64_t places = room.pieces - cp.xfers.size();
+  if (streams && places > 1024) return PieceRoom();
   if (places <= kRunsAlong) return room;
   if (tables_fit) return PieceRoom();
   if (cls != FT_P2P) return places <= 256 + (cp.payload >> 16) || places <= 2 * cp.xfers.size() ? room : PieceRoom();
@@ -542,7 +553,7 @@ PieceRoom job_pieces(const ClassPlan &cp, int cls, uint64_t chunk_bytes, bool ta
 
 uint32_t piece_tile(int cls, uint64_t payload) {
   if (cls != FT_P2P) return payload <= 32u << 10 ? 1024 : payload <= 128u << 10 ? 2048 : 4096;
-  return payload <= 10u << 20 ? 2048 : payload <= 20u << 20 ? 4096 : 8192;
+  return payload <= 10u << 20 ? 2048 : payload <= 20u << 20 ? 4096 : payload <= kCacheResidentBytes ? 8192 : kStreamTile;
 }
 
 uint32_t piece_workgroups(int cls, uint32_t ntiles) {
@@ -562,7 +573,11 @@ uint32_t piece_workgroups(int cls, uint32_t ntiles) {
 // kernel 40.6 and 2379), 100 MiB 49.0 -> 39.0, 2424 -> 2390 (51.3 and 2374), 64 MiB at odd addresses 52 -> 37, 2380 -> 2360.
 // Not uploaded lists, whose wavefronts have more to wait for (600 tensors 100 MiB 39.7 -> 40.3 alone, 1000 of 50 MiB 18.3 -> 18.8; 300 of
 // 60 MiB beside the tensor 63 -> 49, it 2395 -> 2374), nor rows (99.5 MB 36 -> 38 alone; beside the tensor 39 -> 38, it 2440 -> 2362).
+//
+// Tiles of 16 KiB: six on a unit (8 tensors at odd addresses, 400 MiB 156.5, four 159.9, eight 160; 40 of 250 MiB, half of them so, 104; all 16 that the
+// registers allow: 386 for 1000 MiB, with four 369).
 uint32_t piece_lds(int cls, const PieceTables &t) {
+  if (t.tile == kStreamTile) return 160u * 1024 / 6;
   return cls == FT_P2P && t.shape == nullptr && pieces_go_along(t) && t.ntiles > (48u << 20) / 8192 ? 160u * 1024 / 8 : 0u;
 }
 

@@ -75,7 +75,7 @@ static int one(uint32_t n, uint64_t reach, uint32_t tile, bool by_source, bool c
 
 int main() {
   for (uint32_t n : {1u, 2u, 63u, 64u, 65u, 241u, 1024u, 1025u, 4096u, 4097u, 16384u})
-    for (uint32_t tile : {1024u, 4096u, 8192u})
+    for (uint32_t tile : {1024u, 8192u, 16384u})
       for (bool by_source : {false, true}) {
         if (one(n, (1ull << 31) - 1, tile, by_source, true)) return 1;
         if (n > 1 && one(n, (1ull << 31) + 1, tile, by_source, false)) return 1;

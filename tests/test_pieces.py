@@ -222,6 +222,44 @@ def test_lists_in_memory_of_every_size(n, far):
         binding.pool_destroy(pool)
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("shifts,pieces", [([(1, 0), (15, 14), (0, 113), (7, 120)], True), ([(3, 3), (0, 0), (1, 2), (5, 9)], False), ([(0, 1)], True)],
+                         ids=["odd", "half odd", "one"])
+def test_streaming_pieces_at_odd_addresses(shifts, pieces):
+    """Beyond 128 MiB jobs that are mostly misaligned go as pieces of 16 KiB, by submit and static; the first, last and inner tiles of runs."""
+    import torch
+    from paper_2411_01830_amd import binding
+    print(f"case streaming pieces: {shifts}", flush=True)
+    n = (132 * MiB) // len(shifts)
+    slab = -(-(n + 256) // 4096) * 4096
+    mem = torch.empty(2 * slab * len(shifts), dtype=torch.uint8, device="cuda")
+    pool = binding.pool_create(mem.data_ptr(), mem.numel(), 4096, 0)
+    try:
+        at = [binding.slab_alloc(pool, slab) for _ in range(2 * len(shifts))]
+        recs = [dict(func=i % 2, src_space=FT_POOL, dst_space=FT_POOL, src=at[2 * i] + s, dst=at[2 * i + 1] + t, row_bytes=n + i - 2)
+                for i, (s, t) in enumerate(shifts)]
+        d, weights = make_descs(recs), [1, 3][:len(shifts)]
+        g = torch.Generator("cuda").manual_seed(3)
+        stream = torch.cuda.current_stream().cuda_stream
+        for call in ("submit", "static"):
+            mem.random_(0, 256, generator=g)
+            want = mem.clone()
+            for r in recs:
+                want[r["dst"]:r["dst"] + r["row_bytes"]] = mem[r["src"]:r["src"] + r["row_bytes"]]
+            if call == "static":
+                binding.submit_static(pool, d, weights, 1 * MiB, 0, stream)
+            else:
+                job = binding.submit_transfers(pool, d, weights, 1 * MiB, fmt.FT_TIMING, stream)
+                binding.wait(pool, job)
+                assert (binding.job_stats(pool, job).cls[2].tile_bytes == 16 * KiB) == pieces
+                binding.job_release(pool, job)
+            torch.cuda.synchronize()
+            assert torch.equal(mem, want), call
+    finally:
+        torch.cuda.synchronize()
+        binding.pool_destroy(pool)
+
+
 # as above; the tiles are 1, 2 or 4 KiB, the workgroups at most 64 from the host and towards it 128, of more than 256 tiles 48
 LINK_CASES = [
     ("one byte", lambda g: [(1, 1, 0, 0, 0, 3, 9)], [1], 2 * MiB, True),
