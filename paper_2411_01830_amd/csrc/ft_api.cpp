@@ -513,17 +513,6 @@ int prepare_class(ft_pool *p, Job *job, int c, const ClassPlan &cp, const Layout
   return rc;
 }
 
-// Whether a launch's done event is bound to the dispatch itself, which fires with the kernel's own completion signal, instead of being a
-// marker queued behind it: 2 us less from submit to the end of wait. But of launches with a bound event the runtime keeps its records, 1.6 KB
-// each (53 MB after 32 768), until the device is synchronised or a launch without one comes along on the stream, and giving back ten
-// thousand of them makes the next launches slow. So one in 64 is launched without, spread so that streams taken in turn all have their share. The first
-// pass on new inputs after some 10 000 passes, us, before -> now: one of 64 KiB 41..59 -> 26, 32 jobs of one tensor 380..750 -> 193..238, 64 maps
-// 51..105 -> 51..53; passes in between, on two machines, 9.6 -> 9.6 and 11.2 -> 11.8 (64 KiB), 190 -> 175 and 285 -> 290 (32 jobs).
-bool bind_done(DeviceCtx *cx) {
-  std::lock_guard<std::mutex> lock(cx->mu);
-  return (cx->bound_launches++ * 0x9e3779b1u) >> 26 != 63;
-}
-
 // A job of one link class whose tables fit into a kernel argument is launched on the
 // caller's stream itself, tables in the launch: one launch and one event record instead
 // of a table upload, a fork and a join across streams - 4 us of host time instead of
@@ -608,9 +597,14 @@ int launch_with_the_launch(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chun
     T.wg_log = reinterpret_cast<WgLogEntry *>(r.log.dev + T.ntickets * sizeof(LogEntry));
   }
   hipError_t e;
-  const bool bound = r.ev_begin == nullptr && bind_done(p->ctx);
-  e = launch_copy(T, r.code, r.workgroups, user, r.ev_begin, bound ? r.ev_done : r.ev_end, job->inline_tables.get());
-  if (e == hipSuccess && !bound) e = hipEventRecord(r.ev_done, user);
+  if (r.ev_begin == nullptr) {
+    // the done event is bound to the dispatch itself (it fires with the kernel's own completion
+    // signal) instead of being a marker queued behind it: 2 us less from submit to the end of wait
+    e = launch_copy(T, r.code, r.workgroups, user, nullptr, r.ev_done, job->inline_tables.get());
+  } else {
+    e = launch_copy(T, r.code, r.workgroups, user, r.ev_begin, r.ev_end, job->inline_tables.get());
+    if (e == hipSuccess) e = hipEventRecord(r.ev_done, user);
+  }
   if (e != hipSuccess) {
     p->hip_error = std::string("launch on the caller's stream: ") + hipGetErrorString(e);
     (void)hipDeviceSynchronize();  // the kernel may be running: its counter pair must be back at zero
@@ -845,15 +839,15 @@ int launch_as_pieces(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_byte
       done.value = r.done_value;
     }
   }
-  const bool bound = !timing && bind_done(p->ctx);
   hipError_t e = hipSuccess;
   if (!with_launch) {
     const bool in_place = pieces_read_in_place(only, packed_bytes(t));
     if (!in_place) e = upload_pieces(job->tables, packed_bytes(t), user);
     t.packed = in_place ? job->tables.host : job->tables.dev;
   }
-  if (e == hipSuccess) e = launch_pieces(t, only, with_launch, counter, done, user, r.ev_begin, bound ? r.ev_done : r.ev_end);
-  if (e == hipSuccess && !bound) e = hipEventRecord(r.ev_done, user);
+  // without timing the done event is bound to the dispatch itself, which spares a marker behind it
+  if (e == hipSuccess) e = launch_pieces(t, only, with_launch, counter, done, user, r.ev_begin, timing ? r.ev_end : r.ev_done);
+  if (e == hipSuccess && timing) e = hipEventRecord(r.ev_done, user);
   if (e != hipSuccess) {
     p->hip_error = std::string("launch of pieces: ") + hipGetErrorString(e);
     (void)hipDeviceSynchronize();

@@ -132,7 +132,6 @@ struct DeviceCtx {
   uint64_t *done_words = nullptr;
   uint64_t done_value = 0;
   std::vector<uint32_t> free_done;
-  uint32_t bound_launches = 0;  // whose only event is bound to the dispatch (bind_done)
 };
 
 DeviceCtx *device_ctx(int device);
