@@ -132,6 +132,7 @@ struct DeviceCtx {
   uint64_t *done_words = nullptr;
   uint64_t done_value = 0;
   std::vector<uint32_t> free_done;
+  uint32_t in_place_launches = 0;  // of lists that are read in place (record_done)
 };
 
 DeviceCtx *device_ctx(int device);
