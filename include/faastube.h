@@ -245,12 +245,14 @@ int ft_set_stage_threads(ft_pool *p, uint32_t threads);
  * the smallest (served+1)/weight.
  *
  * A job of one link class whose order comes to a short list of pieces is launched as that list, on hip_stream
- * itself: pool->pool up to 128 MiB, pitched rows among them of up to 140 descriptors if their pieces fit a launch; over
- * the host link contiguous transfers (not one of more than 128 KiB between 16-byte aligned addresses from the host,
+ * itself: pool->pool up to 128 MiB, pitched rows among them of up to 140 descriptors if their pieces fit a launch, and beyond that
+ * contiguous transfers five eighths of whose bytes change their alignment; over
+ * the host link contiguous transfers (not one of more than 256 KiB between 16-byte aligned addresses from the host,
  * nor mostly aligned ones of more than 64 MiB); chunks of 1 KiB or more; up to 16384 pieces, and no more than save
  * time. Not with FT_KEEP, FT_LOG, FT_OPEN, FT_PATH_DMA or a tuned launch shape, nor a job with FT_DETACHED other than
- * the small ones above. The tables travel with the launch (up to 240 contiguous pieces) or are copied ahead of it.
- *  - Pool->pool every tile of 2 to 8 KiB has a wavefront of its own, begun in the order but for seven places: the
+ * the small ones above. The tables travel with the launch (up to 240 contiguous pieces), or (pool->pool, up to 2730
+ * pieces) the kernel reads them in pinned memory, or they are copied ahead of it.
+ *  - Pool->pool every tile of 2 to 8 KiB (beyond 128 MiB 16) has a wavefront of its own, begun in the order but for seven places: the
  *    dies of the chip take the tiles in turn, and the eight tiles of a group one further round in each group,
  *    so that all have the same mixture. As many are under way as the chip holds; 16 MiB of those contiguous
  *    jobs of more than 48 MiB whose tables travel with the launch.
@@ -300,7 +302,9 @@ int ft_submit_transfers(ft_pool *p, const ft_desc *descs, uint32_t ndesc, const 
  * (device memory, and host memory for pool->host). A job can be waited for once; unless it
  * was submitted with FT_KEEP/FT_LOG/FT_TIMING the handle is dead afterwards. The pool's
  * lock is not held while the call blocks: other threads may submit, merge and wait for
- * other jobs of the same pool meanwhile (not destroy the pool).
+ * other jobs of the same pool meanwhile (not destroy the pool). The wavefronts of a short job (up to 640 of them, over the
+ * host link up to 8 MiB) tell the host themselves when their bytes are in place, so that the call may return some 2 us before the
+ * stream counts the job's kernel as complete; for up to 200 us the calling thread looks for their words without giving up its core.
  */
 int ft_wait(ft_pool *p, ft_job_t job);
 
