@@ -223,6 +223,43 @@ def test_lists_in_memory_of_every_size(n, far):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("n,size", [(241, 200), (600, 150), (1500, 120)])
+def test_a_list_read_in_place_is_the_one_that_was_written(n, size):
+    """Thirty different lists one after the other in the same pinned buffer, each only waited for with ft_wait: none sees what an earlier one left in a cache."""
+    import torch
+    from paper_2411_01830_amd import binding
+    print(f"case lists one after the other: {n} of {size}", flush=True)
+    lists, half = 30, 16 * MiB
+    mem = torch.zeros(2 * half, dtype=torch.uint8, device="cuda")
+    pool = binding.pool_create(mem.data_ptr(), 2 * half, 4096, 0)
+    try:
+        binding.slab_alloc(pool, 2 * half)
+        step = size + 37
+        assert lists * n * step < half
+        jobs = [binding.Transfers(make_descs([dict(func=0, src_space=FT_POOL, dst_space=FT_POOL, src=(k * n + i) * step, dst=half + (k * n + i) * step + 3,
+                                                   row_bytes=size + (i + k) % 30) for i in range(n)]), [1]) for k in range(lists)]
+        mask = torch.zeros(half, dtype=torch.bool)
+        for k in range(lists):
+            for i in range(n):
+                at = (k * n + i) * step
+                mask[at:at + size + (i + k) % 30] = True
+        mask = mask.cuda()
+        stream = torch.cuda.current_stream().cuda_stream
+        for _ in range(4):
+            mem[:half].random_(0, 256)
+            mem[half:].zero_()
+            torch.cuda.synchronize()
+            for job in jobs:
+                binding.wait(pool, binding.submit_transfers(pool, job, None, 2 * MiB, 0, stream))
+            torch.cuda.synchronize()
+            want = torch.where(mask, mem[:half], torch.zeros_like(mem[:half]))
+            assert torch.equal(mem[half + 3:], want[:half - 3])
+    finally:
+        torch.cuda.synchronize()
+        binding.pool_destroy(pool)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("shifts,pieces", [([(1, 0), (15, 14), (0, 113), (7, 120)], True), ([(3, 3), (0, 0), (1, 2), (5, 9)], False), ([(0, 1)], True)],
                          ids=["odd", "half odd", "one"])
 def test_streaming_pieces_at_odd_addresses(shifts, pieces):
