@@ -29,7 +29,8 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 // of the bits is slower than `nt` alone. (The stores are inline assembly, and the compiler does not keep the next
 // instructions from writing a store's data registers before it has read them, which takes two wait states on this
 // architecture: hence the s_nop behind each.) kFromHost: as kStream, for the wave kernels' sources in host memory.
-// kThrough: ordinary loads, and stores that are in memory once a wait for them is over (`sc1`), for kernels that say themselves when they are done.
+// kThrough: ordinary loads, and stores of system scope (`sc0 sc1`), which the device, the copy engines and the host see once a wait for them is over: for
+// kernels that say themselves when they are done.
 constexpr int kStream = 1, kToHost = 2, kFromHost = 3, kThrough = 4;
 
 // 16 bytes from any address (the hardware splits an access that straddles aligned granules).
@@ -78,7 +79,11 @@ __device__ __forceinline__ V ld_off(uint64_t base, uint32_t off) {
 }
 template <class V, int NT>
 __device__ __forceinline__ void st_off(uint64_t base, uint32_t off, V v) {
-  if ((NT == kToHost || NT == kThrough) && sizeof(V) == 16) {
+  if constexpr (NT == kThrough && sizeof(V) == 16) {
+    asm volatile("global_store_dwordx4 %0, %1, off sc0 sc1\n\ts_nop 1" ::"v"(base + off), "v"(v) : "memory");
+    return;
+  }
+  if (NT == kToHost && sizeof(V) == 16) {
     // Written through to the fabric at once, as st16 does. The whole address in vector registers: between a vector instruction
     // that writes a scalar register and a store that reads it there must be five wait states, which the compiler does not
     // see to for inline assembly.
@@ -86,7 +91,7 @@ __device__ __forceinline__ void st_off(uint64_t base, uint32_t off, V v) {
     return;
   }
   if constexpr (NT == kThrough && sizeof(V) == 1) {
-    asm volatile("global_store_byte %0, %1, off sc1\n\ts_nop 1" ::"v"(base + off), "v"((uint32_t)v) : "memory");
+    asm volatile("global_store_byte %0, %1, off sc0 sc1\n\ts_nop 1" ::"v"(base + off), "v"((uint32_t)v) : "memory");
     return;
   }
   __builtin_nontemporal_store(v, reinterpret_cast<V FT_GLOBAL *>(reinterpret_cast<char FT_GLOBAL *>(base) + off));

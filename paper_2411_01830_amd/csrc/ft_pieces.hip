@@ -208,11 +208,11 @@ __device__ __forceinline__ void move_tile(const Piece &p, uint32_t lane) {
   move_run<NT>(d + begin, s + begin, n, lane);
 }
 
-// A wavefront's last words: what it stored is in memory, for every die, the copy engines and the host. The wait is spelled out because the
+// A wavefront's last words: what it stored is there for the device, the copy engines and the host. The wait is spelled out because the
 // compiler does not count the stores of inline assembly.
 template <int NT>
 __device__ __forceinline__ void say_done(const DoneWords &done) {
-  // Written through to memory when the wait is over; what is not is written back here. (64 KiB pool->pool with that instead 9.6 a pass, so 9.25.)
+  // kThrough's stores are of system scope, like the word; others are released to it here. (64 KiB pool->pool with that instead 9.6 a pass, so 9.25.)
   if (NT != kThrough) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "");
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
   if (threadIdx.x == 0) __hip_atomic_store(done.words + kDoneStride * blockIdx.x, done.value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);

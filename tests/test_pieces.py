@@ -373,7 +373,7 @@ def test_pieces_over_the_host_link(case, to_host):
 
 
 def test_inline_assembly_stores_of_the_piece_kernels_leave_no_hazard(tmp_path):
-    """As for the other kernels: two wait states behind each store that is written through to the host, its address in vector registers."""
+    """As for the other kernels: two wait states behind each store that is written through, its address in vector registers."""
     import os
     import re
     import subprocess
@@ -386,12 +386,13 @@ def test_inline_assembly_stores_of_the_piece_kernels_leave_no_hazard(tmp_path):
     kernels = [l for l in lines if re.match(r"_ZN2ft20ft_link_piece_kernelILi2E\S*:", l)]
     assert len(kernels) >= 6 and len(stores) >= 4 * len(kernels)
     for i in stores:
-        assert re.fullmatch(r"global_store_dwordx4 v\[\d+:\d+\], [va]\[\d+:\d+\], off sc1", lines[i]), lines[i]
+        assert re.fullmatch(r"global_store_dwordx4 v\[\d+:\d+\], [va]\[\d+:\d+\], off (sc0 )?sc1", lines[i]), lines[i]
         assert lines[i + 1] == "s_nop 1", lines[i:i + 2]
 
 
 def test_kernels_that_say_they_are_done_have_waited_for_their_stores(tmp_path):
-    """In front of each word to the host a wait for every store, and nothing stored between the two."""
+    """In front of each word to the host a wait for every store, and nothing stored between the two. What is stored before it is of system scope, as the
+    word is, or written back at that scope in front of the wait."""
     import os
     import re
     import subprocess
@@ -406,6 +407,13 @@ def test_kernels_that_say_they_are_done_have_waited_for_their_stores(tmp_path):
     for i in said:
         j = max(k for k in range(i) if lines[k] == "s_waitcnt vmcnt(0)" and lines[k - 1] == ";;#ASMSTART")
         assert not [l for l in lines[j:i] if re.match(r"(global|flat|buffer|scratch)_(store|atomic)", l)], lines[j:i + 1]
+        begin = max(k for k in range(i) if lines[k].startswith("_ZN2ft"))
+        stores = [k for k in range(begin, j) if re.match(r"(global|flat|buffer|scratch)_store", lines[k])]
+        assert stores
+        if "ft_piece_kernelILi4E" in lines[begin]:
+            assert all(lines[k].endswith(" sc0 sc1") for k in stores), [lines[k] for k in stores]
+        else:
+            assert max(k for k in range(j) if lines[k] == "buffer_wbl2 sc0 sc1") > max(stores)
 
 
 @pytest.mark.gpu
@@ -413,7 +421,7 @@ def test_kernels_that_say_they_are_done_have_waited_for_their_stores(tmp_path):
 @pytest.mark.parametrize("sizes", [[5], [16], [64 * KiB + 3], [640 * 2 * KiB - 128], [640 * 2 * KiB + 1], [31, 700, 5000] * 25, [2 * KiB] * 70],
                          ids=["5", "16", "64K", "640 tiles", "641 tiles", "75 small", "70 jobs"])
 def test_what_has_been_waited_for_is_there(where, sizes):
-    """After ft_wait, with nothing else waited for, the bytes are read by a kernel on another stream, by the copy engine and by the host."""
+    """After ft_wait, with nothing else waited for, the bytes are read by the host, or first of all by a kernel on another stream, or by a copy to the host on it."""
     import torch
     from paper_2411_01830_amd import binding
     print(f"case waited for: {where} {len(sizes)} of {sizes[0]}", flush=True)
@@ -435,24 +443,31 @@ def test_what_has_been_waited_for_is_there(where, sizes):
         mask = torch.zeros(room, dtype=torch.bool, device="cuda")
         for a, n in zip(starts, sizes):
             mask[int(a) + 1:int(a) + 1 + n] = True
-        for _ in range(12):
+        seen, copied = torch.zeros(room, dtype=torch.uint8, device="cuda"), torch.zeros(room, dtype=torch.uint8, pin_memory=True)
+        for k in range(16):
             data = torch.randint(0, 256, (room,), dtype=torch.uint8, device="cuda", generator=g)
             want = torch.where(mask, data, torch.zeros_like(data))
             (host if where == "host_to_pool" else mem[:room]).copy_(data)
             (host if where == "pool_to_host" else mem[room:]).zero_()
+            wanted = want.cpu()
             torch.cuda.synchronize()
             handles = [binding.submit_transfers(pool, l, None, 2 * MiB, 0, jobs.cuda_stream) for l in lists]
             for h in handles:
                 binding.wait(pool, h)
             if where == "pool_to_host":
-                got = torch.from_numpy(host.numpy().copy()).cuda()
+                got = host.clone()
+            elif k % 2 == 0:
+                with torch.cuda.stream(other):
+                    torch.bitwise_or(mem[room:], 0, out=seen)
+                other.synchronize()
+                got = seen.cpu()
             else:
                 with torch.cuda.stream(other):
-                    got = mem[room:] + torch.zeros((), dtype=torch.uint8, device="cuda")
-                    copied = mem[room:].cpu()
-                assert torch.equal(copied.cuda(), want)
+                    copied.copy_(mem[room:], non_blocking=True)
+                other.synchronize()
+                got = copied
+            assert torch.equal(got, wanted)
             torch.cuda.synchronize()
-            assert torch.equal(got, want)
     finally:
         torch.cuda.synchronize()
         binding.pool_destroy(pool)
