@@ -308,6 +308,40 @@ void hold_allocations(Job *job, std::vector<Held> &&allocs) {
   for (const Held &h : job->allocs) h.al->busy += 1;
 }
 
+StreamJobs &jobs_of(ft_pool *p, hipStream_t stream) {
+  constexpr size_t kStreams = 64;  // remembered without an unfinished job
+  StreamJobs *idle = nullptr;
+  for (StreamJobs &u : p->streams) {
+    if (u.stream == stream) return u;
+    if (u.unfinished == 0) idle = &u;
+  }
+  if (idle == nullptr || p->streams.size() < kStreams) {
+    p->streams.emplace_back();
+    idle = &p->streams.back();
+  }
+  *idle = StreamJobs();
+  idle->stream = stream;
+  return *idle;
+}
+
+void goes_on_stream(ft_pool *p, Job *job, hipStream_t stream) {
+  StreamJobs &u = jobs_of(p, stream);
+  u.unfinished += 1;
+  if (u.unfinished > u.most) u.most = u.unfinished;
+  job->on_stream = true;
+  job->stream = stream;
+}
+
+void leaves_its_stream(ft_pool *p, Job *job) {
+  if (!job->on_stream) return;
+  StreamJobs &u = jobs_of(p, job->stream);
+  job->on_stream = false;
+  u.unfinished -= 1;
+  if (u.unfinished != 0) return;
+  u.most_before = u.most;
+  u.most = 0;
+}
+
 uint32_t slab_busy(ft_pool *p, uint64_t off) {
   std::lock_guard<std::mutex> lock(p->mu);
   Allocation *al = p->slabs.at(off);
@@ -838,7 +872,7 @@ int launch_as_pieces(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_byte
   if (rc == FT_OK && timing) rc = get_event(p, true, &r.ev_end);
   if (rc != FT_OK) return fail_submit(p, job, rc);
   DoneWords done;
-  if (!timing && says_done(only, cp.payload, t.ntiles)) {
+  if (!timing && says_done(only, cp.payload, t.ntiles, jobs_of(p, user).burst())) {
     std::lock_guard<std::mutex> ctx_lock(p->ctx->mu);
     if (!p->ctx->free_done.empty()) {
       r.done_slot = (int)p->ctx->free_done.back();
@@ -1007,6 +1041,7 @@ int ft_submit_transfers(ft_pool *p, const ft_desc *descs, uint32_t ndesc, const 
     rc = ensure_device(p);
     if (rc != FT_OK) return rc;
     hipStream_t user = static_cast<hipStream_t>(hip_stream);
+    (void)jobs_of(p, user);  // its place, while there is nothing yet that a lack of memory would leave behind
     if (plan.has_pageable) {
       rc = stage_closed_job(p, job.get(), plan);
       if (rc != FT_OK) return fail_submit(p, job.get(), rc);
@@ -1019,6 +1054,7 @@ int ft_submit_transfers(ft_pool *p, const ft_desc *descs, uint32_t ndesc, const 
     }
     if (rc == FT_OK && !launched) rc = launch_with_uploaded_tables(p, job.get(), plan, chunk_bytes, flags, user);
     if (rc != FT_OK) return rc;
+    if (launched || !(flags & FT_DETACHED)) goes_on_stream(p, job.get(), user);
   }
 
   for (int c = 0; c < FT_NCLASS; ++c) job->run[c].plan = std::move(plan.cls[c]);
@@ -1167,6 +1203,7 @@ int ft_wait(ft_pool *p, ft_job_t id) {
     }
     lock.lock();
     rc = wait_locked(p, job);  // the events have fired: reads times and logs, retires
+    leaves_its_stream(p, job);
   }
   job->waiting = false;
   if (rc != FT_OK) return rc;

@@ -70,6 +70,8 @@ struct Job {
   Blob tables;
   std::unique_ptr<InlineBlob> inline_tables;  // a small job's tables, passed with the launch instead
   std::vector<Held> allocs;  // the pool allocations the job refers to
+  bool on_stream = false;    // counted among the unfinished jobs of `stream`, the caller's (StreamJobs)
+  hipStream_t stream = nullptr;
   uint64_t chunk_bytes = 0;
   uint32_t nfunc = 0;    // functions the job was submitted with
   double host_submit_us = 0;
@@ -81,6 +83,14 @@ struct Job {
   std::vector<HostCopy> unstage;
   uint64_t class_payload[FT_NCLASS] = {0, 0, 0};
   uint64_t class_chunks[FT_NCLASS] = {0, 0, 0};
+};
+
+// How a caller's stream is used: jobs on it that have not been waited for, the most of them since there was none, and the most of the time before that.
+struct StreamJobs {
+  hipStream_t stream = nullptr;
+  uint32_t unfinished = 0, most = 0, most_before = 0;
+  // how many jobs one more is likely to have to share the time until it is waited for with, itself among them
+  uint32_t burst() const { return most_before > unfinished ? most_before : unfinished + 1; }
 };
 
 struct Tuning {
@@ -147,6 +157,7 @@ struct ft_pool {
   ft::DeviceCtx *ctx;
   std::unordered_map<uint64_t, std::unique_ptr<ft::Job>> jobs;
   uint64_t next_job = 1;
+  std::vector<ft::StreamJobs> streams;  // the callers'; those without an unfinished job leave their places when others come
   std::vector<uint64_t> piece_words;  // where a submit writes its pieces out; at most kMaxPieces of them, 393 KB
   ft::Tuning tuning[FT_NCLASS];
   uint32_t batch_chunks = 5;  // chunks per triggered batch of an open job (Sec. 6.1 default)

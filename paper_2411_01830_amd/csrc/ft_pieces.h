@@ -138,8 +138,14 @@ struct DoneWords {
 constexpr uint32_t kDoneStride = 8;    // words from one that is used to the next
 constexpr uint32_t kDoneWords = 640;   // of a launch: more of them cost what they save (1000 in 2 MiB 12.4, by the event 10.9)
 // Over the host link wavefronts are few, so there the line lies where 1.4 us are 1 % of the job (32 tensors, 4 MiB, to the pool and back 166.0 -> 163.2).
-inline bool says_done(int cls, uint64_t payload, uint32_t ntiles) {
-  return piece_workgroups(cls, ntiles) <= kDoneWords && payload <= 8u << 20;
+// And only where few jobs are in flight on the stream at once (StreamJobs::burst): a written-through kernel ends 1 us later than it would, which a wait that ends
+// 2 us earlier makes up for once and a burst pays for every job. Passes, us, n jobs of one tensor each submitted and then waited for, by events -> by words:
+// pool->pool 512 KiB n = 2 15.6 -> 14.9, 3 20.2 -> 18.4, 5 29.2 -> 28.3, 6 33.9 -> 34.5, 8 42.7 -> 47, 32 166 -> 188; 1 MiB 4 24.9 -> 24.2, 5 29.5 -> 30.5; 64 KiB 4 24.7 -> 22.1,
+// 32 170 -> 170; towards the host 16 KiB 4 25.5 -> 22.4, 256 KiB 4 34.8 -> 34.4, 8 61.3 -> 62.3, 1 MiB 2 49.2 -> 48.4, 4 89.9 -> 90.4; from the host 128 KiB 2 20.3 -> 20.0, 4 31.9 -> 33.2,
+// 32 191 -> 219. Words for some of a burst alone are no better: of two of 512 KiB the first one's alone 16.5.
+constexpr uint32_t most_words(int cls) { return cls == FT_H2P ? 2 : 4; }
+inline bool says_done(int cls, uint64_t payload, uint32_t ntiles, uint32_t burst) {
+  return piece_workgroups(cls, ntiles) <= kDoneWords && payload <= 8u << 20 && burst <= most_words(cls) && (cls == FT_P2P || burst == 1 || burst * payload <= 2u << 20);
 }
 
 // LDS that a workgroup asks for without using it, so that a compute unit of 160 KiB takes no more of them at once.

@@ -59,6 +59,10 @@ extern "C" int stand_in_fail(const char *name, int nth) {
 static std::atomic<hipStream_t> g_stream{nullptr};
 extern "C" hipStream_t stand_in_stream(void) { return g_stream.load(); }
 
+// How many launches of pieces had words to write to the host.
+static std::atomic<int> g_words{0};
+extern "C" int stand_in_words(void) { return g_words.load(); }
+
 extern "C" int stand_in_calls(const char *name) {
   for (FailPoint &f : g_fail)
     if (std::strcmp(f.name, name) == 0) return f.calls.load();
@@ -298,6 +302,7 @@ hipError_t launch_pieces(const PieceTables &t, int cls, bool on_host, unsigned l
   }
   for (uint32_t i = 0; i < t.n; ++i)
     for (uint32_t no = 0; no < (i + 1 < t.n ? t.first[i + 1] : t.ntiles) - t.first[i]; ++no) move_tile(t, i, no, cls == 0);
+  if (done.words != nullptr) g_words += 1;
   if (done.words != nullptr && piece_workgroups(cls, t.ntiles) > kDoneWords) return hipErrorInvalidValue;
   for (uint32_t i = 0; done.words != nullptr && i < piece_workgroups(cls, t.ntiles); ++i) __atomic_store_n(done.words + kDoneStride * i, done.value, __ATOMIC_RELEASE);
   return hipSuccess;

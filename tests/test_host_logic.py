@@ -466,6 +466,11 @@ def test_batches_in_parts_with_injected_failures(tmp_path, sanitize):
     _with_the_stand_in(tmp_path, sanitize, 0, program="ring_parts", args=[], expect="ring_parts done")
 
 
+def test_jobs_of_a_burst_are_waited_for_by_their_events(tmp_path):
+    """tests/host/done_words.cpp: kernels say themselves that they are done where few jobs of a stream are in flight at once."""
+    _with_the_stand_in(tmp_path, "address,undefined", 0, program="done_words", args=[], expect="done_words done")
+
+
 def test_rest_of_the_api_under_sanitizers(tmp_path):
     """tests/host/api_tour.cpp: logs with exactly-sized arrays, the device's order against the host planner's, the
     piece-by-piece comparison path, tuned launch shapes, pitched pieces in all classes, pool growth and shrinkage."""
