@@ -247,7 +247,8 @@ int ft_set_stage_threads(ft_pool *p, uint32_t threads);
  * A job of one link class whose order comes to a short list of pieces is launched as that list, on hip_stream
  * itself: pool->pool up to 128 MiB, pitched rows among them of up to 140 descriptors if their pieces fit a launch, and beyond that
  * contiguous transfers five eighths of whose bytes change their alignment; over
- * the host link contiguous transfers (not one of more than 256 KiB between 16-byte aligned addresses from the host,
+ * the host link contiguous transfers (from the host not one of more than 128 KiB between 16-byte aligned addresses, of more than 256 KiB
+ * where hip_stream has been given one job at a time and FT_TIMING is not asked for,
  * nor mostly aligned ones of more than 64 MiB); chunks of 1 KiB or more; up to 16384 pieces, and no more than save
  * time. Not with FT_KEEP, FT_LOG, FT_OPEN, FT_PATH_DMA or a tuned launch shape, nor a job with FT_DETACHED other than
  * the small ones above. The tables travel with the launch (up to 240 contiguous pieces), or (pool->pool, up to 2730
@@ -303,7 +304,7 @@ int ft_submit_transfers(ft_pool *p, const ft_desc *descs, uint32_t ndesc, const 
  * was submitted with FT_KEEP/FT_LOG/FT_TIMING the handle is dead afterwards. The pool's
  * lock is not held while the call blocks: other threads may submit, merge and wait for
  * other jobs of the same pool meanwhile (not destroy the pool). The wavefronts of a short job (up to 640 of them, over the
- * host link up to 8 MiB) tell the host themselves when their bytes are in place, so that the call may return some 2 us before the
+ * host link up to 8 MiB) on a stream with at most four such jobs in flight at a time (from the host two) tell the host themselves when their bytes are in place, so that the call may return some 2 us before the
  * stream counts the job's kernel as complete; for up to 200 us the calling thread looks for their words without giving up its core.
  */
 int ft_wait(ft_pool *p, ft_job_t job);

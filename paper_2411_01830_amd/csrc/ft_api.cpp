@@ -828,7 +828,9 @@ int launch_as_pieces(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_byte
   const ClassPlan &cp = plan.cls[only];
   const auto tables_fit = [&cp] { return inline_layout_of(cp).end <= kInlineBytes; };
   if ((flags & FT_DETACHED) && (cp.payload > (only == FT_P2P ? kWaveTilesBytes : kWaveLinkTilesBytes) || !tables_fit())) return FT_OK;
-  const PieceRoom room = job_pieces(cp, only, chunk_bytes, cp.nchunks > kRunsAlong && tables_fit());  // (of fewer chunks it is not asked)
+  const bool timing = (flags & FT_TIMING) != 0;
+  const uint32_t burst = jobs_of(p, user).burst();
+  const PieceRoom room = job_pieces(cp, only, chunk_bytes, cp.nchunks > kRunsAlong && tables_fit(), !timing && burst == 1);  // (of fewer chunks the tables are not asked for)
   if (room.pieces == 0) return FT_OK;
   const uint64_t bytes = align_up(piece_bytes(room), 256);
   // (written out in ordinary memory: the blob's lines were last read by the device, and every store to one of them would wait for it)
@@ -866,13 +868,12 @@ int launch_as_pieces(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_byte
   r.on_user_stream = with_launch;
   r.stream = user;
   unsigned long long *counter = draws ? p->ctx->counter_pairs + 2 * r.counter_pair : p->ctx->idle_counter;
-  const bool timing = (flags & FT_TIMING) != 0;
   int rc = get_event(p, false, &r.ev_done);
   if (rc == FT_OK && timing) rc = get_event(p, true, &r.ev_begin);
   if (rc == FT_OK && timing) rc = get_event(p, true, &r.ev_end);
   if (rc != FT_OK) return fail_submit(p, job, rc);
   DoneWords done;
-  if (!timing && says_done(only, cp.payload, t.ntiles, jobs_of(p, user).burst())) {
+  if (!timing && says_done(only, cp.payload, t.ntiles, burst)) {
     std::lock_guard<std::mutex> ctx_lock(p->ctx->mu);
     if (!p->ctx->free_done.empty()) {
       r.done_slot = (int)p->ctx->free_done.back();

@@ -108,8 +108,8 @@ struct OneRun {
 };
 
 // The room for a class of a job that is to be launched as pieces, none if it is not; and the tile. tables_fit: the general tables
-// would travel with the launch.
-PieceRoom job_pieces(const ClassPlan &cp, int cls, uint64_t chunk_bytes, bool tables_fit);
+// would travel with the launch. alone: the kernel is to say itself when it is done, and no other job's follows at once.
+PieceRoom job_pieces(const ClassPlan &cp, int cls, uint64_t chunk_bytes, bool tables_fit, bool alone = false);
 uint32_t piece_tile(int cls, uint64_t payload);
 // Workgroups, of one wavefront each, of a launch of that many tiles; and whether they draw tiles beyond their first from a counter: those
 // of one piece, which has no order to keep, are dealt out, unless their number would leave some wavefronts a round more than others.

@@ -505,8 +505,9 @@ void pack_pieces(const PieceTables &t, char *to) {
 // 48 tensors, 30 MB 14.3 -> 10.4; 1024 tensors, 15.6 MB 11.1 -> 7.7; one of 64 KiB 4.0 either way. Beyond it 64 KiB tiles in the order of a counter are faster (382 MB: 127 against 135).
 // Host link, 16 tensors of 8 functions: from the host 16 MiB 298.6 -> 295.7, 64 MiB 1172.8 -> 1169.2, 256 MiB with half of them
 // at odd addresses 4713 -> 4663; to the host 298.3 -> 295.4, 1179.0 -> 1175.8, 128 MiB with odd ones 2400 -> 2349. All but one aligned
-// tensor of more than 256 KiB from the host (kernels 64 KiB 4.5 -> 4.2, 256 KiB 7.5 -> 8.0, 1 MiB 21.0 -> 22.2, 64 MiB 1167.8 -> 1169.6; a pass, where pieces say themselves
-// that they are done, 130 KiB 14.3 -> 12.4, 200 15.6 -> 14.3, 300 18.4 -> 17.9, 500 to 6000 within 1 % of each other), and aligned jobs beyond
+// tensor of more than 128 KiB from the host (kernels 64 KiB 4.5 -> 4.2, 256 KiB 7.5 -> 8.0, 1 MiB 21.0 -> 22.2, 64 MiB 1167.8 -> 1169.6), or of more than 256 KiB where
+// it is the stream's only job and its kernel says itself when it is done (a pass 130 KiB 14.3 -> 12.4, 256 17.3 -> 16.1, 300 18.4 -> 17.9, 500 to 6000 within 1 % of each other;
+// but four of 256 KiB one behind the other 40.2 -> 45.7, 32 of 160 KiB 204 -> 232), and aligned jobs beyond
 // 64 MiB, whose pieces take the host longer to write out than the kernel gains (1 GiB in 2064 pieces 18663 -> 18683 a pass).
 // Rows go as pieces where these go along with the launch (quadrants of 4K frames, 16 descriptors, 99.5 MB, 48 -> 44 a pass,
 // kernel 38.0 -> 35.7); where they would be uploaded, writing them out costs more than the kernel gains (1536 crops 56.0 by the general
@@ -528,14 +529,14 @@ void pack_pieces(const PieceTables &t, char *to) {
 // tensors at odd addresses: 8 tensors 140 MiB 72.1 -> 62.7, 200 96.1 -> 83.6, 250 111.9 -> 102.0, 400 166.2 -> 156.5; 190 tensors 200 MiB 106.4 -> 93.4,
 // 400 178.4 -> 164.9; one tensor 200 MiB 86.5 -> 77.7, 700 259 -> 250. A quarter of 40 tensors so: 140 MiB 66.9 -> 64.7, 200 87.0 -> 85.2. So from five
 // eighths of the bytes on, up to 1024 places, 6 us of writing out.
-PieceRoom job_pieces(const ClassPlan &cp, int cls, uint64_t chunk_bytes, bool tables_fit) {
+PieceRoom job_pieces(const ClassPlan &cp, int cls, uint64_t chunk_bytes, bool tables_fit, bool alone) {
   const bool streams = cls == FT_P2P && cp.payload > kCacheResidentBytes;
   if (streams) {
     uint64_t odd = 0;
     for (const Xfer &x : cp.xfers) odd += ((x.src ^ x.dst) & 15) != 0 ? x.row_bytes : 0;
     if (cp.pitched != 0 || odd < cp.payload / 8 * 5) return PieceRoom();
   }
-  if (cls == FT_H2P && cp.xfers.size() == 1 && cp.payload > 256u << 10 && ((cp.xfers[0].src | cp.xfers[0].dst) & 15) == 0) return PieceRoom();
+  if (cls == FT_H2P && cp.xfers.size() == 1 && cp.payload > (alone ? 256u : 128u) << 10 && ((cp.xfers[0].src | cp.xfers[0].dst) & 15) == 0) return PieceRoom();
   if (cp.pitched != 0 && (cls != FT_P2P || cp.xfers.size() > kRowsAlong)) return PieceRoom();
   if (cls != FT_P2P && cp.payload > 64u << 20) {
     uint64_t odd = 0;

@@ -10,6 +10,7 @@
 #include "../../include/faastube.h"
 
 extern "C" int stand_in_words(void);
+extern "C" int stand_in_calls(const char *name);
 
 #define CHECK(c) do { if (!(c)) { std::fprintf(stderr, "FAIL %s line %d\n", #c, __LINE__); std::abort(); } } while (0)
 
@@ -72,6 +73,35 @@ int main() {
     const ft_job_t j = submit(0, a, FT_DETACHED, true);
     CHECK(burst(4, a) == 4 && burst(1, a) == 1);
     CHECK(ft_wait(g_pool, j) == FT_OK && burst(1, a) == 1);
+  }
+  {  // one aligned tensor from the host: as pieces up to 128 KiB, and up to 256 where it is alone and not timed
+    std::vector<char> host(300 * KiB + 64);
+    const uint64_t at = (reinterpret_cast<uint64_t>(host.data()) + 15) / 16 * 16;
+    CHECK(ft_host_window_add(g_pool, host.data(), host.size()) == FT_OK);
+    const auto pieces = [&](uint64_t bytes, uint32_t n, uint32_t flags) {
+      const int before = stand_in_calls("launch_pieces");
+      std::vector<ft_job_t> jobs(n);
+      for (ft_job_t &job : jobs) {
+        ft_desc d = {};
+        d.rows = 1;
+        d.row_bytes = bytes;
+        d.src_space = FT_HOST;
+        d.dst_space = FT_POOL;
+        d.src = at;
+        d.dst = g_dst;
+        const uint32_t weight = 1;
+        for (char &c : host) c += 7;
+        CHECK(ft_submit_transfers(g_pool, &d, 1, &weight, 1, 2048 * KiB, flags, b, &job) == FT_OK);
+      }
+      const int launches = stand_in_calls("launch_pieces") - before;
+      for (ft_job_t job : jobs) CHECK(ft_wait(g_pool, job) == FT_OK);
+      CHECK(std::memcmp(g_dev + g_dst, reinterpret_cast<char *>(at), bytes) == 0);
+      return launches;
+    };
+    for (int k = 0; k < 2; ++k) CHECK(pieces(128 * KiB, 1, 0) == 1 && pieces(128 * KiB + 16, 1, 0) == 1 && pieces(256 * KiB, 1, 0) == 1 && pieces(256 * KiB + 16, 1, 0) == 0);
+    CHECK(pieces(128 * KiB, 1, FT_TIMING) == 1 && pieces(128 * KiB + 16, 1, FT_TIMING) == 0 && pieces(256 * KiB, 1, FT_TIMING) == 0);
+    CHECK(pieces(256 * KiB, 4, 0) == 1 && pieces(256 * KiB, 4, 0) == 0 && pieces(128 * KiB, 4, 0) == 4 && pieces(200 * KiB, 2, 0) == 0 && pieces(256 * KiB, 1, 0) == 0);
+    CHECK(pieces(256 * KiB, 1, 0) == 1);
   }
   const int before = stand_in_words();
   CHECK(ft_wait(g_pool, submit(0, a, FT_DETACHED)) == FT_OK && stand_in_words() == before + 1);

@@ -302,7 +302,10 @@ LINK_CASES = [
     ("one byte", lambda g: [(1, 1, 0, 0, 0, 3, 9)], [1], 2 * MiB, True),
     *[(f"one tensor of {n}", lambda g, n=n: [(n, 1, 0, 0, 0, 7, 4)], [1], 2 * MiB, True) for n in (15, 17, 1025, 32 * KiB, 32 * KiB + 1, 128 * KiB, 128 * KiB + 1, 3 * MiB)],
     ("one aligned tensor", lambda g: [(3 * MiB + 16, 1, 0, 0, 0, 0, 0)], [1], 2 * MiB, "to the host"),
-    ("one aligned tensor of 256 KiB", lambda g: [(256 * KiB, 1, 0, 0, 0, 0, 0)], [1], 2 * MiB, True),
+    # (from the host as pieces where its kernel says itself when it is done, which one that is timed does not)
+    ("one aligned tensor of 128 KiB", lambda g: [(128 * KiB, 1, 0, 0, 0, 0, 0)], [1], 2 * MiB, True),
+    ("one aligned tensor of 128 KiB and 16", lambda g: [(128 * KiB + 16, 1, 0, 0, 0, 0, 0)], [1], 2 * MiB, "to the host"),
+    ("one aligned tensor of 256 KiB", lambda g: [(256 * KiB, 1, 0, 0, 0, 0, 0)], [1], 2 * MiB, "to the host"),
     ("one aligned tensor of 256 KiB and 16", lambda g: [(256 * KiB + 16, 1, 0, 0, 0, 0, 0)], [1], 2 * MiB, "to the host"),
     *[(f"{n} tensors of one function", lambda g, n=n: _runs(g, n, [1, 15, 16, 17, 127, 4095, 4096, 4097, 9000], 1), [1], 4 * KiB, n <= 240) for n in (16, 48, 128, 129, 240, 241)],
     ("65 tiles of three functions", lambda g: [(4096, 1, 0, 0, i % 3, 0, 0) for i in range(65)], [1, 2, 5], 4 * KiB, True),
