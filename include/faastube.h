@@ -246,7 +246,8 @@ int ft_set_stage_threads(ft_pool *p, uint32_t threads);
  *
  * A job of one link class whose order comes to a short list of pieces is launched as that list, on hip_stream
  * itself: pool->pool up to 128 MiB, pitched rows among them of up to 140 descriptors if their pieces fit a launch, and beyond that
- * contiguous transfers five eighths of whose bytes change their alignment; over
+ * contiguous transfers if five eighths of the bytes have sides 4, 8 or 12 bytes apart modulo 16, or other misaligned ones: of transfers of up to
+ * 768 KiB, or to misaligned destinations (in jobs of more than 256 MiB of up to 2 MiB each); over
  * the host link contiguous transfers (from the host not one of more than 128 KiB between 16-byte aligned addresses, of more than 256 KiB
  * where hip_stream has been given one job at a time and FT_TIMING is not asked for,
  * nor mostly aligned ones of more than 64 MiB); chunks of 1 KiB or more; up to 16384 pieces, and no more than save

@@ -525,16 +525,28 @@ void pack_pieces(const PieceTables &t, char *to) {
 // kernel's jobs, over the link 256 and one for every 64 KiB; and where there are many tensors, which the general tables have to hold too, one
 // for every two of them, over the link two for each.
 // Pool->pool beyond what the cache holds the general tables' 64 KiB tiles, which four wavefronts move line by line, are the faster ones for sides that are
-// aligned alike (382 MB 143 a pass, by pieces 148), and pieces of 16 KiB for those that are not. Three jobs in turn, us a pass, general tables -> pieces, all
-// tensors at odd addresses: 8 tensors 140 MiB 72.1 -> 62.7, 200 96.1 -> 83.6, 250 111.9 -> 102.0, 400 166.2 -> 156.5; 190 tensors 200 MiB 106.4 -> 93.4,
-// 400 178.4 -> 164.9; one tensor 200 MiB 86.5 -> 77.7, 700 259 -> 250. A quarter of 40 tensors so: 140 MiB 66.9 -> 64.7, 200 87.0 -> 85.2. So from five
-// eighths of the bytes on, up to 1024 places, 6 us of writing out.
+// aligned alike (382 MB 143 a pass, by pieces 148), and pieces of 16 KiB for many of those that are not. Two or three jobs in turn, us a pass, general tables -> pieces:
+//   a multiple of four bytes apart, whose loads the hardware does not have to take apart: 8 tensors 140 MiB 70 -> 63, 250 109 -> 101, 400 162 -> 153; 20 of 300 MiB 128 -> 120;
+//     50 of 1000 MiB 410 -> 383; one of 700 MiB 258 -> 250 (but of 1000 MiB 401 -> 407); beside 256 MiB from the host on another stream 8 of 140 MiB 93 -> 86, 200 of 200 MiB 124 -> 116;
+//   any other distance, the destination aligned: 8 of 140 MiB 69 -> 67 (beside the host link 93 -> 96), 250 107 -> 110, 400 159 -> 165, 20 of 300 MiB 125 -> 130, 50 of 1000 MiB
+//     396 -> 411, one of 700 MiB 253 -> 264; but many short ones are written out sooner than as general tables: 200 of 140 MiB 81 -> 71, 400 of 250 MiB 127 -> 116, 600 of 400 MiB
+//     192 -> 178 (beside the link 217 either way), 800 of 500 MiB 234 -> 219; 200 of 200 MiB 96 -> 95 (123 -> 127);
+//   the destination not aligned either, which the general tables' tiles are slower at: one of 140 MiB 66.5 -> 64, 200 76 -> 74, 300 117 -> 117, 700 285 -> 289, 1000 405 -> 424; 8 of
+//     140 MiB 71 -> 66.5 (97 -> 95.5), 250 109 -> 104, 400 170 -> 165 (197 -> 200); 100 of 1000 MiB 395 -> 396; 50 of 500 MiB 208 -> 203, 400 of 1000 MiB 406 -> 403, 800 426 -> 417.
+// So from five eighths of the bytes on that are better off, not one tensor of more than 768 MiB, up to 1024 places, 6 us of writing out.
+static bool better_as_pieces(const Xfer &x, uint64_t payload) {
+  const uint64_t apart = (x.src ^ x.dst) & 15;
+  if (apart % 4 == 0) return apart != 0;
+  if ((x.dst & 15) == 0) return x.row_bytes <= 768u << 10;
+  return payload <= 256u << 20 || x.row_bytes <= 2u << 20;
+}
+
 PieceRoom job_pieces(const ClassPlan &cp, int cls, uint64_t chunk_bytes, bool tables_fit, bool alone) {
   const bool streams = cls == FT_P2P && cp.payload > kCacheResidentBytes;
   if (streams) {
-    uint64_t odd = 0;
-    for (const Xfer &x : cp.xfers) odd += ((x.src ^ x.dst) & 15) != 0 ? x.row_bytes : 0;
-    if (cp.pitched != 0 || odd < cp.payload / 8 * 5) return PieceRoom();
+    uint64_t better = 0;
+    for (const Xfer &x : cp.xfers) better += better_as_pieces(x, cp.payload) ? x.row_bytes : 0;
+    if (cp.pitched != 0 || better < cp.payload / 8 * 5 || (cp.xfers.size() == 1 && cp.payload > 768u << 20)) return PieceRoom();
   }
   if (cls == FT_H2P && cp.xfers.size() == 1 && cp.payload > (alone ? 256u : 128u) << 10 && ((cp.xfers[0].src | cp.xfers[0].dst) & 15) == 0) return PieceRoom();
   if (cp.pitched != 0 && (cls != FT_P2P || cp.xfers.size() > kRowsAlong)) return PieceRoom();

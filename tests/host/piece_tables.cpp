@@ -27,10 +27,10 @@ static uint64_t n_tiles, n_rows, n_parts, n_merged, n_edges;
 
 static void move(uint64_t d, uint64_t s, uint32_t n) { std::memcpy(reinterpret_cast<void *>(d), reinterpret_cast<const void *>(s), n); }
 
-static void move_run(uint64_t d, uint64_t s, uint32_t n, bool by_source) {
+static void move_run(uint64_t d, uint64_t s, uint32_t n, uint32_t tile, bool by_source) {
   if (n < 16) return move(d, s, n);
   const RunWindows w = run_windows(by_source ? s : d, n);
-  CHECK(w.count <= 512);
+  CHECK(w.count <= (tile == kStreamTile ? 1024u : 512u));
   for (uint32_t j = 0; j < w.count; ++j) {
     const uint32_t at = run_window_at(w, j);
     CHECK(at + 16 <= n);
@@ -51,7 +51,7 @@ static void move_piece(const PieceTables &t, uint32_t i, bool by_source) {
       run_tile(side, t.len[i], t.tile, no, &begin, &n);
       CHECK(n > 0 && n <= t.tile && begin + n <= t.len[i] && begin == moved);
       CHECK(no == 0 || (side + begin) % kPieceLine == 0);
-      move_run(d + begin, s + begin, n, by_source);
+      move_run(d + begin, s + begin, n, t.tile, by_source);
       moved += n;
       continue;
     }
@@ -80,7 +80,7 @@ static void move_piece(const PieceTables &t, uint32_t i, bool by_source) {
       row_part(r, no, &row, &begin, &n);
       CHECK(row < t.len[i] && n > 0 && n <= t.tile && begin + n <= r.row_bytes);
       CHECK((uint64_t)row * r.row_bytes + begin == moved);
-      move_run(d + (uint64_t)row * r.dst_pitch + begin, s + (uint64_t)row * r.src_pitch + begin, n, by_source);
+      move_run(d + (uint64_t)row * r.dst_pitch + begin, s + (uint64_t)row * r.src_pitch + begin, n, t.tile, by_source);
       moved += n;
       ++n_parts;
     }
@@ -167,7 +167,8 @@ static void job(std::mt19937_64 &r) {
   for (const Byte &b : order) want[b.dst - reinterpret_cast<uint64_t>(dst.data())] = *reinterpret_cast<const uint8_t *>(b.src);
 
   for (int by_source = 0; by_source < 2; ++by_source)
-    for (uint32_t tile : {1024u, 2048u, 8192u}) {
+    for (uint32_t tile : {1024u, 2048u, 8192u, kStreamTile}) {
+      if (tile == kStreamTile && cp.pitched != 0) continue;
       const PieceRoom room = piece_room(cp, C, tile);
       if (room.pieces == 0) continue;
       if (cp.pitched == 0) CHECK(room.pieces == cp.xfers.size() + (cp.funcs.size() == 1 ? 0 : places));
@@ -298,7 +299,7 @@ static void refused() {
 // What a list would cost the host is known before it is written: `n` tensors of equal size, `total` MiB of `nf` functions in chunks of `chunk`
 // KiB.
 static void priced() {
-  auto takes = [](int cls, uint32_t n, uint64_t total, uint32_t nf, uint64_t chunk, bool odd, bool tables_fit) {
+  auto takes = [](int cls, uint32_t n, uint64_t total, uint32_t nf, uint64_t chunk, uint64_t shift, bool tables_fit, uint64_t dst_shift = 0) {
     ClassPlan cp;
     const uint64_t size = (total << 20) / n / 16 * 16;
     for (uint32_t f = 0; f < nf; ++f) {
@@ -308,8 +309,8 @@ static void priced() {
       fn.desc_off = (uint32_t)cp.xfers.size();
       for (uint32_t i = f; i < n; i += nf) {
         Xfer x{};
-        x.src = 0x100000000000ull + i * (size + 4096) + (odd ? 3 : 0);
-        x.dst = 0x200000000000ull + i * (size + 4096);
+        x.src = 0x100000000000ull + i * (size + 4096) + shift;
+        x.dst = 0x200000000000ull + i * (size + 4096) + dst_shift;
         x.row_bytes = x.src_pitch = x.dst_pitch = size;
         x.rows = 1;
         x.stream_off = fn.stream_bytes;
@@ -332,6 +333,15 @@ static void priced() {
   CHECK(takes(FT_P2P, 64, 64, 8, 8, false, false) && !takes(FT_P2P, 64, 64, 8, 8, true, false) && !takes(FT_P2P, 64, 32, 8, 64, false, false));
   CHECK(takes(FT_P2P, 1024, 16, 4, 256, false, false) && !takes(FT_P2P, 300, 16, 4, 16, false, false) &&
         takes(FT_P2P, 2048, 16, 4, 16, false, false));
+  // beyond the cache: sides 4, 8 or 12 bytes apart; any others of short tensors, and to misaligned destinations in jobs that are not too large
+  for (uint64_t shift = 0; shift <= 32; ++shift)
+    for (uint64_t dst : {0, 1, 4, 8, 15, 16, 33})
+      for (uint32_t n : {1u, 8u, 100u, 200u, 300u, 500u}) {
+        const uint64_t total = n == 8 ? 300 : n == 300 ? 500 : n == 500 ? 260 : 140, apart = (shift ^ dst) & 15;
+        const bool want = apart % 4 == 0 ? apart != 0 : n == 200 || n == 500 || (dst % 16 != 0 && n != 8);
+        CHECK(takes(FT_P2P, n, total, n < 4 ? n : 4, 2048, shift, false, dst) == want);
+      }
+  CHECK(takes(FT_P2P, 1, 768, 1, 2048, 4, true) && !takes(FT_P2P, 1, 769, 1, 2048, 4, true) && takes(FT_P2P, 2, 1000, 2, 2048, 4, true));
   for (int cls : {(int)FT_H2P, (int)FT_P2H})
     CHECK(takes(cls, 64, 4, 4, 16, false, false) && !takes(cls, 64, 4, 4, 4, false, false) && takes(cls, 300, 60, 4, 64, false, false) &&
           !takes(cls, 300, 60, 4, 16, false, false) && !takes(cls, 8, 60, 4, 64, false, true) && takes(cls, 8, 16, 4, 256, false, true) &&

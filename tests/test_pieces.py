@@ -260,10 +260,11 @@ def test_a_list_read_in_place_is_the_one_that_was_written(n, size):
 
 
 @pytest.mark.gpu
-@pytest.mark.parametrize("shifts,pieces", [([(1, 0), (15, 14), (0, 113), (7, 120)], True), ([(3, 3), (0, 0), (1, 2), (5, 9)], False), ([(0, 1)], True)],
-                         ids=["odd", "half odd", "one"])
+@pytest.mark.parametrize("shifts,pieces", [([(1, 5), (15, 3), (0, 116), (7, 123)], True), ([(1, 0), (15, 14), (0, 113), (7, 120)], True), ([(1, 0), (15, 14), (1, 16), (7, 32)], False),
+                                           ([(3, 3), (0, 0), (1, 2), (5, 9)], False), ([(4, 0)], True), ([(0, 1)], True), ([(1, 0)], False)],
+                         ids=["4 apart", "odd", "odd to aligned ones", "half odd", "one 4 apart", "one odd", "one odd to an aligned one"])
 def test_streaming_pieces_at_odd_addresses(shifts, pieces):
-    """Beyond 128 MiB jobs that are mostly misaligned go as pieces of 16 KiB, by submit and static; the first, last and inner tiles of runs."""
+    """Beyond 128 MiB jobs that are mostly misaligned in ways that are better off so go as pieces of 16 KiB, by submit and static; the first, last and inner tiles of runs."""
     import torch
     from paper_2411_01830_amd import binding
     print(f"case streaming pieces: {shifts}", flush=True)
