@@ -341,7 +341,7 @@ static void priced() {
         const bool want = apart % 4 == 0 ? apart != 0 : n == 200 || n == 500 || (dst % 16 != 0 && n != 8);
         CHECK(takes(FT_P2P, n, total, n < 4 ? n : 4, 2048, shift, false, dst) == want);
       }
-  CHECK(takes(FT_P2P, 1, 768, 1, 2048, 4, true) && !takes(FT_P2P, 1, 769, 1, 2048, 4, true) && takes(FT_P2P, 2, 1000, 2, 2048, 4, true));
+  CHECK(takes(FT_P2P, 1, 768, 1, 2048, 4, true) && !takes(FT_P2P, 1, 769, 1, 2048, 4, true) && takes(FT_P2P, 2, 1000, 1, 2048, 4, true));
   for (int cls : {(int)FT_H2P, (int)FT_P2H})
     CHECK(takes(cls, 64, 4, 4, 16, false, false) && !takes(cls, 64, 4, 4, 4, false, false) && takes(cls, 300, 60, 4, 64, false, false) &&
           !takes(cls, 300, 60, 4, 16, false, false) && !takes(cls, 8, 60, 4, 64, false, true) && takes(cls, 8, 16, 4, 256, false, true) &&
