@@ -298,6 +298,42 @@ def test_streaming_pieces_at_odd_addresses(shifts, pieces):
         binding.pool_destroy(pool)
 
 
+@pytest.mark.gpu
+@pytest.mark.parametrize("n", [241, 300, 2730, 3000])
+def test_streaming_pieces_of_lists_in_memory(n):
+    """The same of more tensors than a launch holds: lists read in place, and uploaded ones of more than 2730 pieces. Sizes are odd, distances of every kind."""
+    import torch
+    from paper_2411_01830_amd import binding
+    print(f"case streaming pieces of a list in memory: {n}", flush=True)
+    total = 136 * MiB
+    sizes = [total // n + (i * 7919) % 4099 - 2000 for i in range(n)]
+    slab = -(-(max(sizes) + 32) // 4096) * 4096
+    mem = torch.empty(2 * slab * n, dtype=torch.uint8, device="cuda")
+    pool = binding.pool_create(mem.data_ptr(), mem.numel(), 4096, 0)
+    try:
+        src, dst = binding.slab_alloc(pool, slab * n), binding.slab_alloc(pool, slab * n)
+        recs = [dict(func=i % 3, src_space=FT_POOL, dst_space=FT_POOL, src=src + i * slab + i % 16, dst=dst + i * slab + (5 * i + 3) % 16, row_bytes=b) for i, b in enumerate(sizes)]
+        d = make_descs(recs)
+        g = torch.Generator("cuda").manual_seed(n)
+        stream = torch.cuda.current_stream().cuda_stream
+        for flags in (fmt.FT_TIMING, 0):
+            mem.random_(0, 256, generator=g)
+            want = mem.clone()
+            for r in recs:
+                want[r["dst"]:r["dst"] + r["row_bytes"]] = mem[r["src"]:r["src"] + r["row_bytes"]]
+            job = binding.submit_transfers(pool, d, [1, 2, 5], 2 * MiB, flags, stream)
+            binding.wait(pool, job)
+            if flags:
+                st = binding.job_stats(pool, job).cls[2]
+                assert (st.tile_bytes, st.in_launch, st.workgroups == st.tickets) == (16 * KiB, 0, True)
+                binding.job_release(pool, job)
+            torch.cuda.synchronize()
+            assert torch.equal(mem, want), flags
+    finally:
+        torch.cuda.synchronize()
+        binding.pool_destroy(pool)
+
+
 # as above; the tiles are 1, 2 or 4 KiB, the workgroups at most 64 from the host and towards it 128, of more than 256 tiles 48
 LINK_CASES = [
     ("one byte", lambda g: [(1, 1, 0, 0, 0, 3, 9)], [1], 2 * MiB, True),
