@@ -218,11 +218,13 @@ __device__ __forceinline__ void say_done(const DoneWords &done) {
   if (threadIdx.x == 0) __hip_atomic_store(done.words + kDoneStride * blockIdx.x, done.value, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-template <int NT, class A>
-__global__ __launch_bounds__(64) void ft_piece_kernel(A args, DoneWords done) {
+// (no words, no argument for them)
+template <int NT, class A, class... Done>
+__global__ __launch_bounds__(64) void ft_piece_kernel(A args, Done... done) {
+  static_assert((NT == kThrough) == (sizeof...(Done) == 1), "words, and stores to go with them");
   const uint32_t t = A::kOne ? blockIdx.x : tile_of_workgroup(blockIdx.x, args.ntiles);
   move_tile<NT, A::kRows>(find_piece<NT>(args, t, threadIdx.x), threadIdx.x);
-  if (NT == kThrough) say_done<NT>(done);
+  if constexpr (NT == kThrough) say_done<NT>(done...);
 }
 
 // The same over the host link, which has to be full but not crowded: 64 wavefronts with 4 KiB of loads from host memory each, one on
@@ -289,11 +291,11 @@ hipError_t launch(const A &a, const Launch &l) {
   const dim3 grid(piece_workgroups(l.cls, l.ntiles)), block(64);
   const LinkTiles tiles = {l.counter, l.ntiles, l.done};
   if (l.done.words != nullptr && grid.x > kDoneWords) return hipErrorInvalidValue;
-  if (l.cls == 2 && l.done.words != nullptr) hipExtLaunchKernelGGL((ft_piece_kernel<kThrough, A>), grid, block, l.lds, l.stream, l.ev_start, l.ev_stop, 0, a, l.done);
+  if (l.cls == 2 && l.done.words != nullptr) hipExtLaunchKernelGGL((ft_piece_kernel<kThrough, A, DoneWords>), grid, block, l.lds, l.stream, l.ev_start, l.ev_stop, 0, a, l.done);
   else if (l.cls == 2 && a.tile == kStreamTile) {
     if constexpr (A::kRows) return hipErrorInvalidValue;
-    else hipExtLaunchKernelGGL((ft_piece_kernel<kStream, A>), grid, block, l.lds, l.stream, l.ev_start, l.ev_stop, 0, a, l.done);
-  } else if (l.cls == 2) hipExtLaunchKernelGGL((ft_piece_kernel<0, A>), grid, block, l.lds, l.stream, l.ev_start, l.ev_stop, 0, a, l.done);
+    else hipExtLaunchKernelGGL((ft_piece_kernel<kStream, A>), grid, block, l.lds, l.stream, l.ev_start, l.ev_stop, 0, a);
+  } else if (l.cls == 2) hipExtLaunchKernelGGL((ft_piece_kernel<0, A>), grid, block, l.lds, l.stream, l.ev_start, l.ev_stop, 0, a);
   else if constexpr (A::kRows) return hipErrorInvalidValue;
   else if (l.cls == 0) hipExtLaunchKernelGGL((ft_link_piece_kernel<kFromHost, A>), grid, block, 0, l.stream, l.ev_start, l.ev_stop, 0, a, tiles);
   else hipExtLaunchKernelGGL((ft_link_piece_kernel<kToHost, A>), grid, block, 0, l.stream, l.ev_start, l.ev_stop, 0, a, tiles);

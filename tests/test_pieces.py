@@ -444,6 +444,9 @@ def test_kernels_that_say_they_are_done_have_waited_for_their_stores(tmp_path):
     said = [i for i, l in enumerate(lines) if l.startswith("global_store_dwordx2") and l.endswith(" sc0 sc1")]
     kernels = [l for l in lines if re.match(r"_ZN2ft(15ft_piece_kernelILi4E|20ft_link_piece_kernel)\S*:", l)]
     assert len(said) == len(kernels) >= 20
+    for l in lines:
+        if re.match(r"_ZN2ft15ft_piece_kernel\S*:", l):
+            assert ("DoneWords" in l) == ("ft_piece_kernelILi4E" in l), l
     for i in said:
         j = max(k for k in range(i) if lines[k] == "s_waitcnt vmcnt(0)" and lines[k - 1] == ";;#ASMSTART")
         assert not [l for l in lines[j:i] if re.match(r"(global|flat|buffer|scratch)_(store|atomic)", l)], lines[j:i + 1]
