@@ -21,7 +21,7 @@ namespace ft {
 // 5.8 us with 3 KiB, so there are several sizes.
 template <uint32_t CAP, uint32_t SHAPES>
 struct PieceArgs {
-  static constexpr bool kRows = SHAPES != 0, kOne = CAP == 1;
+  static constexpr bool kRows = SHAPES != 0, kOne = CAP == 1, kSays = true;
   uint32_t n, tile, ntiles;
   uint64_t src0, dst0;
   struct {
@@ -38,6 +38,7 @@ struct PieceArgs {
 template <uint32_t BLOCKS, bool CLOSE>
 struct PieceRefs {
   static constexpr bool kRows = false, kOne = false;
+  static constexpr bool kSays = (BLOCKS / 4) * kPieceBlock < kDoneWords;  // launch_refs takes it for more pieces than a quarter, each at least a tile
   uint32_t n, tile, ntiles;
   uint64_t src0, dst0;
   const char *packed;
@@ -290,9 +291,11 @@ hipError_t launch(const A &a, const Launch &l) {
   static_assert(sizeof(A) + sizeof(LinkTiles) <= 4096, "kernel arguments end at 4 KiB");
   const dim3 grid(piece_workgroups(l.cls, l.ntiles)), block(64);
   const LinkTiles tiles = {l.counter, l.ntiles, l.done};
-  if (l.done.words != nullptr && grid.x > kDoneWords) return hipErrorInvalidValue;
-  if (l.cls == 2 && l.done.words != nullptr) hipExtLaunchKernelGGL((ft_piece_kernel<kThrough, A, DoneWords>), grid, block, l.lds, l.stream, l.ev_start, l.ev_stop, 0, a, l.done);
-  else if (l.cls == 2 && a.tile == kStreamTile) {
+  if (l.done.words != nullptr && (grid.x > kDoneWords || a.tile == kStreamTile)) return hipErrorInvalidValue;
+  if (l.cls == 2 && l.done.words != nullptr) {
+    if constexpr (!A::kSays) return hipErrorInvalidValue;
+    else hipExtLaunchKernelGGL((ft_piece_kernel<kThrough, A, DoneWords>), grid, block, l.lds, l.stream, l.ev_start, l.ev_stop, 0, a, l.done);
+  } else if (l.cls == 2 && a.tile == kStreamTile) {
     if constexpr (A::kRows) return hipErrorInvalidValue;
     else hipExtLaunchKernelGGL((ft_piece_kernel<kStream, A>), grid, block, l.lds, l.stream, l.ev_start, l.ev_stop, 0, a);
   } else if (l.cls == 2) hipExtLaunchKernelGGL((ft_piece_kernel<0, A>), grid, block, l.lds, l.stream, l.ev_start, l.ev_stop, 0, a);

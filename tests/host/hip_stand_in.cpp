@@ -303,7 +303,7 @@ hipError_t launch_pieces(const PieceTables &t, int cls, bool on_host, unsigned l
   for (uint32_t i = 0; i < t.n; ++i)
     for (uint32_t no = 0; no < (i + 1 < t.n ? t.first[i + 1] : t.ntiles) - t.first[i]; ++no) move_tile(t, i, no, cls == 0);
   if (done.words != nullptr) g_words += 1;
-  if (done.words != nullptr && piece_workgroups(cls, t.ntiles) > kDoneWords) return hipErrorInvalidValue;
+  if (done.words != nullptr && (piece_workgroups(cls, t.ntiles) > kDoneWords || t.tile == kStreamTile)) return hipErrorInvalidValue;
   for (uint32_t i = 0; done.words != nullptr && i < piece_workgroups(cls, t.ntiles); ++i) __atomic_store_n(done.words + kDoneStride * i, done.value, __ATOMIC_RELEASE);
   return hipSuccess;
 }

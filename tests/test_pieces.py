@@ -447,6 +447,8 @@ def test_kernels_that_say_they_are_done_have_waited_for_their_stores(tmp_path):
     for l in lines:
         if re.match(r"_ZN2ft15ft_piece_kernel\S*:", l):
             assert ("DoneWords" in l) == ("ft_piece_kernelILi4E" in l), l
+            # a launch with words has at most 640 tiles, so no more pieces, and lists of up to 1024 have a kernel of their own
+            assert not re.search(r"ILi4E\S*PieceRefsILj(64|256)E", l), l
     for i in said:
         j = max(k for k in range(i) if lines[k] == "s_waitcnt vmcnt(0)" and lines[k - 1] == ";;#ASMSTART")
         assert not [l for l in lines[j:i] if re.match(r"(global|flat|buffer|scratch)_(store|atomic)", l)], lines[j:i + 1]
