@@ -112,7 +112,7 @@ void stage_copy(char *dst, const char *src, uint64_t n) {
   else std::memcpy(dst, src, n);
 }
 
-// A batch in flight, or a part of one (kPartBytes): what is counted of a batch is its last part's.
+// A batch in flight, or a part of one (kPartChunk): what is counted of a batch is its last part's.
 struct OpenBatch {
   std::shared_ptr<Generation> gen;
   bool last = true;
@@ -394,6 +394,14 @@ void ticket_of_rank(const Generation &g, uint32_t tpc, uint64_t rank, uint64_t *
   *skip_acc = acc;
 }
 
+// A batch of pageable sources that finds nothing in flight is launched chunk by chunk where chunks are this long, each as soon as it is in the
+// ring, so that the link does not wait for the whole batch: a chunk of 2 MiB takes four threads 38 us, a batch of five 190. Passes, us, 4
+// tensors in chunks of 2 MiB: 16 MiB 433 -> 369, 32 MiB 742 -> 689, 64 MiB 1330 -> 1312, 128 MiB 2494 -> 2480 (the threads are the bound). Shorter chunks or parts cost the threads more than
+// the link gains: 32 MiB in parts of 1 MiB, chunks of 1 MiB 687 -> 714, 512 KiB 680 -> 700, 256 KiB 815 -> 852; 4 MiB in chunks of 512 KiB 136 -> 150.
+// Not towards pageable memory, where the last batch's parts could leave the ring as they arrive: 16 MiB 455 -> 469, 128 MiB 2622 -> 2634; there the
+// threads are behind by then.
+constexpr uint64_t kPartChunk = 2 << 20;
+
 // Tables of the order over everything not yet triggered; uploaded on `user`.
 int build_generation(ft_pool *p, OpenState *st, int c, hipStream_t user, std::shared_ptr<Generation> *out) {
   OpenClass &oc = st->cls[c];
@@ -419,7 +427,7 @@ int build_generation(ft_pool *p, OpenState *st, int c, hipStream_t user, std::sh
   build_chunk_table(cp, st->chunk_bytes, oc.tile_bytes, oc.tiles_per_chunk);
   build_skips(cp, st->chunk_bytes, oc.tile_bytes, oc.tiles_per_chunk, &g->skips, &g->ntickets);
   const uint64_t ncounters = (cp.nchunks + oc.batch_chunks - 1) / oc.batch_chunks;
-  g->parts = oc.ring != nullptr && c == FT_H2P;  // a batch may be launched in as many parts as it has chunks
+  g->parts = oc.ring != nullptr && c == FT_H2P && st->chunk_bytes >= kPartChunk;
   const Layout lay = layout_of(cp, 0, g->parts ? cp.nchunks : ncounters);
   rc = get_blob(p, lay.end, true, &g->blob);
   if (rc != FT_OK) return rc;
@@ -497,13 +505,6 @@ void retire_generation(ft_pool *p, OpenState *st, int c, Generation *g) {
 constexpr uint64_t kStagePiece = 256 * 1024;  // longest single copy handed to a helper
 constexpr uint32_t kOnDeviceBatchScale = 64;  // see OpenClass::batch_chunks
 
-// A batch of pageable sources that finds nothing in flight is launched in parts of so many bytes (of whole chunks), each as soon as it is in
-// the ring, so that the link does not wait for the whole batch: a chunk of 2 MiB takes four threads 38 us, a batch of five 190. Passes, us, 4
-// tensors in chunks of 2 MiB: 16 MiB 427..437 -> 369..377, 32 MiB 741..747 -> 711..717, 64 MiB 1331 -> 1315, 128 MiB 2528 -> 2523 (the threads are the bound).
-// Not towards pageable memory, where the last batch's parts could leave the ring as they arrive: 16 MiB 455 -> 469, 128 MiB 2622 -> 2634; there the
-// threads are behind by then.
-constexpr uint64_t kPartBytes = 1 << 20;
-
 struct Prepared {
   OpenBatch batch;
   ClassTable T;
@@ -561,7 +562,7 @@ bool prepare_batch(OpenState *st, int c, std::vector<Prepared> *out) {
   const uint64_t slot0 = oc.ring_slots ? (oc.batches_triggered % (st->depth + 1)) * oc.batch_chunks : 0;
   const bool timing = (st->flags & FT_TIMING) != 0;
   const bool in_parts = g.parts && !timing && !(st->flags & FT_LOG) && oc.inflight.empty();
-  const uint64_t per = in_parts ? std::max<uint64_t>(1, kPartBytes / st->chunk_bytes) : r1 - r0;
+  const uint64_t per = in_parts ? 1 : r1 - r0;
   out->clear();
   for (uint64_t r = r0; r < r1; r += per) {
     out->emplace_back();

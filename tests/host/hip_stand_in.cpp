@@ -59,6 +59,10 @@ extern "C" int stand_in_fail(const char *name, int nth) {
 static std::atomic<hipStream_t> g_stream{nullptr};
 extern "C" hipStream_t stand_in_stream(void) { return g_stream.load(); }
 
+// Bytes that asynchronous copies have moved.
+static std::atomic<uint64_t> g_copied{0};
+extern "C" uint64_t stand_in_copied(void) { return g_copied.load(); }
+
 // How many launches of pieces had words to write to the host.
 static std::atomic<int> g_words{0};
 extern "C" int stand_in_words(void) { return g_words.load(); }
@@ -123,6 +127,7 @@ hipError_t hipMemset(void *p, int v, size_t n) { std::memset(p, v, n); return hi
 hipError_t hipMemcpy(void *d, const void *s, size_t n, hipMemcpyKind) { std::memcpy(d, s, n); return hipSuccess; }
 hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind, hipStream_t) {
   FAIL_POINT("hipMemcpyAsync", hipErrorUnknown);
+  g_copied += n;
   std::memcpy(d, s, n);
   return hipSuccess;
 }

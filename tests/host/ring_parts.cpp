@@ -10,15 +10,51 @@
 #include "../../include/faastube.h"
 
 extern "C" int stand_in_fail(const char *name, int nth);
+extern "C" uint64_t stand_in_copied(void);
 
 #define CHECK(c) do { if (!(c)) { std::fprintf(stderr, "FAIL %s line %d (%s, n %d)\n", #c, __LINE__, point, n); std::abort(); } } while (0)
 
+// What an open job of 8 MiB uploads for its tables.
+static uint64_t tables_of(uint32_t space, uint64_t chunk, uint32_t batch) {
+  const char *point = "tables";
+  const int n = (int)batch;
+  const uint64_t bytes = 8 << 20;
+  std::vector<char> src(bytes, 5), dev(2 * bytes);
+  ft_pool *pool = nullptr;
+  char *base = reinterpret_cast<char *>((reinterpret_cast<uint64_t>(dev.data()) + 4095) / 4096 * 4096);
+  CHECK(ft_pool_create(&pool, base, bytes, 4096, 0) == FT_OK && ft_set_batch(pool, batch, 3) == FT_OK);
+  CHECK((space == FT_HOST ? ft_host_window_add : ft_pageable_window_add)(pool, src.data(), bytes) == FT_OK);
+  ft_off_t off;
+  CHECK(ft_slab_alloc(pool, bytes, &off) == FT_OK);
+  ft_desc d = {};
+  d.rows = 1;
+  d.row_bytes = bytes;
+  d.src_space = space;
+  d.dst_space = FT_POOL;
+  d.src = reinterpret_cast<uint64_t>(src.data());
+  d.dst = off;
+  const uint32_t weight = 1;
+  ft_job_t job;
+  const uint64_t before = stand_in_copied();
+  CHECK(ft_submit_transfers(pool, &d, 1, &weight, 1, chunk, FT_OPEN, nullptr, &job) == FT_OK && ft_wait(pool, job) == FT_OK);
+  const uint64_t uploaded = stand_in_copied() - before;
+  CHECK(std::memcmp(ft_pool_ptr(pool, off), src.data(), bytes) == 0);
+  CHECK(ft_slab_free(pool, off) == FT_OK && ft_pool_destroy(pool) == FT_OK);
+  return uploaded;
+}
+
+#define CHECK_TABLES(c) do { if (!(c)) { std::fprintf(stderr, "FAIL %s line %d\n", #c, __LINE__); std::abort(); } } while (0)
+
 int main() {
+  // a ticket counter for every launch, 8 bytes in a table of whole 256: of a batch of chunks under 2 MiB one, whatever its sources
+  for (uint64_t chunk : {4096ull, 64 * 1024ull, 1024 * 1024ull})
+    for (uint32_t batch : {1u, 5u, 16u}) CHECK_TABLES(tables_of(FT_PAGEABLE, chunk, batch) == tables_of(FT_HOST, chunk, batch));
+  for (uint32_t batch : {1u, 2u, 20u}) CHECK_TABLES(tables_of(FT_PAGEABLE, 2 << 20, batch) == tables_of(FT_HOST, 2 << 20, batch));
   const uint64_t MiB = 1 << 20, bytes = 7 * MiB + 12345;
   std::vector<char> src(2 * bytes);
   for (size_t i = 0; i < src.size(); ++i) src[i] = (char)(i * 2654435761u >> 13);
   for (const char *point : {"launch_copy", "hipEventRecord", "hipEventSynchronize", "hipEventCreateWithFlags", "hipStreamWaitEvent"})
-    for (uint64_t chunk : {256 * 1024ull, 1ull * MiB, 2ull * MiB})
+    for (uint64_t chunk : {256 * 1024ull, 2ull * MiB})
       for (uint32_t depth : {1u, 3u})
         for (int n = 0; n < 14; ++n) {
           char *dev = static_cast<char *>(std::calloc(32, MiB));
