@@ -561,7 +561,10 @@ bool prepare_batch(OpenState *st, int c, std::vector<Prepared> *out) {
   const uint64_t r1 = std::min<uint64_t>(r0 + oc.batch_chunks, cp.nchunks);
   const uint64_t slot0 = oc.ring_slots ? (oc.batches_triggered % (st->depth + 1)) * oc.batch_chunks : 0;
   const bool timing = (st->flags & FT_TIMING) != 0;
-  const bool in_parts = g.parts && !timing && !(st->flags & FT_LOG) && oc.inflight.empty();
+  bool in_parts = false;  // a batch without a chunk to be staged is ready as it is
+  if (g.parts && !timing && !(st->flags & FT_LOG) && oc.inflight.empty())
+    for (uint64_t r = r0; r < r1; ++r)
+      in_parts = in_parts || oc.fns[cp.funcs[decode_rank(cp.phases.data(), (uint32_t)cp.phases.size(), cp.slots.data(), r).fl].func].staged;
   const uint64_t per = in_parts ? 1 : r1 - r0;
   out->clear();
   for (uint64_t r = r0; r < r1; r += per) {
