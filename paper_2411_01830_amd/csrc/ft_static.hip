@@ -128,17 +128,23 @@ extern "C" int ft_submit_static(ft_pool *p, const ft_desc *descs, uint32_t ndesc
     StaticClass &s = sc[c];
     s.used = any = true;
     if (c == FT_P2P) s.room = job_pieces(cp, c, chunk_bytes, false);  // (there is no counter pair here for the host link's)
-    // Pieces that do not go along with their launch take a small launch for every 3 KiB, and so do the general tables: few tensors in
-    // many chunks are shorter by these (20 tensors of 10 functions in chunks of 64 KiB, 40 MB: 18.4 us, by 640 pieces 26.9).
+    // Pieces that do not go along with their launch take a small launch for every 3 KiB of their list (pack_pieces), and so do the general tables: few tensors
+    // in many chunks are shorter by these (20 tensors of 10 functions in chunks of 64 KiB, 40 MB: 18.4 us, by 640 pieces of 24 bytes 26.9), others by the list (100 of 64 KiB, 8 functions,
+    // chunks of 32 KiB: 32.1 -> 27.6 a call; by 24 bytes a piece they would count as longer).
     const auto launches = [](uint64_t bytes) { return (bytes + kInlineBytes - 1) / kInlineBytes; };
     const Layout general = layout_of(cp, 0, 1);
-    if (s.room.pieces != 0 && piece_bytes(s.room) <= kStaticTableBytes) {
+    if (s.room.pieces != 0 && 12 * s.room.pieces <= kStaticTableBytes) {
       if (tables_with_descriptor_table(cp, c, with_p2p, chunk_bytes) > kStaticClassBytes) return FT_E2BIG;
-      const bool shorter = s.room.shapes == 0 && launches(piece_bytes(s.room)) < launches(general.end - general.phases);
-      if (shorter || s.room.shapes != 0 || s.room.pieces - cp.xfers.size() <= kRunsAlong) {  // (else they can't go along: nothing is written out)
+      const auto shorter = [&](uint64_t bytes) { return bytes <= kStaticTableBytes && launches(bytes) < launches(general.end - general.phases); };
+      const bool list = s.room.shapes == 0 && shorter(12 * s.room.pieces);  // (if its sides are close)
+      if (list || s.room.shapes != 0 || s.room.pieces - cp.xfers.size() <= kRunsAlong) {  // (else they can't go along: nothing is written out)
         s.words.resize((piece_bytes(s.room) + 7) / 8);
         s.pieces = piece_places(reinterpret_cast<char *>(s.words.data()), s.room);
-        if (build_pieces(cp, chunk_bytes, piece_tile(c, cp.payload), false, &s.pieces) && (pieces_go_along(s.pieces) || shorter)) continue;
+        if (build_pieces(cp, chunk_bytes, piece_tile(c, cp.payload), false, &s.pieces)) {
+          if (pieces_go_along(s.pieces)) continue;
+          if (list) find_base(&s.pieces);
+          if (list && shorter(packed_bytes(s.pieces))) continue;
+        }
         s.pieces = PieceTables();
       }
     }
@@ -178,7 +184,6 @@ extern "C" int ft_submit_static(ft_pool *p, const ft_desc *descs, uint32_t ndesc
       const bool with_launch = pieces_go_along(s.pieces);
       PieceTables t = s.pieces;
       if (!with_launch) {
-        find_base(&t);
         h.assign(align_up(packed_bytes(t), 8), 0);
         pack_pieces(t, h.data());
         FT_HIP(p, put_words(d + 256, h.data(), h.size(), nullptr, stream));

@@ -223,6 +223,53 @@ def test_lists_in_memory_of_every_size(n, far):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("far", [False, True])
+@pytest.mark.parametrize("n,funcs,chunk", [(100, 8, 32 * KiB), (900, 2, 2 * KiB), (900, 1, 64 * KiB)])
+def test_static_submits_of_lists_in_memory(n, funcs, chunk, far):
+    """Lists that do not go along, in the library's own array: 12 and 20 bytes a piece, of fewer than 1024 pieces and of more (900 tensors in 450 places)."""
+    import torch
+    from paper_2411_01830_amd import binding
+    print(f"case static lists: {n}, {funcs} functions, far apart: {far}", flush=True)
+    rng = np.random.default_rng(n + funcs)
+    sizes = rng.integers(900, 1100, n) if n == 900 else rng.integers(60 * KiB, 68 * KiB, n)
+    room = -(-int(sizes.max() + 64) // 16) * 16
+    half = -(-n * room // (1 << 20)) * (1 << 20)
+    mem = torch.empty((4 << 30) + half if far else 2 * half, dtype=torch.uint8, device="cuda")
+    lo, hi = mem[:half], mem[-half:]
+    pool = binding.pool_create(lo.data_ptr(), half, 4 * KiB, 0)
+    try:
+        binding.pool_grow(pool, hi.data_ptr(), half)
+        binding.slab_alloc(pool, half)
+        binding.slab_alloc(pool, half)
+        swap = np.arange(n) % 3 == 0  # these from the other side, into what is not read there
+        at = np.arange(n) * room
+        src, dst = np.where(swap, half, 0) + at + rng.integers(0, 16, n), np.where(swap, 0, half) + at + rng.integers(0, 16, n)
+        d = make_descs([dict(func=i % funcs, src_space=FT_POOL, dst_space=FT_POOL, src=int(src[i]), dst=int(dst[i]), row_bytes=int(sizes[i])) for i in range(n)])
+        stream = torch.cuda.current_stream().cuda_stream
+        for call in ("static", "submit", "static"):
+            lo.random_(0, 256)
+            hi.random_(0, 256)
+            before = torch.cat([lo, hi]).cpu().numpy()
+            want = before.copy()
+            for s, t, b in zip(src, dst, sizes):
+                want[t:t + b] = before[s:s + b]
+            if call == "static":
+                binding.submit_static(pool, d, [1] * funcs, chunk, 0, stream)
+            else:
+                job = binding.submit_transfers(pool, d, [1] * funcs, chunk, fmt.FT_TIMING, stream)
+                binding.wait(pool, job)
+                st = binding.job_stats(pool, job).cls[2]
+                if n == 900:
+                    assert (st.tile_bytes, st.in_launch, st.workgroups == st.tickets) == (2 * KiB, 0, True)
+                binding.job_release(pool, job)
+            torch.cuda.synchronize()
+            assert np.array_equal(torch.cat([lo, hi]).cpu().numpy(), want), call
+    finally:
+        torch.cuda.synchronize()
+        binding.pool_destroy(pool)
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("n,size", [(241, 200), (600, 150), (1500, 120)])
 def test_a_list_read_in_place_is_the_one_that_was_written(n, size):
     """Thirty different lists one after the other in the same pinned buffer, each only waited for with ft_wait: none sees what an earlier one left in a cache."""
