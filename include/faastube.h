@@ -307,6 +307,8 @@ int ft_submit_transfers(ft_pool *p, const ft_desc *descs, uint32_t ndesc, const 
  * other jobs of the same pool meanwhile (not destroy the pool). The wavefronts of a short job (up to 640 of them, over the
  * host link up to 8 MiB) on a stream with at most four such jobs in flight at a time (from the host two) tell the host themselves when their bytes are in place, so that the call may return some 2 us before the
  * stream counts the job's kernel as complete; for up to 200 us the calling thread looks for their words without giving up its core.
+ * The HIP runtime keeps 1.2 KB of a job launched on hip_stream until that stream or the device is synchronised or queried, or somebody else launches on the stream; where
+ * nobody does, the pool has them given back after 2^20 jobs (each of n streams after 2^20 / n of its own; beyond 64 streams some share a turn).
  */
 int ft_wait(ft_pool *p, ft_job_t job);
 

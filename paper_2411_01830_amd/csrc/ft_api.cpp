@@ -319,15 +319,18 @@ StreamJobs &jobs_of(ft_pool *p, hipStream_t stream) {
     p->streams.emplace_back();
     idle = &p->streams.back();
   }
-  *idle = StreamJobs();
-  idle->stream = stream;
-  return *idle;
+  StreamJobs u;
+  u.stream = stream;
+  u.jobs = idle->jobs;  // streams that share a place share its turns
+  u.in_place = idle->in_place;
+  return *idle = u;
 }
 
 void goes_on_stream(ft_pool *p, Job *job, hipStream_t stream) {
   StreamJobs &u = jobs_of(p, stream);
   u.unfinished += 1;
   if (u.unfinished > u.most) u.most = u.unfinished;
+  u.jobs += 1;
   job->on_stream = true;
   job->stream = stream;
 }
@@ -804,14 +807,23 @@ int launch_with_uploaded_tables(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t
   return FT_OK;
 }
 
-// Of launches with a bound event the runtime keeps its records, 1.6 KB each, until the device is synchronised or a launch without one comes along on the
-// stream. The upload in front of a list was such a launch; where a list is read in place, one launch in 64 has its event recorded behind it instead, spread so that
-// streams taken in turn all have their share. (257 tensors, 365 KB, the first pass on new inputs after 10 000 passes, us: with the upload 39, without this 95..149,
-// with it 36..44.) Not of all launches: on some machines the runtime's signal thread then wakes for nearly every one (32 jobs of one tensor 165..290 -> 290 a pass).
-bool record_done(DeviceCtx *cx) {
-  std::lock_guard<std::mutex> lock(cx->mu);
-  return (cx->in_place_launches++ * 0x9e3779b1u) >> 26 == 63;
+// Of launches with a bound event the runtime keeps its records, 1.2 KB each, until the device or the stream is synchronised or asked whether it is idle, or a launch
+// without one comes along on the stream. A program that does nothing of the kind, only waits for its jobs, would fill the host's memory; so a launch without
+// an event (16 bytes into a counter that nobody reads) goes in front of a stream's job when its share of kKeptRecords, 1.3 GB, is used up.
+// Not sooner: what is given back is paid for in as many launches as a quarter of it, whether 16 384 records at a time or 524 288. 32 jobs of one tensor, us a pass,
+// 165..175, then 490..630; one job 9.6, then 15..21.
+constexpr uint32_t kKeptRecords = 1 << 20;
+int give_records_back(ft_pool *p, hipStream_t stream) {
+  StreamJobs &u = jobs_of(p, stream);
+  if (u.jobs < kKeptRecords / p->streams.size()) return FT_OK;
+  FT_HIP(p, launch_plain_fill(p->ctx->idle_counter, 16, 0, 1, stream));
+  u.jobs = 0;
+  return FT_OK;
 }
+
+// The upload in front of a list was such a launch; where a list is read in place, one launch in 64 of a stream's has its event recorded behind it instead.
+// (257 tensors, 365 KB, the first pass on new inputs after 10 000 passes, us: with the upload 39, without this 95..149, with it 36..44.)
+bool record_done(StreamJobs &u) { return ++u.in_place % 64 == 0; }
 
 // A job of one link class that is short as a list of pieces (ft_pieces.h) is launched as that list on the caller's stream: tables in the
 // launch where they fit, else in memory, uploaded in front of it or read where they are written. Not a job with a log (FT_LOG), which is one of tickets, nor one that is kept for its
@@ -887,7 +899,7 @@ int launch_as_pieces(ft_pool *p, Job *job, SubmitPlan &plan, uint64_t chunk_byte
   bool record = timing;
   if (!with_launch) {
     const bool in_place = pieces_read_in_place(only, packed_bytes(t));
-    if (in_place && !timing) record = record_done(p->ctx);
+    if (in_place && !timing) record = record_done(jobs_of(p, user));
     if (!in_place) e = upload_pieces(job->tables, packed_bytes(t), user);
     t.packed = in_place ? job->tables.host : job->tables.dev;
   }
@@ -1043,6 +1055,8 @@ int ft_submit_transfers(ft_pool *p, const ft_desc *descs, uint32_t ndesc, const 
     if (rc != FT_OK) return rc;
     hipStream_t user = static_cast<hipStream_t>(hip_stream);
     (void)jobs_of(p, user);  // its place, while there is nothing yet that a lack of memory would leave behind
+    rc = give_records_back(p, user);
+    if (rc != FT_OK) return fail_submit(p, job.get(), rc);
     if (plan.has_pageable) {
       rc = stage_closed_job(p, job.get(), plan);
       if (rc != FT_OK) return fail_submit(p, job.get(), rc);

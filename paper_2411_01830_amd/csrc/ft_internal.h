@@ -89,6 +89,8 @@ struct Job {
 struct StreamJobs {
   hipStream_t stream = nullptr;
   uint32_t unfinished = 0, most = 0, most_before = 0;
+  uint32_t jobs = 0;      // since the runtime was last made to give back what it keeps of them (give_records_back)
+  uint32_t in_place = 0;  // launches of lists that are read in place (record_done)
   // how many jobs one more is likely to have to share the time until it is waited for with, itself among them
   uint32_t burst() const { return most_before > unfinished ? most_before : unfinished + 1; }
 };
@@ -142,7 +144,6 @@ struct DeviceCtx {
   uint64_t *done_words = nullptr;
   uint64_t done_value = 0;
   std::vector<uint32_t> free_done;
-  uint32_t in_place_launches = 0;  // of lists that are read in place (record_done)
 };
 
 DeviceCtx *device_ctx(int device);

@@ -1,5 +1,5 @@
 // Which launches of pieces write words to the host when they are done (ft_pieces.h: says_done), on a machine without a GPU, by
-// tests/host/hip_stand_in.cpp: those of streams on which few jobs are in flight at once.
+// tests/host/hip_stand_in.cpp: those of streams on which few jobs are in flight at once. And when the runtime is made to give back its records of launches.
 #include <hip/hip_runtime_api.h>
 
 #include <cstdio>
@@ -11,6 +11,7 @@
 
 extern "C" int stand_in_words(void);
 extern "C" int stand_in_calls(const char *name);
+extern "C" int stand_in_fail(const char *name, int nth);
 
 #define CHECK(c) do { if (!(c)) { std::fprintf(stderr, "FAIL %s line %d\n", #c, __LINE__); std::abort(); } } while (0)
 
@@ -119,6 +120,32 @@ int main() {
     for (hipStream_t s : many) CHECK(hipStreamDestroy(s) == hipSuccess);
   }
   CHECK(ft_pool_destroy(g_pool) == FT_OK);
+  {  // a launch that gives records back for every 2^20 jobs of all streams at most, each stream's share of them
+    CHECK(ft_pool_create(&g_pool, g_dev, bytes, 4096, 0) == FT_OK);
+    CHECK(ft_slab_alloc(g_pool, 32 * kRoom, &g_src) == FT_OK && ft_slab_alloc(g_pool, 32 * kRoom, &g_dst) == FT_OK);
+    constexpr uint32_t kStreams = 64, kShare = (1u << 20) / kStreams;
+    std::vector<hipStream_t> many(kStreams);
+    const auto run = [&](hipStream_t s, uint32_t n) {
+      const int before = stand_in_calls("launch_plain_fill");
+      for (uint32_t i = 0; i < n; ++i) CHECK(ft_wait(g_pool, submit(0, s, i % 7 == 0 ? FT_TIMING : 0)) == FT_OK);
+      return stand_in_calls("launch_plain_fill") - before;
+    };
+    for (hipStream_t &s : many) CHECK(hipStreamCreate(&s) == hipSuccess && run(s, 1) == 0);
+    CHECK(run(many[3], kShare - 1) == 0 && run(many[3], 1) == 1 && run(many[3], kShare - 1) == 0);
+    CHECK(stand_in_fail("launch_plain_fill", 1) == 0);  // one that fails is made up for by the next job
+    ft_desc d = {};
+    d.rows = 1;
+    d.row_bytes = 40 * KiB;
+    d.src_space = d.dst_space = FT_POOL;
+    d.src = g_src;
+    d.dst = g_dst;
+    const uint32_t weight = 1;
+    ft_job_t job = 0;
+    CHECK(ft_submit_transfers(g_pool, &d, 1, &weight, 1, 256 * KiB, 0, many[3], &job) == FT_EHIP);
+    CHECK(run(many[3], 1) == 1 && run(many[5], 1) == 0);
+    for (hipStream_t s : many) CHECK(hipStreamDestroy(s) == hipSuccess);
+    CHECK(ft_pool_destroy(g_pool) == FT_OK);
+  }
   std::free(g_dev);
   std::printf("done_words done\n");
   return 0;

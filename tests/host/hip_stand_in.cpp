@@ -22,7 +22,7 @@
 
 // Failure injection for tests of the error paths: stand_in_fail("hipMemcpyAsync", 3) makes the
 // third call from now of that function fail once (0 clears it). Names: the HIP calls below that
-// say FAIL_POINT, "launch_copy" and "launch_pieces". stand_in_calls says how often one of them has been called.
+// say FAIL_POINT, "launch_copy", "launch_pieces" and "launch_plain_fill". stand_in_calls says how often one of them has been called.
 namespace {
 struct FailPoint {
   const char *name;
@@ -30,7 +30,7 @@ struct FailPoint {
 };
 FailPoint g_fail[] = {{"hipMemcpyAsync"}, {"hipEventRecord"}, {"hipStreamWaitEvent"}, {"hipEventCreateWithFlags"},
                       {"hipMalloc"},      {"hipHostMalloc"},  {"hipEventSynchronize"}, {"launch_copy"},
-                      {"launch_pieces"}};
+                      {"launch_pieces"},  {"launch_plain_fill"}};
 bool fails_now(const char *name) {
   for (FailPoint &f : g_fail)
     if (std::strcmp(f.name, name) == 0) {
@@ -333,6 +333,7 @@ hipError_t launch_plain_copy(void *dst, const void *src, uint64_t bytes, uint32_
 hipError_t launch_plain_read(const void *, uint64_t, uint32_t, hipStream_t) { return hipSuccess; }
 
 hipError_t launch_plain_fill(void *dst, uint64_t bytes, uint32_t word, uint32_t, hipStream_t) {
+  FAIL_POINT("launch_plain_fill", hipErrorLaunchFailure);
   for (uint64_t i = 0; i + 4 <= bytes; i += 4) std::memcpy(static_cast<char *>(dst) + i, &word, 4);
   return hipSuccess;
 }
