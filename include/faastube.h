@@ -253,11 +253,11 @@ int ft_set_stage_threads(ft_pool *p, uint32_t threads);
  * nor mostly aligned ones of more than 64 MiB); chunks of 1 KiB or more; up to 16384 pieces, and no more than save
  * time. Not with FT_KEEP, FT_LOG, FT_OPEN, FT_PATH_DMA or a tuned launch shape, nor a job with FT_DETACHED other than
  * the small ones above. The tables travel with the launch (up to 240 contiguous pieces), or (pool->pool, up to 2730
- * pieces) the kernel reads them in pinned memory, or they are copied ahead of it.
+ * pieces, 1638 if sides are 2 GiB and more apart) the kernel reads them in pinned memory, or they are copied ahead of it.
  *  - Pool->pool every tile of 2 to 8 KiB (beyond 128 MiB 16) has a wavefront of its own, begun in the order but for seven places: the
  *    dies of the chip take the tiles in turn, and the eight tiles of a group one further round in each group,
  *    so that all have the same mixture. As many are under way as the chip holds; 16 MiB of those contiguous
- *    jobs of more than 48 MiB whose tables travel with the launch.
+ *    jobs of more than 48 MiB whose tables travel with the launch, 24 MiB of all of more than 128 MiB.
  *  - On the host link 64 wavefronts from the host and 48 towards it (128 up to 1 MiB) draw tiles of up to 4 KiB in
  *    the order from a counter.
  *

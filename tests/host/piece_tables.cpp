@@ -2,6 +2,7 @@
 // and the kernels' tile and window arithmetic carried out here moves each byte to its place, touches nothing outside the
 // ranges of the descriptors and keeps to the windows that the kernels hold in registers. Random jobs of runs and pitched rows
 // of every width, pitch and alignment, one to thirty functions, chunks of 1 KiB and more.
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -391,6 +392,71 @@ static void units_kept_free() {
     t.ntiles = (uint32_t)(payload / piece_tile(FT_P2P, payload)) + (payload < 48u << 20 ? t.n : 0);
     CHECK(piece_lds(FT_P2P, t) == 0);
   }
+  for (uint32_t n : {1u, kRunsAlong, kRunsAlong + 1, kMaxPieces})  // beyond 128 MiB six tiles on a unit, 24 MiB on 256, wherever the list lies
+    for (bool close : {false, true}) {
+      t.n = n;
+      t.close = close;
+      t.tile = piece_tile(FT_P2P, kCacheResidentBytes + 1);
+      t.ntiles = kCacheResidentBytes / t.tile + 1;
+      CHECK(t.tile == kStreamTile && (160u << 10) / piece_lds(FT_P2P, t) == 6);
+    }
+}
+
+// The shares of functions whose tensors are misaligned, beyond 128 MiB: when workgroup b begins, each function has begun as many bytes as the order of the
+// chunks gives it among the first b tiles, but for seven of them; and that is its weight's share to two chunks.
+static void streaming_shares() {
+  const uint64_t C = 1 << 20;
+  const uint32_t weights[] = {1, 2, 5}, each = 4;
+  ClassPlan cp;
+  for (uint32_t f = 0; f < 3; ++f) {
+    Func fn{};
+    fn.func = f;
+    fn.weight = weights[f];
+    fn.desc_off = (uint32_t)cp.xfers.size();
+    for (uint32_t i = 0; i < each; ++i) {
+      Xfer x{};
+      const uint64_t n = cp.xfers.size();
+      x.row_bytes = x.src_pitch = x.dst_pitch = (weights[f] * 6ull << 20) + 1000 * f + 7 * i;
+      x.src = 0x100000000000ull + n * (64 << 20) + 4 * n + 1;
+      x.dst = 0x200000000000ull + n * (64 << 20) + 9;
+      x.rows = 1;
+      x.stream_off = fn.stream_bytes;
+      fn.stream_bytes += x.row_bytes;
+      fn.ndesc += 1;
+      cp.xfers.push_back(x);
+    }
+    fn.nchunks = (fn.stream_bytes + C - 1) / C;
+    cp.payload += fn.stream_bytes;
+    cp.funcs.push_back(fn);
+  }
+  CHECK(cp.payload > kCacheResidentBytes && build_phases(cp.funcs, cp.phases, cp.slots, &cp.nchunks) == FT_OK);
+  const PieceRoom room = job_pieces(cp, FT_P2P, C, false);
+  CHECK(room.pieces != 0);
+  std::vector<uint64_t> words(piece_bytes(room) / 8 + 1);
+  PieceTables t = piece_places(reinterpret_cast<char *>(words.data()), room);
+  CHECK(build_pieces(cp, C, piece_tile(FT_P2P, cp.payload), false, &t) && t.tile == kStreamTile);
+  const auto begun = [&](bool turned) {  // bytes of each function begun before each workgroup
+    std::vector<uint64_t> sums(3 * (t.ntiles + 1), 0);
+    for (uint32_t b = 0; b < t.ntiles; ++b) {
+      const uint32_t no = turned ? tile_of_workgroup(b, t.ntiles) : b;
+      const uint32_t i = (uint32_t)(std::upper_bound(t.first, t.first + t.n, no) - t.first - 1);
+      uint32_t begin, n;
+      run_tile(t.at[i].dst, t.len[i], t.tile, no - t.first[i], &begin, &n);
+      for (uint32_t f = 0; f < 3; ++f)
+        sums[3 * b + 3 + f] = sums[3 * b + f] + ((t.at[i].dst - 0x200000000000ull) / (64 << 20) / each == f ? n : 0);
+    }
+    return sums;
+  };
+  const std::vector<uint64_t> kernel = begun(true), order = begun(false);
+  for (uint32_t b = 0; b <= t.ntiles; ++b) {
+    const uint64_t total = order[3 * b] + order[3 * b + 1] + order[3 * b + 2];
+    for (uint32_t f = 0; f < 3; ++f) {
+      const auto apart = [](uint64_t x, uint64_t y) { return x > y ? x - y : y - x; };
+      CHECK(apart(kernel[3 * b + f], order[3 * b + f]) <= 7 * kStreamTile);
+      if (total < cp.payload - (8 << 20)) CHECK(apart(8 * order[3 * b + f], weights[f] * total) <= 8 * 2 * C);  // (the streams end together)
+    }
+  }
+  for (uint32_t f = 0; f < 3; ++f) CHECK(kernel[3 * t.ntiles + f] == cp.funcs[f].stream_bytes);
 }
 
 int main(int argc, char **argv) {
@@ -401,6 +467,7 @@ int main(int argc, char **argv) {
   priced();
   tiles_over_dies();
   units_kept_free();
+  streaming_shares();
   for (g_seed = first; g_seed < first + count; ++g_seed) {
     std::mt19937_64 r(g_seed);
     for (int i = 0; i < 6; ++i) job(r);
