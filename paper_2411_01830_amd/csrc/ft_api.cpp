@@ -363,8 +363,8 @@ void release_device_side(ft_pool *p, Job *job) {
   job->unstage.clear();
   for (int c = 0; c < FT_NCLASS; ++c) {
     if (job->run[c].counter_pair >= 0) {
-      // the kernel is over (the job was waited for, or its launch failed and the device was
-      // drained), so the pair is back at zero
+      // the kernel is over, or all its wavefronts have said that they are done, what they stored before being in place (the job
+      // was waited for), or its launch failed and the device was drained: the pair is back at zero
       std::lock_guard<std::mutex> lock(p->ctx->mu);
       p->ctx->free_pairs.push_back((uint32_t)job->run[c].counter_pair);
       job->run[c].counter_pair = -1;

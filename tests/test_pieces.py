@@ -1,5 +1,5 @@
-"""Jobs that are launched as a list of pieces: of runs, pool->pool at most 128 MiB, and of few pitched rows; none whose schedule may be asked for. Bit-exact
-against the oracle at the sizes where tiles, windows, the forms of the tables and the rule change."""
+"""Jobs that are launched as a list of pieces: of runs, pool->pool at most 128 MiB or beyond that mostly misaligned, and over the host link, and of few pitched rows; none
+whose schedule may be asked for. Bit-exact against the oracle (jobs beyond 128 MiB and lists in memory: against torch's copies) at the sizes where tiles, windows, the forms of the tables and the rule change."""
 import numpy as np
 import pytest
 
